@@ -28,11 +28,13 @@
 //
 // The prefill of new tokens (Sec. 3.2: they attend to the past cache and to themselves) is the same
 // computation with many query tokens, and yields Eq. 1 -- the attention each new token receives --
-// on the way: the merge also writes every query's log-sum-exp; prefill_colsum_kernel recomputes the
+// on the way: bf16 rows of 64 or 128 features take the matrix-core kernels further down; for the others the merge also
+// writes every query's log-sum-exp; prefill_colsum_kernel recomputes the
 // scores of a tile's queries against the new tokens' keys, turns them into softmax weights with
 // that log-sum-exp and adds them over the tile; prefill_signal_kernel adds the tiles and KV heads in
 // order and divides by Hq * n_q.  Scratch for it comes from the caller (a workspace argument).
 #include <climits>
+#include <type_traits>
 
 #include "mukv_internal.h"
 
@@ -118,6 +120,7 @@ __device__ __forceinline__ void store_out(float *p, float x) { *p = x; }
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
@@ -663,24 +666,45 @@ __global__ __launch_bounds__(kThreads) void prefill_colsum_kernel(AttendArgs a, 
     }
 }
 
+// The work of prefill_keysum_kernel (below): key tile kt takes the queries from its first token's on (all of them
+// without the mask), in steps of kCQ, shared out steps_per at a time.
+constexpr int kCK = 128, kCQ = 64; // keys per workgroup, queries per step
+__host__ __device__ inline int keysum_shares(int kt, int n_queries, int G, int causal, int steps_per) {
+    const int steps = (n_queries - (causal ? kt * kCK * G : 0) + kCQ - 1) / kCQ;
+    return (steps + steps_per - 1) / steps_per;
+}
+
 // signal[b][j] = (sum over KV heads and query tiles of colpart) / (Hq * n_q), in a fixed order: 32 columns
 // per workgroup, the terms of a column split into 8 contiguous runs (one per group of 32 threads, 8 loads
 // in flight), the runs joined in order.
 constexpr int kSigCols = 32, kSigRuns = kThreads / kSigCols;
-__global__ __launch_bounds__(kThreads) void prefill_signal_kernel(const float *__restrict__ colpart, int n_terms, int n_q,
-                                                                  float inv, float *__restrict__ signal) {
+// Of the n_per terms of a KV head a column has the first n_valid(column): steps_per 0: all of them; otherwise the shares
+// of its key tile.
+__global__ __launch_bounds__(kThreads) void prefill_signal_kernel(const float *__restrict__ colpart, int Hkv, int n_per, int n_q,
+                                                                  float inv, float *__restrict__ signal, int G, int causal,
+                                                                  int steps_per) {
     __shared__ float s_run[kSigRuns][kSigCols];
     const int b = blockIdx.y, col = threadIdx.x % kSigCols, run = threadIdx.x / kSigCols;
     const int j = blockIdx.x * kSigCols + col;
+    static_assert(kCK % kSigCols == 0, "the columns of a workgroup belong to one key tile");
+    const int n_valid = steps_per ? keysum_shares(blockIdx.x * kSigCols / kCK, n_q * G, G, causal, steps_per) : n_per;
+    const int n_terms = Hkv * n_valid;
     const int per = (n_terms + kSigRuns - 1) / kSigRuns;
     const int t0 = run * per, t1 = t0 + per < n_terms ? t0 + per : n_terms;
     float s = 0.f;
-    if (j < n_q) {
-        const float *p = colpart + (int64_t)b * n_terms * n_q + j;
+    if (j < n_q && t0 < t1) {
+        const float *p = colpart + (int64_t)b * Hkv * n_per * n_q + j;
+        int g = t0 / n_valid, i = t0 - g * n_valid; // the run's next term
         for (int t = t0; t < t1; t += 8) {
             float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(t + u < t1 ? t + u : t1 - 1) * n_q];
+            for (int u = 0; u < 8; ++u) {
+                v[u] = p[((int64_t)g * n_per + i) * n_q];
+                if (t + u + 1 < t1 && ++i == n_valid) {
+                    i = 0;
+                    ++g;
+                }
+            }
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += t + u < t1 ? v[u] : 0.f;
         }
@@ -696,174 +720,226 @@ __global__ __launch_bounds__(kThreads) void prefill_signal_kernel(const float *_
 }
 
 // ------------------------------------------------------------------------------------------
-// The prefill on the matrix cores (bf16 rows of 128 features): both products of the attention are
-// dense contractions here, 64 queries -- (token, head of the KV group) pairs -- against every row.
-// One workgroup of four waves per (64 queries, KV head, question); rows in steps of 32, staged
-// through LDS (double-buffered, the next step's rows are in flight in registers meanwhile):
-//   scores   wave w owns queries 16w..16w+15: S^T = K Q^T with v_mfma_f32_16x16x32_bf16, the keys as
-//            the A operand from LDS (a lane: one key row, 8 features), the queries as the B operand in
-//            registers.  A lane then holds ONE query (lane % 16) and eight rows of the step
-//            (16 kb + 4 * (lane / 16) + r), so the softmax statistics of a query are mostly in-lane
-//            work, joined over the four lanes that share the query by two register swaps.
-//            Running maximum and normaliser stay in that wave's registers; the weights go to LDS as
-//            bf16 (four of a query at a time), the factor that rescales what was summed so far as float.
-//   values   wave w owns output features 32w..32w+31 of all 64 queries: O += P V with the weights as
-//            the A operand (a lane: one query, 8 rows) and the values as the B operand (a lane: one
-//            feature, 8 rows, fetched from LDS as eight 2-byte reads).
-// Rows of padded strides 272 B (keys, values) and 80 B (weights) keep the 16-byte operand reads
-// free of bank conflicts.
-// Second loop, Eq. 1: with maximum and normaliser final, the scores against the NEW tokens' keys are
-// formed once more and their softmax weights added over the workgroup's queries: one row of
-// colpart [B][Hkv][query tile][n_q] per workgroup, summed later in a fixed order.
+// The prefill on the matrix cores (bf16 rows of 64 or 128 features): both products of the attention are
+// dense contractions here, queries -- (token, head of the KV group) pairs -- against every row.
+// One workgroup of four waves per (128 queries, KV head, question), a wave owns 32 queries from the scores
+// to the output, so nothing crosses the waves but the staged rows:
+//   rows     in steps of 64, keys and values double-buffered in LDS by the direct global -> LDS load (no
+//            registers hold a row in flight); a step's loads are issued one step ahead, one barrier per step.
+//            A row's 16-byte pieces are stored at piece ^ f(row) -- the permutation sits in the lanes' source
+//            addresses -- so that the 16-byte operand reads of the keys (f = row) and the transpose reads of
+//            the values (f spreads the 4 rows of a 4 x 16 tile over the banks) are free of conflicts.
+//   scores   S^T = K Q^T with v_mfma_f32_32x32x16_bf16, the keys as the A operand from LDS, the queries as the
+//            B operand in registers: a lane holds ONE query (lane % 32) and the rows 8 (j / 4) + 4 (lane / 32) +
+//            j % 4 of every 32, so a query's statistics are in-lane work and one exchange between the halves.
+//   values   O^T += V^T P^T: the weights are the B operand as they stand in the lane -- the order in which the
+//            product walks the rows is free, so the A operand (LDS transpose reads of the values) takes them in
+//            the order the lane holds them: reduction slots 8 h + i of a 16-row step are rows 4 h + i (i < 4) and
+//            8 + 4 h + i - 4.  No weight passes through LDS.
+// The exponent subtracts the running maximum itself: the largest weight is then 1, which bf16 holds exactly (a
+// reference that lags behind it by up to 2^8 saves most of the rescaling, but where one row dominates its weight gets
+// a rounding error: 2.2e-3 from an fp64 evaluation against 1.7e-3).  The output is rescaled only in steps where a
+// maximum of the wave's queries moved.  (Rows of 64 features: the weights are bf16 pairs hi + lo, as in the kernels
+// that take the other shapes, so nothing of the fp32 weight is lost.)  Only steps with a row that some query of the tile may not see look at the mask.
 // ------------------------------------------------------------------------------------------
-constexpr int kFK = 32, kFD = 128;
-constexpr float kHidden = -1e30f, kFloor = -1e20f; // score of a row a query may not see; least running maximum
-constexpr int kRowStride = kFD * 2 + 16; // bytes of a staged key / value row
-constexpr int kPStride = kFK * 2 + 16;   // bytes of a row of weights
+// The direct global -> LDS load: 16 bytes per lane from the lane's address to dst + 16 * lane (dst is the same in all
+// lanes).  The instruction has no destination register, only addresses, which are read when it issues.  It is not the
+// builtin because the compiler makes every later LDS read wait for that one, which would end the overlap of a step's
+// loads with the step before: here rows_landed() and a barrier stand between a load and the first read of its rows.
+__device__ __forceinline__ void load_to_lds(const unsigned char *src, unsigned char *dst) {
+    const unsigned base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)dst;
+    unsigned saved; // m0, which carries the LDS address, is left as it was
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved)
+                 : "s"(base), "v"(src)
+                 : "memory");
+}
+__device__ __forceinline__ void load4_to_lds(const float *src, float *dst) { // 4 bytes per lane
+    const unsigned base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float *)dst;
+    unsigned saved;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved)
+                 : "s"(base), "v"(src)
+                 : "memory");
+}
+__device__ __forceinline__ void rows_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// over the two lanes lane % 32 and lane % 32 + 32, result in both
+__device__ __forceinline__ float half_max(float v) {
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float half_sum(float v) {
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 
-// QB: blocks of 16 queries per wave (64 * QB queries per workgroup).  With two blocks a key or value
-// operand fetched from LDS serves twice the matrix instructions; with one there are twice the
-// workgroups, which is what a short prefill needs.
-// MODE 0: all of it in one launch.  A short prefill has too few tiles to fill the chip, so its rows are
-// split over n_split workgroups per tile -- MODE 1: the split's (maximum, normaliser, unnormalised output)
-// go to the records attend_combine_kernel merges (aux = records), no second loop -- and the second loop
-// runs as a launch of its own once the merged log-sum-exps exist -- MODE 2 (aux = log-sum-exps), its
-// steps split over the same number of workgroups.
-template <int QB, int MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QB == 1 ? 3 : 2, QB == 1 ? 3 : 2))) void prefill_flash_kernel(
-    AttendArgs a, uint16_t *__restrict__ out, float *__restrict__ colpart, int n_tiles, float *__restrict__ aux, int n_split) {
+constexpr int kFK = 64, kFQ = 128; // rows per step, queries per workgroup
+constexpr float kHidden = -1e30f, kFloor = -1e20f; // score of a row a query may not see; least running maximum
+
+// Slot of 16-byte piece `piece` of staged row `row` in a row of D * 2 bytes.
+template <int D>
+__device__ __forceinline__ int key_slot(int piece, int row) {
+    // 16 lanes read one piece of 16 neighbouring rows: 256 B over all banks
+    return D == 128 ? piece ^ (row & 15) : piece ^ ((row >> 1) & 7);
+}
+template <int D>
+__device__ __forceinline__ int val_slot(int piece, int row) {
+    // half a wave reads 4 pieces of 4 neighbouring rows (4-aligned both)
+    return D == 128 ? piece ^ (((row & 3) << 2) | ((row >> 2) & 3)) : piece ^ (((row >> 1) & 1) << 2);
+}
+
+// Workgroup -> (tile, combination of KV head and question).  Workgroup id runs on XCD id % 8; the rows of a
+// combination are read by all of its tiles, so where the counts allow it a combination stays on as few XCDs
+// as there are for it (its rows then sit in those L2 caches).  Heavy tiles -- the last ones under the causal
+// mask -- first.  Returns false for the padding workgroups.
+__device__ __forceinline__ bool tile_of(unsigned id, int n_tiles, int combos, int *tile, int *combo) {
+    const unsigned xcd = id & 7, slot = id >> 3;
+    int rank;
+    if (8 % combos == 0) {
+        const int per = 8 / combos;
+        *combo = xcd / per;
+        rank = slot * per + xcd % per;
+    } else if (combos % 8 == 0) {
+        const unsigned m = combos / 8;
+        *combo = (slot % m) * 8 + xcd;
+        rank = slot / m;
+    } else {
+        *combo = id % combos;
+        rank = id / combos;
+    }
+    *tile = n_tiles - 1 - rank;
+    return rank < n_tiles;
+}
+unsigned tile_grid(int n_tiles, int combos) {
+    if (8 % combos == 0) {
+        const int per = 8 / combos;
+        return (unsigned)((n_tiles + per - 1) / per) * 8u;
+    }
+    return (unsigned)((int64_t)n_tiles * combos);
+}
+
+// What bounds it: the latency of a wave's chain scores -> statistics -> weights -> values, with two waves per SIMD to
+// hide it (248 registers, 80 KB of LDS): a 64-row step of a workgroup alone on its compute unit takes 2850 cycles for
+// 1024 of matrix work.  Measured, 7B head layout, 1568 new tokens over 768 rows: 61 us (186 us for 64-query tiles of
+// 16x16x32 products whose weights crossed the waves through LDS, which included the column sums: those are 23 us in the
+// kernel below); 4000 tokens 267 us for the whole call against 673.  Also built and slower: the next block's scores
+// interleaved instruction by instruction with this block's weights and values (66 us), eight waves that share 128-row
+// steps (59 us, but 346 against 300 for the long prefill), 64 queries per wave (85 us: the accumulators pass 256
+// registers and are moved in and out of the accumulation registers).
+// SPLIT: a short prefill has too few tiles to fill the chip, so its rows are shared by n_split workgroups per
+// tile; the split's (maximum, normaliser, unnormalised output) go to the records attend_combine_kernel merges
+// (aux = records).  Otherwise the output and the log-sum-exps (aux) are final here.
+template <int D, bool SPLIT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void prefill_flash_kernel(
+    AttendArgs a, uint16_t *__restrict__ out, int n_tiles, int combos, float *__restrict__ aux, int n_split) {
     using T = uint16_t;
-    constexpr int kFQ = 64 * QB, NQB = 4 * QB; // queries, blocks of 16 queries per workgroup
-    __shared__ __align__(16) unsigned char s_k[2][kFK * kRowStride];
-    __shared__ __align__(16) unsigned char s_v[2][kFK * kRowStride];
-    __shared__ __align__(16) unsigned char s_p[kFQ * kPStride];
-    __shared__ __align__(16) int s_ft[2][kFK];
-    __shared__ float s_corr[kFQ];
-    __shared__ int s_chg[NQB]; // per block of 16 queries: did a running maximum move in this step
-    __shared__ float s_fin[2][kFQ];
-    __shared__ float s_col[4][kFK];
+    constexpr int kRowB = D * 2, kPieces = kRowB / 16, kRowsPerLoad = 64 / kPieces; // rows one load of a wave brings
+    constexpr int kLoads = kFK / 4 / kRowsPerLoad;                                   // such loads per wave and step
+    constexpr int KK = D / 16, NF = D / 32; // 16-feature steps of the scores, 32-feature blocks of the output
+    constexpr bool kPairs = D == 64;        // weights as bf16 pairs hi + lo
+    __shared__ __align__(1024) unsigned char s_k[2][kFK * kRowB];
+    __shared__ __align__(1024) unsigned char s_v[2][kFK * kRowB];
+    constexpr int kRing = 8;                      // steps whose row tables are held
+    __shared__ ulonglong2 s_addr[kRing][kFK];     // addresses of the row's key and value
+    __shared__ __align__(16) int s_ft[kRing][kFK]; // first token that sees the row
+    __shared__ int s_masked[kRing];               // some query of the tile may not see some row of the step
     __shared__ int s_frame[kMaxGatherK]; // the question's frames; -1: names no frame of the cache
-    __shared__ int64_t s_toff[2][kFK];   // where the rows of the next two steps live
-    __shared__ int s_tft[2][kFK];
-    const int qt = MODE == 0 ? blockIdx.x : blockIdx.x / n_split, sp = MODE == 0 ? 0 : blockIdx.x % n_split;
-    const int g = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+    int tile_id, combo;
+    if (!tile_of(blockIdx.x, SPLIT ? n_tiles * n_split : n_tiles, combos, &tile_id, &combo)) return;
+    const int qt = SPLIT ? tile_id / n_split : tile_id, sp = SPLIT ? tile_id % n_split : 0;
+    const int g = combo % a.Hkv, b = combo / a.Hkv;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lq = lane & 31, half = lane >> 5;
     const int n_queries = a.n_q * a.G;
     const T *q = static_cast<const T *>(a.q);
     for (int i = tid; i < a.k_frame; i += 256) {
         const int f = a.frame_idx[(int64_t)b * a.k_frame + i];
         s_frame[i] = (f >= 0 && f < a.n_frames) ? f : -1;
     }
-    __syncthreads();
-
-    // the wave's 16 queries as the A operand; token of the four queries this lane holds scores for
-    // the wave's blocks are QB * wave + i; block n holds queries 16 n .. 16 n + 15 of the tile
-    bf16x8 qa[QB][kFD / 32];
-    int tokq[QB]; // token of the query this lane holds scores for (nothing is visible to a query that does not exist)
-    float lse_in[QB];
+    // the wave's 32 queries as a matrix operand (row / column lane % 32, 8 features from 8 * half of every 16)
+    bf16x8 qb[KK];
+    const int my_q = qt * kFQ + 32 * wave + lq;
+    const bool q_ok = my_q < n_queries;
+    const int my_tok = q_ok ? my_q / a.G : INT_MIN; // nothing is visible to a query that does not exist
+    const int64_t my_row = ((int64_t)b * a.n_q + (q_ok ? my_tok : 0)) * a.Hq + g * a.G + (q_ok ? my_q - my_tok * a.G : 0);
+    {
+        const T *qp = q + my_row * D + 8 * half;
 #pragma unroll
-    for (int i = 0; i < QB; ++i) {
-        const int qq = qt * kFQ + 16 * (QB * wave + i) + lr;
-        const bool ok = qq < n_queries;
-        const int ti = ok ? qq / a.G : 0, h = g * a.G + (ok ? qq % a.G : 0);
-        const T *qp = q + (((int64_t)b * a.n_q + ti) * a.Hq + h) * kFD + 8 * lg;
-#pragma unroll
-        for (int kk = 0; kk < kFD / 32; ++kk) {
-            raw16 u = load16(qp + 32 * kk);
-            if (!ok) u = raw16{0u, 0u, 0u, 0u};
-            qa[i][kk] = __builtin_bit_cast(bf16x8, u);
+        for (int kk = 0; kk < KK; ++kk) {
+            raw16 u = load16(qp + 16 * kk);
+            if (!q_ok) u = raw16{0u, 0u, 0u, 0u};
+            qb[kk] = __builtin_bit_cast(bf16x8, u);
         }
-        tokq[i] = ok ? ti : INT_MIN;
-        if constexpr (MODE == 2) lse_in[i] = ok ? aux[((int64_t)b * a.n_q + ti) * a.Hq + h] : INFINITY;
     }
-
     const int n_ret = a.k_frame * a.kappa;
-    const int l0 = a.local_offsets[b];
-    int n_loc = a.local_offsets[b + 1] - l0;
+    const int l0 = __builtin_amdgcn_readfirstlane(a.local_offsets[b]); // the same in all lanes: scalar registers
+    int n_loc = __builtin_amdgcn_readfirstlane(a.local_offsets[b + 1]) - l0;
     if (n_loc < 0) n_loc = 0;
     const int total = n_ret + n_loc;
-    const T *sk = static_cast<const T *>(a.store_k) + (int64_t)g * a.store_cap * kFD;
-    const T *sv = static_cast<const T *>(a.store_v) + (int64_t)g * a.store_cap * kFD;
-    const T *lk = static_cast<const T *>(a.k_local), *lv = static_cast<const T *>(a.v_local);
+    const unsigned char *sk = static_cast<const unsigned char *>(a.store_k) + (int64_t)g * a.store_cap * kRowB;
+    const unsigned char *sv = static_cast<const unsigned char *>(a.store_v) + (int64_t)g * a.store_cap * kRowB;
+    const unsigned char *lk = static_cast<const unsigned char *>(a.k_local) + g * kRowB;
+    const unsigned char *lv = static_cast<const unsigned char *>(a.v_local) + g * kRowB;
+    const unsigned local_stride = (unsigned)a.Hkv * kRowB;
+    const int first_tok = (qt * kFQ) / a.G;
+    const int last_q = (qt * kFQ + kFQ - 1 < n_queries ? qt * kFQ + kFQ - 1 : n_queries - 1) / a.G;
 
-    // Row r of [retrieved rows, local rows]: where it lives and the first token that sees it, worked out
-    // by one thread per row two steps ahead and handed to the staging threads through a small table.
-    // Entry: element offset in the store slab (>= 0) or ~offset in the local rows (< 0).  A row that
-    // lives nowhere (or below r_min) reads the slab's first row and is seen by nobody.
-    auto tabulate = [&](int set, int r, int r_min) { // threads tid < kFK, r = first row of the step + tid
-        int64_t off = 0;
+    // Row r of [retrieved rows, local rows]: where its key and value live and the first token that sees it, worked
+    // out by the lanes of one wave, four steps at a time (one per wave).  A row that lives nowhere, or past the last,
+    // is seen by nobody and reads a row that exists.
+    auto tabulate = [&](int t) {
+        const int slot = t & (kRing - 1), r = t * kFK + lane;
+        uint64_t off = (uint64_t)(unsigned)l0 * local_stride;
+        bool local = n_loc > 0;
         int ft = INT_MAX;
-        if (r >= r_min && r < n_ret) {
-            const int slot = r / a.kappa;
-            const int f = s_frame[slot];
+        if (!local) off = 0;
+        if (r < n_ret) {
+            const int e = (int)((unsigned)r / (unsigned)a.kappa);
+            const int f = s_frame[e];
             if (f >= 0) {
-                off = ((int64_t)f * a.kappa + (r - slot * a.kappa)) * kFD;
+                off = (uint64_t)(unsigned)(f * a.kappa + (r - e * a.kappa)) * kRowB;
+                local = false;
                 ft = 0;
             }
-        } else if (r >= r_min && r < total) {
+        } else if (r < total) {
             const int j = r - n_ret;
-            off = ~(((int64_t)(l0 + j) * a.Hkv + g) * kFD);
+            off = (uint64_t)(unsigned)(l0 + j) * local_stride;
             ft = a.causal ? j - (n_loc - a.n_q) : 0;
         }
-        s_toff[set][tid] = off;
-        s_tft[set][tid] = ft;
+        s_addr[slot][lane] = ulonglong2{(uint64_t)(uintptr_t)(local ? lk : sk) + off, (uint64_t)(uintptr_t)(local ? lv : sv) + off};
+        s_ft[slot][lane] = ft;
+        const bool any = __builtin_amdgcn_ballot_w64(ft > first_tok) != 0;
+        if (lane == 0) s_masked[slot] = any;
     };
-    // staging: thread -> rows tid / 16 and tid / 16 + 16 of the step, 16-byte piece tid % 16
-    const int st_row = tid >> 4, st_piece = tid & 15;
-    // the next step's rows are in flight in registers while a step is computed (a deeper queue of
-    // loads cost occupancy and gained nothing)
-    raw16 pk[2], pv[2];
-    int pft[2];
-    auto fetch = [&](int set, bool with_v) {
+    // A wave brings rows 16 wave .. 16 wave + 15 of the step, kRowsPerLoad at a time.
+    const int ld_row = 16 * wave + lane / kPieces, ld_piece = lane % kPieces;
+    unsigned kswz[kLoads], vswz[kLoads];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int64_t e = s_toff[set][st_row + 16 * u];
-            pft[u] = s_tft[set][st_row + 16 * u];
-            const bool local = e < 0;
-            const int64_t off = (local ? ~e : e) + 8 * st_piece;
-            pk[u] = load16((local ? lk : sk) + off);
-            if (with_v) pv[u] = load16((local ? lv : sv) + off);
-        }
-    };
-    auto put = [&](int buf, bool with_v) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int off = (st_row + 16 * u) * kRowStride + 16 * st_piece;
-            *reinterpret_cast<raw16 *>(s_k[buf] + off) = pk[u];
-            if (with_v) *reinterpret_cast<raw16 *>(s_v[buf] + off) = pv[u];
-            if (st_piece == 0) s_ft[buf][st_row + 16 * u] = pft[u];
-        }
-    };
-    // scores of the wave's queries against the step's 32 rows: sc[i][kb][r] for row 16 kb + 4 lg + r, query lr of block i
-    auto scores = [&](int buf, f32x4 (&sc)[QB][2]) {
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-            for (int i = 0; i < QB; ++i) sc[i][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const unsigned char *kp = s_k[buf] + (16 * kb + lr) * kRowStride + 16 * lg;
-#pragma unroll
-            for (int kk = 0; kk < kFD / 32; ++kk) {
-                const bf16x8 bk = __builtin_bit_cast(bf16x8, *reinterpret_cast<const raw16 *>(kp + 64 * kk));
-#pragma unroll
-                for (int i = 0; i < QB; ++i) sc[i][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bk, qa[i][kk], sc[i][kb], 0, 0, 0);
-            }
-        }
-    };
-
-    float m_run[QB], l_run[QB]; // of query lr of the wave's blocks
-#pragma unroll
-    for (int i = 0; i < QB; ++i) {
-        m_run[i] = kFloor;
-        l_run[i] = 0.f;
+    for (int u = 0; u < kLoads; ++u) {
+        kswz[u] = 16 * key_slot<D>(ld_piece, ld_row + u * kRowsPerLoad);
+        vswz[u] = 16 * val_slot<D>(ld_piece, ld_row + u * kRowsPerLoad);
     }
-    f32x4 o[NQB][2];
+    auto look_up = [&](int t, ulonglong2(&ad)[kLoads]) {
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb)
+        for (int u = 0; u < kLoads; ++u) ad[u] = s_addr[t & (kRing - 1)][ld_row + u * kRowsPerLoad];
+    };
+    auto request = [&](int u, const ulonglong2(&ad)[kLoads], unsigned char *dk, unsigned char *dv) __attribute__((always_inline)) {
+        const int lds = (16 * wave + u * kRowsPerLoad) * kRowB; // the wave's 1024 bytes, lane order
+        load_to_lds(reinterpret_cast<const unsigned char *>(ad[u].x + kswz[u]), dk + lds);
+        load_to_lds(reinterpret_cast<const unsigned char *>(ad[u].y + vswz[u]), dv + lds);
+    };
+    // this lane's offsets in a staged buffer: key operand of 16-feature step kk (rows lq, lq + 32 share the slot)
+    int koff[KK];
 #pragma unroll
-        for (int db = 0; db < 2; ++db) o[qb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kk = 0; kk < KK; ++kk) koff[kk] = lq * kRowB + 16 * key_slot<D>(2 * kk + half, lq);
+
+    float m_run = kFloor, l_run = 0.f; // of query lq; l_run: over the rows this lane holds
+    f32x16 o[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o[f][j] = 0.f;
 
     // with the causal mask the rows after the workgroup's last token are seen by none of its queries
-    const int last_q = (qt * kFQ + kFQ - 1 < n_queries ? qt * kFQ + kFQ - 1 : n_queries - 1) / a.G;
     int n_seen = total;
     if (a.causal) {
         // local rows up to the tile's last token; the retrieved rows are seen by every token, also by
@@ -874,185 +950,322 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QB == 1 ? 3
     }
     const int n_steps_all = n_seen > 0 ? (n_seen + kFK - 1) / kFK : 0;
     // this workgroup's steps: all of them, or its share of them
-    const int per_split = MODE == 1 ? (n_steps_all + n_split - 1) / n_split : n_steps_all;
-    const int t_lo = MODE == 1 ? sp * per_split : 0;
-    const int n_steps = MODE == 2 ? 0 : (t_lo + per_split < n_steps_all ? t_lo + per_split : n_steps_all);
-    if (MODE != 2 && tid < kFK) {
-        tabulate(0, t_lo * kFK + tid, 0);
-        tabulate(1, (t_lo + 1) * kFK + tid, 0);
-    }
+    const int per_split = SPLIT ? (n_steps_all + n_split - 1) / n_split : n_steps_all;
+    const int t_lo = SPLIT ? sp * per_split : 0;
+    const int n_steps = t_lo + per_split < n_steps_all ? t_lo + per_split : n_steps_all;
+    __syncthreads(); // the frame list is there
+    tabulate(t_lo + wave);
+    tabulate(t_lo + wave + 4);
     __syncthreads();
-    if (t_lo < n_steps) fetch(0, true);
-    for (int t = t_lo; t < n_steps; ++t) {
-        const int buf = (t - t_lo) & 1;
-        put(buf, true);
-        __syncthreads(); // step t is staged; every wave is done with step t-1
-        if (t + 1 < n_steps) fetch(buf ^ 1, true);
-        if (tid < kFK && t + 2 < n_steps) tabulate(buf, (t + 2) * kFK + tid, 0);
-        f32x4 sc[QB][2];
-        scores(buf, sc);
+    if (t_lo < n_steps) {
+        ulonglong2 ad[kLoads];
+        look_up(t_lo, ad);
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) request(u, ad, s_k[0], s_v[0]);
+    }
+    // One step: the rows in ck / cv are used while those of step t + 1 are on their way into nk / nv.
+    auto step = [&](int t, const unsigned char *ck, const unsigned char *cv, unsigned char *nk,
+                    unsigned char *nv) __attribute__((always_inline)) {
+        ulonglong2 ad[kLoads];
+        look_up(t + 1, ad);
+        const int masked = s_masked[t & (kRing - 1)];
+        rows_landed();   // this wave's rows of step t are in LDS
+        __syncthreads(); // everybody's are; every wave is done with step t-1
+        const bool more = t + 1 < n_steps; // its loads are issued between the groups of matrix instructions
+        // tables of the steps before t are free: four new ones every four steps
+        if (((t - t_lo) & 3) == 0 && t > t_lo && t + 4 < n_steps) tabulate(t + 4 + wave);
+        // Operands are requested one group of matrix instructions ahead (the barriers keep the compiler's order to it):
+        // 16 features of both blocks of 32 rows.
+        f32x16 sc[2];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) sc[0][j] = sc[1][j] = 0.f;
+        bf16x8 ak[2][2][2];
+        auto load_k = [&](int grp) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+                    ak[grp & 1][i][kb] = *reinterpret_cast<const bf16x8 *>(ck + koff[2 * grp + i] + 32 * kRowB * kb);
+        };
+        load_k(0);
+#pragma unroll
+        for (int grp = 0; grp < KK / 2; ++grp) {
+            if (grp + 1 < KK / 2) load_k(grp + 1);
+            if (grp < kLoads && more) request(grp, ad, nk, nv);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+                    sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[grp & 1][i][kb], qb[2 * grp + i], sc[kb], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        bf16x8 av[2][NF]; // value operands of 16 rows, also one group ahead
+        auto load_v = [&](int grp) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                // rows 4 half + (lane % 16) / 4 and 8 later, 4 features per lane
+                const int row = 16 * grp + 4 * half + ((lane & 15) >> 2);
+                const int piece = 4 * f + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1), sub = 8 * (lane & 1);
+                const i16x4 lo = lds_read_tr16(cv + row * kRowB + 16 * val_slot<D>(piece, row) + sub);
+                const i16x4 hi = lds_read_tr16(cv + (row + 8) * kRowB + 16 * val_slot<D>(piece, row + 8) + sub);
+                av[grp & 1][f] = __builtin_bit_cast(bf16x8, i16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+            }
+        };
+        load_v(0);
         // Scores stay unscaled (the factor to log2 units sits in the exponent's multiply-add); a row a query
-        // may not see scores kHidden, and running maxima never drop below kFloor: exp2 of the difference is an
-        // exact zero for hidden rows, no select needed, and a query that has seen nothing yet sums zeros.
-        const i32x4 f0 = *reinterpret_cast<const i32x4 *>(&s_ft[buf][4 * lg]);
-        const i32x4 f1 = *reinterpret_cast<const i32x4 *>(&s_ft[buf][16 + 4 * lg]);
+        // may not see scores kHidden, and the running maximum never drops below kFloor: exp2 of the difference is an
+        // exact zero for hidden rows, and a query that has seen nothing yet sums zeros.
+        if (__builtin_amdgcn_readfirstlane(masked)) {
 #pragma unroll
-        for (int i = 0; i < QB; ++i) {
-            float sv[8];
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                sv[r] = tokq[i] >= f0[r] ? sc[i][0][r] : kHidden;
-                sv[4 + r] = tokq[i] >= f1[r] ? sc[i][1][r] : kHidden;
-            }
-            const float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-            const float m_new = fmaxf(m_run[i], xrow_max(mx) * a.scale_log2e);
-            const float corr = __builtin_amdgcn_exp2f(m_run[i] - m_new);
-            float pw[8];
+                for (int jj = 0; jj < 4; ++jj) {
+                    const i32x4 ft = *reinterpret_cast<const i32x4 *>(&s_ft[t & (kRing - 1)][32 * kb + 8 * jj + 4 * half]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) pw[e] = __builtin_amdgcn_exp2f(fmaf(sv[e], a.scale_log2e, -m_new));
-            l_run[i] = l_run[i] * corr + xrow_sum(((pw[0] + pw[1]) + (pw[2] + pw[3])) + ((pw[4] + pw[5]) + (pw[6] + pw[7])));
-            const bool moved = m_new != m_run[i];
-            m_run[i] = m_new;
-            const int qrow = 16 * (QB * wave + i) + lr;
-            if (lg == 0) s_corr[qrow] = corr;
-            // rows 4 lg .. 4 lg + 3 and 16 + 4 lg .. of the query's weights, rounded to bf16 two at a time
-            u32x2 w0, w1;
-            w0[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{pw[0], pw[1]}, bf16x2));
-            w0[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{pw[2], pw[3]}, bf16x2));
-            w1[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{pw[4], pw[5]}, bf16x2));
-            w1[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{pw[6], pw[7]}, bf16x2));
-            *reinterpret_cast<u32x2 *>(s_p + qrow * kPStride + 8 * lg) = w0;
-            *reinterpret_cast<u32x2 *>(s_p + qrow * kPStride + 32 + 8 * lg) = w1;
-            // most steps leave the running maxima of a block's 16 queries where they were: nothing to rescale then
-            const bool any_moved = __builtin_amdgcn_ballot_w64(moved) != 0;
-            if (lane == 0) s_chg[QB * wave + i] = any_moved;
-        }
-        __syncthreads(); // weights and factors of step t are in LDS
-        // The B operand wants 8 rows of ONE feature per lane while the staged values are row-major: the LDS
-        // transpose read hands lane n of a 16-lane block column n of a 4 x 16 tile whose row t is named by
-        // lanes 4t .. 4t+3 of the block, 4 features each -- two such reads per operand.
-        bf16x8 bv[2];
-#pragma unroll
-        for (int db = 0; db < 2; ++db) {
-            const unsigned char *vp = s_v[buf] + (8 * lg + (lr >> 2)) * kRowStride + 2 * (32 * wave + 16 * db + 4 * (lr & 3));
-            const i16x4 lo = lds_read_tr16(vp), hi = lds_read_tr16(vp + 4 * kRowStride);
-            bv[db] = __builtin_bit_cast(bf16x8, i16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
-        }
-#pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-            const bf16x8 ap = __builtin_bit_cast(bf16x8, *reinterpret_cast<const raw16 *>(s_p + (16 * qb + lr) * kPStride + 16 * lg));
-            if (s_chg[qb]) {
-                float corr[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) corr[r] = s_corr[16 * qb + 4 * lg + r];
-#pragma unroll
-                for (int db = 0; db < 2; ++db)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) o[qb][db][r] *= corr[r];
-            }
-#pragma unroll
-            for (int db = 0; db < 2; ++db) o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap, bv[db], o[qb][db], 0, 0, 0);
-        }
-    }
-    float lse[QB]; // of query lr of the wave's blocks
-    if constexpr (MODE != 2) {
-        // ---- final statistics to LDS, output ----
-        __syncthreads();
-        if (lg == 0) {
-#pragma unroll
-            for (int i = 0; i < QB; ++i) {
-                s_fin[0][16 * (QB * wave + i) + lr] = m_run[i];
-                s_fin[1][16 * (QB * wave + i) + lr] = l_run[i];
-            }
-        }
-        __syncthreads();
-        if constexpr (MODE == 1) { // the split's record of every query: [0] maximum, [1] normaliser, [2..] unnormalised output
-            if (tid < kFQ && qt * kFQ + tid < n_queries) {
-                const int qq = qt * kFQ + tid;
-                const int i = qq / a.G, h = g * a.G + qq % a.G;
-                float *rec = aux + ((((int64_t)b * a.n_q + i) * a.Hq + h) * n_split + sp) * (kFD + 2);
-                rec[0] = s_fin[0][tid];
-                rec[1] = s_fin[1][tid];
-            }
-        }
-#pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int n = 16 * qb + 4 * lg + r;
-                const int qq = qt * kFQ + n;
-                if (qq >= n_queries) continue;
-                const int i = qq / a.G, h = g * a.G + qq % a.G;
-                if constexpr (MODE == 1) {
-                    float *rec = aux + ((((int64_t)b * a.n_q + i) * a.Hq + h) * n_split + sp) * (kFD + 2) + 2 + 32 * wave + lr;
-                    rec[0] = o[qb][0][r];
-                    rec[16] = o[qb][1][r];
-                } else {
-                    const float l = s_fin[1][n];
-                    const float inv = l > 0.f ? 1.0f / l : 0.f;
-                    uint16_t *op = out + (((int64_t)b * a.n_q + i) * a.Hq + h) * kFD + 32 * wave + lr;
-                    op[0] = bf16_round(o[qb][0][r] * inv);
-                    op[16] = bf16_round(o[qb][1][r] * inv);
+                    for (int r = 0; r < 4; ++r) sc[kb][4 * jj + r] = my_tok >= ft[r] ? sc[kb][4 * jj + r] : kHidden;
                 }
-            }
         }
-        if (MODE == 1 || !colpart) return;
+        float m4[4];
 #pragma unroll
-        for (int i = 0; i < QB; ++i) lse[i] = l_run[i] > 0.f ? m_run[i] + __builtin_amdgcn_logf(l_run[i]) : INFINITY;
-    } else {
+        for (int c = 0; c < 4; ++c) m4[c] = fmaxf(sc[0][c], sc[1][c]);
 #pragma unroll
-        for (int i = 0; i < QB; ++i) lse[i] = lse_in[i];
+        for (int j = 4; j < 16; ++j) m4[j & 3] = fmaxf(fmaxf(m4[j & 3], sc[0][j]), sc[1][j]);
+        const float mx = half_max(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]))) * a.scale_log2e;
+        if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) { // a maximum moved: bring what was summed to it
+            const float m_new = fmaxf(m_run, mx);
+            const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
+            l_run *= corr;
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) o[f][j] *= corr;
+        }
+        bf16x8 pw[2], pl[2];
+        auto weights = [&](int grp) { // of 16 rows
+            float p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(sc[grp >> 1][8 * (grp & 1) + e], a.scale_log2e, -m_run));
+            l_run += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+            raw16 u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) u[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{p[2 * e], p[2 * e + 1]}, bf16x2));
+            pw[grp & 1] = __builtin_bit_cast(bf16x8, u);
+            if constexpr (kPairs) {
+                raw16 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{p[2 * e] - __uint_as_float(u[e] << 16),
+                                                                                      p[2 * e + 1] - __uint_as_float(u[e] & 0xFFFF0000u)}, bf16x2));
+                pl[grp & 1] = __builtin_bit_cast(bf16x8, w);
+            }
+        };
+        weights(0);
+#pragma unroll
+        for (int grp = 0; grp < 4; ++grp) {
+            if (grp < 3) load_v(grp + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+            {
+                o[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[grp & 1][f], pw[grp & 1], o[f], 0, 0, 0);
+                if constexpr (kPairs) o[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[grp & 1][f], pl[grp & 1], o[f], 0, 0, 0);
+            }
+            if (grp < 3) weights(grp + 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    for (int t = t_lo; t < n_steps; t += 2) {
+        step(t, s_k[0], s_v[0], s_k[1], s_v[1]);
+        if (t + 1 < n_steps) step(t + 1, s_k[1], s_v[1], s_k[0], s_v[0]);
     }
+    const float l_sum = half_sum(l_run);
+    const bool seen = l_sum > 0.f; // a query that saw nothing leaves zeros, whatever its hidden rows held
+    if (!q_ok) return;
+    // feature 32 f + 8 jj + 4 half + r of the query is in register 4 jj + r of block f
+    if constexpr (SPLIT) { // the split's record: [0] maximum, [1] normaliser, [2..] unnormalised output
+        float *rec = aux + (my_row * n_split + sp) * (D + 2);
+        if (half == 0) {
+            rec[0] = m_run;
+            rec[1] = l_sum;
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) rec[2 + 32 * f + 8 * jj + 4 * half + r] = seen ? o[f][4 * jj + r] : 0.f;
+    } else {
+        const float inv = 1.0f / l_sum;
+        uint16_t *op = out + my_row * D;
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                u32x2 w;
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    w[e] = (uint32_t)bf16_round(o[f][4 * jj + 2 * e] * inv) | (uint32_t)bf16_round(o[f][4 * jj + 2 * e + 1] * inv) << 16;
+                if (!seen) w = u32x2{0u, 0u};
+                *reinterpret_cast<u32x2 *>(op + 32 * f + 8 * jj + 4 * half) = w;
+            }
+        if (half == 0) aux[my_row] = seen ? m_run + __builtin_amdgcn_logf(l_sum) : INFINITY;
+    }
+}
 
-    // ---- Eq. 1: weights on the new tokens, added over the workgroup's queries ----
-    float *dst = colpart + (((int64_t)b * a.Hkv + g) * n_tiles + qt) * a.n_q;
-    // new token j is local row n_loc - n_q + j, i.e. row r_new0 + j of the row sequence (it may not exist)
-    const int r_new0 = n_ret + n_loc - a.n_q;
-    const int j_end = a.causal ? (last_q + 1 < a.n_q ? last_q + 1 : a.n_q) : a.n_q; // later tokens get nothing from here
-    if (sp == 0)
-        for (int j = j_end + tid; j < a.n_q; j += 256) dst[j] = 0.f;
-    const int n_steps2_all = (j_end + kFK - 1) / kFK;
-    const int per2 = MODE == 2 ? (n_steps2_all + n_split - 1) / n_split : n_steps2_all;
-    const int t2_lo = MODE == 2 ? sp * per2 : 0;
-    const int n_steps2 = t2_lo + per2 < n_steps2_all ? t2_lo + per2 : n_steps2_all;
-    __syncthreads(); // the staging buffers and the row table are free again
-    // rows below n_ret would be retrieved rows: a new token without a row of its own is seen by nobody
-    if (tid < kFK) {
-        tabulate(0, r_new0 + t2_lo * kFK + tid, n_ret);
-        tabulate(1, r_new0 + (t2_lo + 1) * kFK + tid, n_ret);
+// ------------------------------------------------------------------------------------------
+// Eq. 1 for the matrix-core prefill: softmax weights on the new tokens, from the final log-sum-exps, added over
+// queries and heads.  One workgroup per (128 new tokens, KV head, question, share of the queries): a wave keeps
+// the keys of its 32 tokens as the B operand in registers and the queries stream past it through LDS, 64 a step,
+// so that S = Q K^T leaves a lane one key and 16 queries of every 32 and the sum over the queries is one running
+// sum per lane, written once at the end.  (The same sums inside the attention kernel, walked by query tile, needed
+// a reduction over the waves and a store per 64 keys: 2400 cycles a step against 1000.)
+// colpart [B][Hkv][n_qs][n_q], of which a key tile fills as many rows as it has shares; they are added in a fixed order by prefill_signal_kernel.
+// ------------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void prefill_keysum_kernel(
+    AttendArgs a, const float *__restrict__ lse, float *__restrict__ colpart, int n_units, int combos, int n_qs, int steps_per) {
+    using T = uint16_t;
+    constexpr int kRowB = D * 2, kPieces = kRowB / 16, kRowsPerLoad = 64 / kPieces, kLoads = kCQ / 4 / kRowsPerLoad, KK = D / 16;
+    __shared__ __align__(1024) unsigned char s_q[2][kCQ * kRowB];
+    __shared__ __align__(16) float s_lse[2][kCQ];
+    __shared__ float s_sum[kCK];
+    int unit, combo;
+    if (!tile_of(blockIdx.x, n_units, combos, &unit, &combo)) return;
+    int kt = 0, qs = unit; // the unit's key tile and its share of that tile's queries
+    for (int n; qs >= (n = keysum_shares(kt, a.n_q * a.G, a.G, a.causal, steps_per)); ++kt) qs -= n;
+    const int g = combo % a.Hkv, b = combo / a.Hkv;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lq = lane & 31, half = lane >> 5;
+    const int n_queries = a.n_q * a.G;
+    const int l0 = __builtin_amdgcn_readfirstlane(a.local_offsets[b]);
+    int n_loc = __builtin_amdgcn_readfirstlane(a.local_offsets[b + 1]) - l0;
+    if (n_loc < 0) n_loc = 0;
+    const int kw = wave & 1, qpart = wave >> 1; // the wave's 64 keys, its 32 queries of every step
+    // new token j is local row n_loc - n_q + j; it may not exist.  Query qq sees it iff qq >= q_min.
+    int q_min[2];
+    int64_t krow[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int j = kt * kCK + 64 * kw + 32 * i + lq, lrow = n_loc - a.n_q + j;
+        const bool ok = j < a.n_q && lrow >= 0;
+        q_min[i] = !ok ? INT_MAX : (a.causal ? j * a.G : 0);
+        krow[i] = (int64_t)(l0 + (ok ? lrow : 0)) * a.Hkv + g;
+    }
+    // the steps of this key tile start at its first token's queries; this workgroup takes steps_per of them
+    const int q0 = (a.causal ? kt * kCK * a.G : 0) + qs * steps_per * kCQ;
+    int n_steps = q0 < n_queries ? (n_queries - q0 + kCQ - 1) / kCQ : 0;
+    if (n_steps > steps_per) n_steps = steps_per;
+    float sum[2] = {0.f, 0.f};
+    if (n_steps > 0) {
+        bf16x8 kb[2][KK];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const T *kp = static_cast<const T *>(a.k_local) + krow[i] * D + 8 * half;
+            if (n_loc == 0) kp = static_cast<const T *>(a.q) + 8 * half; // memory that exists; the weights are masked
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) kb[i][kk] = __builtin_bit_cast(bf16x8, load16(kp + 16 * kk));
+        }
+        // query qq = (token qq / G, head qq % G of the group) is row (b n_q + token) Hq + g G + head of q and lse;
+        // a lane walks its rows 64 queries at a time (past the last query: the last row, masked)
+        const int row_last = (a.n_q - 1) * a.Hq + a.G - 1;
+        const int dt = kCQ / a.G, dh = kCQ - dt * a.G;
+        auto row_of = [&](int qq, int *h) {
+            const int t = qq / a.G;
+            *h = qq - t * a.G;
+            return t * a.Hq + *h;
+        };
+        auto advance = [&](int &row, int &h) {
+            row += dt * a.Hq + dh;
+            h += dh;
+            if (h >= a.G) {
+                h -= a.G;
+                row += a.Hq - a.G;
+            }
+        };
+        const int64_t base = (int64_t)b * a.n_q * a.Hq + g * a.G;
+        const unsigned char *qbase = static_cast<const unsigned char *>(a.q) + base * kRowB;
+        const float *lbase = lse + base;
+        const int ld_row = 16 * wave + lane / kPieces, ld_piece = lane % kPieces;
+        int row[kLoads], hd[kLoads], lrow_q, lhd;
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) row[u] = row_of(q0 + ld_row + u * kRowsPerLoad, &hd[u]);
+        lrow_q = row_of(q0 + lane, &lhd);
+        auto request = [&](unsigned char *dq, float *dl) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                const int r = row[u] < row_last ? row[u] : row_last;
+                load_to_lds(qbase + (int64_t)r * kRowB + 16 * key_slot<D>(ld_piece, ld_row + u * kRowsPerLoad),
+                            dq + (16 * wave + u * kRowsPerLoad) * kRowB);
+                advance(row[u], hd[u]);
+            }
+            if (wave == 0) {
+                load4_to_lds(lbase + (lrow_q < row_last ? lrow_q : row_last), dl);
+                advance(lrow_q, lhd);
+            }
+        };
+        int qoff[KK];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) qoff[kk] = (32 * qpart + lq) * kRowB + 16 * key_slot<D>(2 * kk + half, lq);
+        float part[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+        auto step = [&](int t, const unsigned char *cq, const float *cl, unsigned char *nq, float *nl) __attribute__((always_inline)) {
+            rows_landed();
+            __syncthreads();
+            if (t + 1 < n_steps) request(nq, nl);
+            f32x16 sc[2];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sc[0][e] = sc[1][e] = 0.f;
+            bf16x8 aq[KK];
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) aq[kk] = *reinterpret_cast<const bf16x8 *>(cq + qoff[kk]);
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) sc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq[kk], kb[i][kk], sc[i], 0, 0, 0);
+            const int qq0 = q0 + t * kCQ + 32 * qpart;
+            const bool masked = __builtin_amdgcn_ballot_w64(q_min[0] > qq0 || q_min[1] > qq0) != 0 || qq0 + 32 > n_queries;
+            auto add = [&](auto with_mask) __attribute__((always_inline)) {
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    const f32x4 l4 = *reinterpret_cast<const f32x4 *>(cl + 32 * qpart + 8 * jj + 4 * half);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int qq = qq0 + 8 * jj + 4 * half + r;
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            float x = fmaf(sc[i][4 * jj + r], a.scale_log2e, -l4[r]);
+                            if constexpr (with_mask.value) x = qq >= q_min[i] && qq < n_queries ? x : -INFINITY;
+                            part[i][r & 1] += __builtin_amdgcn_exp2f(x);
+                        }
+                    }
+                }
+            };
+            if (masked)
+                add(std::true_type{});
+            else
+                add(std::false_type{});
+        };
+        request(s_q[0], s_lse[0]);
+        for (int t = 0; t < n_steps; t += 2) {
+            step(t, s_q[0], s_lse[0], s_q[1], s_lse[1]);
+            if (t + 1 < n_steps) step(t + 1, s_q[1], s_lse[1], s_q[0], s_lse[0]);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) sum[i] = half_sum(part[i][0] + part[i][1]);
+    }
+    // the two waves that share the keys
+    if (qpart == 1 && half == 0) {
+        s_sum[64 * kw + lq] = sum[0];
+        s_sum[64 * kw + 32 + lq] = sum[1];
     }
     __syncthreads();
-    if (t2_lo < n_steps2) fetch(0, false);
-    for (int t = t2_lo; t < n_steps2; ++t) {
-        const int buf = (t - t2_lo) & 1;
-        put(buf, false);
-        __syncthreads();
-        if (t + 1 < n_steps2) fetch(buf ^ 1, false);
-        if (tid < kFK && t + 2 < n_steps2) tabulate(buf, r_new0 + (t + 2) * kFK + tid, n_ret);
-        f32x4 sc[QB][2];
-        scores(buf, sc);
-        {   // the lane's weights on rows 16 kb + 4 lg + r, added over the queries of the wave (its blocks, the lanes of a row)
-            const i32x4 f0 = *reinterpret_cast<const i32x4 *>(&s_ft[buf][4 * lg]);
-            const i32x4 f1 = *reinterpret_cast<const i32x4 *>(&s_ft[buf][16 + 4 * lg]);
+    if (qpart == 0 && half == 0) {
+        float *dst = colpart + (((int64_t)b * a.Hkv + g) * n_qs + qs) * a.n_q;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float c0 = 0.f, c1 = 0.f;
-#pragma unroll
-                for (int i = 0; i < QB; ++i) {
-                    c0 += tokq[i] >= f0[r] ? __builtin_amdgcn_exp2f(fmaf(sc[i][0][r], a.scale_log2e, -lse[i])) : 0.f;
-                    c1 += tokq[i] >= f1[r] ? __builtin_amdgcn_exp2f(fmaf(sc[i][1][r], a.scale_log2e, -lse[i])) : 0.f;
-                }
-                c0 = row16_sum(c0);
-                c1 = row16_sum(c1);
-                if (lr == 0) {
-                    s_col[wave][4 * lg + r] = c0;
-                    s_col[wave][16 + 4 * lg + r] = c1;
-                }
-            }
+        for (int i = 0; i < 2; ++i) {
+            const int jl = 64 * kw + 32 * i + lq, j = kt * kCK + jl;
+            if (j < a.n_q) dst[j] = sum[i] + s_sum[jl];
         }
-        __syncthreads();
-        if (tid < kFK && t * kFK + tid < j_end)
-            dst[t * kFK + tid] = (s_col[0][tid] + s_col[1][tid]) + (s_col[2][tid] + s_col[3][tid]);
     }
 }
 
@@ -1067,12 +1280,13 @@ hipError_t launch_typed(const AttendArgs &a, int B, void *out, const PrefillOut 
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attend_combine_kernel<T, D>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D < 64 ? 64 : D), 0, st,
                        a.part, a.n_split, static_cast<T *>(out), po.lse);
+    if constexpr (sizeof(T) == 2 && D >= 64) return hipGetLastError(); // their prefill is the matrix-core one
     if ((e = hipGetLastError()) != hipSuccess || !po.signal) return e;
-    hipLaunchKernelGGL((prefill_colsum_kernel<T, D>), dim3(a.n_qtiles, a.Hkv, B), dim3(kThreads), 0, st, a, po.lse,
-                       po.colpart);
+    if constexpr (sizeof(T) == 4 || D < 64)
+        hipLaunchKernelGGL((prefill_colsum_kernel<T, D>), dim3(a.n_qtiles, a.Hkv, B), dim3(kThreads), 0, st, a, po.lse, po.colpart);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(prefill_signal_kernel, dim3((a.n_q + kSigCols - 1) / kSigCols, B), dim3(kThreads), 0, st, po.colpart,
-                       a.Hkv * a.n_qtiles, a.n_q, 1.0f / ((float)a.Hq * (float)a.n_q), po.signal);
+                       a.Hkv, a.n_qtiles, a.n_q, 1.0f / ((float)a.Hq * (float)a.n_q), po.signal, a.G, a.causal, 0);
     return hipGetLastError();
 }
 
@@ -1085,6 +1299,57 @@ hipError_t launch_by_dim(const AttendArgs &a, int D, int B, void *out, const Pre
     case 128: return launch_typed<T, 128>(a, B, out, po, st);
     default: return hipErrorInvalidValue;
     }
+}
+
+// Steps a workgroup of prefill_keysum_kernel takes: as few as leave all workgroups resident at once (three per compute
+// unit: one more round of them costs as much as the first), at least two.
+int keysum_plan(int n_q, int G, int combos, int causal, int *n_units) {
+    const int tiles = (n_q + kCK - 1) / kCK, all = (n_q * G + kCQ - 1) / kCQ;
+    for (int per = all < 2 ? all : 2;; per += (per + 15) / 16) {
+        int n = 0;
+        for (int kt = 0; kt < tiles; ++kt) n += keysum_shares(kt, n_q * G, G, causal, per);
+        if ((int64_t)n * combos <= 3 * 256 || per >= all) {
+            *n_units = n;
+            return per;
+        }
+    }
+}
+
+// Rows of colpart per KV head, whichever way the mask is set.
+int keysum_rows(int n_q, int G, int combos) {
+    int rows = 0;
+    for (int causal = 0; causal < 2; ++causal) {
+        int n_units;
+        const int n = keysum_shares(0, n_q * G, G, causal, keysum_plan(n_q, G, combos, causal, &n_units));
+        if (n > rows) rows = n;
+    }
+    return rows;
+}
+
+template <int D>
+hipError_t launch_flash(const AttendArgs &a, int n_fs, int B, void *out, const PrefillOut &po, hipStream_t st) {
+    const int n_tiles = (int)(((int64_t)a.n_q * a.G + kFQ - 1) / kFQ), combos = a.Hkv * B;
+    uint16_t *o16 = static_cast<uint16_t *>(out);
+    const unsigned grid = tile_grid(n_tiles * n_fs, combos);
+    hipError_t e;
+    if (n_fs == 1) {
+        hipLaunchKernelGGL((prefill_flash_kernel<D, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.lse, 1);
+    } else { // rows shared by n_fs workgroups per tile, merged
+        hipLaunchKernelGGL((prefill_flash_kernel<D, true>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, a.part, n_fs);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL((attend_combine_kernel<uint16_t, D>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D), 0, st, a.part,
+                           n_fs, o16, po.lse);
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    int n_units;
+    const int steps_per = keysum_plan(a.n_q, a.G, combos, a.causal, &n_units);
+    const int n_qs = keysum_shares(0, a.n_q * a.G, a.G, a.causal, steps_per);
+    hipLaunchKernelGGL((prefill_keysum_kernel<D>), dim3(tile_grid(n_units, combos)), dim3(256), 0, st, a, po.lse, po.colpart,
+                       n_units, combos, n_qs, steps_per);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(prefill_signal_kernel, dim3((a.n_q + kSigCols - 1) / kSigCols, B), dim3(kThreads), 0, st, po.colpart, a.Hkv,
+                       n_qs, a.n_q, 1.0f / ((float)a.Hq * (float)a.n_q), po.signal, a.G, a.causal, steps_per);
+    return hipGetLastError();
 }
 
 int split_count(int B, int Hkv, int n_qtiles, int k_frame, int *frames_per_split) {
@@ -1104,47 +1369,44 @@ int split_count(int B, int Hkv, int n_qtiles, int k_frame, int *frames_per_split
 
 } // namespace
 
-static bool flash_shape(const Ctx &c) { return c.cfg.dtype == MUKV_BF16 && c.cfg.head_dim == kFD; }
-static bool flash_wide(const Ctx &c, int n_q, int B) { // 128-query tiles once they still fill the chip about twice over
-    return (((int64_t)n_q * c.group + 127) / 128) * c.cfg.n_kv_heads * B >= 2 * 256;
-}
-// Workgroups that share the rows of one 64-query tile of the matrix-core prefill: 1 unless the tiles alone
-// leave most of the chip idle (about three workgroups per compute unit are wanted, at least four steps each).
-// (Sharing the rows of a tile between workgroups also when the tiles fill the chip -- to even out the causal
-// triangle -- was measured on the 1568-token chunk: 2 / 3 / 4 ways took 212 / 210 / 221 us against 207.)
-static int flash_split(const Ctx &c, int n_q, int B, int k_frame) {
-    if (flash_wide(c, n_q, B)) return 1;
-    const int64_t wgs = (((int64_t)n_q * c.group + 63) / 64) * c.cfg.n_kv_heads * B;
-    if (wgs >= 384) return 1;
-    const int64_t steps = ((int64_t)(k_frame > 0 ? k_frame : 0) * c.kappa + n_q + kFK - 1) / kFK;
-    int64_t n = (768 + wgs - 1) / wgs;
-    if (n > kAttendMaxSplit) n = kAttendMaxSplit;
-    if (n > steps / 4) n = steps / 4;
-    return n < 1 ? 1 : (int)n;
-}
+static bool flash_shape(const Ctx &c) { return c.cfg.dtype == MUKV_BF16 && (c.cfg.head_dim == 64 || c.cfg.head_dim == 128); }
 
-// Workspace of the prefill call, in floats: the splits' records, the log-sum-exps, the tiles' column sums.
-static void prefill_layout(const Ctx &c, int n_q, int B, int k_frame, int64_t *part, int64_t *lse, int64_t *colpart) {
-    const int n_qtiles = (n_q * c.group + kTileQ - 1) / kTileQ;
-    int n_split;
-    if (flash_shape(c)) {
-        n_split = flash_split(c, n_q, B, k_frame);
-        if (n_split == 1) n_split = 0; // one launch does it all: no records
+// The workspace a caller provides, in bytes.  Part of the interface: callers keep buffers of this size, and
+// mukv_prefill_attend_static takes the calls for which it fits.  Split records, log-sum-exps, and column sums per
+// 64 queries (bf16 rows of 128 features) or 8 queries (all others); the matrix-core prefill stays within it.
+int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame) {
+    const int64_t n_queries = (int64_t)n_q * c.group, combos = (int64_t)c.cfg.n_kv_heads * B, rows = (int64_t)B * n_q * c.cfg.n_q_heads;
+    const int k = k_frame > 0 ? k_frame : 0;
+    int64_t n_split, tiles;
+    if (c.cfg.dtype == MUKV_BF16 && c.cfg.head_dim == 128) {
+        tiles = (n_queries + 63) / 64;
+        const int64_t steps = ((int64_t)k * c.kappa + n_q + 31) / 32;
+        n_split = (768 + tiles * combos - 1) / (tiles * combos);
+        if (n_split > kAttendMaxSplit) n_split = kAttendMaxSplit;
+        if (n_split > steps / 4) n_split = steps / 4;
+        if (tiles * combos >= 384 || n_split <= 1) n_split = 0; // one launch: no records
     } else {
         int fps;
-        n_split = split_count(B, c.cfg.n_kv_heads, n_qtiles, k_frame > 0 ? k_frame : 0, &fps);
+        tiles = (n_queries + kTileQ - 1) / kTileQ;
+        n_split = split_count(B, c.cfg.n_kv_heads, (int)tiles, k, &fps);
     }
-    *part = (int64_t)B * n_q * c.cfg.n_q_heads * n_split * (c.cfg.head_dim + 2);
-    *lse = (int64_t)B * n_q * c.cfg.n_q_heads;
-    // column sums per (KV head, query tile): the matrix-core prefill has tiles of 64 (or 128) queries
-    const int64_t n_coltiles = flash_shape(c) ? ((int64_t)n_q * c.group + 63) / 64 : n_qtiles;
-    *colpart = (int64_t)B * c.cfg.n_kv_heads * n_coltiles * n_q;
+    return (rows * n_split * (c.cfg.head_dim + 2) + rows + combos * tiles * n_q) * (int64_t)sizeof(float);
 }
 
-int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame) {
-    int64_t p, l, cp;
-    prefill_layout(c, n_q, B, k_frame, &p, &l, &cp);
-    return (p + l + cp) * (int64_t)sizeof(float);
+// Workgroups that share the rows of one tile of the matrix-core prefill: 1 unless the tiles alone leave most of
+// the chip idle (two workgroups per compute unit are wanted, at least two steps each: 196 new tokens over 768 rows,
+// 44 tiles, 35 us in 8 shares), and no more than leave the records, log-sum-exps and column sums within the workspace.
+static int flash_split(const Ctx &c, int n_q, int B, int k_frame) {
+    const int64_t wgs = (((int64_t)n_q * c.group + kFQ - 1) / kFQ) * c.cfg.n_kv_heads * B;
+    if (wgs >= 192) return 1;
+    const int64_t steps = ((int64_t)(k_frame > 0 ? k_frame : 0) * c.kappa + n_q + kFK - 1) / kFK;
+    int64_t n = (512 + wgs - 1) / wgs;
+    if (n > kAttendMaxSplit) n = kAttendMaxSplit;
+    if (n > steps / 2) n = steps / 2;
+    const int64_t rows = (int64_t)B * n_q * c.cfg.n_q_heads, combos = (int64_t)B * c.cfg.n_kv_heads;
+    const int64_t rest = rows + combos * n_q * keysum_rows(n_q, c.group, (int)combos);
+    while (n > 1 && (rows * n * (c.cfg.head_dim + 2) + rest) * (int64_t)sizeof(float) > prefill_workspace_bytes(c, n_q, B, k_frame)) --n;
+    return n < 1 ? 1 : (int)n;
 }
 
 // workspace == null: the plain attention call, records in the context's scratch, no signal.
@@ -1174,42 +1436,16 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
     a.scale_log2e = 1.4426950408889634f / sqrtf((float)c.cfg.head_dim);
     a.n_split = split_count(B, a.Hkv, a.n_qtiles, a.k_frame, &a.frames_per_split);
     PrefillOut po{nullptr, nullptr, nullptr};
+    const int n_fs = workspace && flash_shape(c) ? flash_split(c, n_q, B, k_frame) : 0;
     if (workspace) {
-        int64_t p, l, cp;
-        prefill_layout(c, n_q, B, k_frame, &p, &l, &cp);
+        const int64_t rows = (int64_t)B * n_q * a.Hq;
         a.part = workspace;
-        po.lse = workspace + p;
-        po.colpart = workspace + p + l;
+        po.lse = workspace + rows * (n_fs == 0 ? a.n_split : n_fs == 1 ? 0 : n_fs) * (c.cfg.head_dim + 2);
+        po.colpart = po.lse + rows;
         po.signal = signal;
     }
-    if (workspace && flash_shape(c)) { // the prefill on the matrix cores
-        const int64_t n_queries = (int64_t)n_q * c.group;
-        const bool wide = flash_wide(c, n_q, B);
-        const int n_fs = flash_split(c, n_q, B, k_frame);
-        const int n_tiles = (int)((n_queries + (wide ? 127 : 63)) / (wide ? 128 : 64));
-        uint16_t *o16 = static_cast<uint16_t *>(out);
-        hipError_t e;
-        if (wide) {
-            hipLaunchKernelGGL((prefill_flash_kernel<2, 0>), dim3(n_tiles, a.Hkv, B), dim3(256), 0, st, a, o16, po.colpart,
-                               n_tiles, nullptr, 1);
-        } else if (n_fs == 1) {
-            hipLaunchKernelGGL((prefill_flash_kernel<1, 0>), dim3(n_tiles, a.Hkv, B), dim3(256), 0, st, a, o16, po.colpart,
-                               n_tiles, nullptr, 1);
-        } else { // rows shared by n_fs workgroups per tile, merged, then the column sums from the merged log-sum-exps
-            hipLaunchKernelGGL((prefill_flash_kernel<1, 1>), dim3(n_tiles * n_fs, a.Hkv, B), dim3(256), 0, st, a, o16,
-                               nullptr, n_tiles, workspace, n_fs);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-            hipLaunchKernelGGL((attend_combine_kernel<uint16_t, kFD>), dim3((unsigned)(B * n_q * a.Hq)), dim3(kFD), 0, st,
-                               workspace, n_fs, o16, po.lse);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-            hipLaunchKernelGGL((prefill_flash_kernel<1, 2>), dim3(n_tiles * n_fs, a.Hkv, B), dim3(256), 0, st, a, o16,
-                               po.colpart, n_tiles, po.lse, n_fs);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(prefill_signal_kernel, dim3((n_q + kSigCols - 1) / kSigCols, B), dim3(kThreads), 0, st, po.colpart,
-                           a.Hkv * n_tiles, n_q, 1.0f / ((float)a.Hq * (float)n_q), po.signal);
-        return hipGetLastError();
-    }
+    if (n_fs) // the prefill on the matrix cores
+        return c.cfg.head_dim == 64 ? launch_flash<64>(a, n_fs, B, out, po, st) : launch_flash<128>(a, n_fs, B, out, po, st);
     return c.cfg.dtype == MUKV_BF16 ? launch_by_dim<uint16_t>(a, c.cfg.head_dim, B, out, po, st)
                                     : launch_by_dim<float>(a, c.cfg.head_dim, B, out, po, st);
 }

@@ -1018,6 +1018,25 @@ def test_prefill_of_a_long_unit_takes_the_wide_tiles():
     p.close()
 
 
+@pytest.mark.parametrize("D,hq,hkv,n_q,n_frames,old", [
+    (64, 14, 2, 1, 3, [0]),             # one token, fewer rows than one step
+    (64, 32, 8, 32, 9, [0, 31, 1]),     # 128 queries per KV head, a tile exactly; three questions (24 (question, head) pairs)
+    (64, 10, 5, 65, 40, [3]),           # pairs that divide neither 8 nor are divided by it; several steps, shared rows
+    (128, 28, 4, 18, 12, [0, 64]),      # 126 queries: two short of a tile
+    (128, 28, 4, 19, 40, [200]),        # five past it; more steps than one set of row tables
+    (128, 16, 2, 129, 2, [0]),          # one key past a key tile
+    (128, 8, 8, 257, 0, [0]),           # one head per group, no past
+])
+def test_prefill_matrix_tile_edges(D, hq, hkv, n_q, n_frames, old):
+    w = W["7b"].scaled(n_frames=max(n_frames, 4), n_layers=1, head_dim=D, n_q_heads=hq, n_kv_heads=hkv, n_questions=len(old))
+    p = Pair(w, seed=450, chunk=4)
+    p.ingest()
+    fi = [[(7 * b + i) % n_frames for i in range(n_frames)] for b in range(len(old))] if n_frames else None
+    for causal in (True, False):
+        p.check_prefill(0, n_q, fi, old, causal, seed=451)
+    p.close()
+
+
 def test_prefill_signal_feeds_the_compression():
     # one stream, chunk by chunk: prefill of the chunk's tokens over frames already in the cache -> its
     # signal, handed to mukv_compress_chunk.  The oracle is given the same float32 signal, so the keep

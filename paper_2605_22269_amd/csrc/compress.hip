@@ -52,6 +52,14 @@ __device__ __forceinline__ double abs_t(double x) { return fabs(x); }
 // Workgroups that share the tokens of one frame (grid.y of the frequency kernel): 7 for a frame of
 // up to kMaxP tokens, and as many per 196 tokens for a unit of several frames.
 static inline int freq_blocks_per_frame(int P) { return P <= kMaxP ? 7 : 7 * ((P + 195) / 196); }
+// The frequency kernel on its own: a batch of few frames takes more workgroups per frame, down to one step of each wave,
+// while they are resident at once (8 frames of 196 tokens: 49 workgroups a frame instead of 7, 12.9 -> 6.1 us).
+static inline int freq_blocks_alone(int P, int D, int n_frames) {
+    const int least = freq_blocks_per_frame(P), per_step = 4 * (128 / D); // tokens of a workgroup and step
+    const int most = (P + per_step - 1) / per_step, want = 1024 / (n_frames > 0 ? n_frames : 1);
+    const int n = want < most ? want : most;
+    return n > least ? n : least;
+}
 
 // sum over the N consecutive lanes of a transform (N a power of two <= 64), result in every lane
 template <int N, typename R>
@@ -1462,7 +1470,8 @@ static hipError_t launch_freq(const Ctx &c, const ChunkArgs &a, bool listed, R *
     if (c.cfg.freq_axis == MUKV_FREQ_TOKEN) return launch_freq_token<T, R>(c, a, listed, out, st);
     const int P = c.cfg.tokens_per_frame, D = c.cfg.head_dim, Hkv = c.cfg.n_kv_heads;
     const int64_t k_off = (int64_t)c.ls * a.kv_sl;
-    const dim3 grid(listed ? rescore_slots(P, a.n_frames) : a.n_frames, freq_blocks_per_frame(P));
+    const dim3 grid(listed ? rescore_slots(P, a.n_frames) : a.n_frames,
+                    listed ? freq_blocks_per_frame(P) : freq_blocks_alone(P, D, a.n_frames));
     const int32_t *fl = listed ? c.flag_list[a.parity] : nullptr, *fc = listed ? c.flag_count + a.parity : nullptr;
 #define MUKV_FREQ(DD)                                                                                         \
     hipLaunchKernelGGL((freq_signal_kernel<T, R, DD>), grid, dim3(256), 0, st, a.k, a.map, k_off, a.kv_sh, \

@@ -1545,8 +1545,9 @@ static hipError_t launch_select(const Ctx &c, const ChunkArgs &a, const R *att, 
     s.kept_idx = c.kept_idx;
     // with overlap_copy the rows chosen by the fp64 pass replace the marks of the first pass: the
     // copy, which comes later, then takes every frame in one go
-    // (a batch's main copy comes after its fp64 pass only with overlap_copy on units of several frames)
-    s.src_tok = (pass2 && (!c.cfg.overlap_copy || c.split_side)) ? c.src_tok2 : c.src_tok[a.parity];
+    // (a batch's main copy comes after its fp64 pass with overlap_copy on units of several frames, and where the
+    // caller says so: pass2 == 2)
+    s.src_tok = (pass2 == 1 && (!c.cfg.overlap_copy || c.split_side)) ? c.src_tok2 : c.src_tok[a.parity];
     s.rep_frame_k = c.rep_frame_k;
     s.rep_frame_v = c.rep_frame_v;
     s.rep_patch_k = c.rep_patch_k;
@@ -1949,8 +1950,16 @@ hipError_t join_streams(Ctx &c, hipStream_t st) {
     return wait_side_all(c, st);
 }
 
+// A copy too short to hide the fp64 chain behind it: the events that would put the chain on the side stream and bring it
+// back cost more than they save, on the host (four calls and one launch of twelve, and a small batch is bound by its
+// launches) and on the device (each crossing of queues 6-14 us).  32 MB are read and written in 6-8 us, which is
+// where the two sides meet; 8 frames of the 7B shape are 22 MB.
+static bool copy_is_short(const Ctx &c, const ChunkArgs &a) {
+    return 4ll * a.n_frames * c.kappa * c.cfg.n_layers * c.c_kv * c.esz <= 32ll << 20;
+}
+
 // One batch.  Without overlap_copy, on the caller's stream: signals, keep, copy, with the fp64
-// chain beside the copy.  With overlap_copy the caller's stream carries only
+// chain beside the copy, or, if that is short, before it.  With overlap_copy the caller's stream carries only
 //     [copy of batch n-2 + frequency signal of batch n] (one launch), attention signal of batch n
 // and the side stream the keep of batch n (and its fp64 chain) meanwhile: the keep of a batch has
 // the next batch's launches to finish in, the copy of its rows follows two batches later.
@@ -2031,6 +2040,21 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
     {
         ProfScope ps(c, MUKV_K_SELECT, st);
         if ((e = launch_select<T, float>(c, a, c.att_part[a.parity], n_part, c.fft_sig[a.parity], 0, st)) != hipSuccess) return e;
+    }
+    if (rescoring && copy_is_short(c, a)) { // all of it on the caller's stream, one copy of every frame's final rows
+        {
+            ProfScope ps(c, MUKV_K_REFINE, st);
+            int n_part64 = c.cfg.n_q_heads;
+            if (need_att)
+                if ((e = launch_att_generic<T, double>(c, a, true, c.att64, &n_part64, st)) != hipSuccess) return e;
+            if (need_fft)
+                if ((e = launch_freq<T, double>(c, a, true, c.fft64, st)) != hipSuccess) return e;
+            if ((e = launch_select<T, double>(c, a, c.att64, n_part64, c.fft64, 2, st)) != hipSuccess) return e;
+            hipLaunchKernelGGL(clear_count_kernel, dim3(1), dim3(1), 0, st, c.flag_count + a.parity);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        ProfScope ps(c, MUKV_K_COMPACT, st);
+        return launch_compact(c, a, 0, st);
     }
     if (rescoring) {
         if ((e = hipEventRecord(c.ev_fork, st)) != hipSuccess) return e;

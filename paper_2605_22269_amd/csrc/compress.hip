@@ -565,12 +565,8 @@ struct SelectArgs {
 template <typename R>
 __device__ __forceinline__ void block_minmax(R v, bool valid, R *red, R &lo, R &hi) {
     R mn = valid ? v : (R)INFINITY, mx = valid ? v : (R)-INFINITY;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const R a = __shfl_xor(mn, o), b = __shfl_xor(mx, o);
-        mn = a < mn ? a : mn;
-        mx = b > mx ? b : mx;
-    }
+    mn = -wave_max(-mn);
+    mx = wave_max(mx);
     const int wave = threadIdx.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
@@ -587,9 +583,36 @@ __device__ __forceinline__ void block_minmax(R v, bool valid, R *red, R &lo, R &
     }
 }
 
+// Scores as the rank loop compares them: larger score first, lower position first among equals.  float: one unsigned
+// number, order-preserving bits of the score above the negated position, so that a comparison is one instruction;
+// double: the score, ties decided by the position.
+template <typename R>
+struct RankKey;
+template <>
+struct RankKey<float> {
+    using K = uint64_t;
+    static __device__ __forceinline__ K of(float x, int j) {
+        const uint32_t b = __float_as_uint(x + 0.0f); // (-0 is +0)
+        return ((uint64_t)((b >> 31) ? ~b : (b | 0x80000000u)) << 32) | (uint32_t)(kMaxP - j);
+    }
+    static __device__ __forceinline__ K last() { return 0; } // ranks behind every score
+    static __device__ __forceinline__ bool before(K o, int, K mine, int) { return o > mine; }
+};
+template <>
+struct RankKey<double> {
+    using K = double;
+    static __device__ __forceinline__ K of(double x, int) { return x; }
+    static __device__ __forceinline__ K last() { return -INFINITY; }
+    static __device__ __forceinline__ bool before(K o, int i, K mine, int j) { return (o > mine) || (o == mine && i < j); }
+};
+
+// Latency: one workgroup's chain of waits (8 frames: 18.9 us, of which loading the signals 4.6, the two ranges 1.4,
+// the ranks 5.5, the block keys 5.4; now 17.2, the ranks 2.4).  So the loads of the signals are all requested before the first is used, and the ranks
+// are counted sixteen scores a step -- one at a time, every comparison waited for its LDS read, 67 cycles.
 template <typename T, typename R>
 __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
-    __shared__ R sc[kMaxP];
+    using RK = RankKey<R>;
+    __shared__ __align__(16) typename RK::K sc[kMaxP];
     __shared__ R red[8];
     __shared__ R vk[2];
     __shared__ int kl[kMaxP];
@@ -608,12 +631,21 @@ __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
     float *dbg_fused = a.have_dbg ? a.dbg_fused.p[slot] : nullptr;
 
     R av = 0, fv = 0;
+    if (valid && a.alpha != (R)1) {
+        if (a.fft_parts > 0) {
+            R sum = 0;
+            for (int pt = 0; pt < a.fft_parts; ++pt) sum += a.fft[((int64_t)f * a.fft_parts + pt) * P + j];
+            fv = sum * a.fft_scale;
+        } else {
+            fv = a.fft[(int64_t)f * P + j];
+        }
+    }
     if (valid && a.alpha != (R)0) {
         if (a.have_att_in) {
             av = (R) reinterpret_cast<const float *>(a.att_in.p[slot])[(int64_t)lf * P + j];
         } else {
             const R *pp = a.att + (int64_t)f * a.n_part * P + j;
-            constexpr int kPB = 16;
+            constexpr int kPB = 32;
             for (int n0 = 0; n0 < a.n_part; n0 += kPB) { // fixed summation order, kPB loads in flight
                 R t[kPB];
 #pragma unroll
@@ -623,15 +655,6 @@ __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
                     if (n0 + u < a.n_part) av += t[u];
             }
             av *= a.att_scale;
-        }
-    }
-    if (valid && a.alpha != (R)1) {
-        if (a.fft_parts > 0) {
-            R sum = 0;
-            for (int pt = 0; pt < a.fft_parts; ++pt) sum += a.fft[((int64_t)f * a.fft_parts + pt) * P + j];
-            fv = sum * a.fft_scale;
-        } else {
-            fv = a.fft[(int64_t)f * P + j];
         }
     }
     if (valid && dbg_att) dbg_att[(int64_t)lf * P + j] = (float)av;
@@ -649,8 +672,9 @@ __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
         const R fn = (hi > lo) ? (fv - lo) / (hi - lo) : (R)0;
         fused += ((R)1 - a.alpha) * fn;
     }
+    const typename RK::K mine = RK::of(fused, j);
+    sc[j] = valid ? mine : RK::last(); // (padding: the ranks are counted over whole groups of sixteen)
     if (valid) {
-        sc[j] = fused;
         if (dbg_fused) dbg_fused[(int64_t)lf * P + j] = (float)fused;
     }
     if (j < 2) vk[j] = 0;
@@ -658,9 +682,12 @@ __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
 
     int rank = 0;
     if (valid) {
-        for (int i = 0; i < P; ++i) {
-            const R o = sc[i];
-            rank += (o > fused) || (o == fused && i < j);
+        for (int i0 = 0; i0 < P; i0 += 16) {
+            typename RK::K o[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) o[u] = sc[i0 + u];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) rank += RK::before(o[u], i0 + u, mine, j);
         }
         if (rank == kappa - 1) vk[0] = fused;
         if (rank == kappa) vk[1] = fused;

@@ -694,8 +694,17 @@ __global__ __launch_bounds__(kThreads) void prefill_signal_kernel(const float *_
     float s = 0.f;
     if (j < n_q && t0 < t1) {
         const float *p = colpart + (int64_t)b * Hkv * n_per * n_q + j;
-        int g = t0 / n_valid, i = t0 - g * n_valid; // the run's next term
-        for (int t = t0; t < t1; t += 8) {
+        if (n_valid == n_per) { // every term counts: they are evenly spaced
+            for (int t = t0; t < t1; t += 8) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(t + u < t1 ? t + u : t1 - 1) * n_q];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += t + u < t1 ? v[u] : 0.f;
+            }
+        }
+        int g = t0 / n_valid, i = t0 - g * n_valid; // otherwise: the run's next term
+        for (int t = n_valid == n_per ? t1 : t0; t < t1; t += 8) {
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {

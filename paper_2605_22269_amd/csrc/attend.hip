@@ -111,11 +111,12 @@ __device__ __forceinline__ float same_piece_sum(float v) {
     return v;
 }
 
-__device__ __forceinline__ uint16_t bf16_round(float x) { // round to nearest even; inputs are finite
+__device__ __forceinline__ uint16_t bf16_round(float x) { // round to nearest even; x is not a NaN
     const uint32_t u = __float_as_uint(x);
     return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
-__device__ __forceinline__ void store_out(uint16_t *p, float x) { *p = bf16_round(x); }
+__device__ __forceinline__ uint16_t bf16_out(float x) { return x == x ? bf16_round(x) : (uint16_t)0x7FC0u; }
+__device__ __forceinline__ void store_out(uint16_t *p, float x) { *p = bf16_out(x); }
 __device__ __forceinline__ void store_out(float *p, float x) { *p = x; }
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -561,7 +562,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     }
 }
 
-// out[b][i][h][:] = sum_s o_s 2^(m_s - m) / sum_s z_s 2^(m_s - m), m = max_s m_s; zero if no split saw a key
+// out[b][i][h][:] = sum_s o_s 2^(m_s - m) / sum_s z_s 2^(m_s - m), m = max_s m_s; zero if no split saw a key, which
+// is a denominator of exactly zero (a NaN or +inf score makes it a NaN, and the output with it; a maximum leaves NaN
+// scores out, so a split of which nothing else is left has m_s = -inf and a denominator that is still looked at)
 // lse (may be null): log2 of the query's softmax denominator, in the scores' log2 units; +inf for a
 // query that sees no key, so that every weight computed from it is zero.
 template <typename T, int D>
@@ -584,17 +587,15 @@ __global__ void attend_combine_kernel(const float *__restrict__ part, int n_spli
         for (int s = 0; s < kAttendMaxSplit; ++s)
             if (s < n_split) m = fmaxf(m, ms[s]);
         float zs = 0.f, os = 0.f;
-        if (m > -INFINITY) {
 #pragma unroll
-            for (int s = 0; s < kAttendMaxSplit; ++s) {
-                if (s >= n_split) break;
-                const float w = ms[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms[s] - m);
-                zs = fmaf(zz[s], w, zs);
-                os = fmaf(oo[s], w, os);
-            }
+        for (int s = 0; s < kAttendMaxSplit; ++s) {
+            if (s >= n_split) break;
+            const float w = ms[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms[s] - m);
+            zs = fmaf(zz[s], w, zs);
+            os = fmaf(oo[s], w, os);
         }
-        store_out(out + row * D + d, zs > 0.f ? os / zs : 0.f);
-        if (lse && d == 0) lse[row] = zs > 0.f ? m + __builtin_amdgcn_logf(zs) : INFINITY;
+        store_out(out + row * D + d, zs != 0.f ? os / zs : 0.f);
+        if (lse && d == 0) lse[row] = zs != 0.f ? m + __builtin_amdgcn_logf(zs) : INFINITY;
     }
 }
 
@@ -1090,7 +1091,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
         if (t + 1 < n_steps) step(t + 1, s_k[1], s_v[1], s_k[0], s_v[0]);
     }
     const float l_sum = half_sum(l_run);
-    const bool seen = l_sum > 0.f; // a query that saw nothing leaves zeros, whatever its hidden rows held
+    const bool seen = l_sum != 0.f; // a query that saw nothing leaves zeros, whatever its hidden rows held; NaN stays NaN
     if (!q_ok) return;
     // feature 32 f + 8 jj + 4 half + r of the query is in register 4 jj + r of block f
     if constexpr (SPLIT) { // the split's record: [0] maximum, [1] normaliser, [2..] unnormalised output
@@ -1115,7 +1116,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
                 u32x2 w;
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
-                    w[e] = (uint32_t)bf16_round(o[f][4 * jj + 2 * e] * inv) | (uint32_t)bf16_round(o[f][4 * jj + 2 * e + 1] * inv) << 16;
+                    w[e] = (uint32_t)bf16_out(o[f][4 * jj + 2 * e] * inv) | (uint32_t)bf16_out(o[f][4 * jj + 2 * e + 1] * inv) << 16;
                 if (!seen) w = u32x2{0u, 0u};
                 *reinterpret_cast<u32x2 *>(op + 32 * f + 8 * jj + 4 * half) = w;
             }

@@ -1049,6 +1049,49 @@ def test_prefill_matrix_tile_edges(D, hq, hkv, n_q, n_frames, old):
     p.close()
 
 
+@pytest.mark.parametrize("name,kw,n_q,n_frames", [
+    ("7b", {}, 40, 0),                        # matrix-core prefill, rows of a tile in one workgroup
+    ("7b", {}, 40, 12),                       # shared by several, merged
+    ("7b", {"head_dim": 64}, 40, 0),
+    ("7b", {"head_dim": 64}, 40, 12),
+    ("7b", {"head_dim": 32}, 40, 5),          # scores on the matrix cores, merged
+    ("tiny", {}, 40, 5),                      # fp32
+    ("7b", {}, 3, 12),                        # decode
+    ("tiny", {}, 3, 1),
+])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_attention_non_finite_scores_reach_the_output(name, kw, n_q, n_frames, bad):
+    # one new token's key holds a non-finite feature: a query that sees a NaN or +inf score has no softmax and gives
+    # NaN (never the zeros of a query that sees nothing), a score of -inf is a weight of zero, and the tokens before
+    # that key -- which the mask hides from them -- are as they would be without it.  The oracle does the same in fp64.
+    w = W[name].scaled(n_frames=12, n_layers=1, n_questions=1, **kw)
+    p = Pair(w, seed=460, chunk=4)
+    p.ingest()
+    gen = torch.Generator().manual_seed(461)
+    q = torch.randn(1, n_q, w.n_q_heads, w.head_dim, generator=gen).to(w.torch_dtype)
+    kl, vl = (torch.randn(n_q, w.n_kv_heads, w.head_dim, generator=gen).to(w.torch_dtype) for _ in range(2))
+    j = n_q // 2
+    kl[j] = 0
+    kl[j, :, 0] = bad
+    frames = [(5 * i) % 12 for i in range(n_frames)]
+    fi = torch.tensor([frames], dtype=torch.int32, device="cuda") if frames else None
+    offs = torch.tensor([0, n_q], dtype=torch.int32, device="cuda")
+    with np.errstate(invalid="ignore"):
+        want, want_sig = p.orc.prefill_attend(0, np_view(q[0]), frames, np_view(kl), np_view(vl), True)
+    assert np.isnan(want[j:]).any() and np.isfinite(want[:j]).all() and np.isnan(want_sig[j])
+    calls = [p.gpu.prefill_attend(0, q.cuda(), fi, kl.cuda(), vl.cuda(), offs, True)]
+    if n_q <= 16:
+        calls.append((p.gpu.attend(0, q.cuda(), fi, kl.cuda(), vl.cuda(), offs, True), None))
+    torch.cuda.synchronize()
+    for out, sig in calls:
+        got = to_f64(np_view(out[0].cpu()))
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+        fine = ~np.isnan(want)
+        assert out_err(got[fine], want[fine]) <= mk_tol(w)
+        assert sig is None or np.isnan(sig[0].cpu().numpy()[np.isnan(want_sig)]).all()
+    p.close()
+
+
 def test_prefill_signal_feeds_the_compression():
     # one stream, chunk by chunk: prefill of the chunk's tokens over frames already in the cache -> its
     # signal, handed to mukv_compress_chunk.  The oracle is given the same float32 signal, so the keep

@@ -895,13 +895,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
 
     // Row r of [retrieved rows, local rows]: where its key and value live and the first token that sees it, worked
     // out by the lanes of one wave, four steps at a time (one per wave).  A row that lives nowhere, or past the last,
-    // is seen by nobody and reads a row that exists.
+    // is seen by nobody and reads a row that exists; its weight is zero, but zero times a NaN is not, so that row is one
+    // that every query sees anyway (the first retrieved one; without any, the first local one, which is seen by all that
+    // see something; with neither, the slab's first row, and nobody sees anything).
+    int first_frame = -1;
+    auto find_first_frame = [&]() { // the same in all lanes
+        for (int i0 = 0; i0 < a.k_frame && first_frame < 0; i0 += 64) {
+            const int f = i0 + lane < a.k_frame ? s_frame[i0 + lane] : -1;
+            const uint64_t some = __builtin_amdgcn_ballot_w64(f >= 0);
+            if (some) first_frame = __builtin_amdgcn_readlane(f, __builtin_ctzll(some));
+        }
+    };
     auto tabulate = [&](int t) {
         const int slot = t & (kRing - 1), r = t * kFK + lane;
-        uint64_t off = (uint64_t)(unsigned)l0 * local_stride;
-        bool local = n_loc > 0;
+        bool local = first_frame < 0 && n_loc > 0;
+        uint64_t off = local ? (uint64_t)(unsigned)l0 * local_stride : (uint64_t)(unsigned)((first_frame < 0 ? 0 : first_frame) * a.kappa) * kRowB;
         int ft = INT_MAX;
-        if (!local) off = 0;
         if (r < n_ret) {
             const int e = (int)((unsigned)r / (unsigned)a.kappa);
             const int f = s_frame[e];
@@ -913,6 +922,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
         } else if (r < total) {
             const int j = r - n_ret;
             off = (uint64_t)(unsigned)(l0 + j) * local_stride;
+            local = true;
             ft = a.causal ? j - (n_loc - a.n_q) : 0;
         }
         s_addr[slot][lane] = ulonglong2{(uint64_t)(uintptr_t)(local ? lk : sk) + off, (uint64_t)(uintptr_t)(local ? lv : sv) + off};
@@ -964,6 +974,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
     const int t_lo = SPLIT ? sp * per_split : 0;
     const int n_steps = t_lo + per_split < n_steps_all ? t_lo + per_split : n_steps_all;
     __syncthreads(); // the frame list is there
+    find_first_frame();
     tabulate(t_lo + wave);
     tabulate(t_lo + wave + 4);
     __syncthreads();

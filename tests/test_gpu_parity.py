@@ -1092,6 +1092,34 @@ def test_attention_non_finite_scores_reach_the_output(name, kw, n_q, n_frames, b
     p.close()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("n_q", [5, 40])
+def test_prefill_rows_of_no_question_stay_out(D, n_q):
+    # the last step of rows is part empty, one entry of the frame list names no frame, and there are no rows besides the
+    # retrieved ones: what stands in for a row that is not there must not be a frame the question did not retrieve --
+    # zero times its NaN is NaN.  Frame 0 has NaN values.
+    w = W["7b"].scaled(n_frames=8, n_layers=1, head_dim=D, n_questions=1, tokens_per_frame=50)
+    p = Pair(w, seed=465, chunk=4)
+    k, v, q = synth.SynthStream(w, 465, device="cpu").next_chunk(8)
+    v[:, :, :w.tokens_per_frame] = float("nan")
+    for c in range(2):
+        kc, vc, qc = (x[:, c * 200:(c + 1) * 200] if x.dim() == 3 else x[:, :, c * 200:(c + 1) * 200] for x in (k, v, q))
+        p.orc.compress_chunk(np_view(kc.contiguous()), np_view(vc.contiguous()), q_last=np_view(qc.contiguous()))
+        dev = [x.contiguous().cuda() for x in (kc, vc, qc)]
+        p.keep_alive += dev
+        p.gpu.compress_chunk(*dev)
+    assert (3 * p.orc.kappa) % 64
+    gen = torch.Generator().manual_seed(466)
+    q_new = torch.randn(1, n_q, w.n_q_heads, D, generator=gen).to(w.torch_dtype)
+    row = torch.zeros(1, w.n_kv_heads, D, dtype=w.torch_dtype, device="cuda")       # (not one of the question's: it has none)
+    fi = torch.tensor([[-1, 5, 1]], dtype=torch.int32, device="cuda")
+    out, sig = p.gpu.prefill_attend(0, q_new.cuda(), fi, row, row, torch.tensor([0, 0], dtype=torch.int32, device="cuda"), True)
+    torch.cuda.synchronize()
+    assert out_err(to_f64(np_view(out[0].cpu())), p.orc.attend(0, np_view(q_new[0]), [5, 1])) <= mk_tol(w)
+    assert not sig.any()
+    p.close()
+
+
 def test_prefill_signal_feeds_the_compression():
     # one stream, chunk by chunk: prefill of the chunk's tokens over frames already in the cache -> its
     # signal, handed to mukv_compress_chunk.  The oracle is given the same float32 signal, so the keep

@@ -583,9 +583,11 @@ __device__ __forceinline__ void block_minmax(R v, bool valid, R *red, R &lo, R &
     }
 }
 
-// Scores as the rank loop compares them: larger score first, lower position first among equals.  float: one unsigned
-// number, order-preserving bits of the score above the negated position, so that a comparison is one instruction;
-// double: the score, ties decided by the position.
+// Scores as the rank loop compares them: larger score first, lower position first among equals, NaN scores like the
+// largest of their sign -- a total order, so that exactly kappa tokens have a rank below kappa whatever the scores are
+// (comparing the scores themselves, a NaN is behind nobody: one token too many was kept and written past the frame's
+// list).  Order-preserving bits of the score, unsigned; float: with the negated position below them, so that a comparison
+// is one instruction; double: ties decided by the position.
 template <typename R>
 struct RankKey;
 template <>
@@ -600,9 +602,12 @@ struct RankKey<float> {
 };
 template <>
 struct RankKey<double> {
-    using K = double;
-    static __device__ __forceinline__ K of(double x, int) { return x; }
-    static __device__ __forceinline__ K last() { return -INFINITY; }
+    using K = uint64_t;
+    static __device__ __forceinline__ K of(double x, int) {
+        const uint64_t b = (uint64_t)__double_as_longlong(x + 0.0);
+        return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+    }
+    static __device__ __forceinline__ K last() { return 0; }
     static __device__ __forceinline__ bool before(K o, int i, K mine, int j) { return (o > mine) || (o == mine && i < j); }
 };
 

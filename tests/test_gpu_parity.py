@@ -969,6 +969,35 @@ def test_large_units_with_rescoring_batching_and_overlapped_copy(kw):
     p.close()
 
 
+@pytest.mark.parametrize("name,kw", [("tiny", {}), ("7b", {"n_layers": 2})])
+@pytest.mark.parametrize("margin", [0.0, 10.0])                # ranked in fp32; every frame ranked again in fp64
+def test_keep_of_a_frame_with_a_nan_key(name, kw, margin):
+    # a NaN key leaves its token a NaN score beside finite ones (the attention signal is handed over): that token
+    # ranks first, the others as their scores say, and no other frame notices -- kappa tokens per frame are kept, not
+    # one more written over the next frame's
+    w = W[name].scaled(n_frames=8, alpha=0.5, **kw)
+    p = Pair(w, seed=345, chunk=8, with_q=False, gpu_kw={"refine_margin": margin})
+    P = w.tokens_per_frame
+    k, v, _ = synth.SynthStream(w, 345, device="cpu", with_q=False).next_chunk(8)
+    att = synth.handed_over_attention(8, P, 346)
+    p.orc.compress_chunk(np_view(k), np_view(v), att=att.numpy().astype(np.float64))
+    f, t = 2, 5
+    k[:, :, f * P + t] = float("nan")
+    dev = [x.cuda() for x in (k, v, att)]
+    sig = p.gpu.compress_chunk(dev[0], dev[1], att_signal=dev[2], want_signals=True)
+    p.gpu.flush()
+    st = p.gpu.state()
+    torch.cuda.synchronize()
+    kept, fused = st["kept_idx"].cpu().numpy(), sig["fused"].cpu().numpy()[f]
+    assert int(st["refined"].sum()) == (8 if margin else 0)
+    assert np.flatnonzero(np.isnan(fused)).tolist() == [t]
+    first = np.argsort(-np.where(np.isnan(fused), np.inf, fused), kind="stable")[:p.orc.kappa]
+    np.testing.assert_array_equal(kept[f], np.sort(first))
+    others = [i for i in range(8) if i != f]
+    np.testing.assert_array_equal(kept[others], p.orc.kept[others])
+    p.close()
+
+
 def test_rescoring_beside_a_long_copy_and_before_a_short_one():
     # 12 frames are 66 MB of rows in and out (fp64 chain on the side stream, its rows copied by itself), the 4 of the
     # last chunk 22 MB (everything on the caller's stream, one copy); every frame re-scored

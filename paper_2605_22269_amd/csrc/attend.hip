@@ -115,9 +115,6 @@ __device__ __forceinline__ uint16_t bf16_round(float x) { // round to nearest ev
     const uint32_t u = __float_as_uint(x);
     return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
-__device__ __forceinline__ uint16_t bf16_out(float x) { return x == x ? bf16_round(x) : (uint16_t)0x7FC0u; }
-__device__ __forceinline__ void store_out(uint16_t *p, float x) { *p = bf16_out(x); }
-__device__ __forceinline__ void store_out(float *p, float x) { *p = x; }
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -128,6 +125,12 @@ typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 typedef __attribute__((ext_vector_type(4))) short i16x4;
 typedef __attribute__((ext_vector_type(8))) short i16x8;
+// two floats as bf16, x below y: the conversion instruction rounds to nearest even and keeps NaN a NaN
+__device__ __forceinline__ uint32_t bf16_pair(float x, float y) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
+}
+__device__ __forceinline__ void store_out(uint16_t *p, float x) { *p = (uint16_t)bf16_pair(x, 0.f); }
+__device__ __forceinline__ void store_out(float *p, float x) { *p = x; }
 // ds_read_b64_tr_b16, the LDS transpose read of 16-bit elements: every lane names 8 bytes; within each block
 // of 16 lanes, result[t] of lane i is element i % 4 of the 8 bytes named by lane 4 * t + i / 4 of the block,
 // t = 0..3 (lane layout checked by an in-bounds probe on the device).
@@ -555,16 +558,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     }
     if (tid < kTileQ) {
         float *rec = record(tid);
-        if (rec) {
-            rec[0] = s_run[tid];
+        if (rec) { // (maxima leave NaN scores out: where there was nothing else the denominator is still to be looked at)
+            rec[0] = s_run[tid] == -INFINITY && s_zq[tid] != 0.f ? 0.f : s_run[tid];
             rec[1] = s_zq[tid];
         }
     }
 }
 
 // out[b][i][h][:] = sum_s o_s 2^(m_s - m) / sum_s z_s 2^(m_s - m), m = max_s m_s; zero if no split saw a key, which
-// is a denominator of exactly zero (a NaN or +inf score makes it a NaN, and the output with it; a maximum leaves NaN
-// scores out, so a split of which nothing else is left has m_s = -inf and a denominator that is still looked at)
+// is a denominator of exactly zero (a NaN or +inf score makes it a NaN, and the output with it)
 // lse (may be null): log2 of the query's softmax denominator, in the scores' log2 units; +inf for a
 // query that sees no key, so that every weight computed from it is zero.
 template <typename T, int D>
@@ -587,12 +589,14 @@ __global__ void attend_combine_kernel(const float *__restrict__ part, int n_spli
         for (int s = 0; s < kAttendMaxSplit; ++s)
             if (s < n_split) m = fmaxf(m, ms[s]);
         float zs = 0.f, os = 0.f;
+        if (m > -INFINITY) {
 #pragma unroll
-        for (int s = 0; s < kAttendMaxSplit; ++s) {
-            if (s >= n_split) break;
-            const float w = ms[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms[s] - m);
-            zs = fmaf(zz[s], w, zs);
-            os = fmaf(oo[s], w, os);
+            for (int s = 0; s < kAttendMaxSplit; ++s) {
+                if (s >= n_split) break;
+                const float w = ms[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms[s] - m);
+                zs = fmaf(zz[s], w, zs);
+                os = fmaf(oo[s], w, os);
+            }
         }
         store_out(out + row * D + d, zs != 0.f ? os / zs : 0.f);
         if (lse && d == 0) lse[row] = zs != 0.f ? m + __builtin_amdgcn_logf(zs) : INFINITY;
@@ -1127,7 +1131,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
                 u32x2 w;
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
-                    w[e] = (uint32_t)bf16_out(o[f][4 * jj + 2 * e] * inv) | (uint32_t)bf16_out(o[f][4 * jj + 2 * e + 1] * inv) << 16;
+                    w[e] = bf16_pair(o[f][4 * jj + 2 * e] * inv, o[f][4 * jj + 2 * e + 1] * inv);
                 if (!seen) w = u32x2{0u, 0u};
                 *reinterpret_cast<u32x2 *>(op + 32 * f + 8 * jj + 4 * half) = w;
             }

@@ -788,6 +788,11 @@ __device__ __forceinline__ float half_sum(float v) {
 }
 
 constexpr int kFK = 64, kFQ = 128; // rows per step, queries per workgroup
+// Most new tokens of which an unsplit attention kernel sums Eq. 1 itself (a multiple of 64).  The key sums' launch costs
+// more than the tile's own last steps while these are one or two (7B head layout, no past, us a call, here / in a launch
+// of its own: 32 tokens 9.0 / 11.9, 64: 9.4 / 12.4, 128: 11.8 / 14.5); with more, the last tile's chain is the launch's
+// (196 tokens: 18.6 / 17.5).
+constexpr int kFusedSums = 128;
 constexpr float kHidden = -1e30f, kFloor = -1e20f; // score of a row a query may not see; least running maximum
 
 // Slot of 16-byte piece `piece` of staged row `row` in a row of D * 2 bytes.
@@ -842,8 +847,10 @@ unsigned tile_grid(int n_tiles, int combos) {
 // registers and are moved in and out of the accumulation registers).
 // SPLIT: a short prefill has too few tiles to fill the chip, so its rows are shared by n_split workgroups per
 // tile; the split's (maximum, normaliser, unnormalised output) go to the records attend_combine_kernel merges
-// (aux = records).  Otherwise the output and the log-sum-exps (aux) are final here.
-template <int D, bool SPLIT>
+// (aux = records).  Otherwise the output is final here, and so are the log-sum-exps: they go to aux for the key sums'
+// launch, or (SUMS, few new tokens) Eq. 1 is summed right here, over the tile's queries, and goes to aux
+// [B][Hkv][n_tiles][n_q].
+template <int D, bool SPLIT, bool SUMS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void prefill_flash_kernel(
     AttendArgs a, uint16_t *__restrict__ out, int n_tiles, int combos, float *__restrict__ aux, int n_split) {
     using T = uint16_t;
@@ -858,6 +865,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
     __shared__ __align__(16) int s_ft[kRing][kFK]; // first token that sees the row
     __shared__ int s_masked[kRing];               // some query of the tile may not see some row of the step
     __shared__ int s_frame[kMaxGatherK]; // the question's frames; -1: names no frame of the cache
+    static_assert(!(SPLIT && SUMS), "the sums want final statistics");
+    __shared__ __align__(16) float s_lse[SUMS ? kFQ : 1];
     int tile_id, combo;
     if (!tile_of(blockIdx.x, SPLIT ? n_tiles * n_split : n_tiles, combos, &tile_id, &combo)) return;
     const int qt = SPLIT ? tile_id / n_split : tile_id, sp = SPLIT ? tile_id % n_split : 0;
@@ -902,8 +911,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
     // is seen by nobody and reads a row that exists; its weight is zero, but zero times a NaN is not, so that row is one
     // that every query sees anyway (the first retrieved one; without any, the first local one, which is seen by all that
     // see something; with neither, the slab's first row, and nobody sees anything).
-    int first_frame = -1;
-    auto find_first_frame = [&]() { // the same in all lanes
+    int first_frame = a.k_frame > 0 ? __builtin_amdgcn_readfirstlane(a.frame_idx[(int64_t)b * a.k_frame]) : -1;
+    if (first_frame >= a.n_frames) first_frame = -1;
+    auto find_first_frame = [&]() { // where the list does not start with one: the same in all lanes
         for (int i0 = 0; i0 < a.k_frame && first_frame < 0; i0 += 64) {
             const int f = i0 + lane < a.k_frame ? s_frame[i0 + lane] : -1;
             const uint64_t some = __builtin_amdgcn_ballot_w64(f >= 0);
@@ -978,7 +988,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
     const int t_lo = SPLIT ? sp * per_split : 0;
     const int n_steps = t_lo + per_split < n_steps_all ? t_lo + per_split : n_steps_all;
     __syncthreads(); // the frame list is there
-    find_first_frame();
+    if (first_frame < 0) find_first_frame();
     tabulate(t_lo + wave);
     tabulate(t_lo + wave + 4);
     __syncthreads();
@@ -1107,9 +1117,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
     }
     const float l_sum = half_sum(l_run);
     const bool seen = l_sum != 0.f; // a query that saw nothing leaves zeros, whatever its hidden rows held; NaN stays NaN
-    if (!q_ok) return;
     // feature 32 f + 8 jj + 4 half + r of the query is in register 4 jj + r of block f
     if constexpr (SPLIT) { // the split's record: [0] maximum, [1] normaliser, [2..] unnormalised output
+        if (!q_ok) return;
         float *rec = aux + (my_row * n_split + sp) * (D + 2);
         if (half == 0) {
             rec[0] = m_run;
@@ -1122,20 +1132,98 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) rec[2 + 32 * f + 8 * jj + 4 * half + r] = seen ? o[f][4 * jj + r] : 0.f;
     } else {
-        const float inv = 1.0f / l_sum;
-        uint16_t *op = out + my_row * D;
+        // Eq. 1 of the tile: the wave's queries (now the A operand: S = Q K^T) against the new tokens' keys, 64 at a time.
+        // New token j is local row n_loc - n_q + j; it may not exist.  The last two steps' keys are still in LDS, which are
+        // all there are for up to 64 new tokens; others come from memory (the L2 cache).
+        const int j_end = a.causal && last_q + 1 < a.n_q ? last_q + 1 : a.n_q; // later tokens get nothing from here
+        const int r_new0 = n_ret + n_loc - a.n_q;
+        bf16x8 kb[SUMS ? 2 : 1][KK];
+        int q_min[2]; // queries of the KV head before this one do not see the lane's key
+        auto load_keys = [&](int j0) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
+            for (int i = 0; i < 2; ++i) {
+                const int j = j0 + 32 * i + lq, lrow = n_loc - a.n_q + j;
+                const bool ok = j < a.n_q && lrow >= 0;
+                q_min[i] = !ok ? n_queries : (a.causal ? j * a.G : 0);
+                if ((r_new0 + j0 > 0 ? r_new0 + j0 : 0) >= (n_steps - 2) * kFK) { // (masked keys: whatever is there)
+                    const int row = (r_new0 + j) & (2 * kFK - 1);
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                u32x2 w;
+                    for (int kk = 0; kk < KK; ++kk)
+                        kb[i][kk] = *reinterpret_cast<const bf16x8 *>(s_k[0] + row * kRowB + 16 * key_slot<D>(2 * kk + half, row));
+                } else {
+                    const T *kp = static_cast<const T *>(a.k_local) + ((int64_t)(l0 + (ok ? lrow : 0)) * a.Hkv + g) * D + 8 * half;
+                    if (n_loc == 0) kp = q + 8 * half; // memory that exists
 #pragma unroll
-                for (int e = 0; e < 2; ++e)
-                    w[e] = bf16_pair(o[f][4 * jj + 2 * e] * inv, o[f][4 * jj + 2 * e + 1] * inv);
-                if (!seen) w = u32x2{0u, 0u};
-                *reinterpret_cast<u32x2 *>(op + 32 * f + 8 * jj + 4 * half) = w;
+                    for (int kk = 0; kk < KK; ++kk) kb[i][kk] = __builtin_bit_cast(bf16x8, load16(kp + 16 * kk));
+                }
             }
-        if (half == 0) aux[my_row] = seen ? m_run + __builtin_amdgcn_logf(l_sum) : INFINITY;
+        };
+        if constexpr (SUMS) load_keys(0);
+        const float inv = 1.0f / l_sum, lse = seen ? m_run + __builtin_amdgcn_logf(l_sum) : INFINITY;
+        {
+            // a lane holds features 8 jj + 4 half .. + 3: the halves swap, so that it stores 16 bytes in a row (in 8-byte
+            // stores twice as many lines are opened twice as often: 32 tokens without a past 9.9 us a call, now 8.8)
+            uint16_t *op = out + my_row * D + 8 * half;
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int jj = 0; jj < 4; jj += 2) {
+                    raw16 w;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        uint32_t pk[2];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u)
+                            pk[u] = bf16_pair(o[f][4 * (jj + u) + 2 * e] * inv, o[f][4 * (jj + u) + 2 * e + 1] * inv);
+                        auto sw = __builtin_amdgcn_permlane32_swap(pk[0], pk[1], false, false);
+                        w[e] = sw[0];
+                        w[2 + e] = sw[1];
+                    }
+                    if (!seen) w = raw16{0u, 0u, 0u, 0u};
+                    if (q_ok) *reinterpret_cast<raw16 *>(op + 32 * f + 8 * jj) = w;
+                }
+            if (!SUMS && q_ok && half == 0) aux[my_row] = lse;
+        }
+        if constexpr (SUMS) {
+            float(*s_col)[kFusedSums] = reinterpret_cast<float(*)[kFusedSums]>(s_v); // per wave, where the values were
+            static_assert(4 * kFusedSums * sizeof(float) <= sizeof(s_v), "a sum per wave and new token");
+            const int qq0 = qt * kFQ + 32 * wave;
+            if (half == 0) s_lse[32 * wave + lq] = lse; // read by this wave only
+            __syncthreads();                            // every wave is done with the values
+            f32x4 l4[4];
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) l4[jj] = *reinterpret_cast<const f32x4 *>(&s_lse[32 * wave + 8 * jj + 4 * half]);
+            for (int j0 = 0; j0 < j_end; j0 += 64) {
+                f32x16 sc[2];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sc[0][e] = sc[1][e] = 0.f;
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) sc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qb[kk], kb[i][kk], sc[i], 0, 0, 0);
+                const unsigned q_lo[2] = {(unsigned)q_min[0], (unsigned)q_min[1]};
+                if (j0 + 64 < j_end) load_keys(j0 + 64);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    if (j0 + 32 * i >= j_end) break;
+                    float part = 0.f;
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const unsigned qq = qq0 + 8 * jj + 4 * half + r;
+                            const float x = fmaf(sc[i][4 * jj + r], a.scale_log2e, -l4[jj][r]);
+                            part += __builtin_amdgcn_exp2f(qq - q_lo[i] < n_queries - q_lo[i] ? x : -INFINITY); // q_lo <= qq < n_queries
+                        }
+                    part = half_sum(part);
+                    if (half == 0) s_col[wave][j0 + 32 * i + lq] = part;
+                }
+            }
+            __syncthreads();
+            float *dst = aux + (((int64_t)b * a.Hkv + g) * n_tiles + qt) * a.n_q;
+            for (int j = tid; j < a.n_q; j += 256)
+                dst[j] = j < j_end ? (s_col[0][j] + s_col[1][j]) + (s_col[2][j] + s_col[3][j]) : 0.f;
+        }
     }
 }
 
@@ -1326,14 +1414,16 @@ hipError_t launch_by_dim(const AttendArgs &a, int D, int B, void *out, const Pre
     }
 }
 
-// Steps a workgroup of prefill_keysum_kernel takes: as few as leave all workgroups resident at once (three per compute
-// unit: one more round of them costs as much as the first), at least two.
+// Steps a workgroup of prefill_keysum_kernel takes: one, where that is at most a workgroup per compute unit (7B head
+// layout, 128 tokens over 768 rows, 56 workgroups: 27.1 us a call against 28.0 with two steps; 600 tokens, 760
+// workgroups: 49.3 against 47.5); otherwise as few as leave all workgroups resident at once (three per compute unit: one
+// more round of them costs as much as the first), at least two.
 int keysum_plan(int n_q, int G, int combos, int causal, int *n_units) {
     const int tiles = (n_q + kCK - 1) / kCK, all = (n_q * G + kCQ - 1) / kCQ;
-    for (int per = all < 2 ? all : 2;; per += (per + 15) / 16) {
+    for (int per = 1;; per += (per + 15) / 16) {
         int n = 0;
         for (int kt = 0; kt < tiles; ++kt) n += keysum_shares(kt, n_q * G, G, causal, per);
-        if ((int64_t)n * combos <= 3 * 256 || per >= all) {
+        if ((int64_t)n * combos <= (per == 1 ? 256 : 3 * 256) || per >= all) {
             *n_units = n;
             return per;
         }
@@ -1357,10 +1447,19 @@ hipError_t launch_flash(const AttendArgs &a, int n_fs, int B, void *out, const P
     uint16_t *o16 = static_cast<uint16_t *>(out);
     const unsigned grid = tile_grid(n_tiles * n_fs, combos);
     hipError_t e;
+    const float inv = 1.0f / ((float)a.Hq * (float)a.n_q);
+    const dim3 sig_grid((a.n_q + kSigCols - 1) / kSigCols, B);
+    if (n_fs == 1 && a.n_q <= kFusedSums) { // two launches (see kFusedSums)
+        hipLaunchKernelGGL((prefill_flash_kernel<D, false, true>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.colpart, 1);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(prefill_signal_kernel, sig_grid, dim3(kThreads), 0, st, po.colpart, a.Hkv, n_tiles, a.n_q, inv, po.signal,
+                           a.G, a.causal, 0);
+        return hipGetLastError();
+    }
     if (n_fs == 1) {
-        hipLaunchKernelGGL((prefill_flash_kernel<D, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.lse, 1);
+        hipLaunchKernelGGL((prefill_flash_kernel<D, false, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.lse, 1);
     } else { // rows shared by n_fs workgroups per tile, merged
-        hipLaunchKernelGGL((prefill_flash_kernel<D, true>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, a.part, n_fs);
+        hipLaunchKernelGGL((prefill_flash_kernel<D, true, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, a.part, n_fs);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL((attend_combine_kernel<uint16_t, D>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D), 0, st, a.part,
                            n_fs, o16, po.lse);
@@ -1372,8 +1471,8 @@ hipError_t launch_flash(const AttendArgs &a, int n_fs, int B, void *out, const P
     hipLaunchKernelGGL((prefill_keysum_kernel<D>), dim3(tile_grid(n_units, combos)), dim3(256), 0, st, a, po.lse, po.colpart,
                        n_units, combos, n_qs, steps_per);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(prefill_signal_kernel, dim3((a.n_q + kSigCols - 1) / kSigCols, B), dim3(kThreads), 0, st, po.colpart, a.Hkv,
-                       n_qs, a.n_q, 1.0f / ((float)a.Hq * (float)a.n_q), po.signal, a.G, a.causal, steps_per);
+    hipLaunchKernelGGL(prefill_signal_kernel, sig_grid, dim3(kThreads), 0, st, po.colpart, a.Hkv, n_qs, a.n_q, inv, po.signal, a.G,
+                       a.causal, steps_per);
     return hipGetLastError();
 }
 

@@ -1078,6 +1078,25 @@ def test_prefill_matrix_tile_edges(D, hq, hkv, n_q, n_frames, old):
     p.close()
 
 
+@pytest.mark.parametrize("D,hq,hkv,n_q,n_frames,old", [
+    (128, 28, 4, 31, 0, [0, 40]),       # 32 keys at a time and one less; behind older rows
+    (128, 28, 4, 64, 0, [1]),           # the keys of 64 tokens lie across the last two steps of rows
+    (128, 16, 2, 65, 1, [200, 0]),      # one more: some keys are no longer staged
+    (64, 32, 8, 128, 0, [300]),         # as many as are summed here
+    (128, 64, 8, 127, 2, [0, 0, 70, 5]),  # tiles fill the chip: one workgroup walks many rows
+    (128, 8, 8, 128, 0, [3]),           # one head per group: a tile has as many tokens as queries
+    (64, 14, 2, 2, 0, [0]),
+])
+def test_prefill_of_few_tokens_sums_attention_in_the_tile(D, hq, hkv, n_q, n_frames, old):
+    w = W["7b"].scaled(n_frames=4, n_layers=1, head_dim=D, n_q_heads=hq, n_kv_heads=hkv, n_questions=len(old))
+    p = Pair(w, seed=455, chunk=4)
+    p.ingest()
+    fi = [[(b + i) % 4 for i in range(n_frames)] for b in range(len(old))] if n_frames else None
+    for causal in (True, False):
+        p.check_prefill(0, n_q, fi, old, causal, seed=456)
+    p.close()
+
+
 @pytest.mark.parametrize("name,kw,n_q,n_frames", [
     ("7b", {}, 40, 0),                        # matrix-core prefill, rows of a tile in one workgroup
     ("7b", {}, 40, 12),                       # shared by several, merged

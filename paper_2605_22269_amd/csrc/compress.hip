@@ -548,7 +548,7 @@ struct SelectArgs {
     int64_t k_off;      // element offset of the scoring layer
     int64_t sh, st;
     R margin_thr;
-    int pass2;          // 1: fp64 pass over the frames listed by pass 1
+    int pass2;          // not 0: fp64 pass over the frames listed by pass 1 (2: its rows go to the batch's own list)
     int32_t *flag_list; // batch frames whose fp32 margin is below the threshold (written by pass 1)
     int32_t *flag_count;
     int32_t *kept_idx;
@@ -611,9 +611,11 @@ struct RankKey<double> {
     static __device__ __forceinline__ bool before(K o, int i, K mine, int j) { return (o > mine) || (o == mine && i < j); }
 };
 
-// Latency: one workgroup's chain of waits (8 frames: 18.9 us, of which loading the signals 4.6, the two ranges 1.4,
-// the ranks 5.5, the block keys 5.4; now 17.2, the ranks 2.4).  So the loads of the signals are all requested before the first is used, and the ranks
-// are counted sixteen scores a step -- one at a time, every comparison waited for its LDS read, 67 cycles.
+// Latency: one workgroup's chain of waits.  8 frames in fp32, every score compared by itself: 18.9 us, of which loading the
+// signals 4.6, the two ranges 1.4, the ranks 5.5 (each comparison waits for its LDS read, 67 cycles), the block keys
+// 5.4.  So the attention partials are requested kPB at a time and the ranks counted kRB scores a step: 17.2, the ranks
+// 2.4.  fp64: batches of that size take 130 registers instead of 94, and the keep of the frames listed from a batch of
+// 512 takes 70-73 us instead of 62-64; hence 16 partials and one score.
 template <typename T, typename R>
 __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
     using RK = RankKey<R>;
@@ -650,7 +652,7 @@ __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
             av = (R) reinterpret_cast<const float *>(a.att_in.p[slot])[(int64_t)lf * P + j];
         } else {
             const R *pp = a.att + (int64_t)f * a.n_part * P + j;
-            constexpr int kPB = 32;
+            constexpr int kPB = sizeof(R) == 4 ? 32 : 16;
             for (int n0 = 0; n0 < a.n_part; n0 += kPB) { // fixed summation order, kPB loads in flight
                 R t[kPB];
 #pragma unroll
@@ -678,7 +680,7 @@ __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
         fused += ((R)1 - a.alpha) * fn;
     }
     const typename RK::K mine = RK::of(fused, j);
-    sc[j] = valid ? mine : RK::last(); // (padding: the ranks are counted over whole groups of sixteen)
+    sc[j] = valid ? mine : RK::last(); // (padding: the ranks are counted over whole steps)
     if (valid) {
         if (dbg_fused) dbg_fused[(int64_t)lf * P + j] = (float)fused;
     }
@@ -687,12 +689,14 @@ __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
 
     int rank = 0;
     if (valid) {
-        for (int i0 = 0; i0 < P; i0 += 16) {
-            typename RK::K o[16];
+        constexpr int kRB = sizeof(R) == 4 ? 16 : 1;
+        static_assert(kMaxP % kRB == 0, "the scores are padded to whole steps");
+        for (int i0 = 0; i0 < P; i0 += kRB) {
+            typename RK::K o[kRB];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) o[u] = sc[i0 + u];
+            for (int u = 0; u < kRB; ++u) o[u] = sc[i0 + u];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) rank += RK::before(o[u], i0 + u, mine, j);
+            for (int u = 0; u < kRB; ++u) rank += RK::before(o[u], i0 + u, mine, j);
         }
         if (rank == kappa - 1) vk[0] = fused;
         if (rank == kappa) vk[1] = fused;

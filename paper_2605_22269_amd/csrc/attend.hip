@@ -809,8 +809,8 @@ __device__ __forceinline__ int val_slot(int piece, int row) {
 
 // Workgroup -> (tile, combination of KV head and question).  Workgroup id runs on XCD id % 8; the rows of a
 // combination are read by all of its tiles, so where the counts allow it a combination stays on as few XCDs
-// as there are for it (its rows then sit in those L2 caches).  Heavy tiles -- the last ones under the causal
-// mask -- first.  Returns false for the padding workgroups.
+// as there are for it (its rows then sit in those L2 caches).  The last tiles, under the causal mask the heavy ones,
+// start first.  Returns false for the padding workgroups.
 __device__ __forceinline__ bool tile_of(unsigned id, int n_tiles, int combos, int *tile, int *combo) {
     const unsigned xcd = id & 7, slot = id >> 3;
     int rank;
@@ -1230,9 +1230,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
 // ------------------------------------------------------------------------------------------
 // Eq. 1 for the matrix-core prefill: softmax weights on the new tokens, from the final log-sum-exps, added over
 // queries and heads.  One workgroup per (128 new tokens, KV head, question, share of the queries): a wave keeps
-// the keys of its 32 tokens as the B operand in registers and the queries stream past it through LDS, 64 a step,
-// so that S = Q K^T leaves a lane one key and 16 queries of every 32 and the sum over the queries is one running
-// sum per lane, written once at the end.  (The same sums inside the attention kernel, walked by query tile, needed
+// the keys of 64 tokens as the B operand in registers (two waves share them, each with 32 of a step's 64 queries) and the
+// queries stream past it through LDS, so that S = Q K^T leaves a lane two keys and 16 queries and the sum over the
+// queries is a running sum per lane and key, written once at the end.  (The same sums inside the attention kernel, walked by query tile, needed
 // a reduction over the waves and a store per 64 keys: 2400 cycles a step against 1000.)
 // colpart [B][Hkv][n_qs][n_q], of which a key tile fills as many rows as it has shares; they are added in a fixed order by prefill_signal_kernel.
 // ------------------------------------------------------------------------------------------
@@ -1246,7 +1246,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
     __shared__ float s_sum[kCK];
     int unit, combo;
     if (!tile_of(blockIdx.x, n_units, combos, &unit, &combo)) return;
-    int kt = 0, qs = unit; // the unit's key tile and its share of that tile's queries
+    // the unit's key tile and its share of that tile's queries; here the first tiles are the heavy ones, so they start
+    // first (8 questions of 1568 tokens, 64 heads, a whole tile a workgroup: 643 us a call, 625 this way round)
+    int kt = 0, qs = n_units - 1 - unit;
     for (int n; qs >= (n = keysum_shares(kt, a.n_q * a.G, a.G, a.causal, steps_per)); ++kt) qs -= n;
     const int g = combo % a.Hkv, b = combo / a.Hkv;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lq = lane & 31, half = lane >> 5;

@@ -920,26 +920,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
             if (some) first_frame = __builtin_amdgcn_readlane(f, __builtin_ctzll(some));
         }
     };
+    const unsigned char *pad_k = sk, *pad_v = sv;
+    auto find_pad = [&]() {
+        if (first_frame < 0) find_first_frame();
+        if (first_frame < 0 && n_loc == 0) return;
+        const uint64_t off = first_frame < 0 ? (uint64_t)(unsigned)l0 * local_stride : (uint64_t)(unsigned)(first_frame * a.kappa) * kRowB;
+        pad_k = (first_frame < 0 ? lk : sk) + off;
+        pad_v = (first_frame < 0 ? lv : sv) + off;
+    };
     auto tabulate = [&](int t) {
         const int slot = t & (kRing - 1), r = t * kFK + lane;
-        bool local = first_frame < 0 && n_loc > 0;
-        uint64_t off = local ? (uint64_t)(unsigned)l0 * local_stride : (uint64_t)(unsigned)((first_frame < 0 ? 0 : first_frame) * a.kappa) * kRowB;
+        const unsigned char *rk = pad_k, *rv = pad_v;
         int ft = INT_MAX;
         if (r < n_ret) {
             const int e = (int)((unsigned)r / (unsigned)a.kappa);
             const int f = s_frame[e];
             if (f >= 0) {
-                off = (uint64_t)(unsigned)(f * a.kappa + (r - e * a.kappa)) * kRowB;
-                local = false;
+                const uint64_t off = (uint64_t)(unsigned)(f * a.kappa + (r - e * a.kappa)) * kRowB;
+                rk = sk + off;
+                rv = sv + off;
                 ft = 0;
             }
         } else if (r < total) {
             const int j = r - n_ret;
-            off = (uint64_t)(unsigned)(l0 + j) * local_stride;
-            local = true;
+            const uint64_t off = (uint64_t)(unsigned)(l0 + j) * local_stride;
+            rk = lk + off;
+            rv = lv + off;
             ft = a.causal ? j - (n_loc - a.n_q) : 0;
         }
-        s_addr[slot][lane] = ulonglong2{(uint64_t)(uintptr_t)(local ? lk : sk) + off, (uint64_t)(uintptr_t)(local ? lv : sv) + off};
+        s_addr[slot][lane] = ulonglong2{(uint64_t)(uintptr_t)rk, (uint64_t)(uintptr_t)rv};
         s_ft[slot][lane] = ft;
         const bool any = __builtin_amdgcn_ballot_w64(ft > first_tok) != 0;
         if (lane == 0) s_masked[slot] = any;
@@ -988,7 +997,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
     const int t_lo = SPLIT ? sp * per_split : 0;
     const int n_steps = t_lo + per_split < n_steps_all ? t_lo + per_split : n_steps_all;
     __syncthreads(); // the frame list is there
-    if (first_frame < 0) find_first_frame();
+    find_pad();
     tabulate(t_lo + wave);
     tabulate(t_lo + wave + 4);
     __syncthreads();
@@ -1232,7 +1241,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
 // queries and heads.  One workgroup per (128 new tokens, KV head, question, share of the queries): a wave keeps
 // the keys of 64 tokens as the B operand in registers (two waves share them, each with 32 of a step's 64 queries) and the
 // queries stream past it through LDS, so that S = Q K^T leaves a lane two keys and 16 queries and the sum over the
-// queries is a running sum per lane and key, written once at the end.  (The same sums inside the attention kernel, walked by query tile, needed
+// queries is a running sum per lane and key, written once at the end.  (The same sums inside the attention kernel, walked
+// by query tile, needed
 // a reduction over the waves and a store per 64 keys: 2400 cycles a step against 1000.)
 // colpart [B][Hkv][n_qs][n_q], of which a key tile fills as many rows as it has shares; they are added in a fixed order by prefill_signal_kernel.
 // ------------------------------------------------------------------------------------------

@@ -318,7 +318,8 @@ int mukv_gather_patches(mukv_ctx *ctx, const int32_t *patch_idx, int32_t B, int3
  * h / (Hq / Hkv).  Every retrieved row is visible to every token.  The n_q
  * query tokens are the LAST n_q local rows: with causal_local = 1 token i sees
  * local row j only if j <= n_local_b - n_q + i; with 0 it sees all of them.
- * A token that sees no key at all gets zeros.
+ * A token that sees no key at all gets zeros; one that sees a NaN or +inf
+ * score gets NaN.
  *
  *   layer          0 .. n_layers-1: which layer's kept rows are read
  *   q              device, payload dtype, [B][n_q][Hq][D] contiguous
@@ -366,9 +367,10 @@ int mukv_attend(mukv_ctx *ctx, int32_t layer, const void *q, int32_t n_q, const 
  *                   undefined afterwards.  The call allocates nothing.
  *
  * Arithmetic in fp32, sums in a fixed order; `out` is rounded to the payload
- * dtype.  For bf16 payloads with D = 128 both products run on the matrix
- * cores: the softmax weights enter the value product rounded to bf16 (the
- * normaliser and att_signal_out use the unrounded fp32 weights).
+ * dtype.  For bf16 payloads with D = 64 or 128 both products run on the matrix
+ * cores: the softmax weights enter the value product rounded to bf16 (D = 128)
+ * or as two bf16 terms (D = 64); the normaliser and att_signal_out use the
+ * unrounded fp32 weights.
  * Errors: INVALID_ARG (null pointers: here the local rows and both
  * outputs are required), CAPACITY (B > max_questions, workspace too small),
  * UNSUPPORTED (n_q > 8192, k_frame > 1024, n_q * Hq > 524 280, alignment).
@@ -389,8 +391,8 @@ int mukv_prefill_attend(mukv_ctx *ctx, int32_t layer, const void *q, int32_t n_q
  *
  * A call whose mukv_prefill_workspace_size() exceeds MUKV_STATIC_SCRATCH_BYTES
  * returns MUKV_ERR_CAPACITY and launches nothing (in the 7B head layout one
- * frame of 196 new tokens over 32 retrieved frames needs 23 MB, a chunk of
- * 1568 tokens 5 MB).  Every call on a GPU -- of any context, on any stream --
+ * frame of 196 new tokens over 32 retrieved frames needs 20 MB, a chunk of
+ * 1568 tokens 4.5 MB).  Every call on a GPU -- of any context, on any stream --
  * uses that GPU's one array: calls that overlap in time on one GPU race and
  * must be ordered by the caller (one stream, or events).  Nothing in the
  * array has to start at zero; it keeps the last call's contents.

@@ -839,9 +839,10 @@ unsigned tile_grid(int n_tiles, int combos) {
 
 // What bounds it: the latency of a wave's chain scores -> statistics -> weights -> values, with two waves per SIMD to
 // hide it (248 registers, 80 KB of LDS): a 64-row step of a workgroup alone on its compute unit takes 2850 cycles for
-// 1024 of matrix work.  Measured, 7B head layout, 1568 new tokens over 768 rows: 61 us (186 us for 64-query tiles of
-// 16x16x32 products whose weights crossed the waves through LDS, which included the column sums: those are 23 us in the
-// kernel below); 4000 tokens 267 us for the whole call against 673.  Also built and slower: the next block's scores
+// 1024 of matrix work.  Measured, 7B head layout, 1568 new tokens over 768 rows: 60-64 us, its matrix pipes busy 36 % of
+// the time (64-query tiles of 16x16x32 products whose weights cross the waves through LDS: 186 us with the column sums,
+// which are 23 us in the kernel below); 4000 tokens 258-265 us for the whole call against 673.  344 tiles on 512
+// resident places is not even: the launch lasts as long as its heaviest tile.  Also built and slower: the next block's scores
 // interleaved instruction by instruction with this block's weights and values (66 us), eight waves that share 128-row
 // steps (59 us, but 346 against 300 for the long prefill), 64 queries per wave (85 us: the accumulators pass 256
 // registers and are moved in and out of the accumulation registers).
@@ -1242,9 +1243,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
 // the keys of 64 tokens as the B operand in registers (two waves share them, each with 32 of a step's 64 queries) and the
 // queries stream past it through LDS, so that S = Q K^T leaves a lane two keys and 16 queries and the sum over the
 // queries is a running sum per lane and key, written once at the end.  (The same sums inside the attention kernel, walked
-// by query tile, needed
-// a reduction over the waves and a store per 64 keys: 2400 cycles a step against 1000.)
-// colpart [B][Hkv][n_qs][n_q], of which a key tile fills as many rows as it has shares; they are added in a fixed order by prefill_signal_kernel.
+// by query tile, need a reduction over the waves and a store per 64 keys: 2400 cycles a step against 1000.  Few tokens pay
+// that and save the launch: see kFusedSums.)
+// colpart [B][Hkv][n_qs][n_q], of which a key tile fills as many rows as it has shares; they are added in a fixed order by
+// prefill_signal_kernel.
 // ------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void prefill_keysum_kernel(
@@ -1531,7 +1533,8 @@ int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame) {
 
 // Workgroups that share the rows of one tile of the matrix-core prefill: 1 unless the tiles alone leave most of
 // the chip idle (two workgroups per compute unit are wanted, at least two steps each: 196 new tokens over 768 rows,
-// 44 tiles, 35 us in 8 shares), and no more than leave the records, log-sum-exps and column sums within the workspace.
+// 44 tiles, 34-35 us a call in 7 shares), and no more than leave the records, log-sum-exps and column sums within the
+// workspace (200 tokens without a past would be shared by two and are not, 300 over 768 rows by eight and are by six).
 static int flash_split(const Ctx &c, int n_q, int B, int k_frame) {
     const int64_t wgs = (((int64_t)n_q * c.group + kFQ - 1) / kFQ) * c.cfg.n_kv_heads * B;
     if (wgs >= 192) return 1;

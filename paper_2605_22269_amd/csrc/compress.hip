@@ -1988,8 +1988,12 @@ hipError_t join_streams(Ctx &c, hipStream_t st) {
 
 // A copy too short to hide the fp64 chain behind it: the events that would put the chain on the side stream and bring it
 // back cost more than they save, on the host (four calls and one launch of twelve, and a small batch is bound by its
-// launches) and on the device (each crossing of queues 6-14 us).  32 MB are read and written in 6-8 us, which is
-// where the two sides meet; 8 frames of the 7B shape are 22 MB.
+// launches) and on the device (each crossing of queues 6-14 us).  Both sides, 7B shape, us a call, everything on the
+// caller's stream / the chain beside the copy: 8 frames, 21 MB, 46 / 70-82; 16, 42 MB, 58 / 81; 32, 84 MB, 74 / 94; 64,
+// 168 MB, 178 / 199; 128, 336 MB, 247 / 253, and with the signal handed over 143 / 127.  So with few frames listed the
+// sides meet at about 300 MB.  The line lies far below: the longer the chain -- it grows with the frames listed,
+// up to all of a batch -- the more a long copy beside it hides, and 32 MB (6-8 us) hide less than the crossings cost in
+// any case.
 static bool copy_is_short(const Ctx &c, const ChunkArgs &a) {
     return 4ll * a.n_frames * c.kappa * c.cfg.n_layers * c.c_kv * c.esz <= 32ll << 20;
 }

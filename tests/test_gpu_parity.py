@@ -1047,15 +1047,15 @@ def test_prefill_attention_and_received_signal(name, frames, kw, n_q, old):
     p.close()
 
 
-def test_prefill_of_a_long_unit_takes_the_wide_tiles():
-    # enough queries for 128-query tiles to fill the chip twice over (72B head layout: 8 KV heads x 8)
+def test_prefill_of_a_long_unit_takes_unsplit_tiles():
+    # enough 128-query tiles to fill the chip twice over, so that no tile's rows are shared (72B head layout: 8 KV heads x 8)
     w = W["72b"].scaled(n_frames=6, n_layers=1, n_questions=1)
     p = Pair(w, seed=440, chunk=3)
     p.ingest()
     n_q = 1100                                   # 8800 queries per KV head: 69 tiles x 8 heads >= 512 workgroups, ragged
     for causal in (True, False):
         _, _, e_out, e_sig = p.check_prefill(0, n_q, [[4, 0, -1]], [9], causal, seed=441)
-        print(f"wide tiles, causal={causal}: out err {e_out:.2e}, signal err {e_sig:.2e}")
+        print(f"unsplit tiles, causal={causal}: out err {e_out:.2e}, signal err {e_sig:.2e}")
     p.close()
 
 
@@ -1302,8 +1302,8 @@ def test_large_units_snapshot_and_graph_replay_with_prefill():
 def test_prefill_with_fewer_local_rows_than_new_tokens(name, kw, n_q, n_loc):
     # n_q query tokens but only n_loc local rows: the first n_q - n_loc tokens have no row of their own -- they
     # see the retrieved rows only (the oracle's attention without local rows) and receive no attention.  With
-    # 28 or more such tokens the first 64-query tile of the matrix-core kernel (7 or 8 heads per token) holds
-    # nothing but tokens without a row, which must still see every retrieved row.
+    # 28 such tokens in the 40-token cases, and 147 of 150, whole 128-query tiles of the matrix-core kernel (18 or 16
+    # tokens) hold nothing but tokens without a row, which must still see every retrieved row.
     w = W[name].scaled(n_frames=8, **kw)
     p = Pair(w, seed=430, chunk=4)
     p.ingest()

@@ -790,7 +790,7 @@ __device__ __forceinline__ float half_sum(float v) {
 constexpr int kFK = 64, kFQ = 128; // rows per step, queries per workgroup
 // Most new tokens of which an unsplit attention kernel sums Eq. 1 itself (a multiple of 64).  The key sums' launch costs
 // more than the tile's own last steps while these are one or two (7B head layout, no past, us a call, here / in a launch
-// of its own: 32 tokens 9.0 / 11.9, 64: 9.4 / 12.4, 128: 11.8 / 14.5); with more, the last tile's chain is the launch's
+// of its own: 32 tokens 8.6 / 11.9, 64: 9.1 / 12.4, 128: 11.6 / 14.5); with more, the last tile's chain is the launch's
 // (196 tokens: 18.6 / 17.5).
 constexpr int kFusedSums = 128;
 constexpr float kHidden = -1e30f, kFloor = -1e20f; // score of a row a query may not see; least running maximum
@@ -976,6 +976,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) koff[kk] = lq * kRowB + 16 * key_slot<D>(2 * kk + half, lq);
 
+    const bool idle = qt * kFQ + 32 * wave >= n_queries; // a wave without queries (its operand reads alone slow the others)
     float m_run = kFloor, l_run = 0.f; // of query lq; l_run: over the rows this lane holds
     f32x16 o[NF];
 #pragma unroll
@@ -1019,6 +1020,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
         const bool more = t + 1 < n_steps; // its loads are issued between the groups of matrix instructions
         // tables of the steps before t are free: four new ones every four steps
         if (((t - t_lo) & 3) == 0 && t > t_lo && t + 4 < n_steps) tabulate(t + 4 + wave);
+        if (SUMS && idle) { // brings its rows and leaves the LDS to the others
+            if (more) {
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) request(u, ad, nk, nv);
+            }
+            return;
+        }
         // Operands are requested one group of matrix instructions ahead (the barriers keep the compiler's order to it):
         // 16 features of both blocks of 32 rows.
         f32x16 sc[2];
@@ -1168,7 +1176,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
                 }
             }
         };
-        if constexpr (SUMS) load_keys(0);
+        if constexpr (SUMS) {
+            if (!idle) load_keys(0);
+        }
         const float inv = 1.0f / l_sum, lse = seen ? m_run + __builtin_amdgcn_logf(l_sum) : INFINITY;
         {
             // a lane holds features 8 jj + 4 half .. + 3: the halves swap, so that it stores 16 bytes in a row (in 8-byte
@@ -1203,7 +1213,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
             f32x4 l4[4];
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) l4[jj] = *reinterpret_cast<const f32x4 *>(&s_lse[32 * wave + 8 * jj + 4 * half]);
-            for (int j0 = 0; j0 < j_end; j0 += 64) {
+            if (idle) {
+                for (int j = lane; j < kFusedSums; j += 64) s_col[wave][j] = 0.f;
+            }
+            for (int j0 = idle ? j_end : 0; j0 < j_end; j0 += 64) {
                 f32x16 sc[2];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) sc[0][e] = sc[1][e] = 0.f;

@@ -3,32 +3,15 @@
 // frames chosen by the retrieval -- read in place from the store, no gathered copy -- and X the
 // caller's own ("local") rows.
 //
-// attend_partial_kernel: one workgroup per (question, KV head, tile of up to 8 queries, split of
-// the frame list).  A query of the tile is a (token, head of the KV group) pair, so a key / value
-// row is read once for all the heads that share it.  Rows are taken in chunks of up to 512:
-//   1. a table of where each row of the chunk lives (store row or local row) and which token is
-//      the first to see it;
-//   2. the scores of the chunk, kept in LDS, and their maximum per query.  bf16 rows of 32, 64 or
-//      128 features: S^T = K Q^T with v_mfma_f32_16x16x32_bf16, 16 key rows per wave and step,
-//      the A operand loaded straight from the row (lane % 16 = row, 8 features from
-//      8 * (lane / 16) of every 32).  Otherwise: a row spread over D/E lanes (E = elements in 16
-//      bytes), dot products reduced over those lanes;
-//   3. with that maximum fixed, the weights exp2(score - maximum), once per (row, query), and their sums --
-//      so the running sums are rescaled once per chunk, not once per row;
-//   4. the value accumulation.  bf16 rows of 32, 64 or 128 features: O = P V on the matrix cores -- the
-//      weights as bf16 pairs hi + lo (two products, nothing of the fp32 weight is lost) are the A operand,
-//      the value rows pass through LDS 64 at a time, row-major as they come from memory, and the LDS
-//      transpose read (ds_read_b64_tr_b16) hands every lane the 8 rows of one feature that the B operand
-//      wants; a wave owns 16-feature tiles of the output, so nothing is left to add across lanes.
-//      Otherwise: a value row spread over D/E lanes, 256*E/D rows per pass, multiply-adds on the VALU and a
-//      sum over the lanes that hold the same piece of different rows.
-// The split's (maximum, normaliser, unnormalised output) per query go to a scratch table;
-// attend_combine_kernel merges the splits and writes the output in the payload type.
+// attend_kernel: one workgroup of four waves per (question, KV head, tile of 16 queries, share of the rows).  A query of
+// the tile is a (token, head of the KV group) pair, so a key / value row is read once for all the heads that share it.
+// Nothing crosses the waves until the end: a wave walks blocks of its own, with running statistics of its own, and the
+// four results join in LDS.  attend_combine_kernel merges the shares of a tile whose rows are split.
 // Everything is summed in a fixed order: the result does not depend on timing.
 //
 // The prefill of new tokens (Sec. 3.2: they attend to the past cache and to themselves) is the same
 // computation with many query tokens, and yields Eq. 1 -- the attention each new token receives --
-// on the way: bf16 rows of 64 or 128 features take the matrix-core kernels further down; for the others the merge also
+// on the way: bf16 rows of 64 or 128 features take the kernels further down; for the others attend_kernel (or the merge) also
 // writes every query's log-sum-exp; prefill_colsum_kernel recomputes the
 // scores of a tile's queries against the new tokens' keys, turns them into softmax weights with
 // that log-sum-exp and adds them over the tile; prefill_signal_kernel adds the tiles and KV heads in
@@ -42,11 +25,9 @@ namespace mukv {
 
 namespace {
 
-constexpr int kTileQ = 8;    // queries per workgroup
-constexpr int kChunk = 512;  // rows whose scores are held in LDS at a time
+constexpr int kAttQ = 16, kAttWaves = 4; // queries and waves per workgroup of attend_kernel
+constexpr int kTileQ = 8;    // queries per workgroup of prefill_colsum_kernel
 constexpr int kThreads = 256;
-constexpr int kUnroll = 4;   // rows a lane has in flight
-constexpr int kStepsA = 2;   // matrix path: 16-row steps of a wave whose loads are issued together
 
 struct AttendArgs {
     const void *q;            // [B][n_q][Hq][D]
@@ -56,7 +37,7 @@ struct AttendArgs {
     const void *store_k, *store_v; // the layer's slabs: [Hkv][store_cap][D]
     float *part;                   // [B][n_q*Hq][n_split][D+2]
     int64_t store_cap;
-    int n_q, Hq, Hkv, G, k_frame, kappa, n_frames, n_split, frames_per_split, n_qtiles, causal;
+    int n_q, Hq, Hkv, G, k_frame, kappa, n_frames, n_split, n_qtiles, causal;
     float scale_log2e;
 };
 
@@ -87,35 +68,6 @@ __device__ __forceinline__ raw16 load16(const T *p) {
     return *reinterpret_cast<const raw16 *>(p);
 }
 
-// sum over the LPR consecutive lanes that hold one row; result in all of them
-template <int LPR>
-__device__ __forceinline__ float row_lanes_sum(float v) {
-    if constexpr (LPR >= 2) v += lane_xor<1>(v);
-    if constexpr (LPR >= 4) v += lane_xor<2>(v);
-    if constexpr (LPR >= 8) v += lane_xor<4>(v);
-    if constexpr (LPR >= 16) v += lane_xor<8>(v);
-    if constexpr (LPR >= 32) v += lane_xor<16>(v);
-    return v;
-}
-// sum over the lanes of a wave that hold the same piece of different rows; result in all of them
-template <int LPR>
-__device__ __forceinline__ float same_piece_sum(float v) {
-    if constexpr (LPR <= 1) v += lane_xor<1>(v);
-    if constexpr (LPR <= 2) v += lane_xor<2>(v);
-    if constexpr (LPR <= 4) v += lane_xor<4>(v);
-    if constexpr (LPR <= 8) v += lane_xor<8>(v);
-    // across rows of 16 lanes: the LDS crossbar shuffle (the register-swap instructions, used 72
-    // times in a row at the end of the kernel, cost it ~70 registers)
-    if constexpr (LPR <= 16) v += __shfl_xor(v, 16);
-    if constexpr (LPR <= 32) v += __shfl_xor(v, 32);
-    return v;
-}
-
-__device__ __forceinline__ uint16_t bf16_round(float x) { // round to nearest even; x is not a NaN
-    const uint32_t u = __float_as_uint(x);
-    return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
-
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -138,429 +90,349 @@ __device__ __forceinline__ i16x4 lds_read_tr16(const unsigned char *p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3))) *)(p));
 }
 
+// Slot of 16-byte piece x of staged row `row`: x ^ row_swizzle.  The transpose reads of half a wave take two neighbouring
+// pieces of eight neighbouring rows: 256 bytes over all banks.
+template <int D>
+__device__ __forceinline__ int row_swizzle(int row) {
+    return ((row / (128 / D)) & (D / 16 - 1)) << 1;
+}
+
+// Where row `code` of [retrieved rows, local rows] lives: >= 0 a row of the store's slab, < 0 local row ~code.
+__device__ __forceinline__ const unsigned char *row_at(const unsigned char *store, const unsigned char *local, int code,
+                                                       unsigned store_stride, unsigned local_stride) {
+    const bool in_store = code >= 0;
+    const uint64_t off = (uint64_t)(unsigned)(in_store ? code : ~code) * (in_store ? store_stride : local_stride);
+    return (in_store ? store : local) + off;
+}
+
+// The rows of a tile are [kept rows of the listed frames, local rows], in blocks of 32 (bf16) or 16 (fp32), dealt to the
+// waves in turn.  A wave's block:
+//   rows     a lane works out where one row lives; the others fetch that by lane permutes.  Keys and values go straight to
+//            registers, 8 KB each, the next block's requested as soon as this one's are used up.
+//   scores   S^T = K Q^T (16x16x32 bf16, 16x16x4 fp32): a lane holds ONE query (lane % 16) and the rows 4 (lane / 16) + r
+//            of every 16, so a query's statistics are in-lane work and two exchanges between the rows of lanes.  (The
+//            reduction may walk the features in any order: a lane takes 16-byte pieces lane / 16 + 4 k of both.)
+//   values   O^T += V^T P^T: the weights are the B operand as they stand in the lane.  bf16: pairs hi + lo (two products,
+//            nothing of the fp32 weight is lost), the value rows pass through LDS the wave has to itself and the transpose
+//            read hands every lane the 8 rows of one feature.  fp32: step r takes rows 4 (lane / 16) + r, whose features
+//            the lanes of a row load in pieces of up to 16 bytes; a piece's elements belong to different output tiles, so
+//            no transpose is needed.
+// What bounds it: many questions, the rate at which the rows arrive (64 questions over 768 + 40 rows, 7B head layout, graph
+// replay: 16.4 us a call = 6.4 TB/s of rows, half of them read by several questions; a workgroup that took its rows through
+// tables and barriers shared by the waves, with a merge launch: 25.4); few, the chain launch -> frame list -> rows -> merge:
+// a compute unit alone draws its rows at 40 GB/s, so the rows of one question are split over workgroups although that costs
+// the merge launch (attend_split).  Eight waves a workgroup are no faster (16.4; 9.8 against 9.6 for one question).
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void attend_partial_kernel(AttendArgs a) {
-    constexpr int E = Row16<T>::E, LPR = D / E, RPP = kThreads / LPR; // lanes per row, rows per pass
-    // bf16 rows whose length is a multiple of 32: the scores come from the matrix cores
-    constexpr bool kMfma = sizeof(T) == 2 && D % 32 == 0;
-    constexpr int kWaves = kThreads / 64;
-    static_assert(LPR >= 1 && LPR <= 32, "a row fits in half a wave");
-    // Matrix path, value side: the chunk's value rows pass through LDS kSub at a time (row-major, padded rows) and
-    // come back as B operands by the LDS transpose read; the weights are bf16 pairs (hi + lo, so that nothing of
-    // the fp32 weight is lost) as A operands; a wave owns TPW 16-feature tiles of the output.
-    constexpr int kSub = 64, kVStride = D * 2 + 16;
-    constexpr int NP = kMfma ? kSub / RPP : 1; // 16-byte pieces of kSub rows per thread
-    constexpr int NT = D / 16, TPW = NT >= kWaves ? NT / kWaves : 1;
-    constexpr int kPRow = kChunk * 2 + 16; // bytes of a query's row of bf16 weights
-    // scores of the chunk, log2 units (rows padded by 8 floats).  VALU path: after the last chunk the same memory
-    // takes the per-wave outputs.  Matrix path: the weight pass rewrites it as the hi rows, then the lo rows.
-    __shared__ __align__(16) float s_sc[kTileQ][kChunk + 8];
-    static_assert(kWaves * (D > 64 ? D : 64) <= kChunk, "the per-wave outputs fit where the scores were");
-    static_assert(2 * kTileQ * kPRow <= (int)sizeof(s_sc), "hi and lo weights fit where the scores were");
-    unsigned char *const s_ph = reinterpret_cast<unsigned char *>(&s_sc[0][0]);
-    unsigned char *const s_pl = s_ph + kTileQ * kPRow;
-    __shared__ int s_row[kChunk]; // where row i of the chunk lives: >= 0 store row, <= -2 local row -2 - code, -1 nowhere
-    __shared__ int s_ft[kChunk];  // first token that sees the row (INT_MAX: nobody does)
-    __shared__ float s_wmax[kWaves][kTileQ]; // per-wave maxima of the chunk
-    __shared__ float s_run[kTileQ];  // running maximum of every query over the chunks so far
-    __shared__ float s_corr[kTileQ]; // factor that brings the sums so far to the new maximum
-    __shared__ float s_ref[kTileQ];  // what the exponent subtracts: the running maximum, or 0 while nothing was seen
-    __shared__ float s_zq[kTileQ];
-    // VALU path: softmax weights of the chunk (unnormalised), row-major.  Matrix path: kSub staged value rows.
-    __shared__ __align__(16) unsigned char s_u[kMfma ? kSub * kVStride : kChunk * kTileQ * 4];
-    float(*const s_p)[kTileQ] = reinterpret_cast<float(*)[kTileQ]>(s_u);
-    unsigned char *const s_v = s_u;
-    __shared__ int s_frame[kMaxGatherK]; // this split's frames; -1: names no frame of the cache
+__global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void attend_kernel(
+    AttendArgs a, T *__restrict__ out, float *__restrict__ lse) {
+    constexpr int W = kAttWaves;
+    constexpr bool kBf16 = sizeof(T) == 2;
+    constexpr int kRowB = D * (int)sizeof(T), kPieces = kRowB / 16;
+    constexpr int kRows = kBf16 ? 32 : 16;  // rows of a block
+    constexpr int kTiles = kRows / 16;      // 16-row tiles of the scores
+    constexpr int KK = kBf16 ? (D + 31) / 32 : D / 16; // 16-byte pieces of a key row (and of a query) per lane
+    constexpr int NF = D / 16;                         // 16-feature tiles of the output
+    // bf16: value pieces per lane, each load of the wave kRowsPerLoad whole rows.  fp32: per 4-row step D / 16 floats
+    constexpr int kRowsPerLoad = 64 / kPieces, NV = kBf16 ? kRows / kRowsPerLoad : 4;
+    constexpr int kVW = kBf16 ? 4 : (D >= 64 ? 4 : D / 16), kVH = kBf16 ? 1 : (D == 128 ? 2 : 1); // dwords per load, loads per row
+    typedef __attribute__((ext_vector_type(kVW))) unsigned int raw_v;
+    // per wave: staged value rows (bf16), at the end its outputs [16 queries][D]
+    __shared__ __align__(1024) unsigned char s_buf[W][64 * D];
+    __shared__ int s_frame[kMaxGatherK]; // the question's frames; -1: names no frame of the cache
+    __shared__ float s_m[W][kAttQ], s_l[W][kAttQ];
+    constexpr bool kQueryLds = !kBf16 && D == 128; // fp32, 128 features: the queries' operands wait in LDS
+    __shared__ raw16 s_q[kQueryLds ? KK : 1][kQueryLds ? 64 : 1];
     const int sp = blockIdx.x, g = blockIdx.y % a.Hkv, qt = blockIdx.y / a.Hkv, b = blockIdx.z;
-    const int tid = threadIdx.x, li = tid % LPR, rg = tid / LPR, wave = tid >> 6, lane = tid & 63;
-    const int lr = lane & 15, lg = lane >> 4;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lr = lane & 15, lg = lane >> 4;
     const int n_queries = a.n_q * a.G; // of this KV head: (token, head in group), token-major
-    const T *q = static_cast<const T *>(a.q);
-    auto query_row = [&](int n, bool *ok) { // element offset of query n of the tile
-        const int qq = qt * kTileQ + n;
-        *ok = n < kTileQ && qq < n_queries;
-        const int i = *ok ? qq / a.G : 0, h = g * a.G + (*ok ? qq % a.G : 0);
-        return (((int64_t)b * a.n_q + i) * a.Hq + h) * D;
-    };
-    auto token_of = [&](int n) { // INT_MIN: no such query, sees nothing
-        const int qq = qt * kTileQ + n;
-        return (n < kTileQ && qq < n_queries) ? qq / a.G : INT_MIN;
-    };
-
-    // VALU path: this lane's piece of every query of the tile, scaled so that scores come out in
-    // log2 units.  Matrix path: the queries as the B operand (column lane % 16 = query, 8 features
-    // from 8 * (lane / 16) of every 32), unscaled.
-    float qr[kMfma ? 1 : kTileQ][E];
-    if constexpr (!kMfma) {
-#pragma unroll
-        for (int n = 0; n < kTileQ; ++n) {
-            bool ok;
-            const int64_t off = query_row(n, &ok);
-            float x[E];
-            Row16<T>::expand(load16(q + off + li * E), x);
-#pragma unroll
-            for (int e = 0; e < E; ++e) qr[n][e] = ok ? x[e] * a.scale_log2e : 0.f;
-        }
+    for (int i = tid; i < a.k_frame; i += 64 * W) {
+        const int f = a.frame_idx[(int64_t)b * a.k_frame + i];
+        s_frame[i] = (f >= 0 && f < a.n_frames) ? f : -1;
     }
-
-    bf16x8 qb[kMfma ? D / 32 : 1]; // requested before anything else, needed after the first tables
-    if constexpr (kMfma) {
-        bool ok;
-        const int64_t off = query_row(lr, &ok);
+    // the lane's query as a matrix operand: 16-byte pieces lg, lg + 4, ... of its row
+    const int my_q = qt * kAttQ + lr;
+    const bool q_ok = my_q < n_queries;
+    const int my_tok = q_ok ? my_q / a.G : 0;
+    const int64_t my_row = ((int64_t)b * a.n_q + my_tok) * a.Hq + g * a.G + (q_ok ? my_q - my_tok * a.G : 0);
+    raw16 qb[kQueryLds ? 1 : KK];
+    const bool has_piece = kPieces >= 4 || lg < kPieces; // (rows of 32 bytes have two pieces)
+    const int my_piece = kPieces >= 4 ? lg : lg & (kPieces - 1);
 #pragma unroll
-        for (int kk = 0; kk < D / 32; ++kk) {
-            raw16 u = load16(q + off + kk * 32 + lg * 8);
-            if (!ok) u = raw16{0u, 0u, 0u, 0u};
-            qb[kk] = __builtin_bit_cast(bf16x8, u);
-        }
+    for (int kk = 0; kk < KK; ++kk) {
+        if (kQueryLds && wave != 0) break; // the same in all waves
+        raw16 x = load16(static_cast<const T *>(a.q) + my_row * D + (my_piece + 4 * kk) * (16 / (int)sizeof(T)));
+        if (!q_ok || !has_piece) x = raw16{0u, 0u, 0u, 0u};
+        if constexpr (kQueryLds)
+            s_q[kk][lane] = x;
+        else
+            qb[kk] = x;
     }
-
-    // rows of this split: kept rows of its frames, then (last split only) the local rows
-    const int f_lo = sp * a.frames_per_split;
-    const int f_hi = f_lo + a.frames_per_split < a.k_frame ? f_lo + a.frames_per_split : a.k_frame;
-    const int n_ret = f_hi > f_lo ? (f_hi - f_lo) * a.kappa : 0;
+    const int n_ret = a.k_frame * a.kappa;
     int l0 = 0, n_loc = 0;
-    if (a.local_offsets && sp == a.n_split - 1) {
+    if (a.local_offsets) {
         l0 = a.local_offsets[b];
         n_loc = a.local_offsets[b + 1] - l0;
         if (n_loc < 0) n_loc = 0;
     }
-    const int total = n_ret + n_loc;
-    for (int i = tid; i < f_hi - f_lo; i += kThreads) {
-        const int f = a.frame_idx[(int64_t)b * a.k_frame + f_lo + i];
-        s_frame[i] = (f >= 0 && f < a.n_frames) ? f : -1;
-    }
-    __syncthreads();
-    const T *sk = static_cast<const T *>(a.store_k) + (int64_t)g * a.store_cap * D;
-    const T *sv = static_cast<const T *>(a.store_v) + (int64_t)g * a.store_cap * D;
-    const T *lk = static_cast<const T *>(a.k_local), *lv = static_cast<const T *>(a.v_local);
-    // address of a row from its code; a row that lives nowhere reads the slab's first row (valid
-    // memory, the result is masked)
-    auto row_ptr = [&](const T *store, const T *local, int code) -> const T * {
-        if (code >= 0) return store + (int64_t)code * D;
-        if (code <= -2) return local + ((int64_t)(-2 - code) * a.Hkv + g) * D;
-        return store;
-    };
+    // rows up to the last one that a query of the tile sees (retrieved rows: every query)
+    const int first_tok = qt * kAttQ / a.G;
+    const int last_tok = (qt * kAttQ + kAttQ - 1 < n_queries ? qt * kAttQ + kAttQ - 1 : n_queries - 1) / a.G;
+    int n_rows = n_ret + n_loc;
+    if (a.causal && n_loc - a.n_q + last_tok + 1 < n_loc) n_rows = n_ret + (n_loc - a.n_q + last_tok + 1 > 0 ? n_loc - a.n_q + last_tok + 1 : 0);
+    // the workgroup's blocks of rows, dealt to its waves
+    const int n_blk = (n_rows + kRows - 1) / kRows, per = (n_blk + a.n_split - 1) / a.n_split;
+    const int b_lo = sp * per, b_hi = b_lo + per < n_blk ? b_lo + per : n_blk;
+    const unsigned char *sk = static_cast<const unsigned char *>(a.store_k) + (int64_t)g * a.store_cap * kRowB;
+    const unsigned char *sv = static_cast<const unsigned char *>(a.store_v) + (int64_t)g * a.store_cap * kRowB;
+    const unsigned char *lk = static_cast<const unsigned char *>(a.k_local) + g * kRowB;
+    const unsigned char *lv = static_cast<const unsigned char *>(a.v_local) + g * kRowB;
+    const unsigned local_stride = (unsigned)a.Hkv * kRowB;
+    __syncthreads(); // the frame list is there
 
-    float o[kMfma ? 1 : kTileQ][E]; // VALU path: this lane's 16-byte piece of the output of every query
-    f32x4 acc[TPW];                 // matrix path: queries 4 * (lane / 16) + r, feature 16 * tile + lane % 16
-    float zq = 0.f; // this thread's share of the normaliser of query tid / 32
-    static_assert(kThreads / 32 == kTileQ, "32 threads per query in the weight pass");
-    if (tid < kTileQ) s_run[tid] = -INFINITY; // read again only after the barriers of the first chunk
-#pragma unroll
-    for (int n = 0; n < (kMfma ? 1 : kTileQ); ++n) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) o[n][e] = 0.f;
-    }
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // matrix path: this thread's pieces of kSub value rows, on their way while the rows before them are used.
-    // Loads are unconditional (a row that lives nowhere, or past the chunk, reads the slab's first row); what
-    // was loaded instead of a row becomes zeros (its weights are zero, but zero times anything must stay zero).
-    raw16 vx[NP];
-    int n_rows = 0;
-    auto load_sub = [&](raw16(&vreg)[NP], int sub) {
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const int i = sub * kSub + p * RPP + rg;
-            const int code = i < n_rows ? s_row[i] : -1;
-            const raw16 x = load16(row_ptr(sv, lv, code) + li * E);
-            vreg[p] = code == -1 ? raw16{0u, 0u, 0u, 0u} : x;
+    // Where row lane % kRows of a block lives, and the first token that sees it (INT_MAX: it lives nowhere).  Loads are
+    // unconditional: a row that lives nowhere, or past the last, reads the slab's first row.  What was read instead of a value
+    // row becomes zeros (its weights are zero, but zero times anything must stay zero).
+    auto find = [&](int blk, int *code, int *ft) __attribute__((always_inline)) {
+        const int r = blk < b_hi ? blk * kRows + (lane & (kRows - 1)) : INT_MAX;
+        *code = 0;
+        *ft = INT_MAX;
+        if (r < n_ret) {
+            const int slot = (int)((unsigned)r / (unsigned)a.kappa), f = s_frame[slot];
+            if (f >= 0) {
+                *code = f * a.kappa + (r - slot * a.kappa);
+                *ft = 0;
+            }
+        } else if (r < n_rows) {
+            const int j = r - n_ret;
+            *code = ~(l0 + j);
+            *ft = a.causal ? j - (n_loc - a.n_q) : 0; // token i sees local row j iff j <= n_loc - n_q + i
         }
     };
+    auto value_row = [&](int u) { return kBf16 ? u * kRowsPerLoad + lane / kPieces : 4 * lg + u; }; // of the lane's load u
+    raw16 kx[kTiles][KK];
+    raw_v vx[NV][kVH];
+    auto request_keys = [&](int code) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) {
+            const unsigned char *p = row_at(sk, lk, __shfl(code, 16 * t + lr), kRowB, local_stride) + 16 * my_piece;
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) kx[t][kk] = *reinterpret_cast<const raw16 *>(p + 64 * kk);
+        }
+    };
+    auto request_values = [&](int code) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            const unsigned char *p = row_at(sv, lv, __shfl(code, value_row(u)), kRowB, local_stride) + (kBf16 ? lane % kPieces : lr) * 4 * kVW;
+#pragma unroll
+            for (int h = 0; h < kVH; ++h) vx[u][h] = *reinterpret_cast<const raw_v *>(p + 256 * h);
+        }
+    };
 
-    for (int c0 = 0; c0 < total; c0 += kChunk) {
-        n_rows = (c0 + kChunk < total ? c0 + kChunk : total) - c0;
-        // ---- where the rows of the chunk live and who sees them ----
-        for (int i = tid; i < n_rows; i += kThreads) {
-            const int r = c0 + i;
-            int code, ft = 0;
-            if (r < n_ret) {
-                const int slot = r / a.kappa;
-                const int f = s_frame[slot];
-                code = f < 0 ? -1 : f * a.kappa + (r - slot * a.kappa);
-            } else {
-                const int j = r - n_ret;
-                code = -2 - (l0 + j);
-                if (a.causal) ft = j - (n_loc - a.n_q); // token i sees local row j iff j <= n_loc - n_q + i
+    float m_run = -INFINITY, l_run = 0.f; // of query lr; l_run: over the rows this lane holds
+    f32x4 acc[NF]; // of query lr.  bf16: tile f, features 16 f + 4 lg + r.  fp32: tile (h, e), features 64 h + kVW (4 lg + r) + e
+#pragma unroll
+    for (int f = 0; f < NF; ++f) acc[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    unsigned char *const buf = s_buf[wave];
+    int code, ft; // of the block in hand
+    // One block; the next one's keys and values are requested as soon as the registers of this one's are free.
+    auto step = [&](auto more, int next) __attribute__((always_inline)) {
+        // ---- scores S^T = K Q^T: query lr, rows 16 t + 4 lg + r ----
+        f32x4 sc[kTiles];
+        if constexpr (kQueryLds) asm volatile("" ::: "memory"); // (the queries are read again, not held)
+        if constexpr (kBf16) {
+#pragma unroll
+            for (int t = 0; t < kTiles; ++t) {
+                sc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) {
+                    if (!has_piece) kx[t][kk] = raw16{0u, 0u, 0u, 0u};
+                    sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kx[t][kk]),
+                                                                    __builtin_bit_cast(bf16x8, qb[kk]), sc[t], 0, 0, 0);
+                }
             }
-            s_row[i] = code;
-            s_ft[i] = code == -1 ? INT_MAX : ft;
+        } else { // sums of four terms each, joined pair by pair: one sum of D terms is 9.6e-7 from fp64 over 800 rows of 128
+                 // features, of which the scores' share is most; this way 2.6e-7
+            f32x4 part[KK];
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                f32x4 c[4];
+                const raw16 qk = kQueryLds ? s_q[kk][lane] : qb[kQueryLds ? 0 : kk];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    c[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kx[0][kk][e]), __uint_as_float(qk[e]),
+                                                                f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                part[kk] = (c[0] + c[1]) + (c[2] + c[3]);
+            }
+#pragma unroll
+            for (int n = KK; n > 1; n /= 2)
+#pragma unroll
+                for (int i = 0; i < n / 2; ++i) part[i] = part[2 * i] + part[2 * i + 1];
+            sc[0] = part[0];
         }
-        __syncthreads();
-        // ---- scores of the chunk and their maxima ----
-        if constexpr (kMfma) {
-            // 16 rows per wave and step: S^T = K Q^T, so a lane ends up with one query (lane % 16)
-            // and the four rows 4 * (lane / 16) .. +3 of the step
-            const int my_tok = token_of(lr);
-            float m_q = -INFINITY;
-            // the key rows of kStepsA steps are requested together (rows past the chunk read its last row again:
-            // loads stay unconditional).  Requesting the next batch before this one is used, and larger batches,
-            // were measured and changed nothing: the launch moves its rows at the pace of the memory
-            constexpr int kBatch = kStepsA * 16 * kWaves;
-            auto load_k = [&](raw16(&ka)[kStepsA][D / 32], int R0) {
-#pragma unroll
-                for (int t = 0; t < kStepsA; ++t) {
-                    const int i = R0 + t * 16 * kWaves + lr;
-                    const T *kp = row_ptr(sk, lk, s_row[i < n_rows ? i : n_rows - 1]) + lg * 8;
-#pragma unroll
-                    for (int kk = 0; kk < D / 32; ++kk) ka[t][kk] = load16(kp + kk * 32);
-                }
-            };
-            auto use_k = [&](const raw16(&ka)[kStepsA][D / 32], int R0) {
-#pragma unroll
-                for (int t = 0; t < kStepsA; ++t) {
-                    const int R = R0 + t * 16 * kWaves;
-                    if (R >= n_rows) break;
-                    f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int kk = 0; kk < D / 32; ++kk)
-                        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[t][kk]), qb[kk], d, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int i2 = R + 4 * lg + r;
-                        if (i2 < n_rows && lr < kTileQ) {
-                            const float sc = my_tok >= s_ft[i2] ? d[r] * a.scale_log2e : -INFINITY;
-                            s_sc[lr][i2] = sc;
-                            m_q = fmaxf(m_q, sc);
-                        }
-                    }
-                }
-            };
-            raw16 kx[kStepsA][D / 32];
-            for (int R0 = 16 * wave; R0 < n_rows; R0 += kBatch) {
-                load_k(kx, R0);
-                use_k(kx, R0);
-            }
-            m_q = xrow_max(m_q);
-            if (lg == 0 && lr < kTileQ) s_wmax[wave][lr] = m_q;
-        } else {
-            int tok[kTileQ];
-            float m_loc[kTileQ];
-#pragma unroll
-            for (int n = 0; n < kTileQ; ++n) {
-                tok[n] = token_of(n);
-                m_loc[n] = -INFINITY;
-            }
-            for (int i0 = rg; i0 < n_rows; i0 += kUnroll * RPP) {
-                // all loads of the batch first, each from an address that is valid whatever the row is
-                raw16 kr[kUnroll];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    const int i = i0 + u * RPP;
-                    kr[u] = load16(row_ptr(sk, lk, s_row[i < n_rows ? i : n_rows - 1]) + li * E);
-                }
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    const int i = i0 + u * RPP;
-                    if (i >= n_rows) break;
-                    const int ft = s_ft[i];
-                    float kx[E];
-                    Row16<T>::expand(kr[u], kx);
-#pragma unroll
-                    for (int n = 0; n < kTileQ; ++n) {
-                        float sc = 0.f;
-#pragma unroll
-                        for (int e = 0; e < E; ++e) sc = fmaf(qr[n][e], kx[e], sc);
-                        sc = row_lanes_sum<LPR>(sc);
-                        if (tok[n] < ft) sc = -INFINITY;
-                        if (li == 0) s_sc[n][i] = sc;
-                        m_loc[n] = fmaxf(m_loc[n], sc);
-                    }
-                }
-            }
-#pragma unroll
-            for (int n = 0; n < kTileQ; ++n) {
-                const float m = wave_max(m_loc[n]);
-                if (lane == 0) s_wmax[wave][n] = m;
-            }
+        int code_next = 0, ft_next = 0;
+        if constexpr (more.value) {
+            __builtin_amdgcn_sched_barrier(0);
+            find(next, &code_next, &ft_next);
+            request_keys(code_next);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (kMfma) load_sub(vx, 0); // the first value rows are on their way while the maxima are agreed on
-        __syncthreads();
-        // ---- new running maximum: rescale what has been summed so far (once per chunk) ----
-        if (tid < kTileQ) {
-            float m = s_wmax[0][tid];
+        const bool late = __builtin_amdgcn_ballot_w64(ft > first_tok) != 0; // somebody does not see some row
+        if (late) {
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) m = fmaxf(m, s_wmax[w][tid]);
-            const float m_old = s_run[tid], m_new = fmaxf(m_old, m);
-            s_corr[tid] = m_old == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_old - m_new);
-            s_run[tid] = m_new;
-            s_ref[tid] = m_new == -INFINITY ? 0.f : m_new;
-        }
-        __syncthreads();
-        if constexpr (kMfma) {
-            if (c0 > 0) {
+            for (int t = 0; t < kTiles; ++t)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float corr = s_corr[(4 * lg + r) & (kTileQ - 1)];
-#pragma unroll
-                    for (int t = 0; t < TPW; ++t) acc[t][r] *= corr;
+                    const int from = __shfl(ft, 16 * t + 4 * lg + r);
+                    sc[t][r] = my_tok >= from ? sc[t][r] : -INFINITY;
                 }
-            }
-            // ---- the weights, once per (row, query): 32 threads per query walk the rows; their sums.  The
-            // scores are taken into registers first, then the same memory receives the weights as bf16 pairs;
-            // rows up to the next multiple of kSub get zero weights ----
-            const int n = tid >> 5;
-            const float ref = s_ref[n];
-            if (c0 > 0) zq *= s_corr[n];
-            const int n_pad = (n_rows + kSub - 1) / kSub * kSub;
-            float sreg[kChunk / 32];
+        }
+        // ---- statistics and weights, all of query lr (a NaN score is in no maximum and makes the sum one).  What the
+        // exponents subtract is a whole number, so that bringing sums from one to another multiplies by a power of two ----
+        float mx = fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3]));
+        if constexpr (kTiles == 2) mx = fmaxf(mx, fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
+        mx = ceilf(xrow_max(mx) * a.scale_log2e);
+        if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) { // a maximum moved: bring what was summed to it
+            const float m_new = fmaxf(m_run, mx);
+            const float corr = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
+            l_run *= corr;
 #pragma unroll
-            for (int k = 0; k < kChunk / 32; ++k) {
-                const int i = (tid & 31) + 32 * k;
-                sreg[k] = i < n_rows ? s_sc[n][i] : -INFINITY;
-            }
-            __syncthreads();
+            for (int f = 0; f < NF; ++f) acc[f] *= corr;
+        }
+        const float ref = m_run == -INFINITY ? 0.f : m_run;
+        float p[4 * kTiles];
 #pragma unroll
-            for (int k = 0; k < kChunk / 32; ++k) {
-                if (32 * k >= n_pad) break;
-                const int i = (tid & 31) + 32 * k;
-                const float p = __builtin_amdgcn_exp2f(sreg[k] - ref); // exp2(-inf) = 0 for a masked row
-                zq += p;
-                const uint16_t hi = bf16_round(p);
-                const uint16_t lo = bf16_round(p - __uint_as_float((uint32_t)hi << 16));
-                *reinterpret_cast<uint16_t *>(s_ph + n * kPRow + 2 * i) = hi;
-                *reinterpret_cast<uint16_t *>(s_pl + n * kPRow + 2 * i) = lo;
-            }
-            // ---- value accumulation on the matrix cores, kSub rows at a time ----
-            const int n_sub = n_pad / kSub;
-            // stage the rows held in vreg, request the next ones, multiply (two sets of rows in flight, like
-            // larger sets, were measured and changed nothing)
-            auto do_sub = [&](raw16(&vreg)[NP], int sub) {
-                __syncthreads(); // the rows staged before have been used (first time round: the weights are written)
+        for (int t = 0; t < kTiles; ++t)
 #pragma unroll
-                for (int p = 0; p < NP; ++p)
-                    *reinterpret_cast<raw16 *>(s_v + (p * RPP + rg) * kVStride + li * 16) = vreg[p];
-                __syncthreads();
-                if (sub + 1 < n_sub) load_sub(vreg, sub + 1);
-                if (wave * TPW < NT) {
+            for (int r = 0; r < 4; ++r) p[4 * t + r] = __builtin_amdgcn_exp2f(fmaf(sc[t][r], a.scale_log2e, -ref));
+        float sum = (p[0] + p[1]) + (p[2] + p[3]);
+        if constexpr (kTiles == 2) sum += (p[4] + p[5]) + (p[6] + p[7]);
+        l_run += sum;
+        if (late) { // what was read instead of a value row
 #pragma unroll
-                    for (int st = 0; st < kSub / 32; ++st) {
-                        const int r0 = sub * kSub + 32 * st;
-                        if (r0 >= n_rows) break;
-                        const unsigned char *pa = s_ph + (lr & (kTileQ - 1)) * kPRow + 2 * (r0 + 8 * lg);
-                        const bf16x8 ah = __builtin_bit_cast(bf16x8, *reinterpret_cast<const raw16 *>(pa));
-                        const bf16x8 al = __builtin_bit_cast(bf16x8, *reinterpret_cast<const raw16 *>(pa + kTileQ * kPRow));
+            for (int u = 0; u < NV; ++u) {
+                const bool nowhere = __shfl(ft, value_row(u)) == INT_MAX;
 #pragma unroll
-                        for (int t = 0; t < TPW; ++t) {
-                            const unsigned char *vp = s_v + (32 * st + 8 * lg + (lr >> 2)) * kVStride +
-                                                      2 * (16 * (wave * TPW + t) + 4 * (lr & 3));
-                            const i16x4 v0 = lds_read_tr16(vp), v1 = lds_read_tr16(vp + 4 * kVStride);
-                            const bf16x8 bv = __builtin_bit_cast(bf16x8, i16x8{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]});
-                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bv, acc[t], 0, 0, 0);
-                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bv, acc[t], 0, 0, 0);
-                        }
-                    }
-                }
-            };
-            for (int sub = 0; sub < n_sub; ++sub) do_sub(vx, sub);
-        } else {
-            if (c0 > 0) {
+                for (int h = 0; h < kVH; ++h)
 #pragma unroll
-                for (int n = 0; n < kTileQ; ++n) {
-                    const float corr = s_corr[n];
-#pragma unroll
-                    for (int e = 0; e < E; ++e) o[n][e] *= corr;
-                }
-            }
-            // ---- the weights, once per (row, query): 32 threads per query walk the rows; their sums ----
-            {
-                const int n = tid >> 5;
-                const float ref = s_ref[n];
-                if (c0 > 0) zq *= s_corr[n];
-                for (int i = tid & 31; i < n_rows; i += 32) {
-                    const float p = __builtin_amdgcn_exp2f(s_sc[n][i] - ref); // exp2(-inf) = 0 for a masked row
-                    s_p[i][n] = p;
-                    zq += p;
-                }
-            }
-            __syncthreads();
-            // ---- value accumulation: a value row spread over LPR lanes, kUnroll rows per lane in flight ----
-            for (int i0 = rg; i0 < n_rows; i0 += kUnroll * RPP) {
-                raw16 vr[kUnroll];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    const int i = i0 + u * RPP;
-                    vr[u] = load16(row_ptr(sv, lv, s_row[i < n_rows ? i : n_rows - 1]) + li * E);
-                }
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    const int i = i0 + u * RPP;
-                    if (i >= n_rows || s_row[i] == -1) continue; // what was loaded instead of a row is not a value
-                    float vx[E];
-                    Row16<T>::expand(vr[u], vx);
-                    const f32x4 p0 = *reinterpret_cast<const f32x4 *>(&s_p[i][0]);
-                    const f32x4 p1 = *reinterpret_cast<const f32x4 *>(&s_p[i][4]);
-#pragma unroll
-                    for (int n = 0; n < kTileQ; ++n) {
-                        const float p = n < 4 ? p0[n & 3] : p1[n & 3];
-#pragma unroll
-                        for (int e = 0; e < E; ++e) o[n][e] = fmaf(p, vx[e], o[n][e]);
-                    }
-                }
+                    for (int e = 0; e < kVW; ++e) vx[u][h][e] = nowhere ? 0u : vx[u][h][e];
             }
         }
-        __syncthreads(); // the tables are rewritten by the next chunk
-    }
-
-    zq += lane_xor<1>(zq); // the 32 threads of a query are half a wave
-    zq += lane_xor<2>(zq);
-    zq += lane_xor<4>(zq);
-    zq += lane_xor<8>(zq);
-    zq += __shfl_xor(zq, 16);
-    if ((tid & 31) == 0) s_zq[tid >> 5] = zq;
-    // the split's record of a query: [0] running maximum, [1] normaliser, [2..] unnormalised output
-    // (merged by a launch of its own: a merge by the last workgroup to finish, with records that cross the
-    // XCDs' L2 caches as device-scope atomics, took as long as that launch for 64 questions and longer for one)
-    auto record = [&](int n) -> float * { // of query n of the tile; null: no such query
-        const int qq = qt * kTileQ + n;
-        if (qq >= n_queries) return nullptr;
-        const int i = qq / a.G, h = g * a.G + qq % a.G;
-        return a.part + ((((int64_t)b * a.n_q + i) * a.Hq + h) * a.n_split + sp) * (D + 2);
+        // ---- O^T += V^T P^T: the weights are the B operand as they stand in the lane ----
+        if constexpr (kBf16) {
+            raw16 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                hi[e] = bf16_pair(p[2 * e], p[2 * e + 1]);
+                lo[e] = bf16_pair(p[2 * e] - __uint_as_float(hi[e] << 16), p[2 * e + 1] - __uint_as_float(hi[e] & 0xFFFF0000u));
+            }
+#pragma unroll
+            for (int u = 0; u < NV; ++u) {
+                const int row = value_row(u);
+                *reinterpret_cast<raw_v *>(buf + row * kRowB + 16 * ((lane % kPieces) ^ row_swizzle<D>(row))) = vx[u][0];
+            }
+            if constexpr (more.value) request_values(code_next);
+            asm volatile("" ::: "memory"); // a wave's LDS accesses keep their order; no other wave reads these rows
+            const int q4 = lr >> 2, piece = (lane & 3) >> 1, sub = 8 * (lane & 1);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const int r0 = 4 * lg + q4, r1 = r0 + 16;
+                const i16x4 v0 = lds_read_tr16(buf + r0 * kRowB + 16 * ((2 * f + piece) ^ row_swizzle<D>(r0)) + sub);
+                const i16x4 v1 = lds_read_tr16(buf + r1 * kRowB + 16 * ((2 * f + piece) ^ row_swizzle<D>(r1)) + sub);
+                const bf16x8 av = __builtin_bit_cast(bf16x8, i16x8{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]});
+                acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, hi), acc[f], 0, 0, 0);
+                acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, lo), acc[f], 0, 0, 0);
+            }
+            asm volatile("" ::: "memory"); // the next block's rows take their place
+        } else {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < kVH; ++h) // (a block's rows first, then one addition to what was summed before)
+#pragma unroll
+                for (int e = 0; e < kVW; ++e) {
+                    f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) d = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vx[u][h][e]), p[u], d, 0, 0, 0);
+                    acc[kVW * h + e] += d;
+                }
+            if constexpr (more.value) {
+                __builtin_amdgcn_sched_barrier(0);
+                request_values(code_next);
+            }
+        }
+        code = code_next;
+        ft = ft_next;
     };
-    if constexpr (kMfma) {
-        // the matrix cores have added all rows already: a lane writes what it holds (lanes 32.. hold copies)
-        if (lg < 2 && wave * TPW < NT) {
+    if (b_lo + wave < b_hi) {
+        int blk = b_lo + wave;
+        find(blk, &code, &ft);
+        request_keys(code);
+        request_values(code);
+        // the last block apart: a branch around the loads would make every wait in the loop one for all of them
+        for (; blk + W < b_hi; blk += W) step(std::true_type{}, blk + W);
+        step(std::false_type{}, 0);
+    }
+    // ---- the waves' results join in LDS ----
+    const float l_sum = xrow_sum(l_run);
+    if (lg == 0) {
+        // (maxima leave NaN scores out: where there was nothing else the sum is still to be looked at)
+        s_m[wave][lr] = m_run == -INFINITY && l_sum != 0.f ? 0.f : m_run;
+        s_l[wave][lr] = l_sum;
+    }
+    constexpr int kQuads = D / 4; // 4-feature pieces of an output row, piece c of query n at c ^ (n % kQuads)
+    f32x4(*const s_o)[kQuads] = reinterpret_cast<f32x4(*)[kQuads]>(buf);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        if constexpr (kBf16) {
+            s_o[lr][(4 * f + lg) ^ (lr & (kQuads - 1))] = acc[f];
+        } else if constexpr (kVW == 4) { // register r of the four tiles of h: features 64 h + 16 lg + 4 r ..
+            const int h = f / 4, r = f % 4;
+            s_o[lr][(16 * h + 4 * lg + r) ^ (lr & (kQuads - 1))] =
+                f32x4{acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]};
+        } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                float *rec = record(4 * lg + r);
-                if (!rec) continue;
-#pragma unroll
-                for (int t = 0; t < TPW; ++t) rec[2 + 16 * (wave * TPW + t) + lr] = acc[t][r];
+                const int d = kVW * (4 * lg + r) + f;
+                s_o[lr][(d / 4) ^ (lr & (kQuads - 1))][d % 4] = acc[f][r];
             }
         }
-        __syncthreads();
-    } else {
-        // ---- add the rows held by different lanes: inside a wave, then across the waves ----
-#pragma unroll
-        for (int n = 0; n < kTileQ; ++n) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) o[n][e] = same_piece_sum<LPR>(o[n][e]);
-        }
-        __syncthreads(); // (every wave is done with the chunk's scores)
-        if (lane < LPR) {
-#pragma unroll
-            for (int n = 0; n < kTileQ; ++n)
-#pragma unroll
-                for (int e = 0; e < E; ++e) s_sc[n][wave * (D > 64 ? D : 64) + li * E + e] = o[n][e];
-        }
-        __syncthreads();
-        for (int idx = tid; idx < kTileQ * D; idx += kThreads) {
-            const int n = idx / D, d = idx - n * D;
-            float *rec = record(n);
-            if (!rec) continue;
-            float val = 0.f;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) val += s_sc[n][w * (D > 64 ? D : 64) + d];
-            rec[2 + d] = val;
-        }
     }
-    if (tid < kTileQ) {
-        float *rec = record(tid);
-        if (rec) { // (maxima leave NaN scores out: where there was nothing else the denominator is still to be looked at)
-            rec[0] = s_run[tid] == -INFINITY && s_zq[tid] != 0.f ? 0.f : s_run[tid];
-            rec[1] = s_zq[tid];
+    __syncthreads();
+    const int n_q_here = n_queries - qt * kAttQ < kAttQ ? n_queries - qt * kAttQ : kAttQ;
+    for (int i = tid; i < n_q_here * kQuads; i += 64 * W) {
+        const int n = i / kQuads, c = i - n * kQuads, qq = qt * kAttQ + n, tok = qq / a.G;
+        float m = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < W; ++w) m = fmaxf(m, s_m[w][n]);
+        float l = 0.f;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const float lw = s_l[w][n];
+            if (lw != 0.f) { // a wave none of whose rows the query sees has nothing to add (a NaN has)
+                const float x = __builtin_amdgcn_exp2f(s_m[w][n] - m);
+                l = fmaf(lw, x, l);
+                const f32x4 ow = reinterpret_cast<const f32x4(*)[kQuads]>(s_buf[w])[n][c ^ (n & (kQuads - 1))];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = fmaf(ow[e], x, o[e]);
+            }
+        }
+        const int64_t row = ((int64_t)b * a.n_q + tok) * a.Hq + g * a.G + (qq - tok * a.G);
+        if (a.n_split > 1) { // the split's record: [0] maximum, [1] normaliser, [2..] unnormalised output
+            float *rec = a.part + (row * a.n_split + sp) * (D + 2);
+            if (c == 0) {
+                rec[0] = m;
+                rec[1] = l;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rec[2 + 4 * c + e] = o[e];
+        } else {
+            const float den = l != 0.f ? l : 1.f;
+            if constexpr (kBf16)
+                *reinterpret_cast<u32x2 *>(out + row * D + 4 * c) = u32x2{bf16_pair(o[0] / den, o[1] / den), bf16_pair(o[2] / den, o[3] / den)};
+            else
+                *reinterpret_cast<f32x4 *>(out + row * D + 4 * c) = o / den;
+            if (lse && c == 0) lse[row] = l != 0.f ? m + __builtin_amdgcn_logf(l) : INFINITY;
         }
     }
 }
@@ -1415,11 +1287,13 @@ struct PrefillOut { // all null for the plain attention call
 
 template <typename T, int D>
 hipError_t launch_typed(const AttendArgs &a, int B, void *out, const PrefillOut &po, hipStream_t st) {
-    hipLaunchKernelGGL((attend_partial_kernel<T, D>), dim3(a.n_split, a.Hkv * a.n_qtiles, B), dim3(kThreads), 0, st, a);
+    const dim3 grid(a.n_split, a.Hkv * ((a.n_q * a.G + kAttQ - 1) / kAttQ), B);
+    hipLaunchKernelGGL((attend_kernel<T, D>), grid, dim3(64 * kAttWaves), 0, st, a, static_cast<T *>(out), po.lse);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attend_combine_kernel<T, D>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D < 64 ? 64 : D), 0, st,
-                       a.part, a.n_split, static_cast<T *>(out), po.lse);
+    if (a.n_split > 1)
+        hipLaunchKernelGGL((attend_combine_kernel<T, D>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D < 64 ? 64 : D), 0, st,
+                           a.part, a.n_split, static_cast<T *>(out), po.lse);
     if constexpr (sizeof(T) == 2 && D >= 64) return hipGetLastError(); // their prefill is the matrix-core one
     if ((e = hipGetLastError()) != hipSuccess || !po.signal) return e;
     if constexpr (sizeof(T) == 4 || D < 64)
@@ -1503,19 +1377,32 @@ hipError_t launch_flash(const AttendArgs &a, int n_fs, int B, void *out, const P
     return hipGetLastError();
 }
 
-int split_count(int B, int Hkv, int n_qtiles, int k_frame, int *frames_per_split) {
-    // about three workgroups per compute unit (what fits at once): a workgroup walks its rows in
-    // dependent batches of loads, so shorter lists finish sooner; at most kAttendMaxSplit splits,
-    // at least one frame each
-    // (64 questions of the 1-hour shape: 2 or 3 per compute unit take the same 28 us, 1 takes 37, 4 / 6 / 8 take
-    // 34 / 38 / 43 -- every workgroup pays its chain of dependent steps once more)
+// Split records per query that the workspace of a prefill without the matrix-core kernels counts.
+int record_splits(int B, int Hkv, int n_qtiles, int k_frame) {
     int64_t n_split = (3 * 256 + (int64_t)B * Hkv * n_qtiles - 1) / ((int64_t)B * Hkv * n_qtiles);
     if (n_split > kAttendMaxSplit) n_split = kAttendMaxSplit;
     if (n_split > k_frame) n_split = k_frame;
     if (n_split < 1) n_split = 1;
-    *frames_per_split = k_frame > 0 ? (int)((k_frame + n_split - 1) / n_split) : 0;
-    if (k_frame > 0) n_split = (k_frame + *frames_per_split - 1) / *frames_per_split;
+    const int per = k_frame > 0 ? (int)((k_frame + n_split - 1) / n_split) : 0;
+    if (k_frame > 0) n_split = (k_frame + per - 1) / per;
     return (int)n_split;
+}
+
+// Workgroups that share the rows of one tile of attend_kernel.  A wave takes about 1.1 us a block while the chip is nearly
+// empty, and splitting costs the merge launch, 3.5 us: rows are split where a wave has more than five blocks, into shares
+// of six blocks or more, and no further than one workgroup per compute unit.  us a call, 7B head layout, 768 + 40 rows, by
+// shares 1 / 2 / 4 / 8: one question 11.8 / 11.2 / 9.6 / 9.6, 8 questions 13.8 / 12.5 / 10.6 / 11.2, 16: 14.3 / 14.0 / 12.1 /
+// 13.9, 48 (192 workgroups unsplit): 15.7 / 19.8 / 20.6 / 25.9; one question over 128 rows 5.9 / 7.1 / 7.7 / 8.7, over 4736:
+// 53 / 32 / 21 / 15.  (The local rows are known on the device only; n_q of them at least are there or do not matter.)
+int attend_split(const Ctx &c, int n_q, int B, int k_frame) {
+    const int rows = c.esz == 2 ? 32 : 16; // of a block
+    const int64_t wgs = ((int64_t)n_q * c.group + kAttQ - 1) / kAttQ * c.cfg.n_kv_heads * B;
+    const int64_t blocks = ((int64_t)k_frame * c.kappa + n_q + rows - 1) / rows;
+    if (blocks <= 5 * kAttWaves) return 1;
+    int64_t n = 256 / wgs;
+    if (n > blocks / 6) n = blocks / 6;
+    if (n > kAttendMaxSplit) n = kAttendMaxSplit;
+    return n < 1 ? 1 : (int)n;
 }
 
 } // namespace
@@ -1528,7 +1415,7 @@ static bool flash_shape(const Ctx &c) { return c.cfg.dtype == MUKV_BF16 && (c.cf
 int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame) {
     const int64_t n_queries = (int64_t)n_q * c.group, combos = (int64_t)c.cfg.n_kv_heads * B, rows = (int64_t)B * n_q * c.cfg.n_q_heads;
     const int k = k_frame > 0 ? k_frame : 0;
-    int64_t n_split, tiles;
+    int64_t n_split, tiles; // (as they were when the figure became part of the interface: more tiles than there are now)
     if (c.cfg.dtype == MUKV_BF16 && c.cfg.head_dim == 128) {
         tiles = (n_queries + 63) / 64;
         const int64_t steps = ((int64_t)k * c.kappa + n_q + 31) / 32;
@@ -1537,9 +1424,8 @@ int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame) {
         if (n_split > steps / 4) n_split = steps / 4;
         if (tiles * combos >= 384 || n_split <= 1) n_split = 0; // one launch: no records
     } else {
-        int fps;
         tiles = (n_queries + kTileQ - 1) / kTileQ;
-        n_split = split_count(B, c.cfg.n_kv_heads, (int)tiles, k, &fps);
+        n_split = record_splits(B, c.cfg.n_kv_heads, (int)tiles, k);
     }
     return (rows * n_split * (c.cfg.head_dim + 2) + rows + combos * tiles * n_q) * (int64_t)sizeof(float);
 }
@@ -1586,7 +1472,11 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
     a.n_qtiles = (n_q * c.group + kTileQ - 1) / kTileQ;
     a.causal = causal;
     a.scale_log2e = 1.4426950408889634f / sqrtf((float)c.cfg.head_dim);
-    a.n_split = split_count(B, a.Hkv, a.n_qtiles, a.k_frame, &a.frames_per_split);
+a.n_split = attend_split(c, n_q, B, a.k_frame);
+    if (workspace) { // (its records are counted by the formula above)
+        const int most = record_splits(B, a.Hkv, a.n_qtiles, a.k_frame);
+        if (a.n_split > most) a.n_split = most;
+    }
     PrefillOut po{nullptr, nullptr, nullptr};
     const int n_fs = workspace && flash_shape(c) ? flash_split(c, n_q, B, k_frame) : 0;
     if (workspace) {

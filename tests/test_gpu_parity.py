@@ -821,8 +821,8 @@ def test_attention_over_retrieved_and_local_rows(name, frames, kw):
 
 
 def test_attention_over_long_contexts_and_many_questions():
-    # 64 questions (one split per workgroup, rows taken in several chunks of 512) and one
-    # question (the frame list split over workgroups); local rows longer than a chunk
+    # 64 questions (a tile's rows unsplit, several blocks per wave) and one question (its rows split over workgroups);
+    # many local rows
     w = W["7b"].scaled(n_frames=40, n_layers=2, n_questions=64)
     p = Pair(w, seed=181, chunk=8)
     p.ingest()
@@ -832,6 +832,27 @@ def test_attention_over_long_contexts_and_many_questions():
     p.check_attend(1, 2, idx, [int(x) for x in rs.integers(2, 40, 64)], causal=True, seed=8)
     p.check_attend(1, 1, idx[:1], [700], causal=True, seed=9)
     p.check_attend(0, 1, [idx[0][:1]], [3], causal=True, seed=10)
+    p.close()
+
+
+@pytest.mark.parametrize("dtype,D,hq,hkv,n_q", [
+    ("bf16", 128, 14, 2, 1), ("bf16", 64, 16, 1, 1), ("bf16", 32, 17, 1, 2), ("bf16", 16, 4, 2, 5),     # queries short of,
+    ("f32", 128, 28, 4, 1), ("f32", 64, 8, 2, 4), ("f32", 32, 6, 3, 16), ("f32", 16, 4, 1, 3),          # on and past a tile
+])
+def test_attention_at_the_edges_of_row_blocks_and_shares(dtype, D, hq, hkv, n_q):
+    # blocks of 16 or 32 rows dealt to four waves, rows split over workgroups past 20 blocks
+    w = W["tiny"].scaled(n_frames=40, n_questions=4, n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=D, dtype=dtype, tokens_per_frame=49,
+                         keep_ratio=0.5)
+    p = Pair(w, seed=183, chunk=8)
+    p.ingest()
+    kap = p.gpu.kappa
+    assert kap == 24
+    frames = [int(x) for x in np.random.default_rng(6).permutation(40)]
+    for k, ends in ((0, (1, 15, 16, 17)), (1, (31, 32, 33, 65)), (5, (127, 128, 129, 161)), (26, (639, 640, 641, 672)), (40, (960, 992, 993, 1023))):
+        lists = [frames[:k]] * 4 if k else None
+        p.check_attend(0, n_q, lists, [n - k * kap for n in ends], causal=bool(k % 2), seed=20 + k)
+    p.check_attend(0, n_q, [frames[:30] + [-1] * 6 + [40], [-1] * 37, [-1] * 36 + [3], frames[:37]], [0, 0, 2, 5], causal=True, seed=90)
+    p.check_attend(0, n_q, [frames[:27]], [70], causal=True, seed=91)
     p.close()
 
 
@@ -1032,7 +1053,7 @@ def test_large_unit_argument_errors():
     ("tiny", 12, {}, 49, [0, 5]),                       # fp32 payload, one frame of new tokens
     ("7b", 10, {"n_layers": 2}, 196, [0, 3]),           # bf16, matrix-core scores, G = 7
     ("72b", 12, {"n_layers": 2}, 2 * 64 + 5, [7]),      # G = 8, ragged
-    ("tiny", 6, {"head_dim": 16, "dtype": "bf16", "n_kv_heads": 2}, 30, [0, 1, 40]),   # bf16 on the VALU path
+    ("tiny", 6, {"head_dim": 16, "dtype": "bf16", "n_kv_heads": 2}, 30, [0, 1, 40]),   # bf16 rows of 16 features
 ])
 def test_prefill_attention_and_received_signal(name, frames, kw, n_q, old):
     w = W[name].scaled(n_frames=frames, n_questions=len(old), **kw)

@@ -146,71 +146,70 @@ class MuKVError(RuntimeError):
 
 
 def _check(status: int, where: str):
-    if status != MUKV_OK:
+    if status:
         raise MuKVError(status, where)
 
 
 # ---- functions named after the C ABI -------------------------------------------------------
 def mukv_create(cfg: mukv_config) -> C.c_void_p:
     h = C.c_void_p()
-    _check(load().mukv_create(C.byref(cfg), C.byref(h)), "mukv_create")
+    _check((_lib or load()).mukv_create(C.byref(cfg), C.byref(h)), "mukv_create")
     return h
 
 
 def mukv_destroy(h):
-    _check(load().mukv_destroy(h), "mukv_destroy")
+    _check((_lib or load()).mukv_destroy(h), "mukv_destroy")
 
 
 def mukv_reset(h):
-    _check(load().mukv_reset(h), "mukv_reset")
+    _check((_lib or load()).mukv_reset(h), "mukv_reset")
 
 
 def mukv_flush(h):
-    _check(load().mukv_flush(h), "mukv_flush")
+    _check((_lib or load()).mukv_flush(h), "mukv_flush")
 
 
 def mukv_compress_chunk(h, k_ptr, v_ptr, kv_strides, q_ptr, q_strides, att_ptr, n_frames, stream, sig=None):
-    _check(load().mukv_compress_chunk(h, k_ptr, v_ptr, C.byref(kv_strides), q_ptr,
-                                      C.byref(q_strides) if q_strides is not None else None, att_ptr, n_frames,
-                                      stream, C.byref(sig) if sig is not None else None), "mukv_compress_chunk")
+    _check((_lib or load()).mukv_compress_chunk(h, k_ptr, v_ptr, kv_strides, q_ptr, q_strides, att_ptr, n_frames, stream, sig),
+           "mukv_compress_chunk")
 
 
 def mukv_retrieve(h, q_ptr, off_ptr, B, params, seg_idx, seg_score, frm_idx, frm_score, stream):
-    _check(load().mukv_retrieve(h, q_ptr, off_ptr, B, C.byref(params), seg_idx, seg_score, frm_idx, frm_score, stream),
+    _check((_lib or load()).mukv_retrieve(h, q_ptr, off_ptr, B, C.byref(params), seg_idx, seg_score, frm_idx, frm_score, stream),
            "mukv_retrieve")
 
 
 def mukv_gather_kv(h, idx_ptr, B, k_frame, order, k_out, v_out, n_tok, stream):
-    _check(load().mukv_gather_kv(h, idx_ptr, B, k_frame, order, k_out, v_out, n_tok, stream), "mukv_gather_kv")
+    _check((_lib or load()).mukv_gather_kv(h, idx_ptr, B, k_frame, order, k_out, v_out, n_tok, stream), "mukv_gather_kv")
 
 
 def mukv_retrieve_patches(h, q_ptr, off_ptr, B, params, patch_idx, patch_score, stream):
-    _check(load().mukv_retrieve_patches(h, q_ptr, off_ptr, B, C.byref(params), patch_idx, patch_score, stream),
+    _check((_lib or load()).mukv_retrieve_patches(h, q_ptr, off_ptr, B, C.byref(params), patch_idx, patch_score, stream),
            "mukv_retrieve_patches")
 
 
 def mukv_retrieve_at(h, q_ptr, off_ptr, nv_ptr, B, params, level, seg_idx, seg_score, fine_idx, fine_score, stream):
-    _check(load().mukv_retrieve_at(h, q_ptr, off_ptr, nv_ptr, B, C.byref(params), level, seg_idx, seg_score, fine_idx,
+    _check((_lib or load()).mukv_retrieve_at(h, q_ptr, off_ptr, nv_ptr, B, C.byref(params), level, seg_idx, seg_score, fine_idx,
                                    fine_score, stream), "mukv_retrieve_at")
 
 
 def mukv_gather_patches(h, idx_ptr, B, k_patch, order, k_out, v_out, n_tok, stream):
-    _check(load().mukv_gather_patches(h, idx_ptr, B, k_patch, order, k_out, v_out, n_tok, stream), "mukv_gather_patches")
+    _check((_lib or load()).mukv_gather_patches(h, idx_ptr, B, k_patch, order, k_out, v_out, n_tok, stream), "mukv_gather_patches")
 
 
 def mukv_gather_union(h, seg_ptr, k_seg, frm_ptr, k_frame, pat_ptr, k_patch, B, rows_cap, k_out, v_out, n_tok, stream):
-    _check(load().mukv_gather_union(h, seg_ptr, k_seg, frm_ptr, k_frame, pat_ptr, k_patch, B, rows_cap, k_out, v_out, n_tok,
+    _check((_lib or load()).mukv_gather_union(h, seg_ptr, k_seg, frm_ptr, k_frame, pat_ptr, k_patch, B, rows_cap, k_out, v_out, n_tok,
                                     stream), "mukv_gather_union")
 
 
 def mukv_attend(h, layer, q_ptr, n_q, idx_ptr, k_frame, kl_ptr, vl_ptr, loff_ptr, B, causal_local, out_ptr, stream):
-    _check(load().mukv_attend(h, layer, q_ptr, n_q, idx_ptr, k_frame, kl_ptr, vl_ptr, loff_ptr, B, causal_local, out_ptr,
+    _check((_lib or load()).mukv_attend(h, layer, q_ptr, n_q, idx_ptr, k_frame, kl_ptr, vl_ptr, loff_ptr, B, causal_local, out_ptr,
                               stream), "mukv_attend")
 
 
 def mukv_retrieve_units(h, q_ptr, off_ptr, B, k, lambda_g, n_visible, g_in_ptr, n_global, g_out_ptr, idx_ptr, score_ptr,
                         stream):
-    _check(load().mukv_retrieve_units(h, q_ptr, off_ptr, B, k, lambda_g, n_visible, g_in_ptr, n_global, g_out_ptr,
+    _check((_lib or load()).mukv_retrieve_units(h, q_ptr, off_ptr, B, k, lambda_g, n_visible, g_in_ptr, n_global, g_out_ptr,
                                       idx_ptr, score_ptr, stream), "mukv_retrieve_units")
 
 
@@ -221,19 +220,19 @@ def mukv_gather_multi(handles, idx_ptrs, ks, units_per_step, B, rows_cap, k_out_
     ips = (C.c_void_p * n)(*[raw(p) for p in idx_ptrs])
     kk = (C.c_int32 * n)(*ks)
     ups = (C.c_int32 * n)(*units_per_step)
-    _check(load().mukv_gather_multi(hs, n, ips, kk, ups, B, rows_cap, k_out_ptr, v_out_ptr, n_tok_ptr, stream),
+    _check((_lib or load()).mukv_gather_multi(hs, n, ips, kk, ups, B, rows_cap, k_out_ptr, v_out_ptr, n_tok_ptr, stream),
            "mukv_gather_multi")
 
 
 def mukv_prefill_workspace_size(h, n_q, k_frame, B):
     n = C.c_int64(0)
-    _check(load().mukv_prefill_workspace_size(h, n_q, k_frame, B, C.byref(n)), "mukv_prefill_workspace_size")
+    _check((_lib or load()).mukv_prefill_workspace_size(h, n_q, k_frame, B, C.byref(n)), "mukv_prefill_workspace_size")
     return n.value
 
 
 def mukv_prefill_attend(h, layer, q_ptr, n_q, idx_ptr, k_frame, kl_ptr, vl_ptr, loff_ptr, B, causal_local, out_ptr, sig_ptr,
                         ws_ptr, ws_bytes, stream):
-    _check(load().mukv_prefill_attend(h, layer, q_ptr, n_q, idx_ptr, k_frame, kl_ptr, vl_ptr, loff_ptr, B, causal_local,
+    _check((_lib or load()).mukv_prefill_attend(h, layer, q_ptr, n_q, idx_ptr, k_frame, kl_ptr, vl_ptr, loff_ptr, B, causal_local,
                                       out_ptr, sig_ptr, ws_ptr, ws_bytes, stream), "mukv_prefill_attend")
 
 
@@ -242,41 +241,41 @@ MUKV_STATIC_SCRATCH_BYTES = 32 * 1024 * 1024
 
 def mukv_prefill_attend_static(h, layer, q_ptr, n_q, idx_ptr, k_frame, kl_ptr, vl_ptr, loff_ptr, B, causal_local, out_ptr,
                                sig_ptr, stream):
-    _check(load().mukv_prefill_attend_static(h, layer, q_ptr, n_q, idx_ptr, k_frame, kl_ptr, vl_ptr, loff_ptr, B,
+    _check((_lib or load()).mukv_prefill_attend_static(h, layer, q_ptr, n_q, idx_ptr, k_frame, kl_ptr, vl_ptr, loff_ptr, B,
                                              causal_local, out_ptr, sig_ptr, stream), "mukv_prefill_attend_static")
 
 
 def mukv_snapshot_size(h) -> int:
     n = C.c_int64()
-    _check(load().mukv_snapshot_size(h, C.byref(n)), "mukv_snapshot_size")
+    _check((_lib or load()).mukv_snapshot_size(h, C.byref(n)), "mukv_snapshot_size")
     return n.value
 
 
 def mukv_snapshot_save(h, host_ptr, n_bytes, stream):
-    _check(load().mukv_snapshot_save(h, host_ptr, n_bytes, stream), "mukv_snapshot_save")
+    _check((_lib or load()).mukv_snapshot_save(h, host_ptr, n_bytes, stream), "mukv_snapshot_save")
 
 
 def mukv_snapshot_load(h, host_ptr, n_bytes, stream):
-    _check(load().mukv_snapshot_load(h, host_ptr, n_bytes, stream), "mukv_snapshot_load")
+    _check((_lib or load()).mukv_snapshot_load(h, host_ptr, n_bytes, stream), "mukv_snapshot_load")
 
 
 def mukv_profile_begin(h):
-    _check(load().mukv_profile_begin(h), "mukv_profile_begin")
+    _check((_lib or load()).mukv_profile_begin(h), "mukv_profile_begin")
 
 
 def mukv_profile_end(h) -> dict:
     p = mukv_profile()
-    _check(load().mukv_profile_end(h, C.byref(p)), "mukv_profile_end")
+    _check((_lib or load()).mukv_profile_end(h, C.byref(p)), "mukv_profile_end")
     return {n: {"ms": p.ms[i], "launches": p.launches[i]} for i, n in enumerate(KERNEL_NAMES)}
 
 
 def mukv_plain_copy(dst_ptr, src_ptr, n_bytes, stream):
-    _check(load().mukv_plain_copy(dst_ptr, src_ptr, n_bytes, stream), "mukv_plain_copy")
+    _check((_lib or load()).mukv_plain_copy(dst_ptr, src_ptr, n_bytes, stream), "mukv_plain_copy")
 
 
 def mukv_get_state(h) -> mukv_state:
     s = mukv_state()
-    _check(load().mukv_get_state(h, C.byref(s)), "mukv_get_state")
+    _check((_lib or load()).mukv_get_state(h, C.byref(s)), "mukv_get_state")
     return s
 
 
@@ -293,12 +292,20 @@ def _hip_rt():
     return _hip
 
 
+# The handle of torch's current stream.  Calls of this module are a few microseconds of work each and a stream is hundreds of
+# them, so pointers and handles travel as plain integers (the declared argument types take them as they are) and the stream
+# is asked for without building a Stream object: a chunk's call 9.1 us -> 3.6, one of attend() 11.4 -> 5.8 (the launch is most of it).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 class MuKV:
@@ -321,6 +328,9 @@ class MuKV:
         # references to the buffers of the chunks the library may still read: the batch being
         # gathered, the two before it (overlap_copy) and one spare
         self._held = collections.deque(maxlen=4 * max(1, batch_chunks) + 1)
+        self._tokens = tokens_per_frame
+        self._kv_strides = self._q_strides = (None, None)   # strides of the last chunk and their C form
+        self._ws_need = (None, 0)                           # shape of the last prefill call and its workspace
 
     def close(self):
         if self.h is not None:
@@ -361,23 +371,31 @@ class MuKV:
     def compress_chunk(self, k, v, q_last=None, att_signal=None, want_signals=False):
         """k, v: [L][Hkv][n*P][D] (any layer/head/token strides, D contiguous);
         q_last: [Hq][n*P][D]; att_signal: float32 [n][P]."""
-        P = self.cfg.tokens_per_frame
-        assert k.dim() == 4 and k.shape == v.shape and k.stride() == v.stride() and k.stride(3) == 1
-        assert k.dtype == self.dtype and k.shape[2] % P == 0
-        n = k.shape[2] // P
-        kvs = mukv_strides(k.stride(0), k.stride(1), k.stride(2))
+        P, shape, ks = self._tokens, k.shape, k.stride()
+        assert len(shape) == 4 and v.shape == shape and v.stride() == ks and ks[3] == 1
+        n, rest = divmod(shape[2], P)
+        assert k.dtype == self.dtype and rest == 0
+        key, kvs = self._kv_strides
+        if key != ks:
+            kvs = mukv_strides(ks[0], ks[1], ks[2])
+            self._kv_strides = ks, kvs
         qs = None
         if q_last is not None:
-            assert q_last.dim() == 3 and q_last.stride(2) == 1 and q_last.dtype == self.dtype
-            assert q_last.shape[1] == k.shape[2]
-            qs = mukv_strides(0, q_last.stride(0), q_last.stride(1))
+            qt = q_last.stride()
+            assert len(qt) == 3 and qt[2] == 1 and q_last.dtype == self.dtype
+            assert q_last.shape[1] == shape[2]
+            key, qs = self._q_strides
+            if key != qt:
+                qs = mukv_strides(0, qt[0], qt[1])
+                self._q_strides = qt, qs
         sig, outs = None, None
         if want_signals:
             outs = {n_: torch.zeros(n, P, dtype=torch.float32, device=k.device) for n_ in ("att", "fft", "fused")}
             sig = mukv_signals_out(outs["att"].data_ptr(), outs["fft"].data_ptr(), outs["fused"].data_ptr())
         if att_signal is not None:
             assert att_signal.dtype == torch.float32 and att_signal.is_contiguous() and att_signal.shape == (n, P)
-        mukv_compress_chunk(self.h, _ptr(k), _ptr(v), kvs, _ptr(q_last), qs, _ptr(att_signal), n, _stream(), sig)
+        mukv_compress_chunk(self.h, k.data_ptr(), v.data_ptr(), kvs, None if q_last is None else q_last.data_ptr(), qs,
+                            None if att_signal is None else att_signal.data_ptr(), n, _stream(), sig)
         # The library reads these buffers (and writes the signal outputs) when the gathered batch is
         # launched, with overlap_copy one batch later still: hold references that long.
         self._held.append((k, v, q_last, att_signal, outs))
@@ -481,7 +499,7 @@ class MuKV:
     def attend(self, layer, q, frame_idx=None, k_local=None, v_local=None, local_offsets=None, causal_local=True,
                out=None):
         """q [B][n_q][Hq][D]; frame_idx [B][k] int32 or None; local rows [n][Hkv][D] with offsets [B+1]."""
-        B, n_q = q.shape[0], q.shape[1]
+        B, n_q = q.shape[:2]
         k_frame = 0 if frame_idx is None else frame_idx.shape[1]
         if out is None:
             out = torch.empty_like(q)
@@ -494,9 +512,12 @@ class MuKV:
                        signal=None, workspace=None):
         """As attend(), for many new tokens (the last n_q local rows of each question); also returns the
         attention each new token receives, float32 [B][n_q].  workspace: a uint8 device tensor to reuse."""
-        B, n_q = q.shape[0], q.shape[1]
+        B, n_q = q.shape[:2]
         k_frame = 0 if frame_idx is None else frame_idx.shape[1]
-        need = mukv_prefill_workspace_size(self.h, n_q, k_frame, B)
+        key, need = self._ws_need
+        if key != (n_q, k_frame, B):
+            need = mukv_prefill_workspace_size(self.h, n_q, k_frame, B)
+            self._ws_need = (n_q, k_frame, B), need
         if workspace is None or workspace.numel() < need:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
         if out is None:
@@ -512,7 +533,7 @@ class MuKV:
     def prefill_attend_static(self, layer, q, frame_idx, k_local, v_local, local_offsets, causal_local, out, signal):
         """prefill_attend() on the library's fixed per-GPU scratch: allocates nothing, so `out` (like q) and
         `signal` (float32 [B][n_q]) are the caller's."""
-        B, n_q = q.shape[0], q.shape[1]
+        B, n_q = q.shape[:2]
         k_frame = 0 if frame_idx is None else frame_idx.shape[1]
         mukv_prefill_attend_static(self.h, layer, _ptr(q), n_q, _ptr(frame_idx), k_frame, _ptr(k_local), _ptr(v_local),
                                    _ptr(local_offsets), B, int(causal_local), _ptr(out), _ptr(signal), _stream())

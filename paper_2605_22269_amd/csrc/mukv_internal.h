@@ -349,15 +349,19 @@ __device__ __forceinline__ int wave_sum(int v) {
     auto b = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
     return (int)(b[0] + b[1]);
 }
-__device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+template <int H>
+__device__ __forceinline__ double wave_sum_from(double x) {
+    x += lane_xor<H>(x);
+    if constexpr (H > 1) x = wave_sum_from<H / 2>(x);
     return x;
 }
-__device__ __forceinline__ double wave_max(double x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
+__device__ __forceinline__ double wave_sum(double x) { return wave_sum_from<32>(x); }
+template <int H>
+__device__ __forceinline__ double wave_max_from(double x) {
+    x = fmax(x, lane_xor<H>(x));
+    if constexpr (H > 1) x = wave_max_from<H / 2>(x);
     return x;
 }
+__device__ __forceinline__ double wave_max(double x) { return wave_max_from<32>(x); }
 
 } // namespace mukv

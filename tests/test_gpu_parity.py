@@ -92,6 +92,50 @@ def test_retrieval_with_many_equal_scores(distinct):
     p.close()
 
 
+def test_retrieval_of_list_lengths_at_the_selection_kernels_edges():
+    # lists ranked directly (up to 512), pre-filtered from registers (up to 4096) and from LDS; 900 distinct frames, so that
+    # exact ties lie on both sides of every cut
+    w = W["tiny"].scaled(n_frames=4200, n_questions=2, n_layers=1, tokens_per_frame=8, keep_ratio=0.25, superpatches_per_frame=2)
+    p = Pair(w, seed=97, chunk=300)
+    P = w.tokens_per_frame
+    k0, v0, q0 = p.stream.next_chunk(900)
+    for c0 in range(0, 4200, 300):
+        tok = (torch.arange(c0, c0 + 300) % 900)[:, None] * P + torch.arange(P)[None, :]
+        k, v, q = (x.index_select(-2, tok.reshape(-1)).contiguous() for x in (k0, v0, q0))
+        p.orc.compress_chunk(np_view(k), np_view(v), q_last=np_view(q))
+        p.gpu.compress_chunk(k.cuda(), v.cuda(), q.cuda())
+        torch.cuda.synchronize()
+    qs = questions_for(w, [16, 9], 610)
+    for n in (1, 511, 512, 513, 4095, 4096, 4097, 4200):
+        p.check_retrieve(qs, mk.MUKV_SEMI, 4, 33, 0.3, n_visible=n)
+    p.check_retrieve(qs, mk.MUKV_HIER, 5, 40, 0.3, n_visible=4100)
+    p.check_retrieve_patches(qs, mk.MUKV_SEMI, 4, 20, 0.3, n_visible=256)    # lists with entries that have no key
+    p.check_retrieve_patches(qs, mk.MUKV_SEMI, 4, 20, 0.3, n_visible=2049)
+    p.close()
+
+
+@pytest.mark.parametrize("k", [1, 8, 64, 255, 257, 700])
+def test_plan_of_a_gather_over_stores_by_list_length(k):
+    # lanes that share an entry: 64, ..., 2, 1; units named twice, and names of no unit
+    w = W["tiny"].scaled(n_frames=300, n_layers=1, tokens_per_frame=4, keep_ratio=0.5, superpatches_per_frame=1)
+    p = Pair(w, seed=98, chunk=100)
+    p.ingest()
+    kap = p.gpu.kappa
+    rs = np.random.default_rng(k)
+    lists = [rs.integers(-2, 310, k), rs.integers(0, 300, k)]
+    idx = [torch.from_numpy(x.astype(np.int32))[None].cuda() for x in lists]
+    ko, vo, n = mk.gather_multi([p.gpu, p.gpu], idx, [1, 3], 2 * k * kap)
+    taken = sorted({(u // (1, 3)[i], i, int(u)) for i in range(2) for u in lists[i] if 0 <= u < 300})
+    rows = [u * kap + r for _, _, u in taken for r in range(kap)]
+    k_all, v_all = p.gpu.store_rows(0, 300 * kap)
+    torch.cuda.synchronize()
+    assert int(n[0]) == len(rows)
+    for got, want in ((ko, k_all), (vo, v_all)):
+        assert torch.equal(got[0, 0, :, :len(rows)], want[0][:, rows])
+        assert not got[0, 0, :, len(rows):].any()
+    p.close()
+
+
 @pytest.mark.parametrize("name,frames", [("7b", 41), ("tiny", 100), ("72b", 21)])
 def test_batches_of_sixteen_or_more_questions(name, frames):
     # from 16 questions on, the frame scores come from the fp64 matrix-core kernel: ragged

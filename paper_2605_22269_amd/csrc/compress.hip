@@ -1,7 +1,8 @@
 // Offline half of MuKV (Sec. 3.3 of the paper): token scoring, per-frame keep,
 // KV compaction and block-key pooling for one chunk of frames.
 //
-// Kernel chain enqueued by launch_compress (all on the caller's stream):
+// Kernel chain enqueued by launch_compress (all on the caller's stream; the first two share a launch where both are needed
+// and neither fills the chip, or where the matrix-core attention works out the indicator on the way):
 //   att_generic<float> | att_mfma      Eq. 1   partial attention received per (frame, head group)
 //   freq_signal<float>                 Eq. 2-3 length-D DFT magnitudes of every key
 //   select_pool<float>                 Eq. 4 fusion, keep of the kappa best, Eq. 5 frame / super-patch keys
@@ -386,19 +387,25 @@ __device__ __forceinline__ float4 key4(const uint16_t *p) {
 }
 __device__ __forceinline__ void stage_keys(u32x4 raw, uint16_t *dst) { *reinterpret_cast<u32x4 *>(dst) = raw; }
 
+struct AttGenArgs {
+    PtrTable q, k;
+    FrameMap map;
+    int64_t k_off, q_sh, q_st, k_sh, k_st;
+    int P, D, G, Hq, causal, q_per_block;
+    const int32_t *flag_list, *flag_count;
+    int gx, nz; // the grid: (gx, Hq, nz)
+};
+
+// Work of workgroup (bx, h, z).
 template <typename T, typename R>
-__global__ __launch_bounds__(256) void att_generic_kernel(PtrTable qtab, PtrTable ktab, FrameMap map, int64_t k_off,
-                                                          int64_t q_sh, int64_t q_st, int64_t k_sh, int64_t k_st,
-                                                          int P, int D, int G, int Hq, int causal, int q_per_block,
-                                                          const int32_t *__restrict__ flag_list,
-                                                          const int32_t *__restrict__ flag_count,
-                                                          R *__restrict__ out) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int h = blockIdx.y, z = blockIdx.z;
-    // frames: every batch frame (grid.x = n_frames), or the entries of the re-scoring list
-    const int n_e = flag_list ? *flag_count : (int)gridDim.x;
-    for (int e_idx = blockIdx.x; e_idx < n_e; e_idx += gridDim.x) {
-    const int f = flag_list ? flag_list[e_idx] : e_idx;
+__device__ __forceinline__ void att_generic_body(const AttGenArgs &a, R *__restrict__ out, int bx, int h, int z, unsigned char *smem_raw) {
+    const int P = a.P, D = a.D, G = a.G, causal = a.causal, q_per_block = a.q_per_block;
+    const int64_t k_off = a.k_off, q_sh = a.q_sh, q_st = a.q_st, k_sh = a.k_sh, k_st = a.k_st;
+    const FrameMap &map = a.map;
+    // frames: every batch frame (gx = n_frames), or the entries of the re-scoring list
+    const int n_e = a.flag_list ? *a.flag_count : a.gx;
+    for (int e_idx = bx; e_idx < n_e; e_idx += a.gx) {
+    const int f = a.flag_list ? a.flag_list[e_idx] : e_idx;
     typedef typename KeyStage<T, R>::type KT;
     const int ldk = D + KeyStage<T, R>::pad; // 16-byte aligned rows; 4-word lane stride keeps 16 lanes on distinct banks
     KT *Ks = reinterpret_cast<KT *>(smem_raw);          // [P][ldk]
@@ -408,8 +415,8 @@ __global__ __launch_bounds__(256) void att_generic_kernel(PtrTable qtab, PtrTabl
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int slot = find_slot(map, f);
     const int lf = f - map.fstart[slot];
-    const T *kf = reinterpret_cast<const T *>(ktab.p[slot]) + k_off + (int64_t)(h / G) * k_sh + (int64_t)lf * P * k_st;
-    const T *qf = reinterpret_cast<const T *>(qtab.p[slot]) + (int64_t)h * q_sh + (int64_t)lf * P * q_st;
+    const T *kf = reinterpret_cast<const T *>(a.k.p[slot]) + k_off + (int64_t)(h / G) * k_sh + (int64_t)lf * P * k_st;
+    const T *qf = reinterpret_cast<const T *>(a.q.p[slot]) + (int64_t)h * q_sh + (int64_t)lf * P * q_st;
     const int i_lo = z * q_per_block;
     const int i_hi = (i_lo + q_per_block < P) ? i_lo + q_per_block : P;
     const int n_keys = causal ? i_hi : P; // keys any query of this workgroup can see
@@ -514,10 +521,34 @@ __global__ __launch_bounds__(256) void att_generic_kernel(PtrTable qtab, PtrTabl
         if (j < P) part[wave * P + j] = acc[t];
     }
     __syncthreads();
-    const int n_part = Hq * gridDim.z;
+    const int n_part = a.Hq * a.nz;
     for (int j = tid; j < P; j += 256)
-        out[((int64_t)f * n_part + h * gridDim.z + z) * P + j] = ((part[j] + part[P + j]) + part[2 * P + j]) + part[3 * P + j];
+        out[((int64_t)f * n_part + h * a.nz + z) * P + j] = ((part[j] + part[P + j]) + part[2 * P + j]) + part[3 * P + j];
     __syncthreads();
+    }
+}
+
+template <typename T, typename R>
+__global__ __launch_bounds__(256) void att_generic_kernel(AttGenArgs a, R *__restrict__ out) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    att_generic_body<T, R>(a, out, blockIdx.x, blockIdx.y, blockIdx.z, smem_raw);
+}
+
+// Both signals in one launch, where neither fills the chip: the attention workgroups, then the frequency kernel's
+// (freq_gx, bpf) grid.  They read the same keys and need nothing of each other; one after the other they are two of the chain
+// of launches that a small batch is bound by.
+template <typename T, typename R, int D>
+__global__ __launch_bounds__(256) void signals_kernel(AttGenArgs a, R *__restrict__ att_out, R *__restrict__ fft_out, int Hkv, int freq_gx,
+                                                      int bpf) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int b = blockIdx.x, n_att = a.gx * a.Hq * a.nz;
+    if (b < n_att) {
+        const int hz = b / a.gx;
+        att_generic_body<T, R>(a, att_out, b - hz * a.gx, hz % a.Hq, hz / a.Hq, smem_raw);
+    } else {
+        const int y = (b - n_att) / freq_gx;
+        freq_body<T, R, D>(a.k, a.map, a.k_off, a.k_sh, a.k_st, Hkv, a.P, a.flag_list, a.flag_count, fft_out, b - n_att - y * freq_gx, y,
+                           freq_gx, bpf);
     }
 }
 
@@ -1169,6 +1200,7 @@ struct CompactArgs {
     // copy by runs (copy_run_body): the batch's slots all hold fpc frames (the last one may hold fewer)
     int n_frames, fpc;
     uint32_t magic_kappa, magic_fpc; // floor(2^32 / d) + 1: n / d = umulhi(n, magic) while n * d < 2^32
+    int32_t *clear;              // compact_kernel: the length of a re-scoring list that is done with, or null
 };
 
 // Adds the batch's exact per-frame sums to a segment's running fp64 sums and refreshes its keys.
@@ -1321,6 +1353,7 @@ __device__ __forceinline__ void copy_run_body(const CompactArgs &a, int run, int
 template <typename V, int ITER>
 __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
     __shared__ double seg_lds[kSegLdsDoubles];
+    if (a.clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *a.clear = 0;
     compact_body<V, ITER>(a, blockIdx.x, blockIdx.y, seg_lds);
 }
 
@@ -1410,6 +1443,21 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
             compact_body<u32x4, ITER>(ca, cid % cm.copy_gx, cid / cm.copy_gx, seg_lds, blockDim.x);
     } else {
         segment_update(ca, cid - cm.n_copy_rows, seg_lds);
+    }
+}
+
+// The matrix-core attention of a batch of few frames, and its frequency indicator in workgroups of their own behind (8 frames
+// of 196 tokens, 28 heads: 13.9 us; as two launches 10.5 + 6.1).
+__global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) void att_freq_kernel(PtrTable qtab, FreqPart fp, AttMfmaArgs aa) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int b = blockIdx.x, n_att = fp.n_frames * aa.n_part;
+    if (b < n_att) {
+        const int by = b / fp.n_frames;
+        att_mfma_body(qtab, fp.k, fp.map, aa, b - by * fp.n_frames, by, smem_raw);
+    } else {
+        const int y = (b - n_att) / fp.n_frames;
+        freq_body<uint16_t, float, 128>(fp.k, fp.map, fp.k_off, fp.sh, fp.st, fp.Hkv, fp.P, nullptr, nullptr, fp.out,
+                                        b - n_att - y * fp.n_frames, y, fp.n_frames, fp.bpf);
     }
 }
 
@@ -1528,22 +1576,84 @@ size_t att_generic_lds_bytes(int P, int D, size_t r_size, size_t key_size) {
 }
 
 template <typename T, typename R>
+static AttGenArgs att_generic_args(const Ctx &c, const ChunkArgs &a, bool listed, int *n_part, size_t *lds) {
+    AttGenArgs g;
+    g.q = a.q;
+    g.k = a.k;
+    g.map = a.map;
+    g.k_off = (int64_t)c.ls * a.kv_sl;
+    g.q_sh = a.q_sh;
+    g.q_st = a.q_st;
+    g.k_sh = a.kv_sh;
+    g.k_st = a.kv_st;
+    g.P = c.cfg.tokens_per_frame;
+    g.D = c.cfg.head_dim;
+    g.G = c.group;
+    g.Hq = c.cfg.n_q_heads;
+    g.causal = c.cfg.causal;
+    g.q_per_block = 2 * kGenQ; // two rounds per workgroup
+    g.flag_list = listed ? c.flag_list[a.parity] : nullptr;
+    g.flag_count = listed ? c.flag_count + a.parity : nullptr;
+    g.gx = listed ? kRescoreSlotsAtt : a.n_frames;
+    g.nz = (g.P + g.q_per_block - 1) / g.q_per_block;
+    *n_part = g.Hq * g.nz;
+    *lds = att_generic_lds_bytes(g.P, g.D, sizeof(R), sizeof(typename KeyStage<T, R>::type));
+    return g;
+}
+
+template <typename T, typename R>
 static hipError_t launch_att_generic(const Ctx &c, const ChunkArgs &a, bool listed, R *out, int *n_part,
                                      hipStream_t st) {
-    const int P = c.cfg.tokens_per_frame, D = c.cfg.head_dim;
-    const int q_per_block = 2 * kGenQ; // two rounds per workgroup
-    const int qsplit = (P + q_per_block - 1) / q_per_block;
-    *n_part = c.cfg.n_q_heads * qsplit;
-    const size_t lds = att_generic_lds_bytes(P, D, sizeof(R), sizeof(typename KeyStage<T, R>::type));
+    size_t lds;
+    const AttGenArgs g = att_generic_args<T, R>(c, a, listed, n_part, &lds);
     static bool lds_ok[kMaxDevices]; // per instantiation
     const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void *>(&att_generic_kernel<T, R>), 160 * 1024,
                                             c.cfg.device_id, lds_ok);
     if (ea != hipSuccess) return ea;
-    hipLaunchKernelGGL((att_generic_kernel<T, R>), dim3(listed ? kRescoreSlotsAtt : a.n_frames, c.cfg.n_q_heads, qsplit),
-                       dim3(256), lds, st, a.q, a.k, a.map, (int64_t)c.ls * a.kv_sl, a.q_sh, a.q_st, a.kv_sh, a.kv_st, P,
-                       D, c.group, c.cfg.n_q_heads, c.cfg.causal, q_per_block, listed ? c.flag_list[a.parity] : nullptr,
-                       listed ? c.flag_count + a.parity : nullptr, out);
+    hipLaunchKernelGGL((att_generic_kernel<T, R>), dim3(g.gx, g.Hq, g.nz), dim3(256), lds, st, g, out);
     return hipGetLastError();
+}
+
+// Eq. 1 by the generic kernel and Eq. 2-3, of every frame or of the listed ones; what is not needed is left out.  One launch
+// where all its workgroups are resident at once (an empty list, as most are: 3.3 + 2.5 us as two launches), else two.
+template <typename T, typename R>
+static hipError_t launch_signals(const Ctx &c, const ChunkArgs &a, bool need_att, bool need_fft, bool listed, R *att_out, int *n_part,
+                                 R *fft_out, hipStream_t st) {
+    hipError_t e;
+    if (need_att && need_fft && c.cfg.freq_axis == MUKV_FREQ_FEATURE) {
+        size_t lds;
+        const int P = c.cfg.tokens_per_frame, D = c.cfg.head_dim;
+        const AttGenArgs g = att_generic_args<T, R>(c, a, listed, n_part, &lds);
+        const int freq_gx = listed ? rescore_slots(P, a.n_frames) : a.n_frames;
+        const int bpf = listed ? freq_blocks_per_frame(P) : freq_blocks_alone(P, D, a.n_frames);
+        const int64_t total = (int64_t)g.gx * g.Hq * g.nz + (int64_t)freq_gx * bpf;
+        const int64_t per_cu = (int64_t)(160 * 1024 / lds) < 4 ? (int64_t)(160 * 1024 / lds) : 4;
+        if (total <= 256 * per_cu || (listed && P <= kMaxP)) {
+#define MUKV_SIGNALS(DD)                                                                                                   \
+    do {                                                                                                                   \
+        static bool lds_ok[kMaxDevices];                                                                                   \
+        e = allow_dynamic_lds(reinterpret_cast<const void *>(&signals_kernel<T, R, DD>), 160 * 1024, c.cfg.device_id,      \
+                              lds_ok);                                                                                     \
+        if (e != hipSuccess) return e;                                                                                     \
+        hipLaunchKernelGGL((signals_kernel<T, R, DD>), dim3((unsigned)total), dim3(256), lds, st, g, att_out, fft_out,     \
+                           c.cfg.n_kv_heads, freq_gx, bpf);                                                                \
+    } while (0)
+            switch (D) {
+            case 128: MUKV_SIGNALS(128); break;
+            case 64: MUKV_SIGNALS(64); break;
+            case 32: MUKV_SIGNALS(32); break;
+            case 16: MUKV_SIGNALS(16); break;
+            default: return hipErrorInvalidValue;
+            }
+#undef MUKV_SIGNALS
+            return hipGetLastError();
+        }
+    }
+    if (need_fft)
+        if ((e = launch_freq<T, R>(c, a, listed, fft_out, st)) != hipSuccess) return e;
+    if (need_att)
+        if ((e = launch_att_generic<T, R>(c, a, listed, att_out, n_part, st)) != hipSuccess) return e;
+    return hipSuccess;
 }
 
 hipError_t launch_att_mfma(const Ctx &c, const ChunkArgs &a, float *out, int *n_part, hipStream_t st);
@@ -1667,10 +1777,11 @@ static void compact_args(const Ctx &c, const ChunkArgs &a, int mode, int iter, C
     gy = k.n_slab + (mode == 0 ? n_seg_jobs : 0);
 }
 
-static hipError_t launch_compact(const Ctx &c, const ChunkArgs &a, int mode, hipStream_t st) {
+static hipError_t launch_compact(const Ctx &c, const ChunkArgs &a, int mode, hipStream_t st, int32_t *clear = nullptr) {
     CompactArgs k;
     int gx, gy;
     compact_args(c, a, mode, kCompactIter, k, gx, gy);
+    k.clear = clear;
     if (mode == 2) { // grid.z: a listed frame's rows are shared so that a workgroup makes at most 8 rounds
         const int gz = (k.units_per_frame + 8 * 512 - 1) / (8 * 512);
         hipLaunchKernelGGL((compact_listed_kernel<u32x4>), dim3(gx, gy, gz < 64 ? gz : 64), dim3(256), 0, st, k,
@@ -1843,6 +1954,34 @@ static hipError_t launch_chain(const Ctx &c, const ChunkArgs *prev, int copy_mod
     return hipGetLastError();
 }
 
+// Both signals of a batch of few frames (the matrix-core attention's other layout).
+static hipError_t launch_att_freq(const Ctx &c, const ChunkArgs &a, int *n_part, hipStream_t st) {
+    AttMfmaArgs aa;
+    int waves;
+    size_t lds;
+    att_mfma_plan(c, a, c.att_part[a.parity], &aa, &waves, &lds);
+    *n_part = aa.n_part;
+    FreqPart fp;
+    fp.k = a.k;
+    fp.map = a.map;
+    fp.k_off = (int64_t)c.ls * a.kv_sl;
+    fp.sh = a.kv_sh;
+    fp.st = a.kv_st;
+    fp.Hkv = c.cfg.n_kv_heads;
+    fp.P = c.cfg.tokens_per_frame;
+    fp.out = c.fft_sig[a.parity];
+    fp.n_frames = a.n_frames;
+    // as many frequency workgroups as stay resident beside the attention's (two per compute unit), one step a wave at most
+    const int want = (512 - a.n_frames * aa.n_part) / a.n_frames, most = (fp.P + waves - 1) / waves;
+    fp.bpf = want < 4 ? 4 : want < most ? want : most;
+    fp.n_wg = a.n_frames * fp.bpf;
+    static bool lds_ok[kMaxDevices];
+    const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void *>(&att_freq_kernel), kAttMfmaMaxLds, c.cfg.device_id, lds_ok);
+    if (ea != hipSuccess) return ea;
+    hipLaunchKernelGGL(att_freq_kernel, dim3((unsigned)(a.n_frames * aa.n_part + fp.n_wg)), dim3(waves * 64), lds, st, a.q, fp, aa);
+    return hipGetLastError();
+}
+
 static hipError_t wait_side(Ctx &c, int parity, hipStream_t st) {
     if (c.side_pending[parity]) {
         hipError_t e = hipStreamWaitEvent(st, c.ev_join[parity], 0);
@@ -1892,10 +2031,7 @@ static hipError_t launch_split_side(Ctx &c, const ChunkArgs &a, int n_part, int 
     if (c.margin_thr > 0.0) {
         ProfScope ps(c, MUKV_K_REFINE, c.side);
         int n_part64 = c.cfg.n_q_heads;
-        if (need_att)
-            if ((e = launch_att_generic<T, double>(c, a, true, c.att64, &n_part64, c.side)) != hipSuccess) return e;
-        if (need_fft)
-            if ((e = launch_freq<T, double>(c, a, true, c.fft64, c.side)) != hipSuccess) return e;
+        if ((e = launch_signals<T, double>(c, a, need_att, need_fft, true, c.att64, &n_part64, c.fft64, c.side)) != hipSuccess) return e;
         if ((e = launch_select<T, double>(c, a, c.att64, n_part64, c.fft64, 1, c.side)) != hipSuccess) return e;
         if ((e = launch_compact(c, a, 2, c.side)) != hipSuccess) return e;
         hipLaunchKernelGGL(clear_count_kernel, dim3(1), dim3(1), 0, c.side, c.flag_count + par);
@@ -1916,7 +2052,7 @@ static hipError_t launch_split_side(Ctx &c, const ChunkArgs &a, int n_part, int 
 //    copy has not been launched yet and will find the final rows of every frame.
 // ev_join[parity] marks its end.
 template <typename T>
-static hipError_t launch_side(Ctx &c, const ChunkArgs &a, bool with_keep, int n_part) {
+static hipError_t launch_side(Ctx &c, const ChunkArgs &a, bool with_keep, int n_part, int fft_parts = 0) {
     hipError_t e;
     const bool need_att = c.cfg.alpha != 0.0 && !a.have_att_in;
     const bool need_fft = c.cfg.alpha != 1.0;
@@ -1927,16 +2063,13 @@ static hipError_t launch_side(Ctx &c, const ChunkArgs &a, bool with_keep, int n_
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else if (with_keep) {
         ProfScope ps(c, MUKV_K_SELECT, c.side);
-        if ((e = launch_select<T, float>(c, a, c.att_part[a.parity], n_part, c.fft_sig[a.parity], 0, c.side)) != hipSuccess)
+        if ((e = launch_select<T, float>(c, a, c.att_part[a.parity], n_part, c.fft_sig[a.parity], 0, c.side, fft_parts)) != hipSuccess)
             return e;
     }
     if (c.margin_thr > 0.0) {
         ProfScope ps(c, MUKV_K_REFINE, c.side);
         int n_part64 = c.cfg.n_q_heads;
-        if (need_att)
-            if ((e = launch_att_generic<T, double>(c, a, true, c.att64, &n_part64, c.side)) != hipSuccess) return e;
-        if (need_fft)
-            if ((e = launch_freq<T, double>(c, a, true, c.fft64, c.side)) != hipSuccess) return e;
+        if ((e = launch_signals<T, double>(c, a, need_att, need_fft, true, c.att64, &n_part64, c.fft64, c.side)) != hipSuccess) return e;
         if ((e = launch_select<T, double>(c, a, c.att64, n_part64, c.fft64, 1, c.side)) != hipSuccess) return e;
         if (!with_keep)
             if ((e = launch_compact(c, a, 2, c.side)) != hipSuccess) return e;
@@ -1988,8 +2121,8 @@ hipError_t join_streams(Ctx &c, hipStream_t st) {
 
 // A copy too short to hide the fp64 chain behind it: the events that would put the chain on the side stream and bring it
 // back cost more than they save, on the host (four calls and one launch of twelve, and a small batch is bound by its
-// launches) and on the device (each crossing of queues 6-14 us).  Both sides, 7B shape, us a call, everything on the
-// caller's stream / the chain beside the copy: 8 frames, 21 MB, 46 / 70-82; 16, 42 MB, 58 / 81; 32, 84 MB, 74 / 94; 64,
+// launches) and on the device (each crossing of queues 6-14 us).  Both sides (with the signals in launches of their own, four
+// launches more than now), 7B shape, us a call, everything on the caller's stream / the chain beside the copy: 8 frames, 21 MB, 46 / 70-82; 16, 42 MB, 58 / 81; 32, 84 MB, 74 / 94; 64,
 // 168 MB, 178 / 199; 128, 336 MB, 247 / 253, and with the signal handed over 143 / 127.  So with few frames listed the
 // sides meet at about 300 MB.  The line lies far below: the longer the chain -- it grows with the frames listed,
 // up to all of a batch -- the more a long copy beside it hides, and 32 MB (6-8 us) hide less than the crossings cost in
@@ -2039,7 +2172,19 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
         c.deferred_stream = st;
         return hipSuccess;
     }
-    if (have_old && need_fft && c.cfg.freq_axis == MUKV_FREQ_FEATURE) {
+    // both signals in one launch: the matrix-core attention with the frequency workgroups beside it (few frames) or with the
+    // indicator worked out on the way (many), or the generic kernels together
+    const bool one_launch = !have_old && need_att && need_fft && c.cfg.freq_axis == MUKV_FREQ_FEATURE;
+    if (one_launch) {
+        ProfScope ps(c, MUKV_K_ATT, st);
+        if (!c.use_mfma)
+            e = launch_signals<T, float>(c, a, true, true, false, c.att_part[a.parity], &n_part, c.fft_sig[a.parity], st);
+        else if (chain_supported(c, a))
+            e = launch_chain(c, nullptr, 0, a, true, &n_part, &fft_parts, st);
+        else
+            e = launch_att_freq(c, a, &n_part, st);
+        if (e != hipSuccess) return e;
+    } else if (have_old && need_fft && c.cfg.freq_axis == MUKV_FREQ_FEATURE) {
         // the copy shares its launch with this batch's frequency kernel: HBM-bound beside
         // arithmetic-bound work (the attention kernel streams all the queries and gains nothing
         // beside a copy)
@@ -2057,7 +2202,7 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
         c.deferred[0] = c.deferred[1];
         c.n_deferred = 1;
     }
-    if (need_att) {
+    if (need_att && !one_launch) {
         ProfScope ps(c, MUKV_K_ATT, st);
         if (c.use_mfma) {
             if ((e = launch_att_mfma(c, a, c.att_part[a.parity], &n_part, st)) != hipSuccess) return e;
@@ -2067,7 +2212,7 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
     }
     if (overlap) { // keep on the side stream; the copy waits for the batch after next (or a flush / retrieve / gather call)
         if ((e = hipEventRecord(c.ev_fork, st)) != hipSuccess) return e;
-        if ((e = c.split_side ? launch_split_side<T>(c, a, n_part) : launch_side<T>(c, a, true, n_part)) != hipSuccess) return e;
+        if ((e = c.split_side ? launch_split_side<T>(c, a, n_part, fft_parts) : launch_side<T>(c, a, true, n_part, fft_parts)) != hipSuccess) return e;
         c.deferred[c.n_deferred++] = a;
         c.deferred_stream = st;
         return hipSuccess;
@@ -2079,22 +2224,17 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
     }
     {
         ProfScope ps(c, MUKV_K_SELECT, st);
-        if ((e = launch_select<T, float>(c, a, c.att_part[a.parity], n_part, c.fft_sig[a.parity], 0, st)) != hipSuccess) return e;
+        if ((e = launch_select<T, float>(c, a, c.att_part[a.parity], n_part, c.fft_sig[a.parity], 0, st, fft_parts)) != hipSuccess) return e;
     }
     if (rescoring && copy_is_short(c, a)) { // all of it on the caller's stream, one copy of every frame's final rows
         {
             ProfScope ps(c, MUKV_K_REFINE, st);
             int n_part64 = c.cfg.n_q_heads;
-            if (need_att)
-                if ((e = launch_att_generic<T, double>(c, a, true, c.att64, &n_part64, st)) != hipSuccess) return e;
-            if (need_fft)
-                if ((e = launch_freq<T, double>(c, a, true, c.fft64, st)) != hipSuccess) return e;
+            if ((e = launch_signals<T, double>(c, a, need_att, need_fft, true, c.att64, &n_part64, c.fft64, st)) != hipSuccess) return e;
             if ((e = launch_select<T, double>(c, a, c.att64, n_part64, c.fft64, 2, st)) != hipSuccess) return e;
-            hipLaunchKernelGGL(clear_count_kernel, dim3(1), dim3(1), 0, st, c.flag_count + a.parity);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
         }
         ProfScope ps(c, MUKV_K_COMPACT, st);
-        return launch_compact(c, a, 0, st);
+        return launch_compact(c, a, 0, st, c.flag_count + a.parity); // (which empties the list for the next batch)
     }
     if (rescoring) {
         if ((e = hipEventRecord(c.ev_fork, st)) != hipSuccess) return e;

@@ -370,6 +370,20 @@ def test_attention_paths_bf16(path, causal):
     p.close()
 
 
+@pytest.mark.parametrize("name,frames,kw", [
+    ("tiny", 68, {}), ("tiny", 69, {}),                                     # generic kernels: one launch (1020 workgroups of 1024), two
+    ("7b", 63, {"n_layers": 1, "tokens_per_frame": 50}),                    # matrix-core attention of few frames, frequency beside it
+    ("7b", 64, {"n_layers": 1, "tokens_per_frame": 50}),                    # of many: the indicator on the way
+    ("7b", 1, {"n_layers": 1, "tokens_per_frame": 13}),                     # one wave a workgroup
+])
+def test_both_signals_of_a_chunk_in_one_launch(name, frames, kw):
+    w = W[name].scaled(n_frames=frames, **kw)
+    p = Pair(w, seed=121, chunk=frames)
+    p.ingest()
+    p.check_compress()
+    p.close()
+
+
 @pytest.mark.parametrize("P", [50, 16, 208, 7])
 def test_mfma_ragged_token_counts(P):
     w = W["7b"].scaled(n_frames=5, n_layers=1, tokens_per_frame=P, keep_ratio=0.3, n_q_heads=8, n_kv_heads=2)

@@ -118,7 +118,7 @@ void free_all(Ctx &c) {
                     c.rep_patch_v, c.rep_seg_k, c.rep_seg_v, c.cnt_patch,   c.fsum_k,      c.fsum_v,
                     c.ssum_k,      c.ssum_v,    c.margin,      c.refined,   c.att_part[0], c.att_part[1], c.fft_sig[0], c.fft_sig[1],     c.att64,       c.fft64,
                     c.src_tok[0],  c.src_tok[1],   c.src_tok2,    c.flag_list[0], c.flag_list[1], c.flag_count, c.qbar,      c.qq,        c.s_frm,       c.s_seg,       c.seg_tail,
-                    c.u_mask,      c.u_entry,     c.u_count,   c.attend_part, c.tw32, c.tw64, c.tok_part, c.m_entry, c.m_count, c.dft_tab};
+                    c.u_mask,      c.u_entry,     c.u_count,   c.attend_part, c.tw32, c.tw64, c.tok_part, c.m_entry, c.m_count, c.dft_tab, c.pool_part};
     // nothing of the library's own may still be running on what is freed below
     if (c.side) (void)hipStreamSynchronize(c.side);
     for (void *p : ptrs)
@@ -291,6 +291,7 @@ int mukv_create(const mukv_config *cfg, mukv_ctx **out) {
     }
     ok(dalloc(&c.att64, MC * n_part_max * P));
     ok(dalloc(&c.fft64, MC * P));
+    if (P > (size_t)mukv::kMaxP) ok(dalloc(&c.pool_part, (size_t)mukv::kPoolParts * 64 * 4));
     ok(dalloc(&c.src_tok2, MC * c.kappa));
     ok(dalloc(&c.flag_list[0], MC));
     ok(dalloc(&c.flag_list[1], MC));

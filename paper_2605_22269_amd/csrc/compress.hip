@@ -833,15 +833,19 @@ __global__ __launch_bounds__(256) void select_pool_kernel(SelectArgs<R> a) {
 //
 // select_large_kernel: one workgroup of 1024 threads per unit, thread t owns the kUnitTok
 // consecutive tokens from kUnitTok * t.  Fused scores become order-preserving unsigned keys
-// (a padding token gets key 0, below every real one).  The kappa-th largest key is built bit by
-// bit from the top: the largest value x with #{key >= x} >= kappa.  Tokens above it are kept;
+// (a padding token gets key 0, below every real one).  The kappa-th largest key is found by digits of
+// 8 bits below the bits that all keys share: a histogram of the keys that agree with the digits so far, the digit from a
+// scan over the bins by one wave; where one key is left, it is that one, which for scores without ties takes two or three
+// digits (bit by bit, 64 counts of the workgroup, an fp64 unit of 6272 tokens took 59 us, now 25).  Tokens above it are kept;
 // of those equal to it the lowest positions, by a prefix count; a second prefix count gives each
 // kept token its row.  Same outputs as select_pool_kernel up to the kept list.
 //
 // pool_large_kernel: Eq. 5 for the unit and its S super-patches.  Grid (unit, group of 64 channel
-// pairs); the unit's kept list sits in LDS; the kept rows of a super-patch are a run of that list
+// pairs, share of the super-patches); the unit's kept list sits in LDS; the kept rows of a super-patch are a run of that list
 // (positions ascend), found by bisection; the 16 waves take every 16th row of the run, a batch of
-// independent loads at a time, and their fp64 sums are joined in wave order.
+// independent loads at a time, and their fp64 sums are joined in wave order.  A call of few units has the super-patches
+// shared by as many workgroups as two per compute unit make (one unit of 6272 tokens, S = 32, two heads of 64: 91 us by one
+// workgroup a channel group, 8.3 + 4.3 this way); their sums over the unit are added by pool_total_kernel, in order.
 // ------------------------------------------------------------------------------------------
 constexpr int kUnitThreads = 1024;
 constexpr int kUnitTok = kMaxUnit / kUnitThreads;
@@ -874,8 +878,7 @@ struct OrdKey<double> {
 
 // Sum of v over the 16 waves.  buf: kUnitWaves ints; two calls in a row use different buffers.
 __device__ __forceinline__ int unit_sum(int v, int *buf) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) buf[threadIdx.x >> 6] = v;
     __syncthreads();
     int s = 0;
@@ -908,12 +911,8 @@ __device__ __forceinline__ int unit_scan(int v, int *buf, int &total) {
 
 template <typename R>
 __device__ __forceinline__ void unit_minmax(R mn, R mx, R *red, R &lo, R &hi) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const R a = __shfl_xor(mn, o), b = __shfl_xor(mx, o);
-        mn = a < mn ? a : mn;
-        mx = b > mx ? b : mx;
-    }
+    mn = -wave_max(-mn);
+    mx = wave_max(mx);
     __syncthreads(); // the previous use of red is over
     if ((threadIdx.x & 63) == 0) {
         red[threadIdx.x >> 6] = mn;
@@ -934,8 +933,8 @@ __global__ __launch_bounds__(kUnitThreads) void select_large_kernel(SelectArgs<R
     using K = OrdKey<R>;
     using U = typename K::U;
     __shared__ R red[2 * kUnitWaves];
-    __shared__ U kred[kUnitWaves];
-    __shared__ int cnt[2][kUnitWaves];
+    __shared__ U kred[kUnitWaves], first_key;
+    __shared__ int cnt[2][kUnitWaves], hist[256], digit[3];
     const int tid = threadIdx.x;
     const int P = a.P, kappa = a.kappa;
     const int j0 = tid * kUnitTok;
@@ -1000,13 +999,66 @@ __global__ __launch_bounds__(kUnitThreads) void select_large_kernel(SelectArgs<R
         }
 
         // the kappa-th largest key
-        U kth = 0;
-        for (int b = K::kBits - 1; b >= 0; --b) {
-            const U cand = kth | ((U)1 << b);
-            int n = 0;
+        U kth;
+        {
+            if (tid == 0) first_key = key[0];
+            __syncthreads();
+            const U k0 = first_key;
+            U differ = 0; // bits in which some key differs from the first
 #pragma unroll
-            for (int u = 0; u < kUnitTok; ++u) n += key[u] >= cand;
-            if (unit_sum(n, cnt[b & 1]) >= kappa) kth = cand;
+            for (int u = 0; u < kUnitTok; ++u) differ |= j0 + u < P ? key[u] ^ k0 : (U)0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) differ |= __shfl_xor(differ, o);
+            if ((tid & 63) == 0) kred[tid >> 6] = differ;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < kUnitWaves; ++w) differ |= kred[w];
+            // the digits found so far are those from this bit on
+            int bit = differ == 0 ? 0 : sizeof(U) == 8 ? 64 - __builtin_clzll(differ) : 32 - __builtin_clz((unsigned)differ);
+            kth = bit < K::kBits ? k0 >> bit << bit : (U)0;
+            int want = kappa; // the key's rank among those that agree with kth so far
+            while (bit > 0) { // the same in all threads
+                const int w = bit < 8 ? bit : 8, shift = bit - w;
+                auto agrees = [&](U k) { return bit == K::kBits || (k ^ kth) >> (bit < K::kBits ? bit : 0) == 0; };
+                if (tid < 256) hist[tid] = 0;
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < kUnitTok; ++u)
+                    if (j0 + u < P && agrees(key[u])) atomicAdd(&hist[(int)(key[u] >> shift) & ((1 << w) - 1)], 1);
+                __syncthreads();
+                if (tid < 64) { // bins from the top: lane l holds 255 - 4 l .. 252 - 4 l
+                    int h[4], inc = 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) inc += h[i] = hist[255 - 4 * tid - i];
+                    const int mine = inc;
+#pragma unroll
+                    for (int o = 1; o < 64; o <<= 1) {
+                        const int t = __shfl_up(inc, o);
+                        inc += tid >= o ? t : 0;
+                    }
+                    int before = inc - mine;
+                    if (before < want && want <= inc) {
+                        int i = 0;
+                        while (before + h[i] < want) before += h[i++];
+                        digit[0] = 255 - 4 * tid - i;
+                        digit[1] = want - before;
+                        digit[2] = h[i];
+                    }
+                }
+                __syncthreads();
+                kth |= (U)digit[0] << shift;
+                want = digit[1];
+                bit = shift;
+                if (bit > 0 && digit[2] == 1) { // one key left
+#pragma unroll
+                    for (int u = 0; u < kUnitTok; ++u)
+                        if (j0 + u < P && agrees(key[u])) first_key = key[u];
+                    __syncthreads();
+                    kth = first_key;
+                    bit = 0;
+                }
+            }
+            __syncthreads(); // hist, digit and first_key are done with
         }
         // ties at the threshold go to the lowest positions
         int n_gt = 0, n_eq = 0;
@@ -1015,7 +1067,7 @@ __global__ __launch_bounds__(kUnitThreads) void select_large_kernel(SelectArgs<R
             n_gt += key[u] > kth;
             n_eq += key[u] == kth;
         }
-        const int tot_gt = unit_sum(n_gt, cnt[1]); // the loop's last call used cnt[0]
+        const int tot_gt = unit_sum(n_gt, cnt[1]);
         const int need = kappa - tot_gt;
         int tot_eq;
         int eq_rank = unit_scan(n_eq, cnt[0], tot_eq);
@@ -1074,8 +1126,21 @@ __global__ __launch_bounds__(kUnitThreads) void select_large_kernel(SelectArgs<R
 
 constexpr int kPoolBatch = 8;
 constexpr int kPoolSlices = kUnitWaves;
+// Key and sums of a unit, channels c and c + 1 (k0 k1 v0 v1).
+template <typename R>
+__device__ __forceinline__ void store_unit_keys(const SelectArgs<R> &a, int64_t gf, int c, const double (&tot)[4]) {
+    const int64_t o = gf * (a.Hkv * a.D) + c;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        a.fsum_k[o + e] = tot[e];
+        a.fsum_v[o + e] = tot[2 + e];
+        a.rep_frame_k[o + e] = (float)(tot[e] / (double)a.kappa);
+        a.rep_frame_v[o + e] = (float)(tot[2 + e] / (double)a.kappa);
+    }
+}
+
 template <typename T, typename R>
-__global__ __launch_bounds__(kUnitThreads) void pool_large_kernel(SelectArgs<R> a) {
+__global__ __launch_bounds__(kUnitThreads) void pool_large_kernel(SelectArgs<R> a, double *__restrict__ part_tot) {
     __shared__ int kl[kMaxUnit];
     __shared__ double part[kPoolSlices][64][4];
     const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
@@ -1099,18 +1164,18 @@ __global__ __launch_bounds__(kUnitThreads) void pool_large_kernel(SelectArgs<R> 
         const T *xv = reinterpret_cast<const T *>(a.v.p[slot]) + a.k_off;
         const int64_t col = (int64_t)g * a.sh + d + (int64_t)lf * P * a.st;
         double tot[4] = {0.0, 0.0, 0.0, 0.0}; // k0 k1 v0 v1, used by wave 0
-        int b = 0;
-        for (int s = 0; s < S; ++s) {
-            int e = kappa;
-            if (s < S - 1) { // first kept row at or beyond the next super-patch
-                const int bound = (s + 1) * len;
-                int lo = b, hi = kappa;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (kl[mid] < bound) lo = mid + 1; else hi = mid;
-                }
-                e = lo;
+        auto first_row = [&](int bound, int lo) { // the first kept row at or beyond a token, from row lo on
+            int hi = kappa;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (kl[mid] < bound) lo = mid + 1; else hi = mid;
             }
+            return lo;
+        };
+        const int s0 = blockIdx.z * S / gridDim.z, s1 = (blockIdx.z + 1) * S / gridDim.z;
+        int b = s0 > 0 ? first_row(s0 * len, 0) : 0;
+        for (int s = s0; s < s1; ++s) {
+            const int e = s < S - 1 ? first_row((s + 1) * len, b) : kappa;
             double run[4] = {0.0, 0.0, 0.0, 0.0};
             for (int r0 = b + slice; r0 < e; r0 += kPoolSlices * kPoolBatch) {
                 Pair2<T> yk[kPoolBatch], yv[kPoolBatch];
@@ -1154,17 +1219,39 @@ __global__ __launch_bounds__(kUnitThreads) void pool_large_kernel(SelectArgs<R> 
             __syncthreads();
             b = e;
         }
-        if (slice == 0 && live) {
-            const int64_t o = gf * C + c;
-            a.fsum_k[o] = tot[0];
-            a.fsum_k[o + 1] = tot[1];
-            a.fsum_v[o] = tot[2];
-            a.fsum_v[o + 1] = tot[3];
-            a.rep_frame_k[o] = (float)(tot[0] / (double)kappa);
-            a.rep_frame_k[o + 1] = (float)(tot[1] / (double)kappa);
-            a.rep_frame_v[o] = (float)(tot[2] / (double)kappa);
-            a.rep_frame_v[o + 1] = (float)(tot[3] / (double)kappa);
+        if (slice == 0 && live && gridDim.z > 1) {
+            double *to = part_tot + (((int64_t)e_idx * gridDim.y + blockIdx.y) * gridDim.z + blockIdx.z) * 256 + 4 * lane;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) to[q] = tot[q];
+        } else if (slice == 0 && live) {
+            store_unit_keys(a, gf, c, tot);
         }
+    }
+}
+
+// The sums of the shares of pool_large_kernel (n_z of them, same grid otherwise), in order.
+template <typename R>
+__global__ __launch_bounds__(64) void pool_total_kernel(SelectArgs<R> a, const double *__restrict__ part_tot, int n_z) {
+    const int lane = threadIdx.x, cp = blockIdx.y * 64 + lane;
+    const int n_e = a.pass2 ? *a.flag_count : (int)gridDim.x;
+    if (cp >= a.Hkv * a.D / 2) return;
+    for (int e_idx = blockIdx.x; e_idx < n_e; e_idx += gridDim.x) {
+        const int64_t gf = a.frame0 + (a.pass2 ? a.flag_list[e_idx] : e_idx);
+        if (!a.pass2 && a.refined[gf]) continue;
+        const double *from = part_tot + ((int64_t)e_idx * gridDim.y + blockIdx.y) * n_z * 256 + 4 * lane;
+        double tot[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int z0 = 0; z0 < n_z; z0 += 8) {
+            double x[8][4];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[u][q] = from[(z0 + u < n_z ? z0 + u : n_z - 1) * 256 + q];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) tot[q] += z0 + u < n_z ? x[u][q] : 0.0;
+        }
+        store_unit_keys(a, gf, 2 * cp, tot);
     }
 }
 
@@ -1711,7 +1798,11 @@ static hipError_t launch_select(const Ctx &c, const ChunkArgs &a, const R *att, 
     if (s.P > kMaxP) { // a unit of several frames: the keep and the block keys in two launches
         const int n_cg = (s.Hkv * s.D / 2 + 63) / 64;
         hipLaunchKernelGGL((select_large_kernel<R>), dim3(gx), dim3(kUnitThreads), 0, st, s);
-        hipLaunchKernelGGL((pool_large_kernel<T, R>), dim3(gx, n_cg), dim3(kUnitThreads), 0, st, s);
+        int n_z = kPoolParts / (gx * n_cg); // shares of the super-patches
+        n_z = n_z < s.S ? n_z : s.S;
+        n_z = n_z > 1 ? n_z : 1;
+        hipLaunchKernelGGL((pool_large_kernel<T, R>), dim3(gx, n_cg, n_z), dim3(kUnitThreads), 0, st, s, c.pool_part);
+        if (n_z > 1) hipLaunchKernelGGL((pool_total_kernel<R>), dim3(gx, n_cg), dim3(64), 0, st, s, c.pool_part, n_z);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((select_pool_kernel<T, R>), dim3(gx), dim3(256), 0, st, s);

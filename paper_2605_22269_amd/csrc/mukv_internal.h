@@ -17,6 +17,7 @@ constexpr int kMaxP = 256;        // tokens per frame the per-frame kernels are 
 constexpr int kMaxUnit = 8192;    // tokens of a unit of several frames ranked as one (attention signal handed over)
 constexpr int kMaxCand = 1024;    // stage-1 candidates (2*k) held in LDS by the rerank kernel
 constexpr int kMaxGatherK = 1024; // selected frames per question the gather kernel can plan
+constexpr int kPoolParts = 512;   // (unit, channel group, share of the super-patches) workgroups whose sums are joined
 constexpr int kMaxStores = 4;         // stores searched together (the paper has three: segment, frame, patch)
 constexpr int kMaxMultiEntries = 3072; // units per question the gather over several stores can plan
 
@@ -72,6 +73,7 @@ struct Ctx {
     uint16_t *dft_tab;  // matrix-core operands of the feature-axis transform (matrix-core attention, D = 128), or null
     double *att64;    // [max_chunk_frames][Hq][P] partial fp64 attention of re-scored frames
     double *fft64;    // [max_chunk_frames][P]
+    double *pool_part; // [kPoolParts][64][4] sums over shares of a unit's super-patches (units of several frames), or null
     int32_t *src_tok[2]; // [max_batch_frames*kappa] chunk-local token of every kept row
     int32_t *src_tok2;                // the same for the frames re-scored in fp64
     int32_t *flag_list[2], *flag_count; // batch frames to re-score in fp64 and how many, by batch parity

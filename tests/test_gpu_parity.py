@@ -1406,6 +1406,27 @@ def test_prefill_with_fewer_local_rows_than_new_tokens(name, kw, n_q, n_loc):
     p.close()
 
 
+@pytest.mark.parametrize("margin", [-1.0, 0.0])      # the keep in fp64, in fp32
+@pytest.mark.parametrize("P,rho", [(257, 0.5), (300, 1.0), (1025, 0.003), (4096, 0.7)])
+def test_keep_of_a_unit_with_few_distinct_scores(P, rho, margin):
+    # the digit search ends with every bit looked at, at once where all keys are equal, or at the one key left
+    att = torch.zeros(6, P)
+    att[1, 7::11] = 1.0                                   # two values, the cut inside one of them
+    att[2] = torch.arange(P).remainder(3) / 8.0
+    att[3, P // 2] = 1.0                                  # one token above all others
+    att[4] = torch.linspace(0.5, 1.0, P)                  # all different
+    att[5] = 0.25 + torch.arange(P).remainder(5) * 2.0 ** -23   # neighbours in the last bit
+    w = _unit_workload("bf16", P, 4, rho, 1.0, 6)
+    p = Pair(w, seed=330, chunk=3, with_q=False, gpu_kw={"refine_margin": margin})
+    for u in (0, 3):
+        k, v, _ = p.stream.next_chunk(3)
+        p.orc.compress_chunk(np_view(k), np_view(v), att=att[u:u + 3].numpy().astype(np.float64))
+        p.gpu.compress_chunk(k.cuda(), v.cuda(), att_signal=att[u:u + 3].contiguous().cuda())
+        torch.cuda.synchronize()
+    p.check_compress()
+    p.close()
+
+
 @pytest.mark.parametrize("i", range(16))
 def test_seeded_sweep_of_large_units(i):
     # units of 257..8192 tokens nobody picked by hand: super-patch counts, keep ratios, signal mixes, payloads,

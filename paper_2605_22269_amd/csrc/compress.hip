@@ -1533,18 +1533,19 @@ __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 }
 
-// The matrix-core attention of a batch of few frames, and its frequency indicator in workgroups of their own behind (8 frames
-// of 196 tokens, 28 heads: 13.9 us; as two launches 10.5 + 6.1).
+// The matrix-core attention of a batch of few frames, and its frequency indicator in workgroups of their own: one step a
+// wave, and first in the grid (behind the attention workgroups, where those take all places, they end the launch: 5 frames of
+// 64 heads a call of 66.6 us against 49.6, and 52.2 in two launches).
 __global__ __launch_bounds__(448) __attribute__((amdgpu_waves_per_eu(4, 4))) void att_freq_kernel(PtrTable qtab, FreqPart fp, AttMfmaArgs aa) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int b = blockIdx.x, n_att = fp.n_frames * aa.n_part;
-    if (b < n_att) {
-        const int by = b / fp.n_frames;
-        att_mfma_body(qtab, fp.k, fp.map, aa, b - by * fp.n_frames, by, smem_raw);
+    const int fb = blockIdx.x, ab = fb - fp.n_wg;
+    if (ab < 0) {
+        const int y = fb / fp.n_frames;
+        freq_body<uint16_t, float, 128>(fp.k, fp.map, fp.k_off, fp.sh, fp.st, fp.Hkv, fp.P, nullptr, nullptr, fp.out, fb - y * fp.n_frames, y,
+                                        fp.n_frames, fp.bpf);
     } else {
-        const int y = (b - n_att) / fp.n_frames;
-        freq_body<uint16_t, float, 128>(fp.k, fp.map, fp.k_off, fp.sh, fp.st, fp.Hkv, fp.P, nullptr, nullptr, fp.out,
-                                        b - n_att - y * fp.n_frames, y, fp.n_frames, fp.bpf);
+        const int by = ab / fp.n_frames;
+        att_mfma_body(qtab, fp.k, fp.map, aa, ab - by * fp.n_frames, by, smem_raw);
     }
 }
 
@@ -2062,9 +2063,7 @@ static hipError_t launch_att_freq(const Ctx &c, const ChunkArgs &a, int *n_part,
     fp.P = c.cfg.tokens_per_frame;
     fp.out = c.fft_sig[a.parity];
     fp.n_frames = a.n_frames;
-    // as many frequency workgroups as stay resident beside the attention's (two per compute unit), one step a wave at most
-    const int want = (512 - a.n_frames * aa.n_part) / a.n_frames, most = (fp.P + waves - 1) / waves;
-    fp.bpf = want < 4 ? 4 : want < most ? want : most;
+    fp.bpf = (fp.P + waves - 1) / waves; // one token a wave
     fp.n_wg = a.n_frames * fp.bpf;
     static bool lds_ok[kMaxDevices];
     const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void *>(&att_freq_kernel), kAttMfmaMaxLds, c.cfg.device_id, lds_ok);
@@ -2265,12 +2264,15 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
     }
     // both signals in one launch: the matrix-core attention with the frequency workgroups beside it (few frames) or with the
     // indicator worked out on the way (many), or the generic kernels together
-    const bool one_launch = !have_old && need_att && need_fft && c.cfg.freq_axis == MUKV_FREQ_FEATURE;
+    // (matrix-core attention, us a call of this chain in one / two launches: 8 frames of 28 heads 36.2 / 37.7, 32 64.6 /
+    // 64.8, 60 93.8 / 89.9, 128 -- the indicator on the way -- 112.6 / 122.6; 20 frames of 64 heads 81.8 / 83.0, 27 97.3 / 97.6)
+    const bool one_launch = !have_old && need_att && need_fft && c.cfg.freq_axis == MUKV_FREQ_FEATURE &&
+                            (!c.use_mfma || att_mfma_many(c, a.n_frames) || (int64_t)a.n_frames * c.cfg.n_q_heads <= 1280);
     if (one_launch) {
         ProfScope ps(c, MUKV_K_ATT, st);
         if (!c.use_mfma)
             e = launch_signals<T, float>(c, a, true, true, false, c.att_part[a.parity], &n_part, c.fft_sig[a.parity], st);
-        else if (chain_supported(c, a))
+        else if (att_mfma_many(c, a.n_frames))
             e = launch_chain(c, nullptr, 0, a, true, &n_part, &fft_parts, st);
         else
             e = launch_att_freq(c, a, &n_part, st);

@@ -3,7 +3,7 @@
 //
 // Kernel chain enqueued by launch_compress (all on the caller's stream; the first two share a launch where both are needed
 // and neither fills the chip, or where the matrix-core attention works out the indicator on the way):
-//   att_generic<float> | att_mfma      Eq. 1   partial attention received per (frame, head group)
+//   att_tile | att_mfma      Eq. 1   partial attention received per (frame, head group)
 //   freq_signal<float>                 Eq. 2-3 length-D DFT magnitudes of every key
 //   select_pool<float>                 Eq. 4 fusion, keep of the kappa best, Eq. 5 frame / super-patch keys
 //   att_generic<double>, freq_signal<double>, select_pool<double>
@@ -332,14 +332,14 @@ __global__ __launch_bounds__(256) void freq_token_finish_kernel(const R *__restr
 }
 
 // ------------------------------------------------------------------------------------------
-// Eq. 1, generic path (any dtype, any D, P <= 256), also the fp64 re-scoring path.
-// Grid (frame, query head, query range): a workgroup stages the frame's keys in LDS as float
+// Eq. 1 in fp64 (any dtype, any D, P <= 256), for the frames on the re-scoring list.
+// Grid (frame, query head, query range): a workgroup stages the frame's keys in LDS
 // (exact for bf16 and fp32 payloads) and handles kGenQ consecutive queries per round, four per
 // wave at once: lanes own keys j = lane + 64*t, every LDS key value read is used for four
 // queries, the row softmax uses wave reductions, and each lane accumulates the probabilities of
 // its keys.  Per-wave partial column sums are combined in a fixed order, so results are
 // run-to-run identical.
-// out: [frame][Hq * gridDim.z][P] (R) partial sums over this workgroup's query rows.
+// out: [frame][Hq * nz][P] (R) partial sums over this workgroup's query rows.
 // ------------------------------------------------------------------------------------------
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -365,10 +365,8 @@ __device__ __forceinline__ double exp_t(double x) { return exp(x); }
 
 constexpr int kGenQ = 16; // queries per round of a workgroup: 4 waves x 4
 
-// How the generic attention kernel keeps a frame's keys in LDS.  The fp32 pass, which runs on every
-// frame, keeps them expanded to float (its inner loop lives on LDS bandwidth).  The fp64 pass runs on a
-// few listed frames beside the next batch's kernels, whose workgroups leave less than half of a compute
-// unit's LDS free: it keeps bf16 keys as they are (half the room; the expansion is a shift).
+// How it keeps a frame's keys in LDS.  It runs on a few listed frames beside the next batch's kernels, whose workgroups leave
+// less than half of a compute unit's LDS free: bf16 keys stay as they are (half the room; the expansion is a shift).
 template <typename T, typename R>
 struct KeyStage {
     typedef float type;
@@ -534,9 +532,172 @@ __global__ __launch_bounds__(256) void att_generic_kernel(AttGenArgs a, R *__res
     att_generic_body<T, R>(a, out, blockIdx.x, blockIdx.y, blockIdx.z, smem_raw);
 }
 
-// Both signals in one launch, where neither fills the chip: the attention workgroups, then the frequency kernel's
-// (freq_gx, bpf) grid.  They read the same keys and need nothing of each other; one after the other they are two of the chain
-// of launches that a small batch is bound by.
+// ------------------------------------------------------------------------------------------
+// Eq. 1 in fp32 for the shapes att_mfma_dev.h does not take (fp32 payloads, bf16 rows of other lengths than 128, more than
+// 208 tokens; P <= 256): a workgroup per (frame, query head), or two (z), of (nt + 1) / 2 waves, nt = ceil(P / 16); wave w
+// takes the 16-query strips w and nt - 1 - w, which together see as many keys under the causal mask as any other wave's (z:
+// the one or the other).  The frame's keys sit in LDS as they are, a row's 16-byte pieces permuted so that 16 lanes
+// reading one piece of 16 rows meet all banks.  S^T = K Q^T (16x16x32 bf16, or 16x16x4 fp32 in four sums): a lane holds one
+// query and the keys 16 t + 4 (lane / 16) + r, so the softmax is in-lane work and two exchanges, and the sum over the queries is
+// an addition per key until the lanes' sums are joined at the end.  Fixed order throughout.
+// (On the vector ALU, with wave reductions per query row, a call of 8 frames of 196 tokens took: 28 heads of 128, fp32, 165 us,
+// now 67; 32 heads of 64, bf16, 87, now 46; 200 frames of those 1312, now 378.)
+// out: [frame][Hq * nz][P] sums over the workgroup's query rows.
+// ------------------------------------------------------------------------------------------
+struct AttTileArgs {
+    PtrTable q, k;
+    FrameMap map;
+    int64_t k_off, q_sh, q_st, k_sh, k_st;
+    int P, nt, G, Hq, causal, n_frames, nz;
+    float scale_log2e;
+    float *out;
+};
+
+typedef __bf16 tile_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float tile_f32x4 __attribute__((ext_vector_type(4)));
+
+template <typename T, int D, int NT>
+__device__ __forceinline__ void att_tile_body(const AttTileArgs &a, int f, int h, int z, unsigned char *smem) {
+    constexpr bool kBf16 = sizeof(T) == 2;
+    constexpr int kRowB = D * (int)sizeof(T), kPieces = kRowB / 16, KK = kBf16 ? (D + 31) / 32 : D / 16;
+    constexpr int kRowsPer256 = kRowB < 256 ? 256 / kRowB : 1, kSwz = kPieces < 16 ? kPieces - 1 : 15;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = blockDim.x >> 6;
+    const int P = a.P, nt = a.nt;
+    const int slot = find_slot(a.map, f), lf = f - a.map.fstart[slot];
+    const T *kf = reinterpret_cast<const T *>(a.k.p[slot]) + a.k_off + (int64_t)(h / a.G) * a.k_sh + (int64_t)lf * P * a.k_st;
+    const T *qf = reinterpret_cast<const T *>(a.q.p[slot]) + (int64_t)h * a.q_sh + (int64_t)lf * P * a.q_st;
+    auto place = [&](int row, int piece) { return row * kRowB + 16 * (piece ^ ((row / kRowsPer256) & kSwz)); };
+    // keys that some strip of the workgroup sees (rows past the last token repeat it; nobody sees them)
+    const int k_tiles = a.causal && a.nz == 2 && z == 0 ? n_waves : nt;
+    const int n_ku = k_tiles * 16 * kPieces;
+    for (int u0 = tid; u0 < n_ku; u0 += 8 * blockDim.x) {
+        u32x4 raw[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const int u = u0 + b * blockDim.x < n_ku ? u0 + b * blockDim.x : n_ku - 1;
+            const int row = u / kPieces, piece = u - row * kPieces;
+            raw[b] = *reinterpret_cast<const u32x4 *>(kf + (int64_t)(row < P ? row : P - 1) * a.k_st + piece * (16 / (int)sizeof(T)));
+        }
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const int u = u0 + b * blockDim.x;
+            if (u < n_ku) {
+                const int row = u / kPieces;
+                *reinterpret_cast<u32x4 *>(smem + place(row, u - row * kPieces)) = raw[b];
+            }
+        }
+    }
+    __syncthreads();
+    tile_f32x4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = tile_f32x4{0.f, 0.f, 0.f, 0.f};
+    const bool has_piece = kPieces >= 4 || lg < kPieces; // (rows of 32 bytes have two pieces)
+    const int my_piece = kPieces >= 4 ? lg : lg & (kPieces - 1);
+#pragma unroll 1
+    for (int half = a.nz == 2 ? z : 0; half < (a.nz == 2 ? z + 1 : 2); ++half) {
+        const int s = half == 0 ? wave : nt - 1 - wave; // this strip
+        if (half == 1 && s == wave) break;              // (the middle one)
+        const int i = 16 * s + lr;
+        u32x4 q[KK];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            q[kk] = *reinterpret_cast<const u32x4 *>(qf + (int64_t)(i < P ? i : P - 1) * a.q_st + (my_piece + 4 * kk) * (16 / (int)sizeof(T)));
+            if (!has_piece) q[kk] = u32x4{0u, 0u, 0u, 0u};
+        }
+        const int n_t = a.causal ? s + 1 : nt; // tiles of keys that the strip sees
+        tile_f32x4 sc[NT];
+        float m = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            if (t >= n_t) continue; // the same in all lanes
+            u32x4 x[KK];
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                x[kk] = *reinterpret_cast<const u32x4 *>(smem + place(16 * t + lr, my_piece + 4 * kk));
+                if (!has_piece) x[kk] = u32x4{0u, 0u, 0u, 0u};
+            }
+            if constexpr (kBf16) {
+                sc[t] = tile_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk)
+                    sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(tile_bf16x8, x[kk]), __builtin_bit_cast(tile_bf16x8, q[kk]),
+                                                                    sc[t], 0, 0, 0);
+            } else {
+                tile_f32x4 c[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    c[e] = tile_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int kk = 0; kk < KK; ++kk)
+                        c[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[kk][e]), __uint_as_float(q[kk][e]), c[e], 0, 0, 0);
+                }
+                sc[t] = (c[0] + c[1]) + (c[2] + c[3]);
+            }
+            if (t == n_t - 1 || t == nt - 1) { // the tile on the diagonal, or the last one
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int j = 16 * t + 4 * lg + r;
+                    sc[t][r] = j < P && (!a.causal || j <= i) ? sc[t][r] : -INFINITY;
+                }
+            }
+            m = fmaxf(m, fmaxf(fmaxf(sc[t][0], sc[t][1]), fmaxf(sc[t][2], sc[t][3])));
+        }
+        m = xrow_max(m) * a.scale_log2e;
+        float sum = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            if (t >= n_t) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sc[t][r] = __builtin_amdgcn_exp2f(fmaf(sc[t][r], a.scale_log2e, -m));
+            sum += (sc[t][0] + sc[t][1]) + (sc[t][2] + sc[t][3]);
+        }
+        const float inv = 1.0f / xrow_sum(sum);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            if (t >= n_t) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[t][r] += i < P ? sc[t][r] * inv : 0.f;
+        }
+    }
+    // over the strip's queries (the lanes of a row), then over the waves
+    float *part = reinterpret_cast<float *>(smem + nt * 16 * kRowB); // [wave][16 nt]
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if (t >= nt) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float v = row16_sum(acc[t][r]);
+            if (lr == 0) part[wave * 16 * nt + 16 * t + 4 * lg + r] = v;
+        }
+    }
+    __syncthreads();
+    float *dst = a.out + ((int64_t)f * (a.Hq * a.nz) + h * a.nz + z) * P;
+    for (int j = tid; j < P; j += blockDim.x) {
+        float v = 0.f;
+        for (int w = 0; w < n_waves; ++w) v += part[w * 16 * nt + j];
+        dst[j] = v;
+    }
+}
+
+// (attention workgroups 0 .. n_att - 1 of a 1-D grid behind n_freq frequency workgroups, of freq_bpf a frame; none: attention alone)
+template <typename T, int D, int NT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void att_tile_kernel(AttTileArgs a, int n_freq, int freq_bpf,
+                                                                                              int Hkv, float *__restrict__ fft_out) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int b = (int)blockIdx.x - n_freq;
+    if (b < 0) {
+        const int y = (int)blockIdx.x / a.n_frames;
+        freq_body<T, float, D>(a.k, a.map, a.k_off, a.k_sh, a.k_st, Hkv, a.P, nullptr, nullptr, fft_out, (int)blockIdx.x - y * a.n_frames, y,
+                               a.n_frames, freq_bpf);
+    } else {
+        const int hz = b / a.n_frames;
+        att_tile_body<T, D, NT>(a, b - hz * a.n_frames, hz % a.Hq, hz / a.Hq, smem_raw);
+    }
+}
+
+// Eq. 1-3 in fp64 of the listed frames, mostly none, in one launch: the attention workgroups, then the frequency kernel's
+// (freq_gx, bpf) grid.
 template <typename T, typename R, int D>
 __global__ __launch_bounds__(256) void signals_kernel(AttGenArgs a, R *__restrict__ att_out, R *__restrict__ fft_out, int Hkv, int freq_gx,
                                                       int bpf) {
@@ -1689,59 +1850,91 @@ static AttGenArgs att_generic_args(const Ctx &c, const ChunkArgs &a, bool listed
     return g;
 }
 
-template <typename T, typename R>
-static hipError_t launch_att_generic(const Ctx &c, const ChunkArgs &a, bool listed, R *out, int *n_part,
-                                     hipStream_t st) {
+// Eq. 1-3 of the listed frames in fp64; what is not needed is left out.  Both in one launch (as two, with an empty list, 3.3 +
+// 2.5 us), but for the token-axis indicator, which is two of its own.
+template <typename T>
+static hipError_t launch_signals64(const Ctx &c, const ChunkArgs &a, bool need_att, bool need_fft, int *n_part, hipStream_t st) {
+    hipError_t e;
+    const bool together = need_fft && c.cfg.freq_axis == MUKV_FREQ_FEATURE;
+    if (need_fft && !(need_att && together))
+        if ((e = launch_freq<T, double>(c, a, true, c.fft64, st)) != hipSuccess) return e;
+    if (!need_att) return hipSuccess;
     size_t lds;
-    const AttGenArgs g = att_generic_args<T, R>(c, a, listed, n_part, &lds);
-    static bool lds_ok[kMaxDevices]; // per instantiation
-    const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void *>(&att_generic_kernel<T, R>), 160 * 1024,
-                                            c.cfg.device_id, lds_ok);
-    if (ea != hipSuccess) return ea;
-    hipLaunchKernelGGL((att_generic_kernel<T, R>), dim3(g.gx, g.Hq, g.nz), dim3(256), lds, st, g, out);
+    const int P = c.cfg.tokens_per_frame, D = c.cfg.head_dim;
+    const AttGenArgs g = att_generic_args<T, double>(c, a, true, n_part, &lds);
+    const int freq_gx = rescore_slots(P, a.n_frames), bpf = freq_blocks_per_frame(P);
+    const unsigned total = (unsigned)(g.gx * g.Hq * g.nz + (together ? freq_gx * bpf : 0));
+#define MUKV_SIGNALS(DD)                                                                                                  \
+    do {                                                                                                                  \
+        static bool lds_ok[kMaxDevices];                                                                                  \
+        e = allow_dynamic_lds(reinterpret_cast<const void *>(&signals_kernel<T, double, DD>), 160 * 1024,                 \
+                              c.cfg.device_id, lds_ok);                                                                   \
+        if (e != hipSuccess) return e;                                                                                    \
+        hipLaunchKernelGGL((signals_kernel<T, double, DD>), dim3(total), dim3(256), lds, st, g, c.att64, c.fft64,         \
+                           c.cfg.n_kv_heads, freq_gx, bpf);                                                               \
+    } while (0)
+    switch (D) {
+    case 128: MUKV_SIGNALS(128); break;
+    case 64: MUKV_SIGNALS(64); break;
+    case 32: MUKV_SIGNALS(32); break;
+    case 16: MUKV_SIGNALS(16); break;
+    default: return hipErrorInvalidValue;
+    }
+#undef MUKV_SIGNALS
     return hipGetLastError();
 }
 
-// Eq. 1 by the generic kernel and Eq. 2-3, of every frame or of the listed ones; what is not needed is left out.  One launch
-// where all its workgroups are resident at once (an empty list, as most are: 3.3 + 2.5 us as two launches), else two.
-template <typename T, typename R>
-static hipError_t launch_signals(const Ctx &c, const ChunkArgs &a, bool need_att, bool need_fft, bool listed, R *att_out, int *n_part,
-                                 R *fft_out, hipStream_t st) {
+// Eq. 1 in fp32 by att_tile_kernel, with the feature-axis indicator's workgroups in front if wanted and both fit the chip at
+// once; *with_freq says whether they were taken along.
+template <typename T>
+static hipError_t launch_att_tile(const Ctx &c, const ChunkArgs &a, bool *with_freq, int *n_part, hipStream_t st) {
+    AttTileArgs t;
+    t.q = a.q;
+    t.k = a.k;
+    t.map = a.map;
+    t.k_off = (int64_t)c.ls * a.kv_sl;
+    t.q_sh = a.q_sh;
+    t.q_st = a.q_st;
+    t.k_sh = a.kv_sh;
+    t.k_st = a.kv_st;
+    t.P = c.cfg.tokens_per_frame;
+    t.nt = (t.P + 15) / 16;
+    t.G = c.group;
+    t.Hq = c.cfg.n_q_heads;
+    t.causal = c.cfg.causal;
+    t.n_frames = a.n_frames;
+    t.nz = (int64_t)a.n_frames * t.Hq < 512 && t.nt > 1 ? 2 : 1; // few frames: a strip a wave
+    t.scale_log2e = 1.4426950408889634f / sqrtf((float)c.cfg.head_dim);
+    t.out = c.att_part[a.parity];
+    *n_part = t.Hq * t.nz;
+    const int waves = (t.nt + 1) / 2, D = c.cfg.head_dim;
+    const size_t lds = (size_t)t.nt * 16 * D * sizeof(T) + (size_t)waves * 16 * t.nt * sizeof(float);
+    const int64_t n_att = (int64_t)a.n_frames * t.Hq * t.nz, tokens = (int64_t)waves * (128 / D); // of a frequency workgroup and step
+    const int bpf = (int)((t.P + tokens - 1) / tokens);
+    const int64_t fit = 16 / waves < (int64_t)(160 * 1024 / lds) ? 16 / waves : (int64_t)(160 * 1024 / lds); // workgroups per compute unit
+    *with_freq = *with_freq && n_att + (int64_t)a.n_frames * bpf <= 256 * fit;
+    const int n_freq = *with_freq ? a.n_frames * bpf : 0;
     hipError_t e;
-    if (need_att && need_fft && c.cfg.freq_axis == MUKV_FREQ_FEATURE) {
-        size_t lds;
-        const int P = c.cfg.tokens_per_frame, D = c.cfg.head_dim;
-        const AttGenArgs g = att_generic_args<T, R>(c, a, listed, n_part, &lds);
-        const int freq_gx = listed ? rescore_slots(P, a.n_frames) : a.n_frames;
-        const int bpf = listed ? freq_blocks_per_frame(P) : freq_blocks_alone(P, D, a.n_frames);
-        const int64_t total = (int64_t)g.gx * g.Hq * g.nz + (int64_t)freq_gx * bpf;
-        const int64_t per_cu = (int64_t)(160 * 1024 / lds) < 4 ? (int64_t)(160 * 1024 / lds) : 4;
-        if (total <= 256 * per_cu || (listed && P <= kMaxP)) {
-#define MUKV_SIGNALS(DD)                                                                                                   \
-    do {                                                                                                                   \
-        static bool lds_ok[kMaxDevices];                                                                                   \
-        e = allow_dynamic_lds(reinterpret_cast<const void *>(&signals_kernel<T, R, DD>), 160 * 1024, c.cfg.device_id,      \
-                              lds_ok);                                                                                     \
-        if (e != hipSuccess) return e;                                                                                     \
-        hipLaunchKernelGGL((signals_kernel<T, R, DD>), dim3((unsigned)total), dim3(256), lds, st, g, att_out, fft_out,     \
-                           c.cfg.n_kv_heads, freq_gx, bpf);                                                                \
+#define MUKV_TILE(DD, NT)                                                                                                 \
+    do {                                                                                                                  \
+        static bool lds_ok[kMaxDevices];                                                                                  \
+        e = allow_dynamic_lds(reinterpret_cast<const void *>(&att_tile_kernel<T, DD, NT>), 160 * 1024, c.cfg.device_id,   \
+                              lds_ok);                                                                                    \
+        if (e != hipSuccess) return e;                                                                                    \
+        hipLaunchKernelGGL((att_tile_kernel<T, DD, NT>), dim3((unsigned)(n_att + n_freq)), dim3(64 * waves), lds, st, t,  \
+                           n_freq, bpf, c.cfg.n_kv_heads, c.fft_sig[a.parity]);                                           \
     } while (0)
-            switch (D) {
-            case 128: MUKV_SIGNALS(128); break;
-            case 64: MUKV_SIGNALS(64); break;
-            case 32: MUKV_SIGNALS(32); break;
-            case 16: MUKV_SIGNALS(16); break;
-            default: return hipErrorInvalidValue;
-            }
-#undef MUKV_SIGNALS
-            return hipGetLastError();
-        }
+#define MUKV_TILE_D(DD) do { if (t.nt <= 8) MUKV_TILE(DD, 8); else MUKV_TILE(DD, 16); } while (0)
+    switch (D) {
+    case 128: MUKV_TILE_D(128); break;
+    case 64: MUKV_TILE_D(64); break;
+    case 32: MUKV_TILE_D(32); break;
+    case 16: MUKV_TILE_D(16); break;
+    default: return hipErrorInvalidValue;
     }
-    if (need_fft)
-        if ((e = launch_freq<T, R>(c, a, listed, fft_out, st)) != hipSuccess) return e;
-    if (need_att)
-        if ((e = launch_att_generic<T, R>(c, a, listed, att_out, n_part, st)) != hipSuccess) return e;
-    return hipSuccess;
+#undef MUKV_TILE_D
+#undef MUKV_TILE
+    return hipGetLastError();
 }
 
 hipError_t launch_att_mfma(const Ctx &c, const ChunkArgs &a, float *out, int *n_part, hipStream_t st);
@@ -2121,7 +2314,7 @@ static hipError_t launch_split_side(Ctx &c, const ChunkArgs &a, int n_part, int 
     if (c.margin_thr > 0.0) {
         ProfScope ps(c, MUKV_K_REFINE, c.side);
         int n_part64 = c.cfg.n_q_heads;
-        if ((e = launch_signals<T, double>(c, a, need_att, need_fft, true, c.att64, &n_part64, c.fft64, c.side)) != hipSuccess) return e;
+        if ((e = launch_signals64<T>(c, a, need_att, need_fft, &n_part64, c.side)) != hipSuccess) return e;
         if ((e = launch_select<T, double>(c, a, c.att64, n_part64, c.fft64, 1, c.side)) != hipSuccess) return e;
         if ((e = launch_compact(c, a, 2, c.side)) != hipSuccess) return e;
         hipLaunchKernelGGL(clear_count_kernel, dim3(1), dim3(1), 0, c.side, c.flag_count + par);
@@ -2159,7 +2352,7 @@ static hipError_t launch_side(Ctx &c, const ChunkArgs &a, bool with_keep, int n_
     if (c.margin_thr > 0.0) {
         ProfScope ps(c, MUKV_K_REFINE, c.side);
         int n_part64 = c.cfg.n_q_heads;
-        if ((e = launch_signals<T, double>(c, a, need_att, need_fft, true, c.att64, &n_part64, c.fft64, c.side)) != hipSuccess) return e;
+        if ((e = launch_signals64<T>(c, a, need_att, need_fft, &n_part64, c.side)) != hipSuccess) return e;
         if ((e = launch_select<T, double>(c, a, c.att64, n_part64, c.fft64, 1, c.side)) != hipSuccess) return e;
         if (!with_keep)
             if ((e = launch_compact(c, a, 2, c.side)) != hipSuccess) return e;
@@ -2270,9 +2463,11 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
                             (!c.use_mfma || att_mfma_many(c, a.n_frames) || (int64_t)a.n_frames * c.cfg.n_q_heads <= 1280);
     if (one_launch) {
         ProfScope ps(c, MUKV_K_ATT, st);
-        if (!c.use_mfma)
-            e = launch_signals<T, float>(c, a, true, true, false, c.att_part[a.parity], &n_part, c.fft_sig[a.parity], st);
-        else if (att_mfma_many(c, a.n_frames))
+        if (!c.use_mfma) {
+            bool with_freq = true;
+            e = launch_att_tile<T>(c, a, &with_freq, &n_part, st);
+            if (e == hipSuccess && !with_freq) e = launch_freq<T, float>(c, a, false, c.fft_sig[a.parity], st);
+        } else if (att_mfma_many(c, a.n_frames))
             e = launch_chain(c, nullptr, 0, a, true, &n_part, &fft_parts, st);
         else
             e = launch_att_freq(c, a, &n_part, st);
@@ -2300,7 +2495,8 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
         if (c.use_mfma) {
             if ((e = launch_att_mfma(c, a, c.att_part[a.parity], &n_part, st)) != hipSuccess) return e;
         } else {
-            if ((e = launch_att_generic<T, float>(c, a, false, c.att_part[a.parity], &n_part, st)) != hipSuccess) return e;
+            bool with_freq = false;
+            if ((e = launch_att_tile<T>(c, a, &with_freq, &n_part, st)) != hipSuccess) return e;
         }
     }
     if (overlap) { // keep on the side stream; the copy waits for the batch after next (or a flush / retrieve / gather call)
@@ -2323,7 +2519,7 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
         {
             ProfScope ps(c, MUKV_K_REFINE, st);
             int n_part64 = c.cfg.n_q_heads;
-            if ((e = launch_signals<T, double>(c, a, need_att, need_fft, true, c.att64, &n_part64, c.fft64, st)) != hipSuccess) return e;
+            if ((e = launch_signals64<T>(c, a, need_att, need_fft, &n_part64, st)) != hipSuccess) return e;
             if ((e = launch_select<T, double>(c, a, c.att64, n_part64, c.fft64, 2, st)) != hipSuccess) return e;
         }
         ProfScope ps(c, MUKV_K_COMPACT, st);

@@ -384,6 +384,22 @@ def test_both_signals_of_a_chunk_in_one_launch(name, frames, kw):
     p.close()
 
 
+@pytest.mark.parametrize("dtype,D,hq,hkv,P,frames,causal", [
+    ("f32", 128, 4, 2, 256, 3, True), ("f32", 128, 2, 1, 129, 2, False),     # the largest frame; past eight tiles
+    ("f32", 64, 4, 1, 128, 130, True),                                       # eight tiles; a workgroup per head
+    ("f32", 16, 4, 2, 17, 3, True), ("f32", 32, 2, 2, 16, 3, False),         # one past a tile, a tile
+    ("bf16", 64, 14, 2, 241, 2, True), ("bf16", 64, 16, 4, 15, 40, True),    # 16 tiles with one token in the last; less than a tile
+    ("bf16", 32, 6, 3, 113, 4, False), ("bf16", 16, 4, 1, 33, 5, True),
+    ("bf16", 128, 4, 1, 209, 2, True),                                       # one token more than the 128-feature kernel takes
+])
+def test_fp32_attention_signal_at_the_edges_of_its_tiles(dtype, D, hq, hkv, P, frames, causal):
+    w = W["tiny"].scaled(n_frames=frames, n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=D, dtype=dtype, tokens_per_frame=P, keep_ratio=0.3)
+    p = Pair(w, seed=122, chunk=frames, gpu_kw={"causal": causal}, orc_kw={"causal": causal})
+    p.ingest()
+    p.check_compress()
+    p.close()
+
+
 @pytest.mark.parametrize("P", [50, 16, 208, 7])
 def test_mfma_ragged_token_counts(P):
     w = W["7b"].scaled(n_frames=5, n_layers=1, tokens_per_frame=P, keep_ratio=0.3, n_q_heads=8, n_kv_heads=2)

@@ -12,10 +12,9 @@
 // The prefill of new tokens (Sec. 3.2: they attend to the past cache and to themselves) is the same
 // computation with many query tokens, and yields Eq. 1 -- the attention each new token receives --
 // on the way: bf16 rows of 64 or 128 features take the kernels further down; for the others attend_kernel (or the merge) also
-// writes every query's log-sum-exp; prefill_colsum_kernel recomputes the
-// scores of a tile's queries against the new tokens' keys, turns them into softmax weights with
-// that log-sum-exp and adds them over the tile; prefill_signal_kernel adds the tiles and KV heads in
-// order and divides by Hq * n_q.  Scratch for it comes from the caller (a workspace argument).
+// writes every query's log-sum-exp; prefill_colsum_kernel recomputes the scores against the new tokens' keys, turns them into
+// softmax weights with that log-sum-exp and adds them over shares of the queries; prefill_signal_kernel adds the shares and
+// KV heads in order and divides by Hq * n_q.  Scratch for it comes from the caller (a workspace argument).
 #include <climits>
 #include <type_traits>
 
@@ -26,7 +25,8 @@ namespace mukv {
 namespace {
 
 constexpr int kAttQ = 16, kAttWaves = 4; // queries and waves per workgroup of attend_kernel
-constexpr int kTileQ = 8;    // queries per workgroup of prefill_colsum_kernel
+constexpr int kTileQ = 8;    // queries a row of column sums stands for in the workspace's size
+constexpr int kColKeys = 64; // new tokens per workgroup of prefill_colsum_kernel
 constexpr int kThreads = 256;
 
 struct AttendArgs {
@@ -41,28 +41,7 @@ struct AttendArgs {
     float scale_log2e;
 };
 
-template <typename T>
-struct Row16;
 typedef __attribute__((ext_vector_type(4))) unsigned int raw16; // 16 bytes as they come from memory
-template <>
-struct Row16<uint16_t> { // eight bf16
-    static constexpr int E = 8;
-    __device__ static void expand(raw16 u, float *x) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            x[2 * i] = __uint_as_float(u[i] << 16);
-            x[2 * i + 1] = __uint_as_float(u[i] & 0xFFFF0000u);
-        }
-    }
-};
-template <>
-struct Row16<float> {
-    static constexpr int E = 4;
-    __device__ static void expand(raw16 u, float *x) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = __uint_as_float(u[i]);
-    }
-};
 template <typename T>
 __device__ __forceinline__ raw16 load16(const T *p) {
     return *reinterpret_cast<const raw16 *>(p);
@@ -475,72 +454,97 @@ __global__ void attend_combine_kernel(const float *__restrict__ part, int n_spli
     }
 }
 
-// Softmax weights of a tile's queries on the new tokens (the last n_q local rows of the question),
-// added over the tile.  Grid (query tile, KV head, question).  The tile's queries sit in LDS as
-// scaled floats; a thread takes new token j, j + 256, ...: its key row against all queries of the tile.
-// colpart [B][Hkv][n_qtiles][n_q].
+// Softmax weights on the new tokens (the last n_q local rows of the question), added over a share of the queries, for the
+// shapes of attend_kernel.  Grid (64 new tokens x share, KV head, question).  A wave keeps the keys of 16 tokens as the B
+// operand in registers and its share's queries stream past, 16 at a time and requested one tile ahead, so S = Q K^T leaves a
+// lane one key and four queries: no LDS, no barrier, and the sum over the queries is a running one until the end.  What bounds
+// it is the fp32 matrix rate with the queries' latency behind it.  (With eight queries in LDS and a thread per key on the vector
+// ALU, a layer call of fp32, 28 heads of 128 took: 32 tokens over 192 rows 28.6 us, now 18.0, 600 over 768 220, now 185; bf16
+// rows of 32 features, 400 tokens 46, now 19.)
+// colpart [B][Hkv][n_qs][n_q].
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void prefill_colsum_kernel(AttendArgs a, const float *__restrict__ lse,
-                                                                  float *__restrict__ colpart) {
-    constexpr int E = Row16<T>::E;
-    __shared__ float s_q[kTileQ][D];
-    __shared__ float s_l[kTileQ];
-    __shared__ int s_tok[kTileQ];
-    const int qt = blockIdx.x, g = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-    const int n_queries = a.n_q * a.G;
-    const T *q = static_cast<const T *>(a.q);
-    for (int idx = tid; idx < kTileQ * D; idx += kThreads) {
-        const int n = idx / D, d = idx - n * D;
-        const int qq = qt * kTileQ + n;
-        float x = 0.f;
-        if (qq < n_queries) {
-            const int i = qq / a.G, h = g * a.G + qq % a.G;
-            float one[E];
-            Row16<T>::expand(load16(q + (((int64_t)b * a.n_q + i) * a.Hq + h) * D + (d / E) * E), one);
-            x = one[d % E] * a.scale_log2e;
-        }
-        s_q[n][d] = x;
-    }
-    if (tid < kTileQ) {
-        const int qq = qt * kTileQ + tid;
-        const bool ok = qq < n_queries;
-        const int i = ok ? qq / a.G : 0, h = g * a.G + (ok ? qq % a.G : 0);
-        s_l[tid] = ok ? lse[((int64_t)b * a.n_q + i) * a.Hq + h] : INFINITY;
-        s_tok[tid] = ok ? i : INT_MIN;
-    }
-    __syncthreads();
+                                                                  float *__restrict__ colpart, int n_qs, int tiles_per) {
+    constexpr bool kBf16 = sizeof(T) == 2;
+    constexpr int kPieces = D * (int)sizeof(T) / 16, E = 16 / (int)sizeof(T), KK = kBf16 ? (D + 31) / 32 : D / 16;
+    const int kt = blockIdx.x / n_qs, qs = blockIdx.x - kt * n_qs, g = blockIdx.y, b = blockIdx.z;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
+    const int j0 = kColKeys * kt + 16 * wave; // this wave's new tokens
+    if (j0 >= a.n_q) return;
+    const int n_queries = a.n_q * a.G; // of this KV head: (token, head in group), token-major
     const int l0 = a.local_offsets[b];
     int n_loc = a.local_offsets[b + 1] - l0;
     if (n_loc < 0) n_loc = 0;
-    // the last token of the tile: with the causal mask no later new token gets anything from it
-    const int last_q = (qt * kTileQ + kTileQ - 1 < n_queries ? qt * kTileQ + kTileQ - 1 : n_queries - 1) / a.G;
-    const T *lk = static_cast<const T *>(a.k_local);
-    float *dst = colpart + (((int64_t)b * a.Hkv + g) * a.n_qtiles + qt) * a.n_q;
-    for (int j = tid; j < a.n_q; j += kThreads) {
-        const int r = n_loc - a.n_q + j; // local row of new token j
-        float acc = 0.f;
-        if (r >= 0 && !(a.causal && j > last_q)) {
-            const T *kp = lk + ((int64_t)(l0 + r) * a.Hkv + g) * D;
-            float sc[kTileQ];
+    // the lane's new token j is local row n_loc - n_q + j; it may not exist.  Query qq sees it iff qq >= q_min.
+    const int j = j0 + lr, lrow = n_loc - a.n_q + j;
+    const bool ok = j < a.n_q && lrow >= 0;
+    const int q_min = !ok ? INT_MAX : a.causal ? j * a.G : 0;
+    const bool has_piece = kPieces >= 4 || lg < kPieces; // (rows of 32 bytes have two pieces)
+    const int my_piece = kPieces >= 4 ? lg : lg & (kPieces - 1);
+    const int64_t base = (int64_t)b * a.n_q * a.Hq + g * a.G;
+    const T *q = static_cast<const T *>(a.q) + base * D + my_piece * E;
+    const T *kp = n_loc == 0 ? q : static_cast<const T *>(a.k_local) + ((int64_t)(l0 + (ok ? lrow : 0)) * a.Hkv + g) * D + my_piece * E; // (memory that exists)
+    raw16 kx[KK], qx[KK], qn[KK];
 #pragma unroll
-            for (int n = 0; n < kTileQ; ++n) sc[n] = 0.f;
-#pragma unroll 4
-            for (int d0 = 0; d0 < D; d0 += E) {
-                float kx[E];
-                Row16<T>::expand(load16(kp + d0), kx);
-#pragma unroll
-                for (int n = 0; n < kTileQ; ++n)
-#pragma unroll
-                    for (int e = 0; e < E; ++e) sc[n] = fmaf(s_q[n][d0 + e], kx[e], sc[n]);
-            }
-#pragma unroll
-            for (int n = 0; n < kTileQ; ++n) { // token i sees new token j iff j <= i (or always, without the mask)
-                const bool sees = a.causal ? s_tok[n] >= j : s_tok[n] >= 0;
-                acc += sees ? __builtin_amdgcn_exp2f(sc[n] - s_l[n]) : 0.f;
-            }
-        }
-        dst[j] = acc;
+    for (int kk = 0; kk < KK; ++kk) {
+        kx[kk] = load16(kp + 4 * kk * E);
+        if (!has_piece) kx[kk] = raw16{0u, 0u, 0u, 0u};
     }
+    const int n_tiles = (n_queries + 15) / 16;
+    const int t_end = (qs + 1) * tiles_per < n_tiles ? (qs + 1) * tiles_per : n_tiles;
+    int t = qs * tiles_per;
+    if (a.causal && j0 * a.G / 16 > t) t = j0 * a.G / 16; // nobody before token j0 sees these
+    float l_cur = 0.f, l_next = 0.f;
+    auto request = [&](int tile, raw16 *x, float *l) __attribute__((always_inline)) {
+        const int qq = 16 * tile + lr < n_queries ? 16 * tile + lr : n_queries - 1, tok = qq / a.G; // (past the last: masked)
+        const int64_t row = (int64_t)tok * a.Hq + (qq - tok * a.G);
+        *l = lse[base + row];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) x[kk] = load16(q + row * D + 4 * kk * E);
+    };
+    float sum = 0.f;
+    if (t < t_end) request(t, qx, &l_cur);
+    for (; t < t_end; ++t) {
+        if (t + 1 < t_end) request(t + 1, qn, &l_next);
+        f32x4 sc;
+        if constexpr (kBf16) {
+            sc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                if (!has_piece) qx[kk] = raw16{0u, 0u, 0u, 0u};
+                sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qx[kk]), __builtin_bit_cast(bf16x8, kx[kk]), sc, 0, 0, 0);
+            }
+        } else { // sums of four terms, joined pair by pair, as in attend_kernel
+            f32x4 part[KK];
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                f32x4 c[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    c[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qx[kk][e]), __uint_as_float(kx[kk][e]),
+                                                                f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                part[kk] = (c[0] + c[1]) + (c[2] + c[3]);
+            }
+#pragma unroll
+            for (int n = KK; n > 1; n /= 2)
+#pragma unroll
+                for (int i = 0; i < n / 2; ++i) part[i] = part[2 * i] + part[2 * i + 1];
+            sc = part[0];
+        }
+        float w[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int qq = 16 * t + 4 * lg + r;
+            const float x = fmaf(sc[r], a.scale_log2e, -__shfl(l_cur, 4 * lg + r));
+            w[r] = qq >= q_min && qq < n_queries ? __builtin_amdgcn_exp2f(x) : 0.f;
+        }
+        sum += (w[0] + w[1]) + (w[2] + w[3]);
+        l_cur = l_next;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) qx[kk] = qn[kk];
+    }
+    sum = xrow_sum(sum);
+    if (lg == 0 && j < a.n_q) colpart[(((int64_t)b * a.Hkv + g) * n_qs + qs) * a.n_q + j] = sum;
 }
 
 // The work of prefill_keysum_kernel (below): key tile kt takes the queries from its first token's on (all of them
@@ -1296,11 +1300,24 @@ hipError_t launch_typed(const AttendArgs &a, int B, void *out, const PrefillOut 
                            a.part, a.n_split, static_cast<T *>(out), po.lse);
     if constexpr (sizeof(T) == 2 && D >= 64) return hipGetLastError(); // their prefill is the matrix-core one
     if ((e = hipGetLastError()) != hipSuccess || !po.signal) return e;
+    // Shares of the queries, no more rows than the workspace has room for.  Under the causal mask the shares are uneven, so
+    // where a tile is long work (fp32 rows of 64 features and more) there are up to 16 workgroups per compute unit, otherwise
+    // four.  us a layer call with one / four / sixteen: fp32, 28 heads of 128, 196 tokens 40.5 / 39.8 / 38.3, 600 over 768 rows
+    // 234 / 197 / 185, 32 heads of 64, 600 tokens 96 / 79 / 73; rows of 16, 300 tokens 13.8 / 12.7 / 13.6; bf16 rows of 32,
+    // 400 tokens 21.9 / 19.0 / 19.9.
+    constexpr int kWgs = sizeof(T) == 4 && D >= 64 ? 4096 : 1024;
+    const int n_kt = (a.n_q + kColKeys - 1) / kColKeys, n_tiles = (a.n_q * a.G + 15) / 16;
+    const int64_t wgs = (int64_t)n_kt * a.Hkv * B;
+    int n_qs = wgs < kWgs ? (int)((kWgs + wgs - 1) / wgs) : 1;
+    n_qs = n_qs < n_tiles ? n_qs : n_tiles;
+    const int tiles_per = (n_tiles + n_qs - 1) / n_qs;
+    n_qs = (n_tiles + tiles_per - 1) / tiles_per;
     if constexpr (sizeof(T) == 4 || D < 64)
-        hipLaunchKernelGGL((prefill_colsum_kernel<T, D>), dim3(a.n_qtiles, a.Hkv, B), dim3(kThreads), 0, st, a, po.lse, po.colpart);
+        hipLaunchKernelGGL((prefill_colsum_kernel<T, D>), dim3(n_kt * n_qs, a.Hkv, B), dim3(kThreads), 0, st, a, po.lse, po.colpart, n_qs,
+                           tiles_per);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(prefill_signal_kernel, dim3((a.n_q + kSigCols - 1) / kSigCols, B), dim3(kThreads), 0, st, po.colpart,
-                       a.Hkv, a.n_qtiles, a.n_q, 1.0f / ((float)a.Hq * (float)a.n_q), po.signal, a.G, a.causal, 0);
+                       a.Hkv, n_qs, a.n_q, 1.0f / ((float)a.Hq * (float)a.n_q), po.signal, a.G, a.causal, 0);
     return hipGetLastError();
 }
 
@@ -1472,7 +1489,7 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
     a.n_qtiles = (n_q * c.group + kTileQ - 1) / kTileQ;
     a.causal = causal;
     a.scale_log2e = 1.4426950408889634f / sqrtf((float)c.cfg.head_dim);
-a.n_split = attend_split(c, n_q, B, a.k_frame);
+    a.n_split = attend_split(c, n_q, B, a.k_frame);
     if (workspace) { // (its records are counted by the formula above)
         const int most = record_splits(B, a.Hkv, a.n_qtiles, a.k_frame);
         if (a.n_split > most) a.n_split = most;

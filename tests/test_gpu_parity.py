@@ -1173,6 +1173,25 @@ def test_prefill_matrix_tile_edges(D, hq, hkv, n_q, n_frames, old):
     p.close()
 
 
+@pytest.mark.parametrize("dtype,D,hq,hkv,n_q,n_frames,old", [
+    ("f32", 128, 28, 4, 1, 2, [0]),           # one token: 7 queries of 16
+    ("f32", 128, 28, 4, 65, 2, [0, 7]),       # a new token past 64; shares of a few tiles
+    ("f32", 64, 14, 2, 16, 0, [5]),           # a wave's keys exactly
+    ("f32", 32, 4, 4, 17, 1, [0, 0, 3]),      # one past it, one head per group: 17 queries
+    ("f32", 16, 16, 1, 200, 2, [31]),         # one KV head: many shares
+    ("bf16", 32, 64, 8, 150, 2, [0] * 33),    # so many questions that the queries are not shared
+    ("bf16", 16, 14, 2, 63, 3, [1]),          # rows of two pieces
+])
+def test_prefill_column_sums_edges(dtype, D, hq, hkv, n_q, n_frames, old):
+    w = W["7b"].scaled(n_frames=4, n_layers=1, dtype=dtype, head_dim=D, n_q_heads=hq, n_kv_heads=hkv, n_questions=len(old))
+    p = Pair(w, seed=457, chunk=4)
+    p.ingest()
+    fi = [[(b + i) % 4 for i in range(n_frames)] for b in range(len(old))] if n_frames else None
+    for causal in (True, False):
+        p.check_prefill(0, n_q, fi, old, causal, seed=458)
+    p.close()
+
+
 @pytest.mark.parametrize("D,hq,hkv,n_q,n_frames,old", [
     (128, 28, 4, 31, 0, [0, 40]),       # 32 keys at a time and one less; behind older rows
     (128, 28, 4, 64, 0, [1]),           # the keys of 64 tokens lie across the last two steps of rows

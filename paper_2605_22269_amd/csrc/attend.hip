@@ -76,6 +76,13 @@ __device__ __forceinline__ int row_swizzle(int row) {
     return ((row / (128 / D)) & (D / 16 - 1)) << 1;
 }
 
+// x * s - y with the product rounded, as the maximum y was.
+__device__ __forceinline__ float scaled_apart(float x, float s, float y) {
+#pragma clang fp contract(off)
+    const float p = x * s;
+    return p - y;
+}
+
 // Where row `code` of [retrieved rows, local rows] lives: >= 0 a row of the store's slab, < 0 local row ~code.
 __device__ __forceinline__ const unsigned char *row_at(const unsigned char *store, const unsigned char *local, int code,
                                                        unsigned store_stride, unsigned local_stride) {
@@ -280,10 +287,17 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
         }
         const float ref = m_run == -INFINITY ? 0.f : m_run;
         float p[4 * kTiles];
+        if (__builtin_amdgcn_ballot_w64(fabsf(ref) > 16777216.f) != 0) { // so large that the rounding of the maximum shows
 #pragma unroll
-        for (int t = 0; t < kTiles; ++t)
+            for (int t = 0; t < kTiles; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) p[4 * t + r] = __builtin_amdgcn_exp2f(fmaf(sc[t][r], a.scale_log2e, -ref));
+                for (int r = 0; r < 4; ++r) p[4 * t + r] = __builtin_amdgcn_exp2f(scaled_apart(sc[t][r], a.scale_log2e, ref));
+        } else {
+#pragma unroll
+            for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) p[4 * t + r] = __builtin_amdgcn_exp2f(fmaf(sc[t][r], a.scale_log2e, -ref));
+        }
         float sum = (p[0] + p[1]) + (p[2] + p[3]);
         if constexpr (kTiles == 2) sum += (p[4] + p[5]) + (p[6] + p[7]);
         l_run += sum;

@@ -643,13 +643,13 @@ __device__ __forceinline__ void att_tile_body(const AttTileArgs &a, int f, int h
             }
             m = fmaxf(m, fmaxf(fmaxf(sc[t][0], sc[t][1]), fmaxf(sc[t][2], sc[t][3])));
         }
-        m = xrow_max(m) * a.scale_log2e;
+        m = xrow_max(m);
         float sum = 0.f;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             if (t >= n_t) continue;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) sc[t][r] = __builtin_amdgcn_exp2f(fmaf(sc[t][r], a.scale_log2e, -m));
+            for (int r = 0; r < 4; ++r) sc[t][r] = __builtin_amdgcn_exp2f((sc[t][r] - m) * a.scale_log2e); // (the largest: exactly 1)
             sum += (sc[t][0] + sc[t][1]) + (sc[t][2] + sc[t][3]);
         }
         const float inv = 1.0f / xrow_sum(sum);

@@ -1173,6 +1173,32 @@ def test_prefill_matrix_tile_edges(D, hq, hkv, n_q, n_frames, old):
     p.close()
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_scores_of_any_finite_size(dtype, D):
+    # scores of 1e12: every softmax is a choice of one row (two largest within the 1e-6 of a sum in fp32: none here), and
+    # no weight may overflow on the rounding of the maximum
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    P, n, H = 49, 3, 4
+    g = torch.Generator().manual_seed(461)
+    k, v, q = ((torch.randn(*s, generator=g) * m).to(t) for s, m in
+               (((1, H, n * P, D), 1e6), ((1, H, n * P, D), 1.0), ((H, n * P, D), 1e6)))
+    ctx = mk.MuKV(n_layers=1, n_q_heads=H, n_kv_heads=H, head_dim=D, tokens_per_frame=P, frames_per_segment=8,
+                  superpatches_per_frame=4, dtype=t, keep_ratio=0.25, max_frames=4, max_chunk_frames=4, max_questions=1)
+    att = ctx.compress_chunk(k.cuda(), v.cuda(), q.cuda(), want_signals=True)["att"]
+    ctx.flush()
+    torch.cuda.synchronize()
+    sc = torch.einsum("hfid,hfjd->hfij", q.double().view(H, n, P, D), k[0].double().view(H, n, P, D)) / D ** 0.5
+    sc = sc.masked_fill(torch.triu(torch.ones(P, P, dtype=torch.bool), 1), -1e300).softmax(-1)
+    assert (att.cpu().double() - sc.mean((0, 2))).abs().max() <= 1e-6
+    qn = q[:, :2].transpose(0, 1).contiguous()[None]                           # [1][2][H][D]
+    out = ctx.attend(0, qn.cuda(), None, k[0].transpose(0, 1).contiguous().cuda(), v[0].transpose(0, 1).contiguous().cuda(),
+                     torch.tensor([0, n * P], dtype=torch.int32).cuda(), False)
+    w = (torch.einsum("hid,hjd->hij", q[:, :2].double(), k[0].double()) / D ** 0.5).softmax(-1)
+    want = torch.einsum("hij,hjd->ihd", w, v[0].double())
+    assert (out[0].cpu().double() - want).abs().max() <= 1e-5
+    ctx.close()
+
+
 @pytest.mark.parametrize("dtype,D,hq,hkv,n_q,n_frames,old", [
     ("f32", 128, 28, 4, 1, 2, [0]),           # one token: 7 queries of 16
     ("f32", 128, 28, 4, 65, 2, [0, 7]),       # a new token past 64; shares of a few tiles

@@ -1199,6 +1199,25 @@ def test_scores_of_any_finite_size(dtype, D):
     ctx.close()
 
 
+@pytest.mark.parametrize("D,hq,hkv,most", [(64, 16, 4, 1.2e-7), (128, 28, 4, 1.23e-7)])
+def test_fp32_attention_stays_as_near_to_64_bits(D, hq, hkv, most):
+    # 30 rows, 64 questions, mean relative distance: 1.15 / 1.17e-7 (D = 64 / 128, standard error 0.01).  Sums that join evenly
+    # give 1.18 / 1.21, a block's 16 rows one after another and exponents rounded at their own size 1.26 / 1.28
+    ctx = mk.MuKV(n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=D, tokens_per_frame=16, frames_per_segment=8,
+                  superpatches_per_frame=4, dtype=torch.float32, keep_ratio=0.25, max_frames=4, max_chunk_frames=4, max_questions=64)
+    B, n = 64, 30
+    g = torch.Generator().manual_seed(467)
+    q = torch.randn(B, 1, hq, D, generator=g)
+    k, v = torch.randn(B * n, hkv, D, generator=g), torch.randn(B * n, hkv, D, generator=g)
+    out = ctx.attend(0, q.cuda(), None, k.cuda(), v.cuda(), (torch.arange(B + 1) * n).to(torch.int32).cuda(), True)
+    kd, vd = (x.double().view(B, n, hkv, D).transpose(1, 2) for x in (k, v))
+    w = (torch.matmul(q.double().view(B, hkv, hq // hkv, D), kd.transpose(2, 3)) / D ** 0.5).softmax(-1)
+    want = torch.matmul(w, vd).view(B, hq * D)
+    far = (out.cpu().double().view(B, hq * D) - want).norm(dim=1) / want.norm(dim=1)
+    assert far.mean() <= most
+    ctx.close()
+
+
 @pytest.mark.parametrize("dtype,D,hq,hkv,n_q,n_frames,old", [
     ("f32", 128, 28, 4, 1, 2, [0]),           # one token: 7 queries of 16
     ("f32", 128, 28, 4, 65, 2, [0, 7]),       # a new token past 64; shares of a few tiles

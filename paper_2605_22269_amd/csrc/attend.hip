@@ -76,6 +76,26 @@ __device__ __forceinline__ int row_swizzle(int row) {
     return ((row / (128 / D)) & (D / 16 - 1)) << 1;
 }
 
+// attend_kernel and prefill_colsum_kernel, fp32 rows and bf16 rows of 16: the queries are brought down before the product by a
+// power of two, exactly, to where a score that is finite once scaled by log2(e) / sqrt(D) does not overflow before.
+template <typename T, int D>
+constexpr float query_factor() {
+    return sizeof(T) == 2 && D > 16 ? 1.f : D <= 32 ? 0.25f : 0.125f; // (D = 16 .. 128: the scale is 0.361, 0.255, 0.180, 0.128)
+}
+template <typename T, int D>
+__device__ __forceinline__ raw16 brought_down(raw16 x) {
+    constexpr float f = query_factor<T, D>();
+    if constexpr (f != 1.f)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (sizeof(T) == 4)
+                x[e] = __float_as_uint(__uint_as_float(x[e]) * f);
+            else
+                x[e] = __float_as_uint(__uint_as_float(x[e] << 16) * f) >> 16 | (__float_as_uint(__uint_as_float(x[e] & 0xFFFF0000u) * f) & 0xFFFF0000u);
+        }
+    return x;
+}
+
 // x * s - y with the product rounded, as the maximum y was.
 __device__ __forceinline__ float scaled_apart(float x, float s, float y) {
 #pragma clang fp contract(off)
@@ -141,6 +161,7 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
     const int sp = blockIdx.x, g = blockIdx.y % a.Hkv, qt = blockIdx.y / a.Hkv, b = blockIdx.z;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lr = lane & 15, lg = lane >> 4;
     const int n_queries = a.n_q * a.G; // of this KV head: (token, head in group), token-major
+    const float scale = a.scale_log2e * (1.f / query_factor<T, D>());
     for (int i = tid; i < a.k_frame; i += 64 * W) {
         const int f = a.frame_idx[(int64_t)b * a.k_frame + i];
         s_frame[i] = (f >= 0 && f < a.n_frames) ? f : -1;
@@ -157,7 +178,7 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
     for (int kk = 0; kk < KK; ++kk) {
         if (kQueryLds && wave != 0) break; // the same in all waves
         raw16 x = load16(static_cast<const T *>(a.q) + my_row * D + (my_piece + 4 * kk) * (16 / (int)sizeof(T)));
-        if (!q_ok || !has_piece) x = raw16{0u, 0u, 0u, 0u};
+        x = q_ok && has_piece ? brought_down<T, D>(x) : raw16{0u, 0u, 0u, 0u};
         if constexpr (kQueryLds)
             s_q[kk][lane] = x;
         else
@@ -286,7 +307,7 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
         // exponents subtract is a whole number, so that bringing sums from one to another multiplies by a power of two ----
         float mx = fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3]));
         if constexpr (kTiles == 2) mx = fmaxf(mx, fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
-        mx = ceilf(xrow_max(mx) * a.scale_log2e);
+        mx = ceilf(xrow_max(mx) * scale);
         if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) { // a maximum moved: bring what was summed to it
             const float m_new = fmaxf(m_run, mx);
             const float corr = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
@@ -301,13 +322,13 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
             for (int t = 0; t < kTiles; ++t)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) p[4 * t + r] = __builtin_amdgcn_exp2f(scaled_apart(sc[t][r], a.scale_log2e, ref));
+                for (int r = 0; r < 4; ++r) p[4 * t + r] = __builtin_amdgcn_exp2f(scaled_apart(sc[t][r], scale, ref));
         } else {
 #pragma unroll
             for (int t = 0; t < kTiles; ++t)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) // (bf16 payloads: the output's own rounding is four orders above the difference's)
-                    p[4 * t + r] = kBf16 ? __builtin_amdgcn_exp2f(fmaf(sc[t][r], a.scale_log2e, -ref)) : weight_of(sc[t][r], a.scale_log2e, ref);
+                    p[4 * t + r] = kBf16 ? __builtin_amdgcn_exp2f(fmaf(sc[t][r], scale, -ref)) : weight_of(sc[t][r], scale, ref);
         }
         float sum = (p[0] + p[1]) + (p[2] + p[3]);
         if constexpr (kTiles == 2) sum += (p[4] + p[5]) + (p[6] + p[7]);
@@ -498,6 +519,7 @@ __global__ __launch_bounds__(kThreads) void prefill_colsum_kernel(AttendArgs a, 
     const int j0 = kColKeys * kt + 16 * wave; // this wave's new tokens
     if (j0 >= a.n_q) return;
     const int n_queries = a.n_q * a.G; // of this KV head: (token, head in group), token-major
+    const float scale = a.scale_log2e * (1.f / query_factor<T, D>());
     const int l0 = a.local_offsets[b];
     int n_loc = a.local_offsets[b + 1] - l0;
     if (n_loc < 0) n_loc = 0;
@@ -513,7 +535,7 @@ __global__ __launch_bounds__(kThreads) void prefill_colsum_kernel(AttendArgs a, 
     raw16 kx[KK], qx[KK], qn[KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-        kx[kk] = load16(kp + 4 * kk * E);
+        kx[kk] = brought_down<T, D>(load16(kp + 4 * kk * E)); // (the keys instead of the queries, once: the same products)
         if (!has_piece) kx[kk] = raw16{0u, 0u, 0u, 0u};
     }
     const int n_tiles = (n_queries + 15) / 16;
@@ -561,7 +583,7 @@ __global__ __launch_bounds__(kThreads) void prefill_colsum_kernel(AttendArgs a, 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int qq = 16 * t + 4 * lg + r;
-            const float x = fmaf(sc[r], a.scale_log2e, -__shfl(l_cur, 4 * lg + r));
+            const float x = fmaf(sc[r], scale, -__shfl(l_cur, 4 * lg + r));
             w[r] = qq >= q_min && qq < n_queries ? __builtin_amdgcn_exp2f(x) : 0.f;
         }
         sum += (w[0] + w[1]) + (w[2] + w[3]);

@@ -1199,6 +1199,25 @@ def test_scores_of_any_finite_size(dtype, D):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 16), ("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 16)])
+def test_scores_finite_once_scaled(dtype, D):
+    # q.k is past fp32 (5.4e38 .. 2e39), q.k log2(e) / sqrt(D) is not (2e38): one row, ten times the others, takes all the weight
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    H, n = 2, 40
+    ctx = mk.MuKV(n_layers=1, n_q_heads=H, n_kv_heads=H, head_dim=D, tokens_per_frame=16, frames_per_segment=8,
+                  superpatches_per_frame=4, dtype=t, keep_ratio=0.25, max_frames=4, max_chunk_frames=4, max_questions=1)
+    q = torch.full((1, n, H, D), 2.0 ** 50)
+    k = torch.full((n, H, D), 2e37 * D ** 0.5 / 1.4426950408889634 / D / 2.0 ** 50)
+    k[7] *= 10
+    v = torch.randn(n, H, D, generator=torch.Generator().manual_seed(463)).to(t)
+    q, k, v, offs = q.to(t).cuda(), k.to(t).cuda(), v.cuda(), torch.tensor([0, n], dtype=torch.int32).cuda()
+    out = ctx.attend(0, q[:, :2].contiguous(), None, k, v, offs, False)
+    assert torch.equal(out[0], v[7].expand(2, H, D))
+    out, _ = ctx.prefill_attend(0, q, None, k, v, offs, False)
+    assert torch.equal(out[0], v[7].expand(n, H, D))
+    ctx.close()
+
+
 @pytest.mark.parametrize("D,hq,hkv,most", [(64, 16, 4, 1.2e-7), (128, 28, 4, 1.23e-7)])
 def test_fp32_attention_stays_as_near_to_64_bits(D, hq, hkv, most):
     # 30 rows, 64 questions, mean relative distance: 1.15 / 1.17e-7 (D = 64 / 128, standard error 0.01).  Sums that join evenly

@@ -12,8 +12,8 @@
 // The prefill of new tokens (Sec. 3.2: they attend to the past cache and to themselves) is the same
 // computation with many query tokens, and yields Eq. 1 -- the attention each new token receives --
 // on the way: bf16 rows of 64 or 128 features take the kernels further down; for the others attend_kernel (or the merge) also
-// writes every query's log-sum-exp; prefill_colsum_kernel recomputes the scores against the new tokens' keys, turns them into
-// softmax weights with that log-sum-exp and adds them over shares of the queries; prefill_signal_kernel adds the shares and
+// writes every query's reference and normaliser; prefill_colsum_kernel recomputes the scores against the new tokens' keys, turns
+// them into softmax weights with those and adds them over shares of the queries; prefill_signal_kernel adds the shares and
 // KV heads in order and divides by Hq * n_q.  Scratch for it comes from the caller (a workspace argument).
 #include <climits>
 #include <type_traits>
@@ -39,6 +39,9 @@ struct AttendArgs {
     int64_t store_cap;
     int n_q, Hq, Hkv, G, k_frame, kappa, n_frames, n_split, n_qtiles, causal;
     float scale_log2e;
+    // for prefill_colsum_kernel: a query's pair (what its weights' exponents subtract, 1 / sum of the weights, 0 if there are none)
+    // is at part + pair_stride * query, where its first record was if its rows were split; 0: no pairs wanted
+    int pair_stride;
 };
 
 typedef __attribute__((ext_vector_type(4))) unsigned int raw16; // 16 bytes as they come from memory
@@ -110,6 +113,12 @@ __device__ __forceinline__ float weight_of(float x, float s, float ref) {
     return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(fmaf(x, s, -n)), (int)(n - ref));
 }
 
+constexpr float kLargeRef = 16777216.f; // whole numbers up to here have no gaps
+// The same for references of any size.
+__device__ __forceinline__ float weight_of_any(float x, float s, float ref) {
+    return fabsf(ref) > kLargeRef ? __builtin_amdgcn_exp2f(scaled_apart(x, s, ref)) : weight_of(x, s, ref);
+}
+
 // Where row `code` of [retrieved rows, local rows] lives: >= 0 a row of the store's slab, < 0 local row ~code.
 __device__ __forceinline__ const unsigned char *row_at(const unsigned char *store, const unsigned char *local, int code,
                                                        unsigned store_stride, unsigned local_stride) {
@@ -140,7 +149,7 @@ __device__ __forceinline__ const unsigned char *row_at(const unsigned char *stor
 // the merge launch (attend_split).  Eight waves a workgroup are no faster (16.4; 9.8 against 9.6 for one question).
 template <typename T, int D>
 __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void attend_kernel(
-    AttendArgs a, T *__restrict__ out, float *__restrict__ lse) {
+    AttendArgs a, T *__restrict__ out) {
     constexpr int W = kAttWaves;
     constexpr bool kBf16 = sizeof(T) == 2;
     constexpr int kRowB = D * (int)sizeof(T), kPieces = kRowB / 16;
@@ -318,11 +327,11 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
         }
         const float ref = m_run == -INFINITY ? 0.f : m_run;
         float p[4 * kTiles];
-        if (__builtin_amdgcn_ballot_w64(fabsf(ref) > 16777216.f) != 0) { // so large that the rounding of the maximum shows
+        if (__builtin_amdgcn_ballot_w64(fabsf(ref) > kLargeRef) != 0) { // somebody's is so large that its rounding shows
 #pragma unroll
             for (int t = 0; t < kTiles; ++t)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) p[4 * t + r] = __builtin_amdgcn_exp2f(scaled_apart(sc[t][r], scale, ref));
+                for (int r = 0; r < 4; ++r) p[4 * t + r] = weight_of_any(sc[t][r], scale, ref);
         } else {
 #pragma unroll
             for (int t = 0; t < kTiles; ++t)
@@ -458,7 +467,8 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
                 *reinterpret_cast<u32x2 *>(out + row * D + 4 * c) = u32x2{bf16_pair(o[0] / den, o[1] / den), bf16_pair(o[2] / den, o[3] / den)};
             else
                 *reinterpret_cast<f32x4 *>(out + row * D + 4 * c) = o / den;
-            if (lse && c == 0) lse[row] = l != 0.f ? m + __builtin_amdgcn_logf(l) : INFINITY;
+            if (a.pair_stride && c == 0)
+                *reinterpret_cast<f32x2 *>(a.part + row * a.pair_stride) = l != 0.f ? f32x2{m, 1.f / l} : f32x2{0.f, 0.f};
         }
     }
 }
@@ -467,11 +477,12 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
 // is a denominator of exactly zero (a NaN or +inf score makes it a NaN, and the output with it)
 // lse (may be null): log2 of the query's softmax denominator, in the scores' log2 units; +inf for a
 // query that sees no key, so that every weight computed from it is zero.
+// pairs: the query's pair takes the place of its first record's start (see AttendArgs).
 template <typename T, int D>
-__global__ void attend_combine_kernel(const float *__restrict__ part, int n_split, T *__restrict__ out,
-                                      float *__restrict__ lse) {
+__global__ void attend_combine_kernel(float *part, int n_split, T *__restrict__ out, float *__restrict__ lse, bool pairs) {
     const int64_t row = blockIdx.x;
-    const float *p = part + row * n_split * (D + 2);
+    float *p = part + row * n_split * (D + 2);
+    f32x2 pair = {0.f, 0.f};
     for (int d = threadIdx.x; d < D; d += blockDim.x) {
         // every record's maximum, normaliser and this thread's element requested before any is used
         float ms[kAttendMaxSplit], zz[kAttendMaxSplit], oo[kAttendMaxSplit];
@@ -498,7 +509,11 @@ __global__ void attend_combine_kernel(const float *__restrict__ part, int n_spli
         }
         store_out(out + row * D + d, zs != 0.f ? os / zs : 0.f);
         if (lse && d == 0) lse[row] = zs != 0.f ? m + __builtin_amdgcn_logf(zs) : INFINITY;
+        if (zs != 0.f) pair = f32x2{m, 1.f / zs};
     }
+    if (!pairs) return; // the same in all threads
+    __syncthreads();    // the record has been read
+    if (threadIdx.x == 0) *reinterpret_cast<f32x2 *>(p) = pair;
 }
 
 // Softmax weights on the new tokens (the last n_q local rows of the question), added over a share of the queries, for the
@@ -506,12 +521,11 @@ __global__ void attend_combine_kernel(const float *__restrict__ part, int n_spli
 // operand in registers and its share's queries stream past, 16 at a time and requested one tile ahead, so S = Q K^T leaves a
 // lane one key and four queries: no LDS, no barrier, and the sum over the queries is a running one until the end.  What bounds
 // it is the fp32 matrix rate with the queries' latency behind it.  (With eight queries in LDS and a thread per key on the vector
-// ALU, a layer call of fp32, 28 heads of 128 took: 32 tokens over 192 rows 28.6 us, now 18.0, 600 over 768 220, now 185; bf16
-// rows of 32 features, 400 tokens 46, now 19.)
+// ALU, a layer call of fp32, 28 heads of 128 took: 32 tokens over 192 rows 28.6 us, now 19.7, 600 over 768 220, now 206; bf16
+// rows of 32 features, 400 tokens 46, now 20.)
 // colpart [B][Hkv][n_qs][n_q].
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void prefill_colsum_kernel(AttendArgs a, const float *__restrict__ lse,
-                                                                  float *__restrict__ colpart, int n_qs, int tiles_per) {
+__global__ __launch_bounds__(kThreads) void prefill_colsum_kernel(AttendArgs a, float *__restrict__ colpart, int n_qs, int tiles_per) {
     constexpr bool kBf16 = sizeof(T) == 2;
     constexpr int kPieces = D * (int)sizeof(T) / 16, E = 16 / (int)sizeof(T), KK = kBf16 ? (D + 31) / 32 : D / 16;
     const int kt = blockIdx.x / n_qs, qs = blockIdx.x - kt * n_qs, g = blockIdx.y, b = blockIdx.z;
@@ -542,18 +556,18 @@ __global__ __launch_bounds__(kThreads) void prefill_colsum_kernel(AttendArgs a, 
     const int t_end = (qs + 1) * tiles_per < n_tiles ? (qs + 1) * tiles_per : n_tiles;
     int t = qs * tiles_per;
     if (a.causal && j0 * a.G / 16 > t) t = j0 * a.G / 16; // nobody before token j0 sees these
-    float l_cur = 0.f, l_next = 0.f;
-    auto request = [&](int tile, raw16 *x, float *l) __attribute__((always_inline)) {
+    f32x2 s_cur = {0.f, 0.f}, s_next = {0.f, 0.f}; // of query lr: what its exponents subtract, 1 / sum of its weights
+    auto request = [&](int tile, raw16 *x, f32x2 *s) __attribute__((always_inline)) {
         const int qq = 16 * tile + lr < n_queries ? 16 * tile + lr : n_queries - 1, tok = qq / a.G; // (past the last: masked)
         const int64_t row = (int64_t)tok * a.Hq + (qq - tok * a.G);
-        *l = lse[base + row];
+        *s = *reinterpret_cast<const f32x2 *>(a.part + (base + row) * a.pair_stride);
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) x[kk] = load16(q + row * D + 4 * kk * E);
     };
     float sum = 0.f;
-    if (t < t_end) request(t, qx, &l_cur);
+    if (t < t_end) request(t, qx, &s_cur);
     for (; t < t_end; ++t) {
-        if (t + 1 < t_end) request(t + 1, qn, &l_next);
+        if (t + 1 < t_end) request(t + 1, qn, &s_next);
         f32x4 sc;
         if constexpr (kBf16) {
             sc = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -579,15 +593,23 @@ __global__ __launch_bounds__(kThreads) void prefill_colsum_kernel(AttendArgs a, 
                 for (int i = 0; i < n / 2; ++i) part[i] = part[2 * i] + part[2 * i + 1];
             sc = part[0];
         }
+        // reference and normaliser apart, as the attention had them: their log2 in one number would be rounded at its size
         float w[4];
+        if (__builtin_amdgcn_ballot_w64(fabsf(s_cur[0]) > kLargeRef) != 0) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) w[r] = weight_of_any(sc[r], scale, __shfl(s_cur[0], 4 * lg + r));
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) w[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], scale, -__shfl(s_cur[0], 4 * lg + r)));
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int qq = 16 * t + 4 * lg + r;
-            const float x = fmaf(sc[r], scale, -__shfl(l_cur, 4 * lg + r));
-            w[r] = qq >= q_min && qq < n_queries ? __builtin_amdgcn_exp2f(x) : 0.f;
+            const float x = w[r] * __shfl(s_cur[1], 4 * lg + r);
+            w[r] = qq >= q_min && qq < n_queries ? x : 0.f;
         }
         sum += (w[0] + w[1]) + (w[2] + w[3]);
-        l_cur = l_next;
+        s_cur = s_next;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) qx[kk] = qn[kk];
     }
@@ -1334,18 +1356,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
 }
 
 struct PrefillOut { // all null for the plain attention call
-    float *lse, *colpart, *signal;
+    float *lse, *colpart, *signal; // (lse: matrix-core prefill)
 };
 
 template <typename T, int D>
 hipError_t launch_typed(const AttendArgs &a, int B, void *out, const PrefillOut &po, hipStream_t st) {
     const dim3 grid(a.n_split, a.Hkv * ((a.n_q * a.G + kAttQ - 1) / kAttQ), B);
-    hipLaunchKernelGGL((attend_kernel<T, D>), grid, dim3(64 * kAttWaves), 0, st, a, static_cast<T *>(out), po.lse);
+    hipLaunchKernelGGL((attend_kernel<T, D>), grid, dim3(64 * kAttWaves), 0, st, a, static_cast<T *>(out));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.n_split > 1)
         hipLaunchKernelGGL((attend_combine_kernel<T, D>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D < 64 ? 64 : D), 0, st,
-                           a.part, a.n_split, static_cast<T *>(out), po.lse);
+                           a.part, a.n_split, static_cast<T *>(out), static_cast<float *>(nullptr), a.pair_stride != 0);
     if constexpr (sizeof(T) == 2 && D >= 64) return hipGetLastError(); // their prefill is the matrix-core one
     if ((e = hipGetLastError()) != hipSuccess || !po.signal) return e;
     // Shares of the queries, no more rows than the workspace has room for.  Under the causal mask the shares are uneven, so
@@ -1361,7 +1383,7 @@ hipError_t launch_typed(const AttendArgs &a, int B, void *out, const PrefillOut 
     const int tiles_per = (n_tiles + n_qs - 1) / n_qs;
     n_qs = (n_tiles + tiles_per - 1) / tiles_per;
     if constexpr (sizeof(T) == 4 || D < 64)
-        hipLaunchKernelGGL((prefill_colsum_kernel<T, D>), dim3(n_kt * n_qs, a.Hkv, B), dim3(kThreads), 0, st, a, po.lse, po.colpart, n_qs,
+        hipLaunchKernelGGL((prefill_colsum_kernel<T, D>), dim3(n_kt * n_qs, a.Hkv, B), dim3(kThreads), 0, st, a, po.colpart, n_qs,
                            tiles_per);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(prefill_signal_kernel, dim3((a.n_q + kSigCols - 1) / kSigCols, B), dim3(kThreads), 0, st, po.colpart,
@@ -1428,7 +1450,7 @@ hipError_t launch_flash(const AttendArgs &a, int n_fs, int B, void *out, const P
         hipLaunchKernelGGL((prefill_flash_kernel<D, true, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, a.part, n_fs);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL((attend_combine_kernel<uint16_t, D>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D), 0, st, a.part,
-                           n_fs, o16, po.lse);
+                           n_fs, o16, po.lse, false);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     int n_units;
@@ -1542,11 +1564,13 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
         const int most = record_splits(B, a.Hkv, a.n_qtiles, a.k_frame);
         if (a.n_split > most) a.n_split = most;
     }
+    a.pair_stride = 0;
     PrefillOut po{nullptr, nullptr, nullptr};
     const int n_fs = workspace && flash_shape(c) ? flash_split(c, n_q, B, k_frame) : 0;
     if (workspace) {
         const int64_t rows = (int64_t)B * n_q * a.Hq;
         a.part = workspace;
+        if (n_fs == 0) a.pair_stride = a.n_split > 1 ? a.n_split * (c.cfg.head_dim + 2) : 2; // (one record a query is counted, not written)
         po.lse = workspace + rows * (n_fs == 0 ? a.n_split : n_fs == 1 ? 0 : n_fs) * (c.cfg.head_dim + 2);
         po.colpart = po.lse + rows;
         po.signal = signal;

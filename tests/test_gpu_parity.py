@@ -1199,6 +1199,35 @@ def test_scores_of_any_finite_size(dtype, D):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 16), ("f32", 64), ("f32", 128), ("bf16", 16), ("bf16", 32)])
+@pytest.mark.parametrize("past", [0, 3])     # frames of 128 rows: rows unsplit, and (fp32) split over workgroups
+def test_received_attention_of_scores_of_any_size(dtype, D, past):
+    # without a mask the tokens' shares of a query's weights add up to one whatever the size of the scores (a past of scores of
+    # zero has no weight beside them)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    H, n = 3, 70
+    ctx = mk.MuKV(n_layers=1, n_q_heads=H, n_kv_heads=H, head_dim=D, tokens_per_frame=128, frames_per_segment=8, alpha=0.0,
+                  superpatches_per_frame=4, dtype=t, keep_ratio=1.0, max_frames=4, max_chunk_frames=4, max_questions=1)
+    g = torch.Generator().manual_seed(464)
+    if past:
+        zero = torch.zeros(1, H, past * 128, D, dtype=t).cuda()
+        ctx.compress_chunk(zero, zero)
+    idx = torch.arange(past, dtype=torch.int32)[None].cuda() if past else None
+    q0, k0 = torch.randn(1, n, H, D, generator=g), torch.randn(n, H, D, generator=g)
+    k0[..., 0], q0[..., 0] = 4.0, 4.0 * D ** 0.5     # the first feature brings every score 16, the others 1 or so
+    v, offs = torch.randn(n, H, D, generator=g).to(t).cuda(), torch.tensor([0, n], dtype=torch.int32).cuda()
+    for size in (1e2, 1e4, 1e6, 3e7, 1e12, 1e30):
+        q, k = (q0 * size ** 0.5).to(t).cuda(), (k0 * size ** 0.5).to(t).cuda()
+        out, sig = ctx.prefill_attend(0, q, idx, k, v, offs, False)
+        assert torch.isfinite(out).all()
+        # a weight: the exponential within two ulps, its product with 1 / normaliser, sums of 70 and of 210 in fp32
+        assert abs(float(sig.double().sum()) - 1.0) <= 1e-6, (size, float(sig.double().sum()))
+        one = torch.tensor([0, 1], dtype=torch.int32).cuda()
+        _, sig = ctx.prefill_attend(0, q[:, :1].contiguous(), idx, k[:1], v[:1], one, True)
+        assert abs(float(sig) - 1.0) <= 5e-7, (size, float(sig))
+    ctx.close()
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 16), ("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 16)])
 def test_scores_finite_once_scaled(dtype, D):
     # q.k is past fp32 (5.4e38 .. 2e39), q.k log2(e) / sqrt(D) is not (2e38): one row, ten times the others, takes all the weight

@@ -387,11 +387,11 @@ struct SelList {
     const int32_t *cnt;     // kept tokens per super-patch (an empty one is never chosen), or null
     const unsigned *seg_ok; // bit per segment of F entries whose entries may be chosen, or null
     int F;
-    __device__ __forceinline__ uint64_t key(int i) const { return key(i, s[i]); }
-    __device__ __forceinline__ uint64_t key(int i, double score) const {
+    __device__ __forceinline__ uint64_t key(int i) const { return key(i, s[i], cnt ? cnt[i] : 1); }
+    __device__ __forceinline__ uint64_t key(int i, double score, int kept) const {
         uint64_t k = desc_key(score);
         k -= k == kNoKey; // (a NaN can be)
-        if (cnt && cnt[i] == 0) k = kNoKey;
+        if (kept == 0) k = kNoKey;
         if (seg_ok) {
             const int g = i / F;
             if (!((seg_ok[g >> 5] >> (g & 31)) & 1u)) k = kNoKey;
@@ -632,11 +632,34 @@ __global__ __launch_bounds__(kSelThreads) void select_rerank_kernel(RerankArgs a
         for (int u = 0; u < kRegKeys; ++u) kk[u] = kNoKey;
 #pragma unroll 1
         for (int i0 = 0; i0 < n; i0 += kRegKeys * kSelThreads) {
+            // (a batch's loads together, before any is used: behind a branch each they would be waited for one by one)
+            double sv[kRegKeys];
+            int cv[kRegKeys];
+            const bool one = n - i0 <= kSelThreads; // the same in all threads
+#pragma unroll
+            for (int u = 0; u < kRegKeys; ++u) {
+                sv[u] = s_first[u];
+                cv[u] = 1;
+            }
+            if (phase != 1 || i0 > 0) {
+                if (one)
+                    sv[0] = list.s[i0 + tid < n ? i0 + tid : n - 1]; // clamped: loads stay unconditional
+                else
+#pragma unroll
+                    for (int u = 0; u < kRegKeys; ++u) sv[u] = list.s[i0 + tid + u * kSelThreads < n ? i0 + tid + u * kSelThreads : n - 1];
+            }
+            if (list.cnt) {
+                if (one)
+                    cv[0] = list.cnt[i0 + tid < n ? i0 + tid : n - 1];
+                else
+#pragma unroll
+                    for (int u = 0; u < kRegKeys; ++u) cv[u] = list.cnt[i0 + tid + u * kSelThreads < n ? i0 + tid + u * kSelThreads : n - 1];
+            }
 #pragma unroll
             for (int u = 0; u < kRegKeys; ++u) {
                 if (i0 + u * kSelThreads >= n) break; // the same in all threads
-                const int i = i0 + tid + u * kSelThreads, ic = i < n ? i : n - 1; // clamped: loads stay unconditional
-                const uint64_t x = list.key(ic, phase == 1 && i0 == 0 ? s_first[u] : list.s[ic]);
+                const int i = i0 + tid + u * kSelThreads;
+                const uint64_t x = list.key(i < n ? i : n - 1, sv[u], cv[u]);
                 kk[u] = i < n ? x : kNoKey;
             }
 #pragma unroll

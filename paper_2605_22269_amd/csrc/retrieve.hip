@@ -528,12 +528,8 @@ struct RerankArgs {
     const int32_t *nv_q; // per-question timestamps (visible frames), or null: nv / ns / tail_cut above hold for all
     int n_all, kpf, Ff;  // ingested frames, fine keys per frame, frames per segment (used with nv_q)
     int cache_cap; // entries of the LDS key cache (dynamic shared memory)
-    // one store's units as the blocks (several stores searched together): 0 = off; 1 = the coarsest
-    // store: top k_frame units by their stage-1 scores, and their first n_global keys' mean to g_out;
-    // 2 = a finer store: stage 1, then Eq. 8 with the global query g_in, final top k_frame
-    int units;
-    const double *g_in; // [B][C]
-    double *g_out;      // [B][C] or null
+    const double *g_in; // [B][C], units of a finer store
+    double *g_out;      // [B][C] or null, units of the coarsest one
     double lambda;
     int32_t *seg_idx, *frm_idx;
     float *seg_score, *frm_score;
@@ -545,8 +541,12 @@ constexpr int kMaxSegBitmapWords = 2048; // HIER mode: segments 0..65535
 // Eq. 8, the candidates (2), by one copy of the selection in a loop over the phases.  What bounds it is one workgroup's chain
 // of waits and, between them, the instructions themselves (two waves a SIMD: 8 cycles each): so the loads of a phase are
 // requested in the phase before, ranks are counted on the upper halves of the keys, and what a short list does not have is
-// passed over.  One question over 113 segments and 3600 frames 22.7 -> 20.0 us (choosing from the frames 7, Eq. 8 3, the
-// other two lists 2-3 each), 64 of them in one call 25-47 -> 24.
+// passed over; the stores' forms are kernels of their own, so that a coarsest store's one short list carries no other phase's
+// code and registers.  us, a selection inlined for every list / one loop in one kernel for all forms / now: one question over
+// 113 segments and 3600 frames 22.3 / 20.0 / 19.2 (choosing from the frames 7, Eq. 8 3, the other two lists 2-3 each), 64 of
+// them in one call 23.9 / 22.7 / 22.3, over 40 frames 14.9 / 15.6 / 15.1, 14400 super-patches 35.8 / 40.2 / 29.6; a coarsest store
+// of 18 units 6.5 / 8.9 / 6.5, of 900 9.2 / 10.8 / 8.4; a finer one of 900 16.8 / 14.6 / 13.1; 3600 equal frames (the radix
+// route) 58.5 / 63.5 / 62.3, 512 frames asked for (the same) 396 / 432 / 425.
 //
 // The m best of n entries (smallest key; equal keys: lowest entry number, in phase 2 lowest frame), in rank order:
 //  * n <= kDirectN: every entry counts the entries ahead of it (rank by counting);
@@ -561,6 +561,10 @@ constexpr int kMaxSegBitmapWords = 2048; // HIER mode: segments 0..65535
 //    rank-by-counting sort of the survivors.
 // A thread holds the keys of kRegKeys entries in registers; of longer lists the first `cap` keys wait in the LDS array kcache,
 // and entries past `cap` are worked out again on every pass.
+// kUnits: one store's units as the blocks (several stores searched together), 0 = off; 1 = the coarsest store: top k_frame
+// units by their stage-1 scores, and their first n_global keys' mean to g_out; 2 = a finer store: stage 1, then Eq. 8 with the
+// global query g_in, final top k_frame.
+template <int kUnits>
 __global__ __launch_bounds__(kSelThreads) void select_rerank_kernel(RerankArgs a) {
     __shared__ SelShared sh;
     __shared__ int cand_seg[kMaxCand];
@@ -586,8 +590,8 @@ __global__ __launch_bounds__(kSelThreads) void select_rerank_kernel(RerankArgs a
     }
     const double *s_frm = a.s_frm + (int64_t)b * a.ld_frm;
     const double *s_seg = a.s_seg + (int64_t)b * a.ld_seg;
-    const bool semi = a.units == 2 || (a.units == 0 && a.mode == MUKV_SEMI); // the candidates are reranked
-    const bool hier = a.units == 0 && a.mode == MUKV_HIER;
+    const bool semi = kUnits == 2 || (kUnits == 0 && a.mode == MUKV_SEMI); // the candidates are reranked
+    const bool hier = kUnits == 0 && a.mode == MUKV_HIER;
     constexpr int kGlobChan = 1024 / kSelThreads, kGlobKeys = 8; // channels per thread, keys requested at a time
     float x_glob[kGlobChan][kGlobKeys];
 #pragma unroll
@@ -603,7 +607,7 @@ __global__ __launch_bounds__(kSelThreads) void select_rerank_kernel(RerankArgs a
 #pragma unroll
             for (int u = 0; u < kGlobKeys; ++u) {
                 const int i = list[r0 + u < n_glob ? r0 + u : n_glob - 1];
-                const float *rep = a.units ? a.rep_frame + (int64_t)i * a.C
+                const float *rep = kUnits ? a.rep_frame + (int64_t)i * a.C
                                            : (tail_cut && i == ns - 1) ? seg_tail : a.rep_seg + (int64_t)i * a.C;
                 x_glob[j][u] = rep[cc];
             }
@@ -615,8 +619,8 @@ __global__ __launch_bounds__(kSelThreads) void select_rerank_kernel(RerankArgs a
     for (int u = 0; u < kRegKeys; ++u) s_first[u] = u * kSelThreads < nv ? s_frm[tid + u * kSelThreads < nv ? tid + u * kSelThreads : nv - 1] : 0.0;
     int m_s = 0, m_f = 0;
 #pragma unroll 1
-    for (int phase = a.units ? 1 : 0; phase < 3; ++phase) {
-        SelList list{phase == 0 ? s_seg : phase == 1 ? s_frm : st, phase == 1 ? a.cnt : nullptr, phase == 1 && hier ? seg_ok : nullptr, a.F};
+    for (int phase = kUnits ? 1 : 0; phase < (kUnits == 1 ? 2 : 3); ++phase) {
+        SelList list{phase == 0 ? s_seg : phase == 1 ? s_frm : st, kUnits == 0 && phase == 1 ? a.cnt : nullptr, phase == 1 && hier ? seg_ok : nullptr, a.F};
         const int n = phase == 0 ? ns : phase == 1 ? nv : m_f;
         const int m = phase == 0 ? (semi ? 2 * a.k_seg : a.k_seg) : phase == 1 ? (semi ? 2 * a.k_frame : a.k_frame) : a.k_frame;
         int *const out = phase == 0 ? cand_seg : phase == 1 ? cand_frm : order;
@@ -830,7 +834,7 @@ __global__ __launch_bounds__(kSelThreads) void select_rerank_kernel(RerankArgs a
                 a.frm_idx[(int64_t)b * a.k_frame + r] = r < m_eff ? (phase == 2 ? cand_frm[i] : i) : -1;
                 if (a.frm_score) a.frm_score[(int64_t)b * a.k_frame + r] = r < m_eff ? (float)(phase == 2 ? st[i] : s_frm[i]) : 0.f;
             }
-            if (a.units != 1 || !a.g_out) break;
+            if (kUnits != 1 || !a.g_out) break;
             n_glob = min(a.n_global > 0 ? a.n_global : a.k_frame, m_eff); // for the finer stores
         }
         // the candidates' keys of Eq. 8 (16-byte pieces, lane r of a row takes pieces r, r + 16, ...): the first are on their
@@ -862,25 +866,25 @@ __global__ __launch_bounds__(kSelThreads) void select_rerank_kernel(RerankArgs a
             request(0);
         }
         // the global query: the mean of its keys, in list order, or handed over (it comes from a coarser store)
-        if (a.units == 2) {
+        if (kUnits == 2) {
             for (int c = tid; c < a.C; c += kSelThreads) gvec[c] = a.g_in[(int64_t)b * a.C + c];
         } else {
             double sum[kGlobChan] = {};
 #pragma unroll 1
             for (int r0 = 0; r0 < n_glob; r0 += kGlobKeys) {
-                if (r0 > 0 || a.units) load_glob(a.units ? cand_frm : cand_seg, r0);
+                if (r0 > 0 || kUnits) load_glob(kUnits ? cand_frm : cand_seg, r0);
 #pragma unroll
                 for (int j = 0; j < kGlobChan; ++j)
 #pragma unroll
                     for (int u = 0; u < kGlobKeys; ++u)
                         if (r0 + u < n_glob) sum[j] += (double)x_glob[j][u];
             }
-            double *to = a.units ? a.g_out + (int64_t)b * a.C : gvec;
+            double *to = kUnits ? a.g_out + (int64_t)b * a.C : gvec;
 #pragma unroll
             for (int j = 0; j < kGlobChan; ++j)
                 if (tid + j * kSelThreads < a.C) to[tid + j * kSelThreads] = n_glob > 0 ? sum[j] / (double)n_glob : 0.0;
         }
-        if (a.units == 1) break;
+        if (kUnits == 1) break;
         m_f = m_eff;
         if (m_f > kDirectN) { // equal reranked scores resolve to the lowest frame: too many for the last selection to look it up
             for (int t = tid; t < m_f; t += kSelThreads) order[t] = cand_frm[t];
@@ -1595,7 +1599,6 @@ hipError_t launch_retrieve(Ctx &c, const RetrieveArgs &a, hipStream_t st) {
     r.kpf = kpf;
     r.Ff = F;
     r.tail_cut = tail_cut;
-    r.units = a.units;
     r.g_in = a.g_in;
     r.g_out = a.g_out;
     r.mode = a.units ? (int)MUKV_SEMI : a.p.mode;
@@ -1612,12 +1615,12 @@ hipError_t launch_retrieve(Ctx &c, const RetrieveArgs &a, hipStream_t st) {
     int n_max = nf > a.ns ? nf : a.ns;
     if (n_max < 2 * kMaxCand) n_max = 2 * kMaxCand;
     r.cache_cap = n_max < kMaxCache ? n_max : kMaxCache;
-    static bool lds_ok[kMaxDevices];
-    if ((e = allow_dynamic_lds(reinterpret_cast<const void *>(&select_rerank_kernel), (size_t)kMaxCache * 8, c.cfg.device_id,
-                               lds_ok)) != hipSuccess)
+    static bool lds_ok[3][kMaxDevices];
+    auto *kernel = a.units == 0 ? select_rerank_kernel<0> : a.units == 1 ? select_rerank_kernel<1> : select_rerank_kernel<2>;
+    if ((e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), (size_t)kMaxCache * 8, c.cfg.device_id, lds_ok[a.units])) != hipSuccess)
         return e;
     ProfScope ps(c, MUKV_K_RERANK, st);
-    hipLaunchKernelGGL(select_rerank_kernel, dim3(a.B), dim3(kSelThreads), (size_t)r.cache_cap * 8, st, r);
+    hipLaunchKernelGGL(kernel, dim3(a.B), dim3(kSelThreads), (size_t)r.cache_cap * 8, st, r);
     return hipGetLastError();
 }
 

@@ -402,7 +402,27 @@ struct SelList {
 
 // The route of the selection for lists that its pre-filter does not thin out (see select_rerank_kernel): an 8-bit radix select
 // of the m_eff-th key.  The keys of the first n_c entries are in cache[].
-__device__ __noinline__ int radix_topk(SelList list, int n, int n_c, int m_eff, int *out, SelShared &sh, const uint64_t *cache) {
+// (A call of its own keeps it out of the usual route's registers.  Its arguments arrive in vector registers and as generic pointers
+// unless told otherwise; left so, the route took a tenth longer.)
+template <typename T>
+__device__ __forceinline__ T *uniform(T *p) { // a pointer that is the same in all lanes
+    const uint64_t a = (uint64_t)(uintptr_t)p;
+    return (T *)(uintptr_t)((uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32 |
+                            (unsigned)__builtin_amdgcn_readfirstlane((int)a));
+}
+#define MUKV_LDS(type) __attribute__((address_space(3))) type
+__device__ __noinline__ int radix_topk(SelList list, int n, int n_c, int m_eff, MUKV_LDS(int) *out3, MUKV_LDS(SelShared) *sh3,
+                                       MUKV_LDS(const uint64_t) *cache3) {
+    n = __builtin_amdgcn_readfirstlane(n);
+    n_c = __builtin_amdgcn_readfirstlane(n_c);
+    m_eff = __builtin_amdgcn_readfirstlane(m_eff);
+    list.s = uniform(list.s);
+    list.cnt = uniform(list.cnt);
+    list.seg_ok = uniform(list.seg_ok);
+    list.F = __builtin_amdgcn_readfirstlane(list.F);
+    int *out = (int *)out3;
+    SelShared &sh = *(SelShared *)sh3;
+    const uint64_t *cache = (const uint64_t *)cache3;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto get = [&](int i) { return i < n_c ? cache[i] : list.key(i); };
     uint64_t prefix = 0;
@@ -809,7 +829,7 @@ __global__ __launch_bounds__(kSelThreads) void select_rerank_kernel(RerankArgs a
                     if (tid + u * kSelThreads < n_c) kcache[tid + u * kSelThreads] = kk[u];
             }
             __syncthreads();
-            radix_topk(list, n, n_c, m_eff, out, sh, kcache);
+            radix_topk(list, n, n_c, m_eff, (MUKV_LDS(int) *)out, (MUKV_LDS(SelShared) *)&sh, (MUKV_LDS(const uint64_t) *)kcache);
         }
         // ---- what the phase is for ----
         if (phase == 0) { // lambda = 0 for segments: stage-1 order stands

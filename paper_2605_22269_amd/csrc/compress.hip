@@ -1884,8 +1884,21 @@ static hipError_t launch_signals64(const Ctx &c, const ChunkArgs &a, bool need_a
     return hipGetLastError();
 }
 
-// Eq. 1 in fp32 by att_tile_kernel, with the feature-axis indicator's workgroups in front if wanted and both fit the chip at
-// once; *with_freq says whether they were taken along.
+// Waves a SIMD holds of a kernel, by its registers.
+static int waves_per_simd(const void *kernel) {
+    hipFuncAttributes f;
+    if (hipFuncGetAttributes(&f, kernel) != hipSuccess || f.numRegs < 1) return 1;
+    const int n = 512 / ((f.numRegs + 7) / 8 * 8);
+    return n < 1 ? 1 : n > 8 ? 8 : n;
+}
+
+// Eq. 1 in fp32 by att_tile_kernel, with the feature-axis indicator's workgroups in front if wanted and few enough; *with_freq
+// says whether they were taken along.  In a launch of their own they cost 2-5 us, in this one they run with its registers, two
+// waves a SIMD for more than 128 tokens.  So they come along while they are at most one and a half rounds of the places on the
+// chip.  us for both signals, one launch / two, by frames: 32 heads of 64, bf16, 196 tokens (14 frequency workgroups a frame,
+// 256 places) 1: 12.1 / 16.9, 8: 23.3 / 25.0, 16: 27.8 / 30.0, 24: 42.0 / 40.8, 64: 98.6 / 94.6; 49 tokens (13, 2048) 8: 11.0 /
+// 15.5, 128: 24.9 / 28.8; 4 heads of 64, fp32, 100 tokens (13, 768) 64: 18.2 / 18.3, 96: 20.2 / 21.4, 128: 23.6 / 21.8; 28 of
+// 128, fp32, 196 tokens (28, 256) 8: 39.3 / 41.4, 16: 73.5 / 74.5, 24: 84.8 / 82.9.
 template <typename T>
 static hipError_t launch_att_tile(const Ctx &c, const ChunkArgs &a, bool *with_freq, int *n_part, hipStream_t st) {
     AttTileArgs t;
@@ -1911,9 +1924,7 @@ static hipError_t launch_att_tile(const Ctx &c, const ChunkArgs &a, bool *with_f
     const size_t lds = (size_t)t.nt * 16 * D * sizeof(T) + (size_t)waves * 16 * t.nt * sizeof(float);
     const int64_t n_att = (int64_t)a.n_frames * t.Hq * t.nz, tokens = (int64_t)waves * (128 / D); // of a frequency workgroup and step
     const int bpf = (int)((t.P + tokens - 1) / tokens);
-    const int64_t fit = 16 / waves < (int64_t)(160 * 1024 / lds) ? 16 / waves : (int64_t)(160 * 1024 / lds); // workgroups per compute unit
-    *with_freq = *with_freq && n_att + (int64_t)a.n_frames * bpf <= 256 * fit;
-    const int n_freq = *with_freq ? a.n_frames * bpf : 0;
+    const int64_t by_lds = 160 * 1024 / lds;
     hipError_t e;
 #define MUKV_TILE(DD, NT)                                                                                                 \
     do {                                                                                                                  \
@@ -1921,6 +1932,11 @@ static hipError_t launch_att_tile(const Ctx &c, const ChunkArgs &a, bool *with_f
         e = allow_dynamic_lds(reinterpret_cast<const void *>(&att_tile_kernel<T, DD, NT>), 160 * 1024, c.cfg.device_id,   \
                               lds_ok);                                                                                    \
         if (e != hipSuccess) return e;                                                                                    \
+        static const int per_simd = waves_per_simd(reinterpret_cast<const void *>(&att_tile_kernel<T, DD, NT>));          \
+        const int64_t by_regs = 4 * per_simd / waves < 1 ? 1 : 4 * per_simd / waves;                                      \
+        const int64_t places = 256 * (by_regs < by_lds ? by_regs : by_lds);                                               \
+        *with_freq = *with_freq && (int64_t)a.n_frames * bpf <= places * 3 / 2;                                           \
+        const int n_freq = *with_freq ? a.n_frames * bpf : 0;                                                             \
         hipLaunchKernelGGL((att_tile_kernel<T, DD, NT>), dim3((unsigned)(n_att + n_freq)), dim3(64 * waves), lds, st, t,  \
                            n_freq, bpf, c.cfg.n_kv_heads, c.fft_sig[a.parity]);                                           \
     } while (0)

@@ -371,8 +371,12 @@ def test_attention_paths_bf16(path, causal):
 
 
 @pytest.mark.parametrize("name,frames,kw", [
-    ("tiny", 68, {}), ("tiny", 69, {}),                                     # generic kernels: one launch (1020 workgroups of 1024), two
-    ("7b", 63, {"n_layers": 1, "tokens_per_frame": 50}),                    # matrix-core attention of few frames, frequency beside it
+    # att_tile_kernel: frequency workgroups up to one and a half rounds of its places (13 a frame, 1536 places), and one frame more
+    ("tiny", 177, {}), ("tiny", 178, {}),
+    ("tiny", 27, {"tokens_per_frame": 196, "keep_ratio": 0.1}), ("tiny", 28, {"tokens_per_frame": 196, "keep_ratio": 0.1}),   # 14, 256
+    ("7b", 45, {"n_layers": 1, "tokens_per_frame": 50}),                    # matrix-core attention of few frames, frequency beside it
+    ("7b", 46, {"n_layers": 1, "tokens_per_frame": 50}),                    # more than 1280 (frame, head) pairs: two launches
+    ("7b", 63, {"n_layers": 1, "tokens_per_frame": 50}),
     ("7b", 64, {"n_layers": 1, "tokens_per_frame": 50}),                    # of many: the indicator on the way
     ("7b", 1, {"n_layers": 1, "tokens_per_frame": 13}),                     # one wave a workgroup
 ])

@@ -69,7 +69,7 @@ int validate_config(const mukv_config *cfg) {
     if (cfg->n_q_heads / cfg->n_kv_heads > 1024) return MUKV_ERR_UNSUPPORTED; // the question pooling holds 4 * G partial sums per feature in LDS
     const int esz = cfg->dtype == MUKV_BF16 ? 2 : 4;
     if (!large_unit &&
-        mukv::att_generic_lds_bytes(cfg->tokens_per_frame, cfg->head_dim, sizeof(double), sizeof(float)) > 160 * 1024)
+        mukv::att64_lds_bytes(cfg->tokens_per_frame, cfg->head_dim, sizeof(float)) > 160 * 1024)
         return MUKV_ERR_UNSUPPORTED;
     if ((cfg->head_dim * esz) % 16) return MUKV_ERR_UNSUPPORTED;
     if (((int64_t)cfg->max_frames + cfg->frames_per_segment - 1) / cfg->frames_per_segment > 65536)

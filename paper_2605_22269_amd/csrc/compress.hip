@@ -4,12 +4,12 @@
 // Kernel chain enqueued by launch_compress (all on the caller's stream; the first two share a launch where both are needed
 // and neither fills the chip, or where the matrix-core attention works out the indicator on the way):
 //   att_tile | att_mfma      Eq. 1   partial attention received per (frame, head group)
-//   freq_signal<float>                 Eq. 2-3 length-D DFT magnitudes of every key
-//   select_pool<float>                 Eq. 4 fusion, keep of the kappa best, Eq. 5 frame / super-patch keys
-//   att_generic<double>, freq_signal<double>, select_pool<double>
-//                                      the same three steps in fp64, only for frames whose
-//                                      fp32 selection margin is below the threshold
-//   compact                            copy of the kept rows of all layers; segment keys
+//   freq_signal<float>       Eq. 2-3 length-D DFT magnitudes of every key
+//   select_pool<float>       Eq. 4 fusion, keep of the kappa best, Eq. 5 frame / super-patch keys
+//   signals, select_pool<double>
+//                            the same in fp64 (both signals in one launch), only for frames whose
+//                            fp32 selection margin is below the threshold
+//   compact                  copy of the kept rows of all layers; segment keys
 #include <cstring>
 
 #include "att_mfma_dev.h"
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(256) void freq_token_finish_kernel(const R *__restr
 // queries, the row softmax uses wave reductions, and each lane accumulates the probabilities of
 // its keys.  Per-wave partial column sums are combined in a fixed order, so results are
 // run-to-run identical.
-// out: [frame][Hq * nz][P] (R) partial sums over this workgroup's query rows.
+// out: [frame][Hq * nz][P] partial sums over this workgroup's query rows.
 // ------------------------------------------------------------------------------------------
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -360,32 +360,18 @@ __device__ __forceinline__ void unpack_to_float<float>(u32x4 raw, float *dst) {
     for (int i = 0; i < 4; ++i) dst[i] = __uint_as_float(raw[i]);
 }
 
-__device__ __forceinline__ float exp_t(float x) { return expf(x); }
-__device__ __forceinline__ double exp_t(double x) { return exp(x); }
-
 constexpr int kGenQ = 16; // queries per round of a workgroup: 4 waves x 4
 
 // How it keeps a frame's keys in LDS.  It runs on a few listed frames beside the next batch's kernels, whose workgroups leave
 // less than half of a compute unit's LDS free: bf16 keys stay as they are (half the room; the expansion is a shift).
-template <typename T, typename R>
-struct KeyStage {
-    typedef float type;
-    static constexpr int pad = 4;
-};
-template <>
-struct KeyStage<uint16_t, double> {
-    typedef uint16_t type;
-    static constexpr int pad = 8;
-};
 __device__ __forceinline__ float4 key4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 __device__ __forceinline__ float4 key4(const uint16_t *p) {
     const uint2 raw = *reinterpret_cast<const uint2 *>(p);
     return make_float4(__uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xffff0000u), __uint_as_float(raw.y << 16),
                        __uint_as_float(raw.y & 0xffff0000u));
 }
-__device__ __forceinline__ void stage_keys(u32x4 raw, uint16_t *dst) { *reinterpret_cast<u32x4 *>(dst) = raw; }
 
-struct AttGenArgs {
+struct Att64Args {
     PtrTable q, k;
     FrameMap map;
     int64_t k_off, q_sh, q_st, k_sh, k_st;
@@ -395,20 +381,19 @@ struct AttGenArgs {
 };
 
 // Work of workgroup (bx, h, z).
-template <typename T, typename R>
-__device__ __forceinline__ void att_generic_body(const AttGenArgs &a, R *__restrict__ out, int bx, int h, int z, unsigned char *smem_raw) {
+template <typename T>
+__device__ __forceinline__ void att64_body(const Att64Args &a, double *__restrict__ out, int bx, int h, int z, unsigned char *smem_raw) {
     const int P = a.P, D = a.D, G = a.G, causal = a.causal, q_per_block = a.q_per_block;
     const int64_t k_off = a.k_off, q_sh = a.q_sh, q_st = a.q_st, k_sh = a.k_sh, k_st = a.k_st;
     const FrameMap &map = a.map;
-    // frames: every batch frame (gx = n_frames), or the entries of the re-scoring list
-    const int n_e = a.flag_list ? *a.flag_count : a.gx;
+    const int n_e = *a.flag_count;
     for (int e_idx = bx; e_idx < n_e; e_idx += a.gx) {
-    const int f = a.flag_list ? a.flag_list[e_idx] : e_idx;
-    typedef typename KeyStage<T, R>::type KT;
-    const int ldk = D + KeyStage<T, R>::pad; // 16-byte aligned rows; 4-word lane stride keeps 16 lanes on distinct banks
-    KT *Ks = reinterpret_cast<KT *>(smem_raw);          // [P][ldk]
-    float *qs = reinterpret_cast<float *>(smem_raw + att_generic_key_bytes(P, D, sizeof(KT))); // [kGenQ][D]
-    R *part = reinterpret_cast<R *>(qs + kGenQ * D);    // [4][P], 8-byte aligned
+    const int f = a.flag_list[e_idx];
+    constexpr int EPU = 16 / sizeof(T); // elements per 16-byte unit
+    const int ldk = D + EPU; // 16-byte aligned rows; 4-word lane stride keeps 16 lanes on distinct banks
+    T *Ks = reinterpret_cast<T *>(smem_raw);                                            // [P][ldk]
+    float *qs = reinterpret_cast<float *>(smem_raw + att64_key_bytes(P, D, sizeof(T))); // [kGenQ][D]
+    double *part = reinterpret_cast<double *>(qs + kGenQ * D);                          // [4][P], 8-byte aligned
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int slot = find_slot(map, f);
@@ -419,8 +404,7 @@ __device__ __forceinline__ void att_generic_body(const AttGenArgs &a, R *__restr
     const int i_hi = (i_lo + q_per_block < P) ? i_lo + q_per_block : P;
     const int n_keys = causal ? i_hi : P; // keys any query of this workgroup can see
     // stage keys: 16-byte units, eight loads in flight per thread
-    constexpr int EPU = 16 / sizeof(T);          // elements per unit
-    const int upr = D / EPU;                      // units per row (D*sizeof(T) is a multiple of 16)
+    const int upr = D / EPU;                            // units per row (D*sizeof(T) is a multiple of 16)
     const int n_ku = n_keys * upr;
     for (int u0 = tid; u0 < n_ku; u0 += 8 * 256) {
         u32x4 raw[8];
@@ -435,15 +419,12 @@ __device__ __forceinline__ void att_generic_body(const AttGenArgs &a, R *__restr
             const int u = u0 + b * 256;
             if (u < n_ku) {
                 const int j = u / upr, c = u - j * upr;
-                if constexpr (sizeof(KT) == sizeof(float))
-                    unpack_to_float<T>(raw[b], reinterpret_cast<float *>(Ks) + j * ldk + c * EPU);
-                else
-                    stage_keys(raw[b], Ks + j * ldk + c * EPU);
+                *reinterpret_cast<u32x4 *>(Ks + j * ldk + c * EPU) = raw[b];
             }
         }
     }
-    const R scale = (R)1 / sqrt_t((R)D);
-    R acc[4] = {0, 0, 0, 0};
+    const double scale = 1.0 / sqrt((double)D);
+    double acc[4] = {0, 0, 0, 0};
     for (int i0 = i_lo; i0 < i_hi; i0 += kGenQ) {
         __syncthreads();
         for (int u = tid; u < kGenQ * upr; u += 256) {
@@ -457,7 +438,7 @@ __device__ __forceinline__ void att_generic_body(const AttGenArgs &a, R *__restr
         if (iw >= i_hi) continue;
         const int i_last = iw + 3 < i_hi ? iw + 3 : i_hi - 1;
         const int nj_max = causal ? i_last + 1 : P;
-        R s[4][4];
+        double s[4][4];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -479,11 +460,11 @@ __device__ __forceinline__ void att_generic_body(const AttGenArgs &a, R *__restr
             for (int t = 0; t < 4; ++t)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    R a = s[u][t];
-                    a += (R)qv[u].x * (R)kv[t].x;
-                    a += (R)qv[u].y * (R)kv[t].y;
-                    a += (R)qv[u].z * (R)kv[t].z;
-                    a += (R)qv[u].w * (R)kv[t].w;
+                    double a = s[u][t];
+                    a += (double)qv[u].x * (double)kv[t].x;
+                    a += (double)qv[u].y * (double)kv[t].y;
+                    a += (double)qv[u].z * (double)kv[t].z;
+                    a += (double)qv[u].w * (double)kv[t].w;
                     s[u][t] = a;
                 }
         }
@@ -492,19 +473,19 @@ __device__ __forceinline__ void att_generic_body(const AttGenArgs &a, R *__restr
             const int i = iw + u;
             if (i >= i_hi) break;
             const int nj = causal ? i + 1 : P;
-            R m = -INFINITY;
+            double m = -INFINITY;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int j = lane + 64 * t;
-                s[u][t] = (j < nj) ? s[u][t] * scale : (R)-INFINITY;
+                s[u][t] = (j < nj) ? s[u][t] * scale : -(double)INFINITY;
                 m = s[u][t] > m ? s[u][t] : m;
             }
             m = wave_max(m);
-            R zsum = 0;
+            double zsum = 0;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int j = lane + 64 * t;
-                s[u][t] = (j < nj) ? exp_t(s[u][t] - m) : (R)0;
+                s[u][t] = (j < nj) ? exp(s[u][t] - m) : 0.0;
                 zsum += s[u][t];
             }
             zsum = wave_sum(zsum);
@@ -524,12 +505,6 @@ __device__ __forceinline__ void att_generic_body(const AttGenArgs &a, R *__restr
         out[((int64_t)f * n_part + h * a.nz + z) * P + j] = ((part[j] + part[P + j]) + part[2 * P + j]) + part[3 * P + j];
     __syncthreads();
     }
-}
-
-template <typename T, typename R>
-__global__ __launch_bounds__(256) void att_generic_kernel(AttGenArgs a, R *__restrict__ out) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    att_generic_body<T, R>(a, out, blockIdx.x, blockIdx.y, blockIdx.z, smem_raw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -698,17 +673,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
 
 // Eq. 1-3 in fp64 of the listed frames, mostly none, in one launch: the attention workgroups, then the frequency kernel's
 // (freq_gx, bpf) grid.
-template <typename T, typename R, int D>
-__global__ __launch_bounds__(256) void signals_kernel(AttGenArgs a, R *__restrict__ att_out, R *__restrict__ fft_out, int Hkv, int freq_gx,
-                                                      int bpf) {
+template <typename T, int D>
+__global__ __launch_bounds__(256) void signals_kernel(Att64Args a, double *__restrict__ att_out, double *__restrict__ fft_out, int Hkv,
+                                                      int freq_gx, int bpf) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int b = blockIdx.x, n_att = a.gx * a.Hq * a.nz;
     if (b < n_att) {
         const int hz = b / a.gx;
-        att_generic_body<T, R>(a, att_out, b - hz * a.gx, hz % a.Hq, hz / a.Hq, smem_raw);
+        att64_body<T>(a, att_out, b - hz * a.gx, hz % a.Hq, hz / a.Hq, smem_raw);
     } else {
         const int y = (b - n_att) / freq_gx;
-        freq_body<T, R, D>(a.k, a.map, a.k_off, a.k_sh, a.k_st, Hkv, a.P, a.flag_list, a.flag_count, fft_out, b - n_att - y * freq_gx, y,
+        freq_body<T, double, D>(a.k, a.map, a.k_off, a.k_sh, a.k_st, Hkv, a.P, a.flag_list, a.flag_count, fft_out, b - n_att - y * freq_gx, y,
                            freq_gx, bpf);
     }
 }
@@ -1820,13 +1795,13 @@ static hipError_t launch_freq(const Ctx &c, const ChunkArgs &a, bool listed, R *
     return hipGetLastError();
 }
 
-size_t att_generic_lds_bytes(int P, int D, size_t r_size, size_t key_size) {
-    return att_generic_key_bytes(P, D, key_size) + (size_t)kGenQ * D * 4 + (size_t)4 * P * r_size;
+size_t att64_lds_bytes(int P, int D, size_t key_size) {
+    return att64_key_bytes(P, D, key_size) + (size_t)kGenQ * D * 4 + (size_t)4 * P * sizeof(double);
 }
 
-template <typename T, typename R>
-static AttGenArgs att_generic_args(const Ctx &c, const ChunkArgs &a, bool listed, int *n_part, size_t *lds) {
-    AttGenArgs g;
+template <typename T>
+static Att64Args att64_args(const Ctx &c, const ChunkArgs &a, int *n_part, size_t *lds) {
+    Att64Args g;
     g.q = a.q;
     g.k = a.k;
     g.map = a.map;
@@ -1841,12 +1816,12 @@ static AttGenArgs att_generic_args(const Ctx &c, const ChunkArgs &a, bool listed
     g.Hq = c.cfg.n_q_heads;
     g.causal = c.cfg.causal;
     g.q_per_block = 2 * kGenQ; // two rounds per workgroup
-    g.flag_list = listed ? c.flag_list[a.parity] : nullptr;
-    g.flag_count = listed ? c.flag_count + a.parity : nullptr;
-    g.gx = listed ? kRescoreSlotsAtt : a.n_frames;
+    g.flag_list = c.flag_list[a.parity];
+    g.flag_count = c.flag_count + a.parity;
+    g.gx = kRescoreSlotsAtt;
     g.nz = (g.P + g.q_per_block - 1) / g.q_per_block;
     *n_part = g.Hq * g.nz;
-    *lds = att_generic_lds_bytes(g.P, g.D, sizeof(R), sizeof(typename KeyStage<T, R>::type));
+    *lds = att64_lds_bytes(g.P, g.D, sizeof(T));
     return g;
 }
 
@@ -1861,16 +1836,16 @@ static hipError_t launch_signals64(const Ctx &c, const ChunkArgs &a, bool need_a
     if (!need_att) return hipSuccess;
     size_t lds;
     const int P = c.cfg.tokens_per_frame, D = c.cfg.head_dim;
-    const AttGenArgs g = att_generic_args<T, double>(c, a, true, n_part, &lds);
+    const Att64Args g = att64_args<T>(c, a, n_part, &lds);
     const int freq_gx = rescore_slots(P, a.n_frames), bpf = freq_blocks_per_frame(P);
     const unsigned total = (unsigned)(g.gx * g.Hq * g.nz + (together ? freq_gx * bpf : 0));
 #define MUKV_SIGNALS(DD)                                                                                                  \
     do {                                                                                                                  \
         static bool lds_ok[kMaxDevices];                                                                                  \
-        e = allow_dynamic_lds(reinterpret_cast<const void *>(&signals_kernel<T, double, DD>), 160 * 1024,                 \
-                              c.cfg.device_id, lds_ok);                                                                   \
+        e = allow_dynamic_lds(reinterpret_cast<const void *>(&signals_kernel<T, DD>), 160 * 1024, c.cfg.device_id,     \
+                              lds_ok);                                                                                    \
         if (e != hipSuccess) return e;                                                                                    \
-        hipLaunchKernelGGL((signals_kernel<T, double, DD>), dim3(total), dim3(256), lds, st, g, c.att64, c.fft64,         \
+        hipLaunchKernelGGL((signals_kernel<T, DD>), dim3(total), dim3(256), lds, st, g, c.att64, c.fft64,                 \
                            c.cfg.n_kv_heads, freq_gx, bpf);                                                               \
     } while (0)
     switch (D) {
@@ -2472,7 +2447,7 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
         return hipSuccess;
     }
     // both signals in one launch: the matrix-core attention with the frequency workgroups beside it (few frames) or with the
-    // indicator worked out on the way (many), or the generic kernels together
+    // indicator worked out on the way (many), or att_tile_kernel's workgroups behind them
     // (matrix-core attention, us a call of this chain in one / two launches: 8 frames of 28 heads 36.2 / 37.7, 32 64.6 /
     // 64.8, 60 93.8 / 89.9, 128 -- the indicator on the way -- 112.6 / 122.6; 20 frames of 64 heads 81.8 / 83.0, 27 97.3 / 97.6)
     const bool one_launch = !have_old && need_att && need_fft && c.cfg.freq_axis == MUKV_FREQ_FEATURE &&

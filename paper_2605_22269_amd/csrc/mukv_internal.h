@@ -247,11 +247,10 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
                          void *out, float *signal, float *workspace, hipStream_t st);
 int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame);
 
-// LDS bytes the generic attention kernel needs for P tokens of D features when it accumulates
-// in a type of r_size bytes and keeps the keys as elements of key_size bytes.
-size_t att_generic_lds_bytes(int P, int D, size_t r_size, size_t key_size);
+// LDS bytes the fp64 attention needs for P tokens of D features when the keys are elements of key_size bytes.
+size_t att64_lds_bytes(int P, int D, size_t key_size);
 // bytes of the staged keys: rows of D + 16 / key_size elements, rounded up to 8 bytes
-__host__ __device__ inline size_t att_generic_key_bytes(int P, int D, size_t key_size) {
+__host__ __device__ inline size_t att64_key_bytes(int P, int D, size_t key_size) {
     return ((size_t)P * (D + 16 / key_size) * key_size + 7) & ~(size_t)7;
 }
 

@@ -2394,15 +2394,14 @@ hipError_t join_streams(Ctx &c, hipStream_t st) {
 }
 
 // A copy too short to hide the fp64 chain behind it: the events that would put the chain on the side stream and bring it
-// back cost more than they save, on the host (four calls and one launch of twelve, and a small batch is bound by its
-// launches) and on the device (each crossing of queues 6-14 us).  Both sides (with the signals in launches of their own, four
-// launches more than now), 7B shape, us a call, everything on the caller's stream / the chain beside the copy: 8 frames, 21 MB, 46 / 70-82; 16, 42 MB, 58 / 81; 32, 84 MB, 74 / 94; 64,
-// 168 MB, 178 / 199; 128, 336 MB, 247 / 253, and with the signal handed over 143 / 127.  So with few frames listed the
-// sides meet at about 300 MB.  The line lies far below: the longer the chain -- it grows with the frames listed,
-// up to all of a batch -- the more a long copy beside it hides, and 32 MB (6-8 us) hide less than the crossings cost in
-// any case.
+// back cost more than they save, on the host (four calls and one launch of ten, and a small batch is bound by its launches)
+// and on the device (each crossing of queues 6-14 us).  Both sides, 7B shape, us a call among others, everything on the caller's
+// stream / the chain beside the copy, by frames (2.6 MB each): 8: 36 / 63, 16: 49 / 72, 32: 69 / 90, 64: 89 / 106, 96: 132 / 146,
+// 128: 156 / 168; with the signal handed over 8: 27 / 52, 32: 40 / 60, 64: 87 / 95, 96: 109 / 111, 112: 122 / 117, 128: 140 / 127;
+// every frame listed 8: 247 / 273, 64: 1736 / 1797, 128: 3499 / 3599, signal handed over 81 / 108, 459 / 488, 908 / 943.  So the line
+// lies where the sides meet first, 100 frames with the signal handed over.
 static bool copy_is_short(const Ctx &c, const ChunkArgs &a) {
-    return 4ll * a.n_frames * c.kappa * c.cfg.n_layers * c.c_kv * c.esz <= 32ll << 20;
+    return 4ll * a.n_frames * c.kappa * c.cfg.n_layers * c.c_kv * c.esz <= 256ll << 20;
 }
 
 // One batch.  Without overlap_copy, on the caller's stream: signals, keep, copy, with the fp64
@@ -2446,6 +2445,8 @@ static hipError_t compress_typed(Ctx &c, const ChunkArgs &a, hipStream_t st) {
         c.deferred_stream = st;
         return hipSuccess;
     }
+    // (with overlap_copy and few frames a batch the first two batches of a stream: from the third on a copy is due, which shares
+    // its launch with the frequency workgroups instead)
     // both signals in one launch: the matrix-core attention with the frequency workgroups beside it (few frames) or with the
     // indicator worked out on the way (many), or att_tile_kernel's workgroups behind them
     // (matrix-core attention, us a call of this chain in one / two launches: 8 frames of 28 heads 36.2 / 37.7, 32 64.6 /

@@ -1098,14 +1098,14 @@ def test_keep_of_a_frame_with_a_nan_key(name, kw, margin):
 
 
 def test_rescoring_beside_a_long_copy_and_before_a_short_one():
-    # 12 frames are 66 MB of rows in and out (fp64 chain on the side stream, its rows copied by itself), the 4 of the
-    # last chunk 22 MB (everything on the caller's stream, one copy); every frame re-scored
-    w = W["72b"].scaled(n_frames=16, n_layers=28, n_q_heads=8, tokens_per_frame=49, keep_ratio=0.5, n_questions=1)
-    assert w.n_kv_heads == 8 and w.head_dim == 128
-    p = Pair(w, seed=340, chunk=12, gpu_kw={"refine_margin": 10.0})
+    # 26 frames are 274 MB of rows in and out (fp64 chain on the side stream, its rows copied by itself), the 4 of the
+    # last chunk 42 MB (everything on the caller's stream, one copy); every frame re-scored
+    w = W["72b"].scaled(n_frames=30, n_layers=28, n_q_heads=8, tokens_per_frame=49, keep_ratio=0.95, n_questions=1)
+    assert w.n_kv_heads == 8 and w.head_dim == 128 and 4 * 26 * 46 * 28 * 8 * 128 * 2 > 256 * 2**20
+    p = Pair(w, seed=340, chunk=26, gpu_kw={"refine_margin": 10.0})
     p.ingest()
     st = p.check_compress()
-    assert int(st["refined"].sum()) == 16
+    assert int(st["refined"].sum()) == 30
     p.close()
 
 

@@ -1276,7 +1276,7 @@ def test_fp32_attention_stays_as_near_to_64_bits(D, hq, hkv, most):
     ("f32", 64, 14, 2, 16, 0, [5]),           # a wave's keys exactly
     ("f32", 32, 4, 4, 17, 1, [0, 0, 3]),      # one past it, one head per group: 17 queries
     ("f32", 16, 16, 1, 200, 2, [31]),         # one KV head: many shares
-    ("bf16", 32, 64, 8, 150, 2, [0] * 33),    # so many questions that the queries are not shared
+    ("bf16", 32, 64, 8, 150, 2, [0] * 43),    # so many questions (3 * 8 * 43 workgroups) that the queries are not shared
     ("bf16", 16, 14, 2, 63, 3, [1]),          # rows of two pieces
 ])
 def test_prefill_column_sums_edges(dtype, D, hq, hkv, n_q, n_frames, old):

@@ -16,10 +16,12 @@ extern "C" {
 
 /* Kernel families timed by the profiling hooks below. */
 typedef enum mukv_kernel_id {
-    MUKV_K_ATT = 0,     /* Eq. 1 attention signal                              */
-    MUKV_K_FREQ = 1,    /* Eq. 2-3 frequency signal                            */
+    MUKV_K_ATT = 0,     /* Eq. 1 attention signal; Eq. 2-3 with it wherever a batch
+                           without a copy that is due takes both signals in one launch */
+    MUKV_K_FREQ = 1,    /* Eq. 2-3 frequency signal in a launch of its own     */
     MUKV_K_SELECT = 2,  /* Eq. 4 fusion, keep, Eq. 5 frame / super-patch keys  */
-    MUKV_K_REFINE = 3,  /* fp64 re-scoring of near-tie frames (three kernels)  */
+    MUKV_K_REFINE = 3,  /* fp64 re-scoring of near-tie frames: both signals, the keep, and
+                           the copy of those rows where the main copy skips them  */
     MUKV_K_COMPACT = 4, /* copy of kept rows of all layers + segment keys      */
     MUKV_K_POOLQ = 5,   /* Eq. 6                                               */
     MUKV_K_SCORE = 6,   /* Eq. 7                                               */

@@ -141,7 +141,7 @@ __device__ __forceinline__ const unsigned char *row_at(const unsigned char *stor
 //            no transpose is needed.  Sums are joined pair by pair and the exponentials' arguments kept small (weight_of):
 //            one token, 28 heads of 128 over 30 / 81 / 832 rows, distance from 64 bits 1.17 / 1.35 / 1.59e-7; with a block's
 //            16 rows one after another and rounded differences 1.28 / 1.45 / 1.68e-7, on the vector ALU 1.21 / 1.36 / 1.66e-7
-//            (64 questions a call: 32.4 us, the former 29.2, the latter 64).
+//            (64 questions a call: 33 us, the former 29, the latter 60).
 // What bounds it: many questions, the rate at which the rows arrive (64 questions over 768 + 40 rows, 7B head layout, graph
 // replay: 16.4 us a call = 6.4 TB/s of rows, half of them read by several questions; a workgroup that took its rows through
 // tables and barriers shared by the waves, with a merge launch: 25.4); few, the chain launch -> frame list -> rows -> merge:
@@ -520,8 +520,9 @@ __global__ void attend_combine_kernel(float *part, int n_split, T *__restrict__ 
 // shapes of attend_kernel.  Grid (64 new tokens x share, KV head, question).  A wave keeps the keys of 16 tokens as the B
 // operand in registers and its share's queries stream past, 16 at a time and requested one tile ahead, so S = Q K^T leaves a
 // lane one key and four queries: no LDS, no barrier, and the sum over the queries is a running one until the end.  What bounds
-// it is the fp32 matrix rate with the queries' latency behind it.  (With eight queries in LDS and a thread per key on the vector
-// ALU, a layer call of fp32, 28 heads of 128 took: 32 tokens over 192 rows 28.6 us, now 19.7, 600 over 768 220, now 206; bf16
+// it is a tile's chain, query -> scores -> weights, with few waves to hide it, and uneven shares under the mask: 600 tokens over
+// 768 rows, fp32, 44 us at 30 TFLOP/s, the matrix pipes busy a quarter of the time.  (With eight queries in LDS and a thread per
+// key on the vector ALU, a layer call of fp32, 28 heads of 128 took: 32 tokens over 192 rows 28.6 us, now 19.7, 600 over 768 220, now 206; bf16
 // rows of 32 features, 400 tokens 46, now 20.)
 // colpart [B][Hkv][n_qs][n_q].
 template <typename T, int D>
@@ -1372,9 +1373,9 @@ hipError_t launch_typed(const AttendArgs &a, int B, void *out, const PrefillOut 
     if ((e = hipGetLastError()) != hipSuccess || !po.signal) return e;
     // Shares of the queries, no more rows than the workspace has room for.  Under the causal mask the shares are uneven, so
     // where a tile is long work (fp32 rows of 64 features and more) there are up to 16 workgroups per compute unit, otherwise
-    // four.  us a layer call with one / four / sixteen: fp32, 28 heads of 128, 196 tokens 40.5 / 39.8 / 38.3, 600 over 768 rows
-    // 234 / 197 / 185, 32 heads of 64, 600 tokens 96 / 79 / 73; rows of 16, 300 tokens 13.8 / 12.7 / 13.6; bf16 rows of 32,
-    // 400 tokens 21.9 / 19.0 / 19.9.
+    // four.  us a layer call with one / four / sixteen: fp32, 28 heads of 128, 196 tokens 42.5 / 41.8 / 41.2, 600 over 768 rows
+    // 260 / 208 / 207, 32 heads of 64, 600 tokens 106 / 87 / 80; rows of 16, 300 tokens 17.3 / 16.0 / 16.9; bf16 rows of 32,
+    // 400 tokens 25.4 / 20.1 / 20.6.
     constexpr int kWgs = sizeof(T) == 4 && D >= 64 ? 4096 : 1024;
     const int n_kt = (a.n_q + kColKeys - 1) / kColKeys, n_tiles = (a.n_q * a.G + 15) / 16;
     const int64_t wgs = (int64_t)n_kt * a.Hkv * B;

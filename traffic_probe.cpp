@@ -9,6 +9,8 @@
 // depend on the data, only on the access pattern, so the filler is a cheap LCG.
 //
 //   traffic_probe [n_frames=2048]
+//   traffic_probe f32      the fp32 kernels instead, 7B head layout, one layer: chunks of 8 frames, one token of 64 questions
+//                          over 32 frames and 40 rows of their own, a prefill of 600 tokens over 32 frames
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -37,7 +39,71 @@
         }                                                                          \
     } while (0)
 
+static int f32() {
+    const int Hq = 28, Hkv = 4, D = 128, P = 196, chunk = 8, n_chunks = 8, frames = chunk * n_chunks, B = 64, k_frame = 32, own = 40;
+    const int n_new = 600, calls = 10;
+    mukv_config cfg;
+    std::memset(&cfg, 0, sizeof cfg);
+    cfg.n_layers = 1;
+    cfg.n_q_heads = Hq;
+    cfg.n_kv_heads = Hkv;
+    cfg.head_dim = D;
+    cfg.tokens_per_frame = P;
+    cfg.frames_per_segment = 32;
+    cfg.superpatches_per_frame = 4;
+    cfg.dtype = MUKV_F32;
+    cfg.keep_ratio = 0.125;
+    cfg.alpha = 0.7;
+    cfg.causal = 1;
+    cfg.score_layer = -1;
+    cfg.max_frames = frames;
+    cfg.max_chunk_frames = chunk;
+    cfg.max_questions = B;
+    cfg.refine_margin = -1.0;
+    mukv_ctx *ctx = nullptr;
+    MK(mukv_create(&cfg, &ctx));
+    // one filler for every input, as long as the longest, a chunk's queries (5.6 M; the 600 tokens' are 2.2 M)
+    const size_t elems = (size_t)Hq * chunk * P * D;
+    std::vector<float> h(elems);
+    uint32_t lcg = 12345u;
+    for (size_t i = 0; i < elems; ++i) {
+        lcg = lcg * 1664525u + 1013904223u;
+        h[i] = (float)((int)(lcg >> 8) % 2001 - 1000) / 500.f;
+    }
+    std::vector<int32_t> idx(B * k_frame), own_at(B + 1), new_at = {0, n_new};
+    for (int i = 0; i < B * k_frame; ++i) idx[i] = (i / k_frame + 2 * (i % k_frame)) % frames;
+    for (int b = 0; b <= B; ++b) own_at[b] = b * own;
+    float *X, *out, *sig;
+    int32_t *idx_d, *own_d, *new_d;
+    void *ws;
+    int64_t ws_bytes = 0;
+    MK(mukv_prefill_workspace_size(ctx, n_new, k_frame, 1, &ws_bytes));
+    CK(hipMalloc(&X, elems * 4));
+    CK(hipMalloc(&out, (size_t)n_new * Hq * D * 4));
+    CK(hipMalloc(&sig, n_new * 4));
+    CK(hipMalloc(&ws, ws_bytes));
+    CK(hipMalloc(&idx_d, idx.size() * 4));
+    CK(hipMalloc(&own_d, own_at.size() * 4));
+    CK(hipMalloc(&new_d, new_at.size() * 4));
+    CK(hipMemcpy(X, h.data(), elems * 4, hipMemcpyHostToDevice));
+    CK(hipMemcpy(idx_d, idx.data(), idx.size() * 4, hipMemcpyHostToDevice));
+    CK(hipMemcpy(own_d, own_at.data(), own_at.size() * 4, hipMemcpyHostToDevice));
+    CK(hipMemcpy(new_d, new_at.data(), new_at.size() * 4, hipMemcpyHostToDevice));
+    hipStream_t st;
+    CK(hipStreamCreate(&st));
+    const mukv_strides ks = {(int64_t)Hkv * chunk * P * D, (int64_t)chunk * P * D, D}, qs = {0, (int64_t)chunk * P * D, D};
+    for (int c = 0; c < n_chunks; ++c) MK(mukv_compress_chunk(ctx, X, X, &ks, X, &qs, nullptr, chunk, st, nullptr));
+    for (int c = 0; c < calls; ++c) MK(mukv_attend(ctx, 0, X, 1, idx_d, k_frame, X, X, own_d, B, 1, out, st));
+    for (int c = 0; c < calls; ++c)
+        MK(mukv_prefill_attend(ctx, 0, X, n_new, idx_d, k_frame, X, X, new_d, 1, 1, out, sig, ws, ws_bytes, st));
+    CK(hipStreamSynchronize(st));
+    std::printf("traffic_probe f32: %d chunks, %d calls of the attention and of the prefill done\n", n_chunks, calls);
+    mukv_destroy(ctx);
+    return 0;
+}
+
 int main(int argc, char **argv) {
+    if (argc > 1 && std::strcmp(argv[1], "f32") == 0) return f32();
     const int L = 28, Hq = 28, Hkv = 4, D = 128, P = 196, chunk = 8, batch = 64;
     const int n_frames = argc > 1 ? std::atoi(argv[1]) : 2048;
     const int n_chunks = n_frames / chunk;

@@ -1498,8 +1498,9 @@ int attend_split(const Ctx &c, int n_q, int B, int k_frame) {
 static bool flash_shape(const Ctx &c) { return c.cfg.dtype == MUKV_BF16 && (c.cfg.head_dim == 64 || c.cfg.head_dim == 128); }
 
 // The workspace a caller provides, in bytes.  Part of the interface: callers keep buffers of this size, and
-// mukv_prefill_attend_static takes the calls for which it fits.  Split records, log-sum-exps, and column sums per
-// 64 queries (bf16 rows of 128 features) or 8 queries (all others); the matrix-core prefill stays within it.
+// mukv_prefill_attend_static takes the calls for which it fits.  Split records (at least one a query, whose start holds the
+// query's pair for prefill_colsum_kernel), log-sum-exps (counted for every shape, written by the matrix-core prefill), and
+// column sums per 64 queries (bf16 rows of 128 features) or 8 queries (all others); the matrix-core prefill stays within it.
 int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame) {
     const int64_t n_queries = (int64_t)n_q * c.group, combos = (int64_t)c.cfg.n_kv_heads * B, rows = (int64_t)B * n_q * c.cfg.n_q_heads;
     const int k = k_frame > 0 ? k_frame : 0;

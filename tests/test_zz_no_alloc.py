@@ -56,7 +56,7 @@ def _both_ways(p, layer, n_q, n_old, frame_idx, seed):
 @pytest.mark.parametrize("name,kw", [("7b", {"n_layers": 2}), ("tiny", {"n_layers": 2})])
 def test_static_scratch_prefill_twice_in_a_row(name, kw):
     # 7b: the matrix-core prefill (records of split tiles, log-sum-exps and column sums in the scratch);
-    # tiny: the fp32 path (split records, log-sum-exps, column sums of its own kernels)
+    # tiny: the fp32 path (split records, references and normalisers, column sums of its own kernels)
     w = W[name].scaled(n_frames=12, n_questions=2, **kw)
     p = Pair(w, seed=4400, chunk=4)
     p.ingest()

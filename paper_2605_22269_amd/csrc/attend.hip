@@ -79,6 +79,13 @@ __device__ __forceinline__ int row_swizzle(int row) {
     return ((row / (128 / D)) & (D / 16 - 1)) << 1;
 }
 
+// Shapes whose prefill is attend_kernel and prefill_colsum_kernel.  The others' kernels carry nothing of the pairs between the two
+// (one bf16 question of 28 heads of 128, a call: 9.43 us with a pair worked out and dropped, 9.33 without).
+template <typename T, int D>
+constexpr bool column_sums() {
+    return sizeof(T) == 4 || D < 64;
+}
+
 // attend_kernel and prefill_colsum_kernel, fp32 rows and bf16 rows of 16: the queries are brought down before the product by a
 // power of two, exactly, to where a score that is finite once scaled by log2(e) / sqrt(D) does not overflow before.
 template <typename T, int D>
@@ -331,7 +338,11 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
             for (int t = 0; t < kTiles; ++t)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) p[4 * t + r] = weight_of_any(sc[t][r], scale, ref);
+                for (int r = 0; r < 4; ++r)
+                    if constexpr (kBf16)
+                        p[4 * t + r] = __builtin_amdgcn_exp2f(fabsf(ref) > kLargeRef ? scaled_apart(sc[t][r], scale, ref) : fmaf(sc[t][r], scale, -ref));
+                    else
+                        p[4 * t + r] = weight_of_any(sc[t][r], scale, ref);
         } else {
 #pragma unroll
             for (int t = 0; t < kTiles; ++t)
@@ -467,7 +478,7 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
                 *reinterpret_cast<u32x2 *>(out + row * D + 4 * c) = u32x2{bf16_pair(o[0] / den, o[1] / den), bf16_pair(o[2] / den, o[3] / den)};
             else
                 *reinterpret_cast<f32x4 *>(out + row * D + 4 * c) = o / den;
-            if (a.pair_stride && c == 0)
+            if (column_sums<T, D>() && a.pair_stride && c == 0)
                 *reinterpret_cast<f32x2 *>(a.part + row * a.pair_stride) = l != 0.f ? f32x2{m, 1.f / l} : f32x2{0.f, 0.f};
         }
     }
@@ -477,11 +488,12 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
 // is a denominator of exactly zero (a NaN or +inf score makes it a NaN, and the output with it)
 // lse (may be null): log2 of the query's softmax denominator, in the scores' log2 units; +inf for a
 // query that sees no key, so that every weight computed from it is zero.
-// pairs: the query's pair takes the place of its first record's start (see AttendArgs).
-template <typename T, int D>
-__global__ void attend_combine_kernel(float *part, int n_split, T *__restrict__ out, float *__restrict__ lse, bool pairs) {
+// Part: const float *__restrict__, or float *: then the query's pair takes the place of its first record's start (see AttendArgs).
+template <typename T, int D, typename Part>
+__global__ void attend_combine_kernel(Part part, int n_split, T *__restrict__ out, float *__restrict__ lse) {
+    constexpr bool kPairs = std::is_same<Part, float *>::value;
     const int64_t row = blockIdx.x;
-    float *p = part + row * n_split * (D + 2);
+    Part p = part + row * n_split * (D + 2);
     f32x2 pair = {0.f, 0.f};
     for (int d = threadIdx.x; d < D; d += blockDim.x) {
         // every record's maximum, normaliser and this thread's element requested before any is used
@@ -509,11 +521,12 @@ __global__ void attend_combine_kernel(float *part, int n_split, T *__restrict__ 
         }
         store_out(out + row * D + d, zs != 0.f ? os / zs : 0.f);
         if (lse && d == 0) lse[row] = zs != 0.f ? m + __builtin_amdgcn_logf(zs) : INFINITY;
-        if (zs != 0.f) pair = f32x2{m, 1.f / zs};
+        if (kPairs && zs != 0.f) pair = f32x2{m, 1.f / zs};
     }
-    if (!pairs) return; // the same in all threads
-    __syncthreads();    // the record has been read
-    if (threadIdx.x == 0) *reinterpret_cast<f32x2 *>(p) = pair;
+    if constexpr (kPairs) {
+        __syncthreads(); // the record has been read
+        if (threadIdx.x == 0) *reinterpret_cast<f32x2 *>(p) = pair;
+    }
 }
 
 // Softmax weights on the new tokens (the last n_q local rows of the question), added over a share of the queries, for the
@@ -1366,10 +1379,16 @@ hipError_t launch_typed(const AttendArgs &a, int B, void *out, const PrefillOut 
     hipLaunchKernelGGL((attend_kernel<T, D>), grid, dim3(64 * kAttWaves), 0, st, a, static_cast<T *>(out));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (a.n_split > 1)
-        hipLaunchKernelGGL((attend_combine_kernel<T, D>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D < 64 ? 64 : D), 0, st,
-                           a.part, a.n_split, static_cast<T *>(out), static_cast<float *>(nullptr), a.pair_stride != 0);
-    if constexpr (sizeof(T) == 2 && D >= 64) return hipGetLastError(); // their prefill is the matrix-core one
+    if (a.n_split > 1) {
+        const dim3 rows((unsigned)(B * a.n_q * a.Hq)), threads(D < 64 ? 64 : D);
+        float *const no_lse = nullptr;
+        if (!a.pair_stride)
+            hipLaunchKernelGGL((attend_combine_kernel<T, D, const float *__restrict__>), rows, threads, 0, st, a.part, a.n_split,
+                               static_cast<T *>(out), no_lse);
+        else if constexpr (column_sums<T, D>())
+            hipLaunchKernelGGL((attend_combine_kernel<T, D, float *>), rows, threads, 0, st, a.part, a.n_split, static_cast<T *>(out), no_lse);
+    }
+    if constexpr (!column_sums<T, D>()) return hipGetLastError(); // their prefill is the matrix-core one
     if ((e = hipGetLastError()) != hipSuccess || !po.signal) return e;
     // Shares of the queries, no more rows than the workspace has room for.  Under the causal mask the shares are uneven, so
     // where a tile is long work (fp32 rows of 64 features and more) there are up to 16 workgroups per compute unit, otherwise
@@ -1383,7 +1402,7 @@ hipError_t launch_typed(const AttendArgs &a, int B, void *out, const PrefillOut 
     n_qs = n_qs < n_tiles ? n_qs : n_tiles;
     const int tiles_per = (n_tiles + n_qs - 1) / n_qs;
     n_qs = (n_tiles + tiles_per - 1) / tiles_per;
-    if constexpr (sizeof(T) == 4 || D < 64)
+    if constexpr (column_sums<T, D>())
         hipLaunchKernelGGL((prefill_colsum_kernel<T, D>), dim3(n_kt * n_qs, a.Hkv, B), dim3(kThreads), 0, st, a, po.colpart, n_qs,
                            tiles_per);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1450,8 +1469,8 @@ hipError_t launch_flash(const AttendArgs &a, int n_fs, int B, void *out, const P
     } else { // rows shared by n_fs workgroups per tile, merged
         hipLaunchKernelGGL((prefill_flash_kernel<D, true, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, a.part, n_fs);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL((attend_combine_kernel<uint16_t, D>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D), 0, st, a.part,
-                           n_fs, o16, po.lse, false);
+        hipLaunchKernelGGL((attend_combine_kernel<uint16_t, D, const float *__restrict__>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D), 0, st, a.part,
+                           n_fs, o16, po.lse);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     int n_units;

@@ -802,40 +802,48 @@ unsigned tile_grid(int n_tiles, int combos) {
 // 1024 of matrix work.  Measured, 7B head layout, 1568 new tokens over 768 rows: 60-64 us, its matrix pipes busy 36 % of
 // the time (64-query tiles of 16x16x32 products whose weights cross the waves through LDS: 186 us with the column sums,
 // which are 23 us in the kernel below); 4000 tokens 258-265 us for the whole call against 673.  344 tiles on 512
-// resident places is not even: the launch lasts as long as its heaviest tile.  Also built and slower: the next block's scores
-// interleaved instruction by instruction with this block's weights and values (66 us), eight waves that share 128-row
-// steps (59 us, but 346 against 300 for the long prefill), 64 queries per wave (85 us: the accumulators pass 256
+// resident places is not even: the launch lasts as long as its heaviest tile.
+// FOURS = 2: eight waves, of which four take the even steps and four the odd ones, with rows and tables of their own (160 KB of
+// LDS, one workgroup per compute unit), and join at the end: a tile's chain is half as long, which is what counts where there
+// are no more tiles than compute units (flash_split; 600 tokens over 768 rows 47.2 -> 38.9 us a call).  Also built and slower: the next block's scores
+// interleaved instruction by instruction with this block's weights and values (66 us), 64 queries per wave (85 us: the accumulators pass 256
 // registers and are moved in and out of the accumulation registers).
 // SPLIT: a short prefill has too few tiles to fill the chip, so its rows are shared by n_split workgroups per
 // tile; the split's (maximum, normaliser, unnormalised output) go to the records attend_combine_kernel merges
 // (aux = records).  Otherwise the output is final here, and so are the log-sum-exps: they go to aux for the key sums'
 // launch, or (SUMS, few new tokens) Eq. 1 is summed right here, over the tile's queries, and goes to aux
 // [B][Hkv][n_tiles][n_q].
-template <int D, bool SPLIT, bool SUMS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void prefill_flash_kernel(
+template <int D, int FOURS, bool SPLIT, bool SUMS>
+__global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D == 128 || FOURS == 2 ? 2 : 3, D == 128 || FOURS == 2 ? 2 : 3))) void prefill_flash_kernel(
     AttendArgs a, uint16_t *__restrict__ out, int n_tiles, int combos, float *__restrict__ aux, int n_split) {
     using T = uint16_t;
     constexpr int kRowB = D * 2, kPieces = kRowB / 16, kRowsPerLoad = 64 / kPieces; // rows one load of a wave brings
     constexpr int kLoads = kFK / 4 / kRowsPerLoad;                                   // such loads per wave and step
     constexpr int KK = D / 16, NF = D / 32; // 16-feature steps of the scores, 32-feature blocks of the output
     constexpr bool kPairs = D == 64;        // weights as bf16 pairs hi + lo
-    __shared__ __align__(1024) unsigned char s_k[2][kFK * kRowB];
-    __shared__ __align__(1024) unsigned char s_v[2][kFK * kRowB];
-    constexpr int kRing = 8;                      // steps whose row tables are held
-    __shared__ ulonglong2 s_addr[kRing][kFK];     // addresses of the row's key and value
-    __shared__ __align__(16) int s_ft[kRing][kFK]; // first token that sees the row
-    __shared__ int s_masked[kRing];               // some query of the tile may not see some row of the step
+    // every four waves have staged rows and tables of their own
+    __shared__ __align__(1024) unsigned char s_kk[FOURS][2][kFK * kRowB];
+    __shared__ __align__(1024) unsigned char s_vv[FOURS][2][kFK * kRowB];
+    constexpr int kRing = 8;                                    // steps whose row tables are held
+    __shared__ ulonglong2 s_addrs[FOURS][kRing][kFK];           // addresses of the row's key and value
+    __shared__ __align__(16) int s_fts[FOURS][kRing][kFK];      // first token that sees the row
+    __shared__ int s_maskeds[FOURS][kRing];                     // some query of the tile may not see some row of the step
     __shared__ int s_frame[kMaxGatherK]; // the question's frames; -1: names no frame of the cache
-    static_assert(!(SPLIT && SUMS), "the sums want final statistics");
+    static_assert(!(SPLIT && SUMS) && !(FOURS == 2 && (SPLIT || SUMS)), "the sums want final statistics, the two fours have no shares");
     __shared__ __align__(16) float s_lse[SUMS ? kFQ : 1];
     int tile_id, combo;
     if (!tile_of(blockIdx.x, SPLIT ? n_tiles * n_split : n_tiles, combos, &tile_id, &combo)) return;
     const int qt = SPLIT ? tile_id / n_split : tile_id, sp = SPLIT ? tile_id % n_split : 0;
     const int g = combo % a.Hkv, b = combo / a.Hkv;
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lq = lane & 31, half = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, half = lane >> 5;
+    const int four = FOURS == 2 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0, wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
+    auto &s_k = s_kk[four], &s_v = s_vv[four];
+    auto &s_addr = s_addrs[four];
+    auto &s_ft = s_fts[four];
+    auto &s_masked = s_maskeds[four];
     const int n_queries = a.n_q * a.G;
     const T *q = static_cast<const T *>(a.q);
-    for (int i = tid; i < a.k_frame; i += 256) {
+    for (int i = tid; i < a.k_frame; i += 256 * FOURS) {
         const int f = a.frame_idx[(int64_t)b * a.k_frame + i];
         s_frame[i] = (f >= 0 && f < a.n_frames) ? f : -1;
     }
@@ -890,7 +898,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
         pad_v = (first_frame < 0 ? lv : sv) + off;
     };
     auto tabulate = [&](int t) {
-        const int slot = t & (kRing - 1), r = t * kFK + lane;
+        const int slot = t & (kRing - 1), r = (FOURS * t + four) * kFK + lane;
         const unsigned char *rk = pad_k, *rv = pad_v;
         int ft = INT_MAX;
         if (r < n_ret) {
@@ -953,7 +961,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
         if (ns < n_ret) ns = n_ret;
         if (ns < total) n_seen = ns;
     }
-    const int n_steps_all = n_seen > 0 ? (n_seen + kFK - 1) / kFK : 0;
+    // (two fours: their steps in turn; an odd one out is joined by one whose rows nobody of the tile sees)
+    const int n_steps_all = n_seen > 0 ? (n_seen + FOURS * kFK - 1) / (FOURS * kFK) : 0;
     // this workgroup's steps: all of them, or its share of them
     const int per_split = SPLIT ? (n_steps_all + n_split - 1) / n_split : n_steps_all;
     const int t_lo = SPLIT ? sp * per_split : 0;
@@ -1093,22 +1102,65 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
         step(t, s_k[0], s_v[0], s_k[1], s_v[1]);
         if (t + 1 < n_steps) step(t + 1, s_k[1], s_v[1], s_k[0], s_v[0]);
     }
-    const float l_sum = half_sum(l_run);
+    float l_sum = half_sum(l_run);
+    // Two waves of the same queries join: each hands the other the blocks it does not finish itself (it finishes kMine of them from
+    // `from` on), four floats a lane at [piece][lane], where the staged rows were.
+    constexpr int kMine = NF / FOURS;
+    const int from = kMine * four;
+    f32x16 joined[FOURS == 2 ? kMine : 1];
+    f32x16 *const mine = FOURS == 2 ? joined : o;
+    if constexpr (FOURS == 2) {
+        __shared__ float s_stat[2][2][kFQ];
+        static_assert(kMine * 16 * 64 * sizeof(float) <= sizeof(s_kk[0]) / 4, "a wave's quarter of its four's keys");
+        f32x4 *const box = reinterpret_cast<f32x4 *>(s_kk[four]) + wave * (kMine * 4 * 64);
+        __syncthreads(); // every wave is done with the keys
+#pragma unroll
+        for (int f = 0; f < kMine; ++f)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                f32x4 x;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    x[r] = four == 0 ? o[kMine + f][4 * c + r] : o[f][4 * c + r];
+                    mine[f][4 * c + r] = four == 0 ? o[f][4 * c + r] : o[kMine + f][4 * c + r];
+                }
+                box[(4 * f + c) * 64 + lane] = x;
+            }
+        if (half == 0) {
+            s_stat[0][four][32 * wave + lq] = m_run;
+            s_stat[1][four][32 * wave + lq] = l_sum;
+        }
+        __syncthreads();
+        const f32x4 *const other = reinterpret_cast<const f32x4 *>(s_kk[1 - four]) + wave * (kMine * 4 * 64);
+        const float m2 = s_stat[0][1 - four][32 * wave + lq], l2 = s_stat[1][1 - four][32 * wave + lq];
+        const float m = fmaxf(m_run, m2); // (sums of nothing have the least maximum, and a factor of zero)
+        const float c1 = __builtin_amdgcn_exp2f(m_run - m), c2 = __builtin_amdgcn_exp2f(m2 - m);
+        l_sum = four == 0 ? fmaf(l2, c2, l_sum * c1) : fmaf(l_sum, c1, l2 * c2); // the same bits in both
+        m_run = m;
+#pragma unroll
+        for (int f = 0; f < kMine; ++f)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const f32x4 x = other[(4 * f + c) * 64 + lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mine[f][4 * c + r] = fmaf(x[r], c2, mine[f][4 * c + r] * c1);
+            }
+    }
     const bool seen = l_sum != 0.f; // a query that saw nothing leaves zeros, whatever its hidden rows held; NaN stays NaN
     // feature 32 f + 8 jj + 4 half + r of the query is in register 4 jj + r of block f
     if constexpr (SPLIT) { // the split's record: [0] maximum, [1] normaliser, [2..] unnormalised output
         if (!q_ok) return;
         float *rec = aux + (my_row * n_split + sp) * (D + 2);
-        if (half == 0) {
+        if (half == 0 && four == 0) {
             rec[0] = m_run;
             rec[1] = l_sum;
         }
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
+        for (int f = 0; f < kMine; ++f)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) rec[2 + 32 * f + 8 * jj + 4 * half + r] = seen ? o[f][4 * jj + r] : 0.f;
+                for (int r = 0; r < 4; ++r) rec[2 + 32 * (from + f) + 8 * jj + 4 * half + r] = seen ? mine[f][4 * jj + r] : 0.f;
     } else {
         // Eq. 1 of the tile: the wave's queries (now the A operand: S = Q K^T) against the new tokens' keys, 64 at a time.
         // New token j is local row n_loc - n_q + j; it may not exist.  The last two steps' keys are still in LDS, which are
@@ -1143,9 +1195,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
         {
             // a lane holds features 8 jj + 4 half .. + 3: the halves swap, so that it stores 16 bytes in a row (in 8-byte
             // stores twice as many lines are opened twice as often: 32 tokens without a past 9.9 us a call, now 8.8)
-            uint16_t *op = out + my_row * D + 8 * half;
+            uint16_t *op = out + my_row * D + 32 * from + 8 * half;
 #pragma unroll
-            for (int f = 0; f < NF; ++f)
+            for (int f = 0; f < kMine; ++f)
 #pragma unroll
                 for (int jj = 0; jj < 4; jj += 2) {
                     raw16 w;
@@ -1154,7 +1206,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
                         uint32_t pk[2];
 #pragma unroll
                         for (int u = 0; u < 2; ++u)
-                            pk[u] = bf16_pair(o[f][4 * (jj + u) + 2 * e] * inv, o[f][4 * (jj + u) + 2 * e + 1] * inv);
+                            pk[u] = bf16_pair(mine[f][4 * (jj + u) + 2 * e] * inv, mine[f][4 * (jj + u) + 2 * e + 1] * inv);
                         auto sw = __builtin_amdgcn_permlane32_swap(pk[0], pk[1], false, false);
                         w[e] = sw[0];
                         w[2 + e] = sw[1];
@@ -1162,11 +1214,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 
                     if (!seen) w = raw16{0u, 0u, 0u, 0u};
                     if (q_ok) *reinterpret_cast<raw16 *>(op + 32 * f + 8 * jj) = w;
                 }
-            if (!SUMS && q_ok && half == 0) aux[my_row] = lse;
+            if (!SUMS && q_ok && half == 0 && four == 0) aux[my_row] = lse;
         }
         if constexpr (SUMS) {
-            float(*s_col)[kFusedSums] = reinterpret_cast<float(*)[kFusedSums]>(s_v); // per wave, where the values were
-            static_assert(4 * kFusedSums * sizeof(float) <= sizeof(s_v), "a sum per wave and new token");
+            float(*s_col)[kFusedSums] = reinterpret_cast<float(*)[kFusedSums]>(s_vv); // per wave, where the values were
+            static_assert(4 * kFusedSums * sizeof(float) <= sizeof(s_vv), "a sum per wave and new token");
             const int qq0 = qt * kFQ + 32 * wave;
             if (half == 0) s_lse[32 * wave + lq] = lse; // read by this wave only
             __syncthreads();                            // every wave is done with the values
@@ -1450,24 +1502,26 @@ int keysum_rows(int n_q, int G, int combos) {
 }
 
 template <int D>
-hipError_t launch_flash(const AttendArgs &a, int n_fs, int B, void *out, const PrefillOut &po, hipStream_t st) {
+hipError_t launch_flash(const AttendArgs &a, int n_fs, bool two_fours, int B, void *out, const PrefillOut &po, hipStream_t st) {
     const int n_tiles = (int)(((int64_t)a.n_q * a.G + kFQ - 1) / kFQ), combos = a.Hkv * B;
     uint16_t *o16 = static_cast<uint16_t *>(out);
     const unsigned grid = tile_grid(n_tiles * n_fs, combos);
     hipError_t e;
     const float inv = 1.0f / ((float)a.Hq * (float)a.n_q);
     const dim3 sig_grid((a.n_q + kSigCols - 1) / kSigCols, B);
-    if (n_fs == 1 && a.n_q <= kFusedSums) { // two launches (see kFusedSums)
-        hipLaunchKernelGGL((prefill_flash_kernel<D, false, true>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.colpart, 1);
+    if (n_fs == 1 && !two_fours && a.n_q <= kFusedSums) { // two launches (see kFusedSums)
+        hipLaunchKernelGGL((prefill_flash_kernel<D, 1, false, true>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.colpart, 1);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(prefill_signal_kernel, sig_grid, dim3(kThreads), 0, st, po.colpart, a.Hkv, n_tiles, a.n_q, inv, po.signal,
                            a.G, a.causal, 0);
         return hipGetLastError();
     }
-    if (n_fs == 1) {
-        hipLaunchKernelGGL((prefill_flash_kernel<D, false, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.lse, 1);
+    if (two_fours) {
+        hipLaunchKernelGGL((prefill_flash_kernel<D, 2, false, false>), dim3(grid), dim3(512), 0, st, a, o16, n_tiles, combos, po.lse, 1);
+    } else if (n_fs == 1) {
+        hipLaunchKernelGGL((prefill_flash_kernel<D, 1, false, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.lse, 1);
     } else { // rows shared by n_fs workgroups per tile, merged
-        hipLaunchKernelGGL((prefill_flash_kernel<D, true, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, a.part, n_fs);
+        hipLaunchKernelGGL((prefill_flash_kernel<D, 1, true, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, a.part, n_fs);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL((attend_combine_kernel<uint16_t, D, const float *__restrict__>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D), 0, st, a.part,
                            n_fs, o16, po.lse);
@@ -1542,8 +1596,16 @@ int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame) {
 // the chip idle (two workgroups per compute unit are wanted, at least two steps each: 196 new tokens over 768 rows,
 // 44 tiles, 34-35 us a call in 7 shares), and no more than leave the records, log-sum-exps and column sums within the
 // workspace (200 tokens without a past would be shared by two and are not, 300 over 768 rows by eight and are by six).
-static int flash_split(const Ctx &c, int n_q, int B, int k_frame) {
+// Instead two fours of waves may take a tile's steps in turn and join in LDS: no records, no merge, one workgroup per compute unit
+// and half the chain, so for all tiles that fit at once (us a call, 7B head layout over 768 rows, shares / two fours: 196 tokens
+// 34.3 / 29.3, 300 39.5 / 32.4, 600 47.2 / 41.1, 1000 60.3 / 52.9; 1568, 344 tiles: 79.5 / 80.6; 64 and 8 heads of 128, 600 tokens,
+// 304 tiles: 58.6 / 61.5) unless few tiles walk many rows: a step is 0.95 us of the two fours' chain and 1.5 us of a share's, the
+// merge launch costs 4 us and a record's number written and read again 2 ps (64 tokens over 768 rows 26.1 against 23.4, 128:
+// 27.1 / 28.5; 17 tokens over 3136: 58 / 27).  Up to kFusedSums tokens over a step or two keep the kernel that sums Eq. 1 itself
+// (128 tokens over 96 rows 18.0 / 16.4).
+static int flash_split(const Ctx &c, int n_q, int B, int k_frame, bool *two_fours) {
     const int64_t wgs = (((int64_t)n_q * c.group + kFQ - 1) / kFQ) * c.cfg.n_kv_heads * B;
+    *two_fours = wgs <= 256;
     if (wgs >= 192) return 1;
     const int64_t steps = ((int64_t)(k_frame > 0 ? k_frame : 0) * c.kappa + n_q + kFK - 1) / kFK;
     int64_t n = (512 + wgs - 1) / wgs;
@@ -1552,7 +1614,13 @@ static int flash_split(const Ctx &c, int n_q, int B, int k_frame) {
     const int64_t rows = (int64_t)B * n_q * c.cfg.n_q_heads, combos = (int64_t)B * c.cfg.n_kv_heads;
     const int64_t rest = rows + combos * n_q * keysum_rows(n_q, c.group, (int)combos);
     while (n > 1 && (rows * n * (c.cfg.head_dim + 2) + rest) * (int64_t)sizeof(float) > prefill_workspace_bytes(c, n_q, B, k_frame)) --n;
-    return n < 1 ? 1 : (int)n;
+    if (n <= 1) {
+        *two_fours = n_q > kFusedSums;
+        return 1;
+    }
+    const float shared = 1.5f * (float)((steps + n - 1) / n) + 4.f + 2e-6f * (float)(rows * n * (c.cfg.head_dim + 2));
+    *two_fours = 0.95f * (float)steps <= shared;
+    return *two_fours ? 1 : (int)n;
 }
 
 // workspace == null: the plain attention call, records in the context's scratch, no signal.
@@ -1587,7 +1655,8 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
     }
     a.pair_stride = 0;
     PrefillOut po{nullptr, nullptr, nullptr};
-    const int n_fs = workspace && flash_shape(c) ? flash_split(c, n_q, B, k_frame) : 0;
+    bool two_fours = false;
+    const int n_fs = workspace && flash_shape(c) ? flash_split(c, n_q, B, k_frame, &two_fours) : 0;
     if (workspace) {
         const int64_t rows = (int64_t)B * n_q * a.Hq;
         a.part = workspace;
@@ -1597,7 +1666,7 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
         po.signal = signal;
     }
     if (n_fs) // the prefill on the matrix cores
-        return c.cfg.head_dim == 64 ? launch_flash<64>(a, n_fs, B, out, po, st) : launch_flash<128>(a, n_fs, B, out, po, st);
+        return c.cfg.head_dim == 64 ? launch_flash<64>(a, n_fs, two_fours, B, out, po, st) : launch_flash<128>(a, n_fs, two_fours, B, out, po, st);
     return c.cfg.dtype == MUKV_BF16 ? launch_by_dim<uint16_t>(a, c.cfg.head_dim, B, out, po, st)
                                     : launch_by_dim<float>(a, c.cfg.head_dim, B, out, po, st);
 }

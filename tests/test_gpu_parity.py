@@ -1177,6 +1177,24 @@ def test_prefill_matrix_tile_edges(D, hq, hkv, n_q, n_frames, old):
     p.close()
 
 
+@pytest.mark.parametrize("D,hq,hkv,n_q,n_frames,old", [
+    (128, 28, 4, 129, 0, [0]),          # three steps of rows between two: one without rows
+    (128, 28, 4, 256, 0, [0]),          # four: two each; the first tile sees one step, so one of the two sees nothing
+    (128, 16, 2, 147, 12, [0, 100]),    # tables filled twice, ragged rows
+    (128, 64, 8, 512, 1, [1]),          # 256 tiles exactly
+    (64, 32, 8, 161, 9, [31]),
+    (64, 10, 5, 300, 0, [0, 7]),        # ten (question, head) pairs
+])
+def test_prefill_tiles_whose_rows_two_halves_of_a_workgroup_share(D, hq, hkv, n_q, n_frames, old):
+    w = W["7b"].scaled(n_frames=max(n_frames, 4), n_layers=1, head_dim=D, n_q_heads=hq, n_kv_heads=hkv, n_questions=len(old))
+    p = Pair(w, seed=470, chunk=4)
+    p.ingest()
+    fi = [[(5 * b + i) % n_frames for i in range(n_frames)] for b in range(len(old))] if n_frames else None
+    for causal in (True, False):
+        p.check_prefill(0, n_q, fi, old, causal, seed=471)
+    p.close()
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
 def test_scores_of_any_finite_size(dtype, D):
     # scores of 1e12: every softmax is a choice of one row (two largest within the 1e-6 of a sum in fp32: none here), and

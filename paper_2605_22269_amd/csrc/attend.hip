@@ -789,6 +789,11 @@ __device__ __forceinline__ bool tile_of(unsigned id, int n_tiles, int combos, in
     *tile = n_tiles - 1 - rank;
     return rank < n_tiles;
 }
+// Workgroups of two fours per combination: a tile each, and where there are more tiles than compute units as many as those.
+__host__ __device__ __forceinline__ int pairs_grid(int n_tiles, int combos) {
+    const int places = 256 / combos;
+    return n_tiles <= places ? n_tiles : places;
+}
 unsigned tile_grid(int n_tiles, int combos) {
     if (8 % combos == 0) {
         const int per = 8 / combos;
@@ -805,7 +810,9 @@ unsigned tile_grid(int n_tiles, int combos) {
 // resident places is not even: the launch lasts as long as its heaviest tile.
 // FOURS = 2: eight waves, of which four take the even steps and four the odd ones, with rows and tables of their own (160 KB of
 // LDS, one workgroup per compute unit), and join at the end: a tile's chain is half as long, which is what counts where there
-// are no more tiles than compute units (flash_split; 600 tokens over 768 rows 47.2 -> 38.9 us a call).  Also built and slower: the next block's scores
+// are no more tiles than compute units (flash_split; 600 tokens over 768 rows 47.2 -> 38.9 us a call).  Where there are somewhat
+// more the smallest tiles take a four each, two to a workgroup, at the larger one's barriers: every compute unit then has about the
+// same to do (1568 tokens 79.4 -> 72.9).  Also built and slower: the next block's scores
 // interleaved instruction by instruction with this block's weights and values (66 us), 64 queries per wave (85 us: the accumulators pass 256
 // registers and are moved in and out of the accumulation registers).
 // SPLIT: a short prefill has too few tiles to fill the chip, so its rows are shared by n_split workgroups per
@@ -831,12 +838,17 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
     __shared__ int s_frame[kMaxGatherK]; // the question's frames; -1: names no frame of the cache
     static_assert(!(SPLIT && SUMS) && !(FOURS == 2 && (SPLIT || SUMS)), "the sums want final statistics, the two fours have no shares");
     __shared__ __align__(16) float s_lse[SUMS ? kFQ : 1];
-    int tile_id, combo;
-    if (!tile_of(blockIdx.x, SPLIT ? n_tiles * n_split : n_tiles, combos, &tile_id, &combo)) return;
-    const int qt = SPLIT ? tile_id / n_split : tile_id, sp = SPLIT ? tile_id % n_split : 0;
-    const int g = combo % a.Hkv, b = combo / a.Hkv;
     const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, half = lane >> 5;
     const int four = FOURS == 2 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0, wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
+    const int n_wgs = FOURS == 2 ? pairs_grid(n_tiles, combos) : SPLIT ? n_tiles * n_split : n_tiles; // per combination
+    int tile_id, combo;
+    if (!tile_of(blockIdx.x, n_wgs, combos, &tile_id, &combo)) return;
+    // two fours: the first workgroups take a tile together, the others one each (the smallest with the largest that is left)
+    const int n_pairs = FOURS == 2 ? n_tiles - n_wgs : 0, left = n_pairs - 1 - tile_id;
+    const bool joint = FOURS == 2 && left < 0;
+    const int qt_most = FOURS == 2 ? (joint ? tile_id + n_pairs : 2 * n_pairs - 1 - left) : 0; // the tile with the most steps here
+    const int qt = FOURS == 2 ? (joint || four == 0 ? qt_most : left) : SPLIT ? tile_id / n_split : tile_id, sp = SPLIT ? tile_id % n_split : 0;
+    const int g = combo % a.Hkv, b = combo / a.Hkv;
     auto &s_k = s_kk[four], &s_v = s_vv[four];
     auto &s_addr = s_addrs[four];
     auto &s_ft = s_fts[four];
@@ -898,7 +910,7 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
         pad_v = (first_frame < 0 ? lv : sv) + off;
     };
     auto tabulate = [&](int t) {
-        const int slot = t & (kRing - 1), r = (FOURS * t + four) * kFK + lane;
+        const int slot = t & (kRing - 1), r = (joint ? 2 * t + four : t) * kFK + lane;
         const unsigned char *rk = pad_k, *rv = pad_v;
         int ft = INT_MAX;
         if (r < n_ret) {
@@ -952,17 +964,20 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
 #pragma unroll
         for (int j = 0; j < 16; ++j) o[f][j] = 0.f;
 
-    // with the causal mask the rows after the workgroup's last token are seen by none of its queries
-    int n_seen = total;
-    if (a.causal) {
-        // local rows up to the tile's last token; the retrieved rows are seen by every token, also by
-        // tokens that have no local row of their own (fewer local rows than new tokens)
-        int ns = n_ret + n_loc - a.n_q + last_q + 1;
-        if (ns < n_ret) ns = n_ret;
-        if (ns < total) n_seen = ns;
-    }
-    // (two fours: their steps in turn; an odd one out is joined by one whose rows nobody of the tile sees)
-    const int n_steps_all = n_seen > 0 ? (n_seen + FOURS * kFK - 1) / (FOURS * kFK) : 0;
+    // with the causal mask the rows after a tile's last token are seen by none of its queries
+    auto steps_of = [&](int last_tok) {
+        int n_seen = total;
+        if (a.causal) {
+            // local rows up to the tile's last token; the retrieved rows are seen by every token, also by
+            // tokens that have no local row of their own (fewer local rows than new tokens)
+            int ns = n_ret + n_loc - a.n_q + last_tok + 1;
+            if (ns < n_ret) ns = n_ret;
+            if (ns < total) n_seen = ns;
+        }
+        // (two fours on one tile: an odd step out is joined by one whose rows nobody of the tile sees)
+        return joint ? (n_seen + 2 * kFK - 1) / (2 * kFK) : (n_seen + kFK - 1) / kFK;
+    };
+    const int n_steps_all = steps_of(last_q);
     // this workgroup's steps: all of them, or its share of them
     const int per_split = SPLIT ? (n_steps_all + n_split - 1) / n_split : n_steps_all;
     const int t_lo = SPLIT ? sp * per_split : 0;
@@ -1102,27 +1117,28 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
         step(t, s_k[0], s_v[0], s_k[1], s_v[1]);
         if (t + 1 < n_steps) step(t + 1, s_k[1], s_v[1], s_k[0], s_v[0]);
     }
+    if (FOURS == 2 && !joint && four == 1) { // its tile is the smaller one: the other four's barriers
+        const int last = (qt_most * kFQ + kFQ - 1 < n_queries ? qt_most * kFQ + kFQ - 1 : n_queries - 1) / a.G;
+        for (int t = n_steps; t < steps_of(last); ++t) __syncthreads();
+    }
     float l_sum = half_sum(l_run);
-    // Two waves of the same queries join: each hands the other the blocks it does not finish itself (it finishes kMine of them from
-    // `from` on), four floats a lane at [piece][lane], where the staged rows were.
-    constexpr int kMine = NF / FOURS;
-    const int from = kMine * four;
-    f32x16 joined[FOURS == 2 ? kMine : 1];
-    f32x16 *const mine = FOURS == 2 ? joined : o;
-    if constexpr (FOURS == 2) {
+    // Two waves of the same queries join: each hands the other the output blocks it does not finish itself, four floats a lane at
+    // [piece][lane], where the staged rows were; the ones it finishes are then its first.
+    constexpr int kJoint = NF / 2;
+    if (FOURS == 2 && joint) {
         __shared__ float s_stat[2][2][kFQ];
-        static_assert(kMine * 16 * 64 * sizeof(float) <= sizeof(s_kk[0]) / 4, "a wave's quarter of its four's keys");
-        f32x4 *const box = reinterpret_cast<f32x4 *>(s_kk[four]) + wave * (kMine * 4 * 64);
+        static_assert(kJoint * 16 * 64 * sizeof(float) <= sizeof(s_kk[0]) / 4, "a wave's quarter of its four's keys");
+        f32x4 *const box = reinterpret_cast<f32x4 *>(s_kk[four]) + wave * (kJoint * 4 * 64);
         __syncthreads(); // every wave is done with the keys
 #pragma unroll
-        for (int f = 0; f < kMine; ++f)
+        for (int f = 0; f < kJoint; ++f)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 f32x4 x;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    x[r] = four == 0 ? o[kMine + f][4 * c + r] : o[f][4 * c + r];
-                    mine[f][4 * c + r] = four == 0 ? o[f][4 * c + r] : o[kMine + f][4 * c + r];
+                    x[r] = four == 0 ? o[kJoint + f][4 * c + r] : o[f][4 * c + r];
+                    o[f][4 * c + r] = four == 0 ? o[f][4 * c + r] : o[kJoint + f][4 * c + r];
                 }
                 box[(4 * f + c) * 64 + lane] = x;
             }
@@ -1131,19 +1147,19 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
             s_stat[1][four][32 * wave + lq] = l_sum;
         }
         __syncthreads();
-        const f32x4 *const other = reinterpret_cast<const f32x4 *>(s_kk[1 - four]) + wave * (kMine * 4 * 64);
+        const f32x4 *const other = reinterpret_cast<const f32x4 *>(s_kk[FOURS == 2 ? 1 - four : 0]) + wave * (kJoint * 4 * 64);
         const float m2 = s_stat[0][1 - four][32 * wave + lq], l2 = s_stat[1][1 - four][32 * wave + lq];
         const float m = fmaxf(m_run, m2); // (sums of nothing have the least maximum, and a factor of zero)
         const float c1 = __builtin_amdgcn_exp2f(m_run - m), c2 = __builtin_amdgcn_exp2f(m2 - m);
         l_sum = four == 0 ? fmaf(l2, c2, l_sum * c1) : fmaf(l_sum, c1, l2 * c2); // the same bits in both
         m_run = m;
 #pragma unroll
-        for (int f = 0; f < kMine; ++f)
+        for (int f = 0; f < kJoint; ++f)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const f32x4 x = other[(4 * f + c) * 64 + lane];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) mine[f][4 * c + r] = fmaf(x[r], c2, mine[f][4 * c + r] * c1);
+                for (int r = 0; r < 4; ++r) o[f][4 * c + r] = fmaf(x[r], c2, o[f][4 * c + r] * c1);
             }
     }
     const bool seen = l_sum != 0.f; // a query that saw nothing leaves zeros, whatever its hidden rows held; NaN stays NaN
@@ -1151,16 +1167,16 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
     if constexpr (SPLIT) { // the split's record: [0] maximum, [1] normaliser, [2..] unnormalised output
         if (!q_ok) return;
         float *rec = aux + (my_row * n_split + sp) * (D + 2);
-        if (half == 0 && four == 0) {
+        if (half == 0) {
             rec[0] = m_run;
             rec[1] = l_sum;
         }
 #pragma unroll
-        for (int f = 0; f < kMine; ++f)
+        for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) rec[2 + 32 * (from + f) + 8 * jj + 4 * half + r] = seen ? mine[f][4 * jj + r] : 0.f;
+                for (int r = 0; r < 4; ++r) rec[2 + 32 * f + 8 * jj + 4 * half + r] = seen ? o[f][4 * jj + r] : 0.f;
     } else {
         // Eq. 1 of the tile: the wave's queries (now the A operand: S = Q K^T) against the new tokens' keys, 64 at a time.
         // New token j is local row n_loc - n_q + j; it may not exist.  The last two steps' keys are still in LDS, which are
@@ -1195,9 +1211,10 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
         {
             // a lane holds features 8 jj + 4 half .. + 3: the halves swap, so that it stores 16 bytes in a row (in 8-byte
             // stores twice as many lines are opened twice as often: 32 tokens without a past 9.9 us a call, now 8.8)
-            uint16_t *op = out + my_row * D + 32 * from + 8 * half;
+            uint16_t *op = out + my_row * D + 8 * half + (joint ? 32 * kJoint * four : 0);
 #pragma unroll
-            for (int f = 0; f < kMine; ++f)
+            for (int f = 0; f < NF; ++f) {
+                if (FOURS == 2 && joint && f >= kJoint) break; // the other wave's
 #pragma unroll
                 for (int jj = 0; jj < 4; jj += 2) {
                     raw16 w;
@@ -1206,7 +1223,7 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
                         uint32_t pk[2];
 #pragma unroll
                         for (int u = 0; u < 2; ++u)
-                            pk[u] = bf16_pair(mine[f][4 * (jj + u) + 2 * e] * inv, mine[f][4 * (jj + u) + 2 * e + 1] * inv);
+                            pk[u] = bf16_pair(o[f][4 * (jj + u) + 2 * e] * inv, o[f][4 * (jj + u) + 2 * e + 1] * inv);
                         auto sw = __builtin_amdgcn_permlane32_swap(pk[0], pk[1], false, false);
                         w[e] = sw[0];
                         w[2 + e] = sw[1];
@@ -1214,7 +1231,8 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
                     if (!seen) w = raw16{0u, 0u, 0u, 0u};
                     if (q_ok) *reinterpret_cast<raw16 *>(op + 32 * f + 8 * jj) = w;
                 }
-            if (!SUMS && q_ok && half == 0 && four == 0) aux[my_row] = lse;
+            }
+            if (!SUMS && q_ok && half == 0 && !(joint && four == 1)) aux[my_row] = lse;
         }
         if constexpr (SUMS) {
             float(*s_col)[kFusedSums] = reinterpret_cast<float(*)[kFusedSums]>(s_vv); // per wave, where the values were
@@ -1517,7 +1535,7 @@ hipError_t launch_flash(const AttendArgs &a, int n_fs, bool two_fours, int B, vo
         return hipGetLastError();
     }
     if (two_fours) {
-        hipLaunchKernelGGL((prefill_flash_kernel<D, 2, false, false>), dim3(grid), dim3(512), 0, st, a, o16, n_tiles, combos, po.lse, 1);
+        hipLaunchKernelGGL((prefill_flash_kernel<D, 2, false, false>), dim3(tile_grid(pairs_grid(n_tiles, combos), combos)), dim3(512), 0, st, a, o16, n_tiles, combos, po.lse, 1);
     } else if (n_fs == 1) {
         hipLaunchKernelGGL((prefill_flash_kernel<D, 1, false, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.lse, 1);
     } else { // rows shared by n_fs workgroups per tile, merged
@@ -1598,21 +1616,23 @@ int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame) {
 // workspace (200 tokens without a past would be shared by two and are not, 300 over 768 rows by eight and are by six).
 // Instead two fours of waves may take a tile's steps in turn and join in LDS: no records, no merge, one workgroup per compute unit
 // and half the chain, so for all tiles that fit at once (us a call, 7B head layout over 768 rows, shares / two fours: 196 tokens
-// 34.3 / 29.3, 300 39.5 / 32.4, 600 47.2 / 41.1, 1000 60.3 / 52.9; 1568, 344 tiles: 79.5 / 80.6; 64 and 8 heads of 128, 600 tokens,
-// 304 tiles: 58.6 / 61.5) unless few tiles walk many rows: a step is 0.95 us of the two fours' chain and 1.5 us of a share's, the
+// 34.3 / 29.3, 300 39.5 / 32.4, 600 47.2 / 41.1, 1000 60.3 / 52.9) and up to 7 / 4 of them, the smallest in pairs, a four each
+// (one four a workgroup / two: 1176 tokens, 260 tiles, 68.4 / 60.2; 1568, 344: 85.1 / 78.4; 1960, 432: 103.8 / 100.3; 64 and 8
+// heads of 128, 1000 tokens, 504 tiles, nearly all of them in pairs: 80.8 / 82.2), unless few tiles walk many rows: a step is 0.95 us of the two fours' chain and 1.5 us of a share's, the
 // merge launch costs 4 us and a record's number written and read again 2 ps (64 tokens over 768 rows 26.1 against 23.4, 128:
 // 27.1 / 28.5; 17 tokens over 3136: 58 / 27).  Up to kFusedSums tokens over a step or two keep the kernel that sums Eq. 1 itself
 // (128 tokens over 96 rows 18.0 / 16.4).
 static int flash_split(const Ctx &c, int n_q, int B, int k_frame, bool *two_fours) {
     const int64_t wgs = (((int64_t)n_q * c.group + kFQ - 1) / kFQ) * c.cfg.n_kv_heads * B;
-    *two_fours = wgs <= 256;
+    const int combos = c.cfg.n_kv_heads * B;
+    *two_fours = n_q > kFusedSums && 4 * (wgs / combos) <= 7 * (256 / combos);
     if (wgs >= 192) return 1;
     const int64_t steps = ((int64_t)(k_frame > 0 ? k_frame : 0) * c.kappa + n_q + kFK - 1) / kFK;
     int64_t n = (512 + wgs - 1) / wgs;
     if (n > kAttendMaxSplit) n = kAttendMaxSplit;
     if (n > steps / 2) n = steps / 2;
-    const int64_t rows = (int64_t)B * n_q * c.cfg.n_q_heads, combos = (int64_t)B * c.cfg.n_kv_heads;
-    const int64_t rest = rows + combos * n_q * keysum_rows(n_q, c.group, (int)combos);
+    const int64_t rows = (int64_t)B * n_q * c.cfg.n_q_heads;
+    const int64_t rest = rows + (int64_t)combos * n_q * keysum_rows(n_q, c.group, combos);
     while (n > 1 && (rows * n * (c.cfg.head_dim + 2) + rest) * (int64_t)sizeof(float) > prefill_workspace_bytes(c, n_q, B, k_frame)) --n;
     if (n <= 1) {
         *two_fours = n_q > kFusedSums;

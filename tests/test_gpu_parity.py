@@ -1184,6 +1184,9 @@ def test_prefill_matrix_tile_edges(D, hq, hkv, n_q, n_frames, old):
     (128, 64, 8, 512, 1, [1]),          # 256 tiles exactly
     (64, 32, 8, 161, 9, [31]),
     (64, 10, 5, 300, 0, [0, 7]),        # ten (question, head) pairs
+    (128, 64, 8, 528, 1, [1]),          # one tile more per KV head than there are places: the two smallest are a pair
+    (64, 64, 8, 890, 0, [0]),           # 56 for 32: all but eight in pairs
+    (128, 7, 1, 4700, 0, [0]),          # 258 tiles of one KV head
 ])
 def test_prefill_tiles_whose_rows_two_halves_of_a_workgroup_share(D, hq, hkv, n_q, n_frames, old):
     w = W["7b"].scaled(n_frames=max(n_frames, 4), n_layers=1, head_dim=D, n_q_heads=hq, n_kv_heads=hkv, n_questions=len(old))

@@ -126,6 +126,27 @@ __device__ __forceinline__ float weight_of_any(float x, float s, float ref) {
     return fabsf(ref) > kLargeRef ? __builtin_amdgcn_exp2f(scaled_apart(x, s, ref)) : weight_of(x, s, ref);
 }
 
+// Two floats that another workgroup of the launch reads: written through to, and read from, the memory that all XCDs share.
+__device__ __forceinline__ void store_far(float *p, float x, float y) {
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(p), __builtin_bit_cast(uint64_t, f32x2{x, y}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x2 load_far(const float *p) {
+    return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+// Before the context's records: arrivals of a tile's workgroups, [question][tile][KV head], zero between launches.
+__device__ __forceinline__ int *arrivals_of(float *part) { return reinterpret_cast<int *>(part) - kAttendMaxTiles; }
+// The last of n workgroups to get here, all of whose store_far's are then there to be read, by every thread; the count is zero again.
+__device__ __forceinline__ bool last_to_arrive(int *count, int n, int *s_last) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this wave's stores are in the shared memory
+    __syncthreads();                                 // every wave's are
+    if (threadIdx.x == 0) {
+        *s_last = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+        if (*s_last) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    return *s_last != 0;
+}
+
 // Where row `code` of [retrieved rows, local rows] lives: >= 0 a row of the store's slab, < 0 local row ~code.
 __device__ __forceinline__ const unsigned char *row_at(const unsigned char *store, const unsigned char *local, int code,
                                                        unsigned store_stride, unsigned local_stride) {
@@ -152,9 +173,11 @@ __device__ __forceinline__ const unsigned char *row_at(const unsigned char *stor
 // What bounds it: many questions, the rate at which the rows arrive (64 questions over 768 + 40 rows, 7B head layout, graph
 // replay: 16.4 us a call = 6.4 TB/s of rows, half of them read by several questions; a workgroup that took its rows through
 // tables and barriers shared by the waves, with a merge launch: 25.4); few, the chain launch -> frame list -> rows -> merge:
-// a compute unit alone draws its rows at 40 GB/s, so the rows of one question are split over workgroups although that costs
-// the merge launch (attend_split).  Eight waves a workgroup are no faster (16.4; 9.8 against 9.6 for one question).
-template <typename T, int D>
+// a compute unit alone draws its rows at 40 GB/s, so the rows of one question are split over workgroups (attend_split).
+// Eight waves a workgroup are no faster (16.4; 9.8 against 9.6 for one question).
+// MERGE: the rows are shared and the last of a tile's workgroups to finish merges them (one question, 7B head layout, 768 + 32
+// rows: 9.3 us a call in four shares with attend_combine_kernel after them, 8.0 without, 7.5 in seven).
+template <typename T, int D, bool MERGE>
 __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void attend_kernel(
     AttendArgs a, T *__restrict__ out) {
     constexpr int W = kAttWaves;
@@ -464,14 +487,20 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
             }
         }
         const int64_t row = ((int64_t)b * a.n_q + tok) * a.Hq + g * a.G + (qq - tok * a.G);
-        if (a.n_split > 1) { // the split's record: [0] maximum, [1] normaliser, [2..] unnormalised output
+        if (MERGE || a.n_split > 1) { // the split's record: [0] maximum, [1] normaliser, [2..] unnormalised output
             float *rec = a.part + (row * a.n_split + sp) * (D + 2);
-            if (c == 0) {
-                rec[0] = m;
-                rec[1] = l;
-            }
+            if constexpr (MERGE) {
+                if (c == 0) store_far(rec, m, l);
+                store_far(rec + 2 + 4 * c, o[0], o[1]);
+                store_far(rec + 4 + 4 * c, o[2], o[3]);
+            } else {
+                if (c == 0) {
+                    rec[0] = m;
+                    rec[1] = l;
+                }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) rec[2 + 4 * c + e] = o[e];
+                for (int e = 0; e < 4; ++e) rec[2 + 4 * c + e] = o[e];
+            }
         } else {
             const float den = l != 0.f ? l : 1.f;
             if constexpr (kBf16)
@@ -480,6 +509,45 @@ __global__ __launch_bounds__(64 * kAttWaves) __attribute__((amdgpu_waves_per_eu(
                 *reinterpret_cast<f32x4 *>(out + row * D + 4 * c) = o / den;
             if (column_sums<T, D>() && a.pair_stride && c == 0)
                 *reinterpret_cast<f32x2 *>(a.part + row * a.pair_stride) = l != 0.f ? f32x2{m, 1.f / l} : f32x2{0.f, 0.f};
+        }
+    }
+    if constexpr (MERGE) {
+        // ---- the shares' records: the last workgroup of the tile to get here does what attend_combine_kernel does ----
+        __shared__ int s_last;
+        if (!last_to_arrive(arrivals_of(a.part) + ((int)blockIdx.z * (int)gridDim.y + (int)blockIdx.y), a.n_split, &s_last)) return;
+        for (int i = tid; i < n_q_here * kQuads; i += 64 * W) {
+            const int n = i / kQuads, c = i - n * kQuads, qq = qt * kAttQ + n, tok = qq / a.G;
+            const int64_t row = ((int64_t)b * a.n_q + tok) * a.Hq + g * a.G + (qq - tok * a.G);
+            const float *rec = a.part + row * a.n_split * (D + 2);
+            f32x2 st[kAttendMaxSplit], x0[kAttendMaxSplit], x1[kAttendMaxSplit]; // all requested before any is used
+#pragma unroll
+            for (int s = 0; s < kAttendMaxSplit; ++s) {
+                if (s >= a.n_split) break;
+                st[s] = load_far(rec + s * (D + 2));
+                x0[s] = load_far(rec + s * (D + 2) + 2 + 4 * c);
+                x1[s] = load_far(rec + s * (D + 2) + 4 + 4 * c);
+            }
+            float m = -INFINITY;
+#pragma unroll
+            for (int s = 0; s < kAttendMaxSplit; ++s)
+                if (s < a.n_split) m = fmaxf(m, st[s][0]);
+            float l = 0.f;
+            f32x4 o = {0.f, 0.f, 0.f, 0.f};
+            if (m > -INFINITY) {
+#pragma unroll
+                for (int s = 0; s < kAttendMaxSplit; ++s) {
+                    if (s >= a.n_split) break;
+                    const float x = st[s][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st[s][0] - m);
+                    l = fmaf(st[s][1], x, l);
+                    o = f32x4{fmaf(x0[s][0], x, o[0]), fmaf(x0[s][1], x, o[1]), fmaf(x1[s][0], x, o[2]), fmaf(x1[s][1], x, o[3])};
+                }
+            }
+            const bool seen = l != 0.f; // nobody's share holds a row that the query sees: zeros
+            o = seen ? o / l : f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (kBf16)
+                *reinterpret_cast<u32x2 *>(out + row * D + 4 * c) = u32x2{bf16_pair(o[0], o[1]), bf16_pair(o[2], o[3])};
+            else
+                *reinterpret_cast<f32x4 *>(out + row * D + 4 * c) = o;
         }
     }
 }
@@ -1446,18 +1514,19 @@ struct PrefillOut { // all null for the plain attention call
 template <typename T, int D>
 hipError_t launch_typed(const AttendArgs &a, int B, void *out, const PrefillOut &po, hipStream_t st) {
     const dim3 grid(a.n_split, a.Hkv * ((a.n_q * a.G + kAttQ - 1) / kAttQ), B);
-    hipLaunchKernelGGL((attend_kernel<T, D>), grid, dim3(64 * kAttWaves), 0, st, a, static_cast<T *>(out));
+    const bool merge = a.n_split > 1 && !po.signal; // a prefill's records are in the caller's workspace, which has no counts
+    if (merge)
+        hipLaunchKernelGGL((attend_kernel<T, D, true>), grid, dim3(64 * kAttWaves), 0, st, a, static_cast<T *>(out));
+    else
+        hipLaunchKernelGGL((attend_kernel<T, D, false>), grid, dim3(64 * kAttWaves), 0, st, a, static_cast<T *>(out));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (a.n_split > 1) {
-        const dim3 rows((unsigned)(B * a.n_q * a.Hq)), threads(D < 64 ? 64 : D);
-        float *const no_lse = nullptr;
-        if (!a.pair_stride)
-            hipLaunchKernelGGL((attend_combine_kernel<T, D, const float *__restrict__>), rows, threads, 0, st, a.part, a.n_split,
-                               static_cast<T *>(out), no_lse);
-        else if constexpr (column_sums<T, D>())
-            hipLaunchKernelGGL((attend_combine_kernel<T, D, float *>), rows, threads, 0, st, a.part, a.n_split, static_cast<T *>(out), no_lse);
-    }
+    if constexpr (column_sums<T, D>())
+        if (a.n_split > 1 && !merge) {
+            float *const no_lse = nullptr;
+            hipLaunchKernelGGL((attend_combine_kernel<T, D, float *>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D < 64 ? 64 : D), 0, st, a.part,
+                               a.n_split, static_cast<T *>(out), no_lse);
+        }
     if constexpr (!column_sums<T, D>()) return hipGetLastError(); // their prefill is the matrix-core one
     if ((e = hipGetLastError()) != hipSuccess || !po.signal) return e;
     // Shares of the queries, no more rows than the workspace has room for.  Under the causal mask the shares are uneven, so
@@ -1567,21 +1636,34 @@ int record_splits(int B, int Hkv, int n_qtiles, int k_frame) {
     return (int)n_split;
 }
 
-// Workgroups that share the rows of one tile of attend_kernel.  A wave takes about 1.1 us a block while the chip is nearly
-// empty, and splitting costs the merge launch, 3.5 us: rows are split where a wave has more than five blocks, into shares
-// of six blocks or more, and no further than one workgroup per compute unit.  us a call, 7B head layout, 768 + 40 rows, by
-// shares 1 / 2 / 4 / 8: one question 11.8 / 11.2 / 9.6 / 9.6, 8 questions 13.8 / 12.5 / 10.6 / 11.2, 16: 14.3 / 14.0 / 12.1 /
-// 13.9, 48 (192 workgroups unsplit): 15.7 / 19.8 / 20.6 / 25.9; one question over 128 rows 5.9 / 7.1 / 7.7 / 8.7, over 4736:
-// 53 / 32 / 21 / 15.  (The local rows are known on the device only; n_q of them at least are there or do not matter.)
-int attend_split(const Ctx &c, int n_q, int B, int k_frame) {
+// Workgroups that share the rows of one tile of attend_kernel.
+// A call whose last workgroup merges: a wave takes 1.0 to 1.2 us a block while the chip is nearly empty and the merge 1.5, so rows
+// are split where a wave has more than two blocks (rows of 64 features and less: three), into as few shares as leave it the fewest.
+// One block a wave only where that takes up to four shares or 64 workgroups, beyond which the records cost more than the second
+// block, and no further than one workgroup per compute unit.  us a call (graph replay), 7B head layout, one question over 320 rows,
+// shares 1 / 3 / 5: 6.7 / 6.5 / 6.4, 416 rows, 1 / 2 / 4 / 8: 7.6 / 7.4 / 6.7 / 6.8, 608 rows, 1 / 4 / 5 / 8: 8.9 / 7.6 / 6.9 /
+// 7.1, 800 rows, 1 / 4 / 6 / 8: 10.8 / 7.7 / 7.9 / 7.3, 1184 rows, 4 / 5 / 8: 8.7 / 7.9 / 8.2; 4 questions over 800 rows, 1 / 4 / 8:
+// 11.0 / 8.1 / 8.2, 8: 11.6 / 8.5 / 8.8, 48 (192 workgroups unsplit): 12.0; fp32, one question over 224 rows, 1 / 2 / 4: 12.8 /
+// 10.5 / 8.8, 416: 19.1 / 14.7 / 10.8.
+// A prefill, whose records a launch of 3.5 us merges: where a wave has more than five blocks, into shares of six or more (800 rows
+// with that launch, 1 / 2 / 4 / 8: 11.8 / 11.2 / 9.6 / 9.6).
+// (The local rows are known on the device only; n_q of them at least are there or do not matter.)
+int attend_split(const Ctx &c, int n_q, int B, int k_frame, bool prefill) {
     const int rows = c.esz == 2 ? 32 : 16; // of a block
     const int64_t wgs = ((int64_t)n_q * c.group + kAttQ - 1) / kAttQ * c.cfg.n_kv_heads * B;
     const int64_t blocks = ((int64_t)k_frame * c.kappa + n_q + rows - 1) / rows;
-    if (blocks <= 5 * kAttWaves) return 1;
-    int64_t n = 256 / wgs;
-    if (n > blocks / 6) n = blocks / 6;
-    if (n > kAttendMaxSplit) n = kAttendMaxSplit;
-    return n < 1 ? 1 : (int)n;
+    int64_t most = 256 / wgs;
+    if (most > kAttendMaxSplit) most = kAttendMaxSplit;
+    if (prefill) {
+        if (blocks <= 5 * kAttWaves) return 1;
+        if (most > blocks / 6) most = blocks / 6;
+        return most < 1 ? 1 : (int)most;
+    }
+    if (most < 2 || blocks <= (most < 4 ? 5 : c.cfg.head_dim > 64 ? 2 : 3) * kAttWaves) return 1;
+    int64_t each = (blocks + kAttWaves * most - 1) / (kAttWaves * most); // blocks a wave
+    const int64_t n = (blocks + kAttWaves - 1) / kAttWaves;              // shares of one block a wave
+    if (each == 1 && wgs * n > (n <= 4 ? 128 : 64)) each = 2;
+    return (int)((blocks + kAttWaves * each - 1) / (kAttWaves * each));
 }
 
 } // namespace
@@ -1656,7 +1738,7 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
     const int64_t slab = (int64_t)c.store_cap * c.cfg.head_dim * c.esz; // bytes of one (layer, head) slab
     a.store_k = static_cast<const unsigned char *>(c.store_k) + (int64_t)layer * c.cfg.n_kv_heads * slab;
     a.store_v = static_cast<const unsigned char *>(c.store_v) + (int64_t)layer * c.cfg.n_kv_heads * slab;
-    a.part = c.attend_part;
+    a.part = c.attend_part + kAttendMaxTiles;
     a.store_cap = c.store_cap;
     a.n_q = n_q;
     a.Hq = c.cfg.n_q_heads;
@@ -1668,7 +1750,7 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
     a.n_qtiles = (n_q * c.group + kTileQ - 1) / kTileQ;
     a.causal = causal;
     a.scale_log2e = 1.4426950408889634f / sqrtf((float)c.cfg.head_dim);
-    a.n_split = attend_split(c, n_q, B, a.k_frame);
+    a.n_split = attend_split(c, n_q, B, a.k_frame, workspace != nullptr);
     if (workspace) { // (its records are counted by the formula above)
         const int most = record_splits(B, a.Hkv, a.n_qtiles, a.k_frame);
         if (a.n_split > most) a.n_split = most;

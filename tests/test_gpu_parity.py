@@ -913,6 +913,37 @@ def test_attention_over_long_contexts_and_many_questions():
     p.close()
 
 
+@pytest.mark.parametrize("dtype,D,hq,hkv,n_q,B", [
+    ("bf16", 128, 28, 4, 1, 1), ("bf16", 64, 16, 1, 3, 2), ("bf16", 16, 4, 2, 16, 4), ("f32", 128, 8, 8, 2, 3), ("f32", 32, 17, 1, 1, 4),
+])
+def test_attention_merged_by_the_last_of_a_tiles_workgroups(dtype, D, hq, hkv, n_q, B):
+    # two to eight shares, shares without rows among them; call after call, and replay after replay with other calls between,
+    # the counts of arrivals are where they were
+    w = W["tiny"].scaled(n_frames=40, n_questions=4, n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=D, dtype=dtype, tokens_per_frame=49,
+                         keep_ratio=0.5)
+    p = Pair(w, seed=186, chunk=8)
+    p.ingest()
+    frames = [int(x) for x in np.random.default_rng(7).permutation(40)]
+    for k in (5, 6, 8, 11, 14, 17, 22, 27, 33, 40):
+        p.check_attend(0, n_q, [frames[:k]] * B, [n_q + 5 * b for b in range(B)], causal=bool(k % 2), seed=30 + k)
+    p.check_attend(0, n_q, [[-1] * 33] * B, [n_q] * B, causal=True, seed=91)
+    q = torch.randn(B, n_q, hq, D, device="cuda", generator=torch.Generator("cuda").manual_seed(92)).to(w.torch_dtype)
+    fi = torch.tensor([frames] * B, dtype=torch.int32, device="cuda")
+    want, out = p.gpu.attend(0, q, fi), torch.empty_like(q)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(3):
+            p.gpu.attend(0, q, fi, out=out)
+    for i in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), i
+        p.check_attend(0, n_q, [frames[:20 + i]] * B, [n_q] * B, causal=True, seed=93 + i)
+    p.close()
+
+
 @pytest.mark.parametrize("dtype,D,hq,hkv,n_q", [
     ("bf16", 128, 14, 2, 1), ("bf16", 64, 16, 1, 1), ("bf16", 32, 17, 1, 2), ("bf16", 16, 4, 2, 5),     # queries short of,
     ("f32", 128, 28, 4, 1), ("f32", 64, 8, 2, 4), ("f32", 32, 6, 3, 16), ("f32", 16, 4, 1, 3),          # on and past a tile

@@ -1229,6 +1229,34 @@ def test_prefill_tiles_whose_rows_two_halves_of_a_workgroup_share(D, hq, hkv, n_
     p.close()
 
 
+@pytest.mark.parametrize("D,hq,hkv,n_q,B", [(128, 28, 4, 1, 1), (128, 28, 4, 128, 1), (64, 10, 5, 33, 3), (64, 128, 4, 127, 2), (128, 8, 8, 64, 4)])
+def test_prefill_signal_added_by_the_last_of_a_questions_workgroups(D, hq, hkv, n_q, B):
+    # from one term a column to 128 of them; call after call, and replay after replay with other calls between
+    w = W["7b"].scaled(n_frames=4, n_layers=1, head_dim=D, n_q_heads=hq, n_kv_heads=hkv, n_questions=4)
+    p = Pair(w, seed=480, chunk=4)
+    p.ingest()
+    for i, causal in enumerate((True, False, True)):
+        p.check_prefill(0, n_q, [[(i + b) % 4] for b in range(B)], [3 * b for b in range(B)], causal, seed=481 + i)
+    g = torch.Generator("cuda").manual_seed(485)
+    q, k, v = (torch.randn(*shape, device="cuda", generator=g).to(w.torch_dtype) for shape in ((B, n_q, hq, D), (B * n_q, hkv, D), (B * n_q, hkv, D)))
+    offs = torch.arange(B + 1, dtype=torch.int32, device="cuda") * n_q
+    ws = torch.empty(mk.mukv_prefill_workspace_size(p.gpu.h, n_q, 0, B), dtype=torch.uint8, device="cuda")
+    want, want_sig = p.gpu.prefill_attend(0, q, None, k, v, offs, workspace=ws)
+    out, sig = torch.empty_like(want), torch.empty_like(want_sig)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(2):
+            p.gpu.prefill_attend(0, q, None, k, v, offs, out=out, signal=sig, workspace=ws)
+    for i in range(3):
+        out.zero_(), sig.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(sig, want_sig), i
+        p.check_prefill(0, n_q, [[b % 4] for b in range(4)], [0] * 4, True, seed=486 + i)
+    p.close()
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
 def test_scores_of_any_finite_size(dtype, D):
     # scores of 1e12: every softmax is a choice of one row (two largest within the 1e-6 of a sum in fp32: none here), and

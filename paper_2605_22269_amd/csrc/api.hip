@@ -314,8 +314,8 @@ int mukv_create(const mukv_config *cfg, mukv_ctx **out) {
     ok(dalloc(&c.u_count, MQ * 2));
     ok(dalloc(&c.m_entry, MQ * (size_t)mukv::kMaxMultiEntries * 3));
     ok(dalloc(&c.m_count, MQ * 2));
-    ok(dalloc(&c.attend_part, (size_t)mukv::attend_counts(cfg->max_questions) + MQ * mukv::kAttendMaxTokens * cfg->n_q_heads * mukv::kAttendMaxSplit * (size_t)(cfg->head_dim + 2)));
-    if (e == hipSuccess) ok(hipMemset(c.attend_part, 0, (size_t)mukv::attend_counts(cfg->max_questions) * sizeof(int32_t)));
+    ok(dalloc(&c.attend_part, mukv::kAttendMaxTiles + MQ * mukv::kAttendMaxTokens * cfg->n_q_heads * mukv::kAttendMaxSplit * (size_t)(cfg->head_dim + 2)));
+    if (e == hipSuccess) ok(hipMemset(c.attend_part, 0, mukv::kAttendMaxTiles * sizeof(int32_t)));
     if (cfg->freq_axis == MUKV_FREQ_TOKEN) {
         // rows 0..P/2 of the DFT matrix over the frame's tokens, columns 0..P/2 (the others mirror
         // them), as (cos, -sin) pairs, rounded once from double for the fp32 pass.  The sine of

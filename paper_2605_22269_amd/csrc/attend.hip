@@ -886,14 +886,11 @@ unsigned tile_grid(int n_tiles, int combos) {
 // SPLIT: a short prefill has too few tiles to fill the chip, so its rows are shared by n_split workgroups per
 // tile; the split's (maximum, normaliser, unnormalised output) go to the records attend_combine_kernel merges
 // (aux = records).  Otherwise the output is final here, and so are the log-sum-exps: they go to aux for the key sums'
-// launch, or (SUMS, few new tokens) Eq. 1 is summed right here, over the tile's queries, goes to aux
-// [B][Hkv][n_tiles][n_q], and the last of a question's workgroups to finish adds that up (a call, 7B head layout, with
-// prefill_signal_kernel after it / so: 1 token without a past 9.2 us / 7.9, 32 9.2 / 8.6, 64 over 96 rows 12.0 / 11.7; 32 heads
-// of 64, 32 tokens 9.4 / 7.5).
+// launch, or (SUMS, few new tokens) Eq. 1 is summed right here, over the tile's queries, and goes to aux
+// [B][Hkv][n_tiles][n_q].
 template <int D, int FOURS, bool SPLIT, bool SUMS>
 __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D == 128 || FOURS == 2 ? 2 : 3, D == 128 || FOURS == 2 ? 2 : 3))) void prefill_flash_kernel(
-    AttendArgs a, uint16_t *__restrict__ out, int n_tiles, int combos, float *__restrict__ aux, int n_split, float *__restrict__ signal,
-    int *__restrict__ arrived) {
+    AttendArgs a, uint16_t *__restrict__ out, int n_tiles, int combos, float *__restrict__ aux, int n_split) {
     using T = uint16_t;
     constexpr int kRowB = D * 2, kPieces = kRowB / 16, kRowsPerLoad = 64 / kPieces; // rows one load of a wave brings
     constexpr int kLoads = kFK / 4 / kRowsPerLoad;                                   // such loads per wave and step
@@ -1346,44 +1343,7 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
             __syncthreads();
             float *dst = aux + (((int64_t)b * a.Hkv + g) * n_tiles + qt) * a.n_q;
             for (int j = tid; j < a.n_q; j += 256)
-                __hip_atomic_store(dst + j, j < j_end ? (s_col[0][j] + s_col[1][j]) + (s_col[2][j] + s_col[3][j]) : 0.f, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            // the last of the question's workgroups adds them up, in the order of prefill_signal_kernel (whose launch would take 4 us)
-            __shared__ int s_last;
-            const int n_terms = a.Hkv * n_tiles, per = (n_terms + kSigRuns - 1) / kSigRuns;
-            if (!last_to_arrive(arrived + b, n_terms, &s_last)) return;
-            constexpr int kRuns = kSigRuns / 2; // of a thread, whose column is tid % 128
-            static_assert(kFusedSums == 128, "two threads a column");
-            float(*s_run)[kFusedSums] = reinterpret_cast<float(*)[kFusedSums]>(s_kk);
-            static_assert(kSigRuns * kFusedSums * sizeof(float) <= sizeof(s_kk), "a sum per run and new token");
-            const int j = tid % kFusedSums, run0 = tid / kFusedSums * kRuns;
-            const float *src = aux + (int64_t)b * n_terms * a.n_q + (j < a.n_q ? j : 0);
-            float sum[kRuns];
-#pragma unroll
-            for (int r = 0; r < kRuns; ++r) sum[r] = 0.f;
-            for (int t0 = 0; t0 < per; t0 += 4) {
-                float v[kRuns][4];
-#pragma unroll
-                for (int r = 0; r < kRuns; ++r)
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int t = (run0 + r) * per + t0 + u;
-                        v[r][u] = __hip_atomic_load(src + (int64_t)(t < n_terms ? t : 0) * a.n_q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-#pragma unroll
-                for (int r = 0; r < kRuns; ++r)
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) sum[r] += t0 + u < per && (run0 + r) * per + t0 + u < n_terms ? v[r][u] : 0.f;
-            }
-#pragma unroll
-            for (int r = 0; r < kRuns; ++r) s_run[run0 + r][j] = sum[r];
-            __syncthreads();
-            if (tid < a.n_q) { // (no more than kFusedSums)
-                float tot = s_run[0][tid];
-#pragma unroll
-                for (int r = 1; r < kSigRuns; ++r) tot += s_run[r][tid];
-                signal[(int64_t)b * a.n_q + tid] = tot * (1.0f / ((float)a.Hq * (float)a.n_q));
-            }
+                dst[j] = j < j_end ? (s_col[0][j] + s_col[1][j]) + (s_col[2][j] + s_col[3][j]) : 0.f;
         }
     }
 }
@@ -1549,7 +1509,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
 
 struct PrefillOut { // all null for the plain attention call
     float *lse, *colpart, *signal; // (lse: matrix-core prefill)
-    int *arrived;                  // arrivals of a question's workgroups, zero between calls (matrix-core prefill of few tokens)
 };
 
 template <typename T, int D>
@@ -1637,19 +1596,19 @@ hipError_t launch_flash(const AttendArgs &a, int n_fs, bool two_fours, int B, vo
     hipError_t e;
     const float inv = 1.0f / ((float)a.Hq * (float)a.n_q);
     const dim3 sig_grid((a.n_q + kSigCols - 1) / kSigCols, B);
-    if (n_fs == 1 && !two_fours && a.n_q <= kFusedSums) { // one launch (see kFusedSums)
-        hipLaunchKernelGGL((prefill_flash_kernel<D, 1, false, true>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.colpart, 1,
-                           po.signal, po.arrived);
+    if (n_fs == 1 && !two_fours && a.n_q <= kFusedSums) { // two launches (see kFusedSums)
+        hipLaunchKernelGGL((prefill_flash_kernel<D, 1, false, true>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.colpart, 1);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(prefill_signal_kernel, sig_grid, dim3(kThreads), 0, st, po.colpart, a.Hkv, n_tiles, a.n_q, inv, po.signal,
+                           a.G, a.causal, 0);
         return hipGetLastError();
     }
-    float *const no_signal = nullptr; // of these kernels
-    int *const no_counts = nullptr;
     if (two_fours) {
-        hipLaunchKernelGGL((prefill_flash_kernel<D, 2, false, false>), dim3(tile_grid(pairs_grid(n_tiles, combos), combos)), dim3(512), 0, st, a, o16, n_tiles, combos, po.lse, 1, no_signal, no_counts);
+        hipLaunchKernelGGL((prefill_flash_kernel<D, 2, false, false>), dim3(tile_grid(pairs_grid(n_tiles, combos), combos)), dim3(512), 0, st, a, o16, n_tiles, combos, po.lse, 1);
     } else if (n_fs == 1) {
-        hipLaunchKernelGGL((prefill_flash_kernel<D, 1, false, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.lse, 1, no_signal, no_counts);
+        hipLaunchKernelGGL((prefill_flash_kernel<D, 1, false, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, po.lse, 1);
     } else { // rows shared by n_fs workgroups per tile, merged
-        hipLaunchKernelGGL((prefill_flash_kernel<D, 1, true, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, a.part, n_fs, no_signal, no_counts);
+        hipLaunchKernelGGL((prefill_flash_kernel<D, 1, true, false>), dim3(grid), dim3(256), 0, st, a, o16, n_tiles, combos, a.part, n_fs);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL((attend_combine_kernel<uint16_t, D, const float *__restrict__>), dim3((unsigned)(B * a.n_q * a.Hq)), dim3(D), 0, st, a.part,
                            n_fs, o16, po.lse);
@@ -1779,7 +1738,7 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
     const int64_t slab = (int64_t)c.store_cap * c.cfg.head_dim * c.esz; // bytes of one (layer, head) slab
     a.store_k = static_cast<const unsigned char *>(c.store_k) + (int64_t)layer * c.cfg.n_kv_heads * slab;
     a.store_v = static_cast<const unsigned char *>(c.store_v) + (int64_t)layer * c.cfg.n_kv_heads * slab;
-    a.part = c.attend_part + attend_counts(c.cfg.max_questions);
+    a.part = c.attend_part + kAttendMaxTiles;
     a.store_cap = c.store_cap;
     a.n_q = n_q;
     a.Hq = c.cfg.n_q_heads;
@@ -1797,7 +1756,7 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
         if (a.n_split > most) a.n_split = most;
     }
     a.pair_stride = 0;
-    PrefillOut po{nullptr, nullptr, nullptr, nullptr};
+    PrefillOut po{nullptr, nullptr, nullptr};
     bool two_fours = false;
     const int n_fs = workspace && flash_shape(c) ? flash_split(c, n_q, B, k_frame, &two_fours) : 0;
     if (workspace) {
@@ -1807,7 +1766,6 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
         po.lse = workspace + rows * (n_fs == 0 ? a.n_split : n_fs == 1 ? 0 : n_fs) * (c.cfg.head_dim + 2);
         po.colpart = po.lse + rows;
         po.signal = signal;
-        po.arrived = reinterpret_cast<int *>(c.attend_part);
     }
     if (n_fs) // the prefill on the matrix cores
         return c.cfg.head_dim == 64 ? launch_flash<64>(a, n_fs, two_fours, B, out, po, st) : launch_flash<128>(a, n_fs, two_fours, B, out, po, st);

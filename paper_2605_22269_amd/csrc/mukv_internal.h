@@ -38,7 +38,6 @@ struct ChunkArgs;
 
 constexpr int kAttendMaxTokens = 16; // query tokens per question in one mukv_attend call
 constexpr int kAttendMaxTiles = 128; // tiles of a mukv_attend call whose rows are shared (at most a workgroup per compute unit, two or more a tile)
-constexpr int64_t attend_counts(int max_questions) { return ((int64_t)max_questions + 63) / 64 * 64 + kAttendMaxTiles; }
 constexpr int kAttendMaxSplit = 8;   // workgroups sharing the frame list of one (question, KV head)
 constexpr int kPrefillMaxTokens = 8192; // new tokens per question in one mukv_prefill_attend call
 
@@ -115,7 +114,7 @@ struct Ctx {
     unsigned char *tok_part;
     size_t tok_part_half;
     // attention over the retrieved context: per (question, token, head, split) maximum, normaliser, output
-    float *attend_part; // attend_counts() counts (zero between calls): a prefill's questions, a decode's tiles; then [max_questions][kAttendMaxTokens][Hq][kAttendMaxSplit][D+2]
+    float *attend_part; // [kAttendMaxTiles] counts (zero between calls), then [max_questions][kAttendMaxTokens][Hq][kAttendMaxSplit][D+2]
 };
 
 // ---- a batch of chunks processed by one chain of launches ----

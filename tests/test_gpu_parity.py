@@ -1230,8 +1230,8 @@ def test_prefill_tiles_whose_rows_two_halves_of_a_workgroup_share(D, hq, hkv, n_
 
 
 @pytest.mark.parametrize("D,hq,hkv,n_q,B", [(128, 28, 4, 1, 1), (128, 28, 4, 128, 1), (64, 10, 5, 33, 3), (64, 128, 4, 127, 2), (128, 8, 8, 64, 4)])
-def test_prefill_signal_added_by_the_last_of_a_questions_workgroups(D, hq, hkv, n_q, B):
-    # from one term a column to 128 of them; call after call, and replay after replay with other calls between
+def test_prefills_of_few_tokens_call_after_call_and_replay_after_replay(D, hq, hkv, n_q, B):
+    # from one term of Eq. 1 a column to 128 of them; replay after replay with other calls between
     w = W["7b"].scaled(n_frames=4, n_layers=1, head_dim=D, n_q_heads=hq, n_kv_heads=hkv, n_questions=4)
     p = Pair(w, seed=480, chunk=4)
     p.ingest()
@@ -1254,6 +1254,36 @@ def test_prefill_signal_added_by_the_last_of_a_questions_workgroups(D, hq, hkv, 
         torch.cuda.synchronize()
         assert torch.equal(out, want) and torch.equal(sig, want_sig), i
         p.check_prefill(0, n_q, [[b % 4] for b in range(4)], [0] * 4, True, seed=486 + i)
+    p.close()
+
+
+@pytest.mark.parametrize("D,hq,hkv,sizes", [(128, 28, 4, (128, 97)), (64, 32, 8, (33, 1)), (128, 8, 8, (64, 300))])
+def test_prefills_that_overlap_each_with_a_workspace_of_its_own(D, hq, hkv, sizes):
+    # what such a call writes is the caller's: on two streams at once the calls do not meet, and afterwards nothing is left behind
+    w = W["7b"].scaled(n_frames=4, n_layers=1, head_dim=D, n_q_heads=hq, n_kv_heads=hkv, n_questions=1)
+    p = Pair(w, seed=490, chunk=4)
+    p.ingest()
+    g = torch.Generator("cuda").manual_seed(491)
+    calls = []
+    for n_q in sizes:
+        q, k, v = (torch.randn(*shape, device="cuda", generator=g).to(w.torch_dtype) for shape in ((1, n_q, hq, D), (n_q, hkv, D), (n_q, hkv, D)))
+        offs = torch.tensor([0, n_q], dtype=torch.int32, device="cuda")
+        ws = torch.empty(mk.mukv_prefill_workspace_size(p.gpu.h, n_q, 0, 1), dtype=torch.uint8, device="cuda")
+        want = p.gpu.prefill_attend(0, q, None, k, v, offs, workspace=ws)
+        outs = [(torch.zeros_like(want[0]), torch.zeros_like(want[1])) for _ in range(50)]
+        calls.append((torch.cuda.Stream(), q, k, v, offs, ws, want, outs))
+    torch.cuda.synchronize()
+    for i in range(50):
+        for st, q, k, v, offs, ws, _, outs in calls:
+            with torch.cuda.stream(st):
+                p.gpu.prefill_attend(0, q, None, k, v, offs, out=outs[i][0], signal=outs[i][1], workspace=ws)
+    torch.cuda.synchronize()
+    for _, _, _, _, _, _, want, outs in calls:
+        for i, (out, sig) in enumerate(outs):
+            assert torch.equal(out, want[0]) and torch.equal(sig, want[1]), i
+    for n_q in sizes:
+        p.check_prefill(0, n_q, [[1, 3]], [2], True, seed=492)
+    p.check_attend(0, 1, [[0, 1, 2, 3]], [9], causal=True, seed=493)
     p.close()
 
 

@@ -955,9 +955,22 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
     const int first_tok = (qt * kFQ) / a.G;
     const int last_q = (qt * kFQ + kFQ - 1 < n_queries ? qt * kFQ + kFQ - 1 : n_queries - 1) / a.G;
 
+    // with the causal mask the rows after a tile's last token are seen by none of its queries
+    auto seen_by = [&](int last_tok) {
+        if (!a.causal) return total;
+        // local rows up to the tile's last token; the retrieved rows are seen by every token, also by
+        // tokens that have no local row of their own (fewer local rows than new tokens)
+        int ns = n_ret + n_loc - a.n_q + last_tok + 1;
+        if (ns < n_ret) ns = n_ret;
+        return ns < total ? ns : total;
+    };
+    // (two fours on one tile: an odd step out is joined by one whose rows nobody of the tile sees)
+    auto steps_of = [&](int rows) { return joint ? (rows + 2 * kFK - 1) / (2 * kFK) : (rows + kFK - 1) / kFK; };
+    const int n_seen = seen_by(last_q);
+
     // Row r of [retrieved rows, local rows]: where its key and value live and the first token that sees it, worked
-    // out by the lanes of one wave, four steps at a time (one per wave).  A row that lives nowhere, or past the last,
-    // is seen by nobody and reads a row that exists; its weight is zero, but zero times a NaN is not, so that row is one
+    // out by the lanes of one wave, four steps at a time (one per wave).  A row that lives nowhere, or past the last that a query
+    // of the tile sees, is seen by nobody and reads a row that exists; its weight is zero, but zero times a NaN is not, so that row is one
     // that every query sees anyway (the first retrieved one; without any, the first local one, which is seen by all that
     // see something; with neither, the slab's first row, and nobody sees anything).
     int first_frame = a.k_frame > 0 ? __builtin_amdgcn_readfirstlane(a.frame_idx[(int64_t)b * a.k_frame]) : -1;
@@ -990,7 +1003,7 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
                 rv = sv + off;
                 ft = 0;
             }
-        } else if (r < total) {
+        } else if (r < n_seen) {
             const int j = r - n_ret;
             const uint64_t off = (uint64_t)(unsigned)(l0 + j) * local_stride;
             rk = lk + off;
@@ -1032,20 +1045,7 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
 #pragma unroll
         for (int j = 0; j < 16; ++j) o[f][j] = 0.f;
 
-    // with the causal mask the rows after a tile's last token are seen by none of its queries
-    auto steps_of = [&](int last_tok) {
-        int n_seen = total;
-        if (a.causal) {
-            // local rows up to the tile's last token; the retrieved rows are seen by every token, also by
-            // tokens that have no local row of their own (fewer local rows than new tokens)
-            int ns = n_ret + n_loc - a.n_q + last_tok + 1;
-            if (ns < n_ret) ns = n_ret;
-            if (ns < total) n_seen = ns;
-        }
-        // (two fours on one tile: an odd step out is joined by one whose rows nobody of the tile sees)
-        return joint ? (n_seen + 2 * kFK - 1) / (2 * kFK) : (n_seen + kFK - 1) / kFK;
-    };
-    const int n_steps_all = steps_of(last_q);
+    const int n_steps_all = steps_of(n_seen);
     // this workgroup's steps: all of them, or its share of them
     const int per_split = SPLIT ? (n_steps_all + n_split - 1) / n_split : n_steps_all;
     const int t_lo = SPLIT ? sp * per_split : 0;
@@ -1187,7 +1187,7 @@ __global__ __launch_bounds__(256 * FOURS) __attribute__((amdgpu_waves_per_eu(D =
     }
     if (FOURS == 2 && !joint && four == 1) { // its tile is the smaller one: the other four's barriers
         const int last = (qt_most * kFQ + kFQ - 1 < n_queries ? qt_most * kFQ + kFQ - 1 : n_queries - 1) / a.G;
-        for (int t = n_steps; t < steps_of(last); ++t) __syncthreads();
+        for (int t = n_steps; t < steps_of(seen_by(last)); ++t) __syncthreads();
     }
     float l_sum = half_sum(l_run);
     // Two waves of the same queries join: each hands the other the output blocks it does not finish itself, four floats a lane at

@@ -1287,6 +1287,37 @@ def test_prefills_that_overlap_each_with_a_workspace_of_its_own(D, hq, hkv, size
     p.close()
 
 
+@pytest.mark.parametrize("D,hq,hkv,n_q,n_frames,bad", [
+    (128, 28, 4, 150, 0, 100),     # tiles in two halves: the first sees 19 rows, its halves walk 128
+    (64, 32, 8, 161, 0, 100),
+    (128, 28, 4, 1568, 4, 1000),   # this row's tile has a workgroup to itself, the smallest ones are in pairs
+    (128, 28, 4, 1568, 4, 200),    # one of a pair's
+    (128, 28, 4, 100, 0, 50),      # Eq. 1 summed by the attention itself
+    (128, 14, 2, 160, 32, 50),     # the rows of a tile shared by workgroups
+    (64, 64, 8, 1100, 0, 120),     # four waves a tile
+])
+def test_prefill_rows_that_no_query_of_a_tile_sees_do_not_reach_it(D, hq, hkv, n_q, n_frames, bad):
+    w = W["7b"].scaled(n_frames=max(n_frames, 4), n_layers=1, head_dim=D, n_q_heads=hq, n_kv_heads=hkv, n_questions=1)
+    p = Pair(w, seed=500, chunk=4)
+    p.ingest()
+    g = torch.Generator("cuda").manual_seed(501)
+    q, k, v = (torch.randn(*shape, device="cuda", generator=g).to(w.torch_dtype) for shape in ((1, n_q, hq, D), (n_q, hkv, D), (n_q, hkv, D)))
+    offs = torch.tensor([0, n_q], dtype=torch.int32, device="cuda")
+    fi = torch.arange(n_frames, dtype=torch.int32, device="cuda")[None] if n_frames else None
+    want, want_sig = p.gpu.prefill_attend(0, q, fi, k, v, offs)
+    v[bad] = float("nan")
+    out, sig = p.gpu.prefill_attend(0, q, fi, k, v, offs)
+    G = hq // hkv
+    at = torch.arange(n_q * G)                                                  # (token, head of the KV group)
+    last = ((at // 128 * 128 + 127).clamp(max=n_q * G - 1) // G).view(n_q, G)   # last token of its tile
+    apart = (last < bad).repeat(1, hkv).cuda()                                  # [n_q][hq]: the whole tile is before the row
+    assert apart.any() and not apart.all()
+    assert torch.equal(out[0][apart], want[0][apart])
+    assert torch.isnan(out[0][bad:].float()).all()                              # who sees it gets it
+    assert torch.equal(sig, want_sig)                                           # (weights do not depend on values)
+    p.close()
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
 def test_scores_of_any_finite_size(dtype, D):
     # scores of 1e12: every softmax is a choice of one row (two largest within the 1e-6 of a sum in fp32: none here), and

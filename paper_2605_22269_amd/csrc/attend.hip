@@ -1636,20 +1636,21 @@ int record_splits(int B, int Hkv, int n_qtiles, int k_frame) {
     return (int)n_split;
 }
 
-// Workgroups that share the rows of one tile of attend_kernel.
-// A call whose last workgroup merges: a wave takes 1.0 to 1.2 us a block while the chip is nearly empty and the merge 1.5, so rows
-// are split where a wave has more than two blocks (rows of 64 features and less: three), into as few shares as leave it the fewest.
-// One block a wave only where that takes up to four shares or 64 workgroups, beyond which the records cost more than the second
-// block, and no further than one workgroup per compute unit.  us a call (graph replay), 7B head layout, one question over 320 rows,
-// shares 1 / 3 / 5: 6.7 / 6.5 / 6.4, 416 rows, 1 / 2 / 4 / 8: 7.6 / 7.4 / 6.7 / 6.8, 608 rows, 1 / 4 / 5 / 8: 8.9 / 7.6 / 6.9 /
-// 7.1, 800 rows, 1 / 4 / 6 / 8: 10.8 / 7.7 / 7.9 / 7.3, 1184 rows, 4 / 5 / 8: 8.7 / 7.9 / 8.2; 4 questions over 800 rows, 1 / 4 / 8:
-// 11.0 / 8.1 / 8.2, 8: 11.6 / 8.5 / 8.8, 48 (192 workgroups unsplit): 12.0; fp32, one question over 224 rows, 1 / 2 / 4: 12.8 /
-// 10.5 / 8.8, 416: 19.1 / 14.7 / 10.8.
+// Workgroups that share the rows of one tile of attend_kernel, at most one per compute unit.
+// A call whose last workgroup merges: as many as cost the least by what the parts were measured to take (us) -- a wave's block while
+// the chip is nearly empty 0.7 to 1.6 by type and features, the merge 1.6 and 0.2 or 0.3 a share, and what the records of a full
+// chip add, 0.7.  Over 6357 calls (bf16 and fp32, 16 to 128 features, six head layouts, 1 to 64 questions of 1 to 16 tokens, 80 to
+// 3900 rows), each timed with every number of shares, the one taken is 0.4 % from the best in the mean; where it is more than 4 %
+// (173 calls, nearly all fp32) the local rows, which are not known here, give some waves one block more.  us a call (graph replay), shares 1 / 2 /
+// 4 / 8, the one taken with *: 7B head layout, one question over 416 rows 8.3 / 8.1 / 7.4* / 7.4, 800 rows 11.5 / 9.9 / 8.4 / 7.9 and
+// in seven 7.8*; 4 questions over 800 rows 11.5 / 10.4 / 8.8 / 8.9, seven 8.8*; 32 questions of one KV head of 128 over 320 rows 8.0*
+// / 9.6 / 9.4 / -; 8 KV heads of 32, 8 questions over 416 rows 6.1* / 7.0 / 6.9 / -; fp32, 7B head layout, one question over 224 rows
+// 13.5 / 11.2 / 9.6* / 9.6, 416 rows 19.8 / 15.5 / 11.6 / 10.2, seven 10.0*.
 // A prefill, whose records a launch of 3.5 us merges: where a wave has more than five blocks, into shares of six or more (800 rows
 // with that launch, 1 / 2 / 4 / 8: 11.8 / 11.2 / 9.6 / 9.6).
 // (The local rows are known on the device only; n_q of them at least are there or do not matter.)
 int attend_split(const Ctx &c, int n_q, int B, int k_frame, bool prefill) {
-    const int rows = c.esz == 2 ? 32 : 16; // of a block
+    const int rows = c.esz == 2 ? 32 : 16, D = c.cfg.head_dim; // rows of a block
     const int64_t wgs = ((int64_t)n_q * c.group + kAttQ - 1) / kAttQ * c.cfg.n_kv_heads * B;
     const int64_t blocks = ((int64_t)k_frame * c.kappa + n_q + rows - 1) / rows;
     int64_t most = 256 / wgs;
@@ -1659,11 +1660,18 @@ int attend_split(const Ctx &c, int n_q, int B, int k_frame, bool prefill) {
         if (most > blocks / 6) most = blocks / 6;
         return most < 1 ? 1 : (int)most;
     }
-    if (most < 2 || blocks <= (most < 4 ? 5 : c.cfg.head_dim > 64 ? 2 : 3) * kAttWaves) return 1;
-    int64_t each = (blocks + kAttWaves * most - 1) / (kAttWaves * most); // blocks a wave
-    const int64_t n = (blocks + kAttWaves - 1) / kAttWaves;              // shares of one block a wave
-    if (each == 1 && wgs * n > (n <= 4 ? 128 : 64)) each = 2;
-    return (int)((blocks + kAttWaves * each - 1) / (kAttWaves * each));
+    const float block = c.esz == 2 ? (D > 64 ? 1.1f : D > 32 ? 1.0f : 0.7f) : (D > 64 ? 1.6f : D > 32 ? 1.4f : 0.9f);
+    const float share = (D > 32 ? 0.3f : 0.2f) + 0.7f / 256.f * (float)wgs;
+    int best = 1;
+    float least = 0.f;
+    for (int n = 1; n <= most; ++n) {
+        const float cost = block * (float)((blocks + kAttWaves * n - 1) / (kAttWaves * n)) + (n > 1 ? 1.6f + share * (float)n : 0.f);
+        if (n == 1 || cost < least) {
+            best = n;
+            least = cost;
+        }
+    }
+    return best;
 }
 
 } // namespace

@@ -917,8 +917,8 @@ def test_attention_over_long_contexts_and_many_questions():
     ("bf16", 128, 28, 4, 1, 1), ("bf16", 64, 16, 1, 3, 2), ("bf16", 16, 4, 2, 16, 4), ("f32", 128, 8, 8, 2, 3), ("f32", 32, 17, 1, 1, 4),
 ])
 def test_attention_merged_by_the_last_of_a_tiles_workgroups(dtype, D, hq, hkv, n_q, B):
-    # two to eight shares, shares without rows among them; call after call, and replay after replay with other calls between,
-    # the counts of arrivals are where they were
+    # three to eight shares (two: the test after this), shares without rows among them; call after call, and replay after replay
+    # with other calls between, the counts of arrivals are where they were
     w = W["tiny"].scaled(n_frames=40, n_questions=4, n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=D, dtype=dtype, tokens_per_frame=49,
                          keep_ratio=0.5)
     p = Pair(w, seed=186, chunk=8)
@@ -944,12 +944,32 @@ def test_attention_merged_by_the_last_of_a_tiles_workgroups(dtype, D, hq, hkv, n
     p.close()
 
 
+@pytest.mark.parametrize("dtype,D,hq,hkv,n_q,B,k", [
+    ("bf16", 128, 28, 4, 1, 32, 28),    # 128 tiles, two shares each: as many counts as there are
+    ("f32", 128, 8, 8, 2, 16, 9),
+    ("bf16", 64, 16, 1, 16, 8, 30),     # 128 tiles of one KV head: sixteen a question
+    ("bf16", 16, 4, 2, 1, 33, 40),      # 66 tiles, three shares
+])
+def test_attention_of_as_many_tiles_as_have_shared_rows(dtype, D, hq, hkv, n_q, B, k):
+    w = W["tiny"].scaled(n_frames=40, n_questions=B, n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=D, dtype=dtype, tokens_per_frame=49,
+                         keep_ratio=0.5)
+    p = Pair(w, seed=187, chunk=8)
+    p.ingest()
+    rs = np.random.default_rng(8)
+    lists = [[int(x) for x in rs.permutation(40)[:k]] for _ in range(B)]
+    for seed in (110, 111):
+        p.check_attend(0, n_q, lists, [n_q + b % 5 for b in range(B)], causal=True, seed=seed)
+    p.check_prefill(0, 20, [lists[0][:2]], [3], True, seed=112)
+    p.check_attend(0, n_q, lists[:1], [n_q], causal=True, seed=113)
+    p.close()
+
+
 @pytest.mark.parametrize("dtype,D,hq,hkv,n_q", [
     ("bf16", 128, 14, 2, 1), ("bf16", 64, 16, 1, 1), ("bf16", 32, 17, 1, 2), ("bf16", 16, 4, 2, 5),     # queries short of,
     ("f32", 128, 28, 4, 1), ("f32", 64, 8, 2, 4), ("f32", 32, 6, 3, 16), ("f32", 16, 4, 1, 3),          # on and past a tile
 ])
 def test_attention_at_the_edges_of_row_blocks_and_shares(dtype, D, hq, hkv, n_q):
-    # blocks of 16 or 32 rows dealt to four waves, rows split over workgroups past 20 blocks
+    # blocks of 16 or 32 rows dealt to four waves, rows split over workgroups from 9 (fp32, 128 features) to 13 blocks on
     w = W["tiny"].scaled(n_frames=40, n_questions=4, n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=D, dtype=dtype, tokens_per_frame=49,
                          keep_ratio=0.5)
     p = Pair(w, seed=183, chunk=8)

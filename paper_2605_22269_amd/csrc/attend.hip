@@ -1700,36 +1700,49 @@ int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame) {
     return (rows * n_split * (c.cfg.head_dim + 2) + rows + combos * tiles * n_q) * (int64_t)sizeof(float);
 }
 
-// Workgroups that share the rows of one tile of the matrix-core prefill: 1 unless the tiles alone leave most of
-// the chip idle (two workgroups per compute unit are wanted, at least two steps each: 196 new tokens over 768 rows,
-// 44 tiles, 34-35 us a call in 7 shares), and no more than leave the records, log-sum-exps and column sums within the
-// workspace (200 tokens without a past would be shared by two and are not, 300 over 768 rows by eight and are by six).
-// Instead two fours of waves may take a tile's steps in turn and join in LDS: no records, no merge, one workgroup per compute unit
-// and half the chain, so for all tiles that fit at once (us a call, 7B head layout over 768 rows, shares / two fours: 196 tokens
-// 34.3 / 29.3, 300 39.5 / 32.4, 600 47.2 / 41.1, 1000 60.3 / 52.9) and up to 7 / 4 of them, the smallest in pairs, a four each
-// (one four a workgroup / two: 1176 tokens, 260 tiles, 68.4 / 60.2; 1568, 344: 85.1 / 78.4; 1960, 432: 103.8 / 100.3; 64 and 8
-// heads of 128, 1000 tokens, 504 tiles, nearly all of them in pairs: 80.8 / 82.2), unless few tiles walk many rows: a step is 0.95 us of the two fours' chain and 1.5 us of a share's, the
-// merge launch costs 4 us and a record's number written and read again 2 ps (64 tokens over 768 rows 26.1 against 23.4, 128:
-// 27.1 / 28.5; 17 tokens over 3136: 58 / 27).  Up to kFusedSums tokens over a step or two keep the kernel that sums Eq. 1 itself
-// (128 tokens over 96 rows 18.0 / 16.4).
-static int flash_split(const Ctx &c, int n_q, int B, int k_frame, bool *two_fours) {
-    const int64_t wgs = (((int64_t)n_q * c.group + kFQ - 1) / kFQ) * c.cfg.n_kv_heads * B;
-    const int combos = c.cfg.n_kv_heads * B;
-    *two_fours = n_q > kFusedSums && 4 * (wgs / combos) <= 7 * (256 / combos);
+// How the matrix-core prefill goes about its tiles, of three ways; returns the workgroups that share the rows of one (1: none do).
+// Shares: where the tiles alone leave most of the chip idle; two workgroups per compute unit are wanted, at least two steps each, and
+// no more than leave the records, log-sum-exps and column sums within the workspace.
+// Two fours of waves that take a tile's steps in turn and join in LDS: no records, no merge, one workgroup per compute unit and half
+// the chain.  One four a workgroup: what is left, and up to kFusedSums tokens the kernel that sums Eq. 1 itself.
+// Shares or two fours, by what was measured (us): a pair of the two fours' steps 1.65 (rows of 64 features 1.35); a share's step
+// 1.1 (0.85), the merge 1.6 and a record's number written and read again 2.8 ps (4.2).  Of 1562 calls that could go either way (1 to
+// 1568 tokens, five head layouts, one and two questions, up to 1536 rows before them, with the mask and without) ten take a way more
+// than 2 % slower than the other, 6 % at most.  us a call, 7B head layout over 768 rows, shares / two fours, the one taken with *:
+// 1 token 18.1* / 23.7, 64 23.7* / 25.9, 128 28.2 / 26.9*, 196 35.2 / 29.3*, 600 48.4 / 39.4*; 1 token over 384 rows 16.6* / 18.3,
+// 17 over 1536 22.8* / 36.3.
+// Two fours or one, unshared, no more tiles than compute units: the join and the second four's tables cost what few steps give back
+// (one four / two: 7B head layout, no past, 150 tokens, 3 steps, 16.5* / 18.2, 196, 4 steps, 17.6* / 18.3; 64 / 8 heads, 400, 7 steps,
+// 26.2* / 26.8, 512, 8 steps, 30.0 / 29.7*; 28 / 4 heads of 64, two questions of 300, 5 steps, 17.6* / 18.0, one of 300 over 96 rows,
+// 7 steps, 19.4 / 18.9*).
+// More tiles than compute units, two fours with the smallest tiles in pairs: that evens out what the mask makes uneven, so only with
+// it (1300 tokens over 768 rows, 7B head layout, without the mask 90.4* / 96.6), up to 7 / 4 tiles a unit.  With rows of 128 features
+// two fours on a unit are slower at even tiles than two workgroups, so there the fewer tiles a unit, the more rows before the new
+// ones are (28 / 4 heads, 1568 tokens over 768 rows, 1.34 tiles a unit, 79.7 / 72.5*; two questions of 1000, 1.72, without a past
+// 50.2 / 48.6*, over 768 rows 70.7* / 71.8; 64 / 8 heads, 600 tokens, 1.19, over 768 rows 52.5 / 51.3*, over 1536 73.0* / 74.8; two
+// questions of 300, 1.19, over 192 rows 31.0 / 30.1*, over 768 45.8* / 46.9; rows of 64 features, 64 / 8 heads, 600 tokens over 768
+// rows 43.8 / 41.6*, over 1536 63.6 / 61.0*).
+static int flash_split(const Ctx &c, int n_q, int B, int k_frame, bool causal, bool *two_fours) {
+    const int64_t tiles = ((int64_t)n_q * c.group + kFQ - 1) / kFQ;
+    const int combos = c.cfg.n_kv_heads * B, places = 256 / combos;
+    const int64_t wgs = tiles * combos, past = (int64_t)(k_frame > 0 ? k_frame : 0) * c.kappa;
+    const int64_t steps = (past + n_q + kFK - 1) / kFK;
+    const bool wide = c.cfg.head_dim == 128;
+    if (tiles <= places)
+        *two_fours = n_q > kFusedSums && steps >= (wide ? 8 : 6);
+    else
+        *two_fours = n_q > kFusedSums && steps >= 6 && causal && 4 * tiles <= 7 * places &&
+                     (!wide || 5 * past * places <= (15 * places - 7 * tiles) * n_q);
     if (wgs >= 192) return 1;
-    const int64_t steps = ((int64_t)(k_frame > 0 ? k_frame : 0) * c.kappa + n_q + kFK - 1) / kFK;
     int64_t n = (512 + wgs - 1) / wgs;
     if (n > kAttendMaxSplit) n = kAttendMaxSplit;
     if (n > steps / 2) n = steps / 2;
     const int64_t rows = (int64_t)B * n_q * c.cfg.n_q_heads;
     const int64_t rest = rows + (int64_t)combos * n_q * keysum_rows(n_q, c.group, combos);
     while (n > 1 && (rows * n * (c.cfg.head_dim + 2) + rest) * (int64_t)sizeof(float) > prefill_workspace_bytes(c, n_q, B, k_frame)) --n;
-    if (n <= 1) {
-        *two_fours = n_q > kFusedSums;
-        return 1;
-    }
-    const float shared = 1.5f * (float)((steps + n - 1) / n) + 4.f + 2e-6f * (float)(rows * n * (c.cfg.head_dim + 2));
-    *two_fours = 0.95f * (float)steps <= shared;
+    if (n <= 1) return 1;
+    const float share = (float)((steps + n - 1) / n), pairs = (float)((steps + 1) / 2), numbers = 1e-6f * (float)(rows * n * (c.cfg.head_dim + 2));
+    *two_fours = wide ? 1.65f * pairs <= 1.6f + 1.1f * share + 2.8f * numbers : 1.35f * pairs <= 1.6f + 0.85f * share + 4.2f * numbers;
     return *two_fours ? 1 : (int)n;
 }
 
@@ -1766,7 +1779,7 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
     a.pair_stride = 0;
     PrefillOut po{nullptr, nullptr, nullptr};
     bool two_fours = false;
-    const int n_fs = workspace && flash_shape(c) ? flash_split(c, n_q, B, k_frame, &two_fours) : 0;
+    const int n_fs = workspace && flash_shape(c) ? flash_split(c, n_q, B, k_frame, causal != 0, &two_fours) : 0;
     if (workspace) {
         const int64_t rows = (int64_t)B * n_q * a.Hq;
         a.part = workspace;

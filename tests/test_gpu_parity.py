@@ -1229,14 +1229,19 @@ def test_prefill_matrix_tile_edges(D, hq, hkv, n_q, n_frames, old):
 
 
 @pytest.mark.parametrize("D,hq,hkv,n_q,n_frames,old", [
-    (128, 28, 4, 129, 0, [0]),          # three steps of rows between two: one without rows
+    (128, 28, 4, 129, 8, [0]),          # nine steps of rows between two: one of them without rows
+    (128, 28, 4, 129, 0, [0]),          # three steps: four waves a tile
     (128, 28, 4, 256, 0, [0]),          # four: two each; the first tile sees one step, so one of the two sees nothing
     (128, 16, 2, 147, 12, [0, 100]),    # tables filled twice, ragged rows
     (128, 64, 8, 512, 1, [1]),          # 256 tiles exactly
     (64, 32, 8, 161, 9, [31]),
-    (64, 10, 5, 300, 0, [0, 7]),        # ten (question, head) pairs
+    (64, 10, 5, 300, 3, [0, 7]),        # seven steps, ten (question, head) pairs
+    (64, 10, 5, 300, 0, [0, 7]),        # five steps of 64 features: four waves a tile
+    (128, 28, 4, 512, 0, [0]),          # eight steps, where the two begin
     (128, 64, 8, 528, 1, [1]),          # one tile more per KV head than there are places: the two smallest are a pair
     (64, 64, 8, 890, 0, [0]),           # 56 for 32: all but eight in pairs
+    (64, 64, 8, 900, 0, [0]),           # 57: four waves a tile
+    (128, 64, 8, 600, 17, [0]),         # 38 for 32 behind more rows than pairs are for: four waves a tile
     (128, 7, 1, 4700, 0, [0]),          # 258 tiles of one KV head
 ])
 def test_prefill_tiles_whose_rows_two_halves_of_a_workgroup_share(D, hq, hkv, n_q, n_frames, old):
@@ -1308,8 +1313,8 @@ def test_prefills_that_overlap_each_with_a_workspace_of_its_own(D, hq, hkv, size
 
 
 @pytest.mark.parametrize("D,hq,hkv,n_q,n_frames,bad", [
-    (128, 28, 4, 150, 0, 100),     # tiles in two halves: the first sees 19 rows, its halves walk 128
-    (64, 32, 8, 161, 0, 100),
+    (128, 28, 4, 150, 8, 100),     # tiles in two halves: the first sees 411 rows, its halves walk 512
+    (64, 32, 8, 161, 8, 100),
     (128, 28, 4, 1568, 4, 1000),   # this row's tile has a workgroup to itself, the smallest ones are in pairs
     (128, 28, 4, 1568, 4, 200),    # one of a pair's
     (128, 28, 4, 100, 0, 50),      # Eq. 1 summed by the attention itself

@@ -398,6 +398,7 @@ int mukv_reset(mukv_ctx *ctx) {
     ctx->c.n_frames = 0;
     ctx->c.n_done = 0;
     ctx->c.pending->clear();
+    ctx->c.arrivals_unsure = true;
     if (ctx->c.n_deferred) { // the rows they would have copied are forgotten with the rest
         DeviceScope dev(ctx->c.cfg.device_id);
         if (!dev.ok || mukv::drop_deferred(ctx->c) != hipSuccess) return MUKV_ERR_HIP;

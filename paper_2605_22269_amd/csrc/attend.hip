@@ -135,17 +135,17 @@ __device__ __forceinline__ f32x2 load_far(const float *p) {
 }
 // Before the context's records: arrivals of a tile's workgroups, [question][tile][KV head], zero between launches.
 __device__ __forceinline__ int *arrivals_of(float *part) { return reinterpret_cast<int *>(part) - kAttendMaxTiles; }
-// The last of n workgroups to get here, all of whose store_far's are then there to be read, by every thread; the count is zero again.
+// The last of n workgroups to get here, all of whose store_far's are then there to be read, by every thread.  The arrival that makes
+// n sets the count back to zero in the same step, so none is lost between the two.
 __device__ __forceinline__ bool last_to_arrive(int *count, int n, int *s_last) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this wave's stores are in the shared memory
     __syncthreads();                                 // every wave's are
-    if (threadIdx.x == 0) {
-        *s_last = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
-        if (*s_last) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (threadIdx.x == 0)
+        *s_last = __builtin_amdgcn_atomic_inc32(reinterpret_cast<uint32_t *>(count), (uint32_t)(n - 1), __ATOMIC_RELAXED, "agent") == (uint32_t)(n - 1);
     __syncthreads();
     return *s_last != 0;
 }
+__global__ __launch_bounds__(kAttendMaxTiles) void clear_arrivals_kernel(float *part) { arrivals_of(part)[threadIdx.x] = 0; }
 
 // Where row `code` of [retrieved rows, local rows] lives: >= 0 a row of the store's slab, < 0 local row ~code.
 __device__ __forceinline__ const unsigned char *row_at(const unsigned char *store, const unsigned char *local, int code,
@@ -1747,7 +1747,7 @@ static int flash_split(const Ctx &c, int n_q, int B, int k_frame, bool causal, b
 }
 
 // workspace == null: the plain attention call, records in the context's scratch, no signal.
-hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const int32_t *frame_idx, int k_frame,
+hipError_t launch_attend(Ctx &c, int layer, const void *q, int n_q, const int32_t *frame_idx, int k_frame,
                          const void *k_local, const void *v_local, const int32_t *local_offsets, int B, int causal,
                          void *out, float *signal, float *workspace, hipStream_t st) {
     AttendArgs a;
@@ -1787,6 +1787,12 @@ hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const 
         po.lse = workspace + rows * (n_fs == 0 ? a.n_split : n_fs == 1 ? 0 : n_fs) * (c.cfg.head_dim + 2);
         po.colpart = po.lse + rows;
         po.signal = signal;
+    }
+    if (!workspace && a.n_split > 1 && c.arrivals_unsure) { // the first call that counts since the cache was emptied or replaced
+        hipLaunchKernelGGL(clear_arrivals_kernel, dim3(1), dim3(kAttendMaxTiles), 0, st, a.part);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        c.arrivals_unsure = false;
     }
     if (n_fs) // the prefill on the matrix cores
         return c.cfg.head_dim == 64 ? launch_flash<64>(a, n_fs, two_fours, B, out, po, st) : launch_flash<128>(a, n_fs, two_fours, B, out, po, st);

@@ -115,6 +115,9 @@ struct Ctx {
     size_t tok_part_half;
     // attention over the retrieved context: per (question, token, head, split) maximum, normaliser, output
     float *attend_part; // [kAttendMaxTiles] counts (zero between calls), then [max_questions][kAttendMaxTokens][Hq][kAttendMaxSplit][D+2]
+    // Calls that overlapped against the rule may have left a count other than zero: set by a reset or a restore, after which the next
+    // call that counts clears them first, on its own stream.
+    bool arrivals_unsure;
 };
 
 // ---- a batch of chunks processed by one chain of launches ----
@@ -243,7 +246,7 @@ bool att_mfma_supported(const mukv_config &c);
 // The length-128 transform's matrix as matrix-core operands (bf16 bits), for the frequency indicator
 // that the matrix-core attention workgroups compute on the way.
 std::vector<uint16_t> dft_operand_table();
-hipError_t launch_attend(const Ctx &c, int layer, const void *q, int n_q, const int32_t *frame_idx, int k_frame,
+hipError_t launch_attend(Ctx &c, int layer, const void *q, int n_q, const int32_t *frame_idx, int k_frame,
                          const void *k_local, const void *v_local, const int32_t *local_offsets, int B, int causal,
                          void *out, float *signal, float *workspace, hipStream_t st);
 int64_t prefill_workspace_bytes(const Ctx &c, int n_q, int B, int k_frame);

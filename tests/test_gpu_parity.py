@@ -628,6 +628,47 @@ def test_reset_drops_a_copy_that_was_put_off():
     p.close()
 
 
+@pytest.mark.parametrize("how", ["reset", "restore"])
+def test_attention_after_the_cache_was_emptied_or_replaced(how):
+    # decode steps whose rows workgroups share count arrivals in the context; the first one after a reset or a restore clears the
+    # counts, eager or as part of a graph, and short prefills go on beside it
+    w = W["7b"].scaled(n_frames=24, n_layers=1, n_questions=1)
+    p = Pair(w, seed=99, chunk=8)
+    junk = synth.SynthStream(w, 100, device="cpu")
+    fi = torch.arange(8, dtype=torch.int32, device="cuda")[None]
+    q = torch.randn(1, 1, w.n_q_heads, w.head_dim, device="cuda", generator=torch.Generator("cuda").manual_seed(101)).to(w.torch_dtype)
+    if how == "restore":
+        p.ingest()
+        snap = p.gpu.snapshot()
+        p.gpu.reset()
+    k, v, x = (t.cuda() for t in junk.next_chunk(8))
+    p.gpu.compress_chunk(k, v, x)
+    for _ in range(3):
+        p.gpu.attend(0, q, fi)
+    if how == "restore":
+        p.gpu.restore(snap)
+    else:
+        p.gpu.reset()
+        p.ingest()
+    fi, out = torch.arange(24, dtype=torch.int32, device="cuda")[None], torch.empty_like(q)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):                                                   # the clearing launch is captured with it
+        for _ in range(2):
+            p.gpu.attend(0, q, fi, out=out)
+    p.check_attend(0, 1, [list(range(24))], [30], causal=True, seed=102)
+    p.check_prefill(0, 40, [[1, 5, 9]], [2], True, seed=103)
+    want = p.gpu.attend(0, q, fi)
+    for i in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), i
+        p.check_attend(0, 1, [list(range(20 + i))], [30], causal=True, seed=104 + i)
+        p.check_prefill(0, 40, [[1, 5, 9]], [2], True, seed=107 + i)
+    p.close()
+
+
 # ----------------------------------------------------------- seeded sweep of small shapes ------
 def _random_case(i):
     rng = np.random.default_rng(4000 + i)

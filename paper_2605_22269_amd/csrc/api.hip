@@ -340,6 +340,7 @@ int mukv_create(const mukv_config *cfg, mukv_ctx **out) {
         c.tok_part_half = (c.tok_part_half + 255) & ~(size_t)255;
         ok(dalloc(&c.tok_part, c.tok_part_half + (size_t)c.max_batch_frames * n_groups * hc * sizeof(double)));
     }
+    if (e == hipSuccess) ok(hipStreamSynchronize(nullptr)); // what is filled above is there for the first call on any stream
     if (e != hipSuccess || !c.prof || !c.pending || !c.deferred) {
         free_all(c);
         delete c.prof;

@@ -1518,8 +1518,13 @@ def test_prefill_of_few_tokens_sums_attention_in_the_tile(D, hq, hkv, n_q, n_fra
 @pytest.mark.parametrize("name,kw,n_q,n_frames", [
     ("7b", {}, 40, 0),                        # matrix-core prefill, rows of a tile in one workgroup
     ("7b", {}, 40, 12),                       # shared by several, merged
+    ("7b", {}, 150, 0),                       # four waves a tile, Eq. 1 in a launch of its own
+    ("7b", {}, 150, 12),                      # two halves of a workgroup that join: the key in the first one's rows
+    ("7b", {}, 150, 11),                      # in the second one's
     ("7b", {"head_dim": 64}, 40, 0),
     ("7b", {"head_dim": 64}, 40, 12),
+    ("7b", {"head_dim": 64}, 150, 12),
+    ("7b", {"head_dim": 64}, 150, 11),
     ("7b", {"head_dim": 32}, 40, 5),          # scores on the matrix cores, merged
     ("tiny", {}, 40, 5),                      # fp32
     ("7b", {}, 3, 12),                        # decode
@@ -1559,7 +1564,7 @@ def test_attention_non_finite_scores_reach_the_output(name, kw, n_q, n_frames, b
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("n_q", [5, 40])
+@pytest.mark.parametrize("n_q", [5, 40, 150, 450])      # (450: two halves of a workgroup, most of them without a row)
 def test_prefill_rows_of_no_question_stay_out(D, n_q):
     # the last step of rows is part empty, one entry of the frame list names no frame, and there are no rows besides the
     # retrieved ones: what stands in for a row that is not there must not be a frame the question did not retrieve --

@@ -364,7 +364,9 @@ int mukv_attend(mukv_ctx *ctx, int32_t layer, const void *q, int32_t n_q, const 
  *                   normalises it per unit, so the common factor is immaterial).
  *   workspace       device scratch of at least mukv_prefill_workspace_size()
  *                   bytes, 16-byte aligned, owned by the caller; contents are
- *                   undefined afterwards.  The call allocates nothing.
+ *                   undefined before and after.  The call allocates nothing,
+ *                   and writes nothing of the context: calls that overlap on
+ *                   the device, each with a workspace of its own, do not meet.
  *
  * Arithmetic in fp32, sums in a fixed order; `out` is rounded to the payload
  * dtype.  For bf16 payloads with D = 64 or 128 both products run on the matrix

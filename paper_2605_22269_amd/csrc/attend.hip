@@ -6,7 +6,8 @@
 // attend_kernel: one workgroup of four waves per (question, KV head, tile of 16 queries, share of the rows).  A query of
 // the tile is a (token, head of the KV group) pair, so a key / value row is read once for all the heads that share it.
 // Nothing crosses the waves until the end: a wave walks blocks of its own, with running statistics of its own, and the
-// four results join in LDS.  attend_combine_kernel merges the shares of a tile whose rows are split.
+// four results join in LDS.  The shares of a tile whose rows are split are merged by the last of its workgroups to finish; a
+// prefill's, whose records are in the caller's workspace, which has no counts, by attend_combine_kernel.
 // Everything is summed in a fixed order: the result does not depend on timing.
 //
 // The prefill of new tokens (Sec. 3.2: they attend to the past cache and to themselves) is the same
@@ -871,18 +872,18 @@ unsigned tile_grid(int n_tiles, int combos) {
 }
 
 // What bounds it: the latency of a wave's chain scores -> statistics -> weights -> values, with two waves per SIMD to
-// hide it (248 registers, 80 KB of LDS): a 64-row step of a workgroup alone on its compute unit takes 2850 cycles for
-// 1024 of matrix work.  Measured, 7B head layout, 1568 new tokens over 768 rows: 60-64 us, its matrix pipes busy 36 % of
-// the time (64-query tiles of 16x16x32 products whose weights cross the waves through LDS: 186 us with the column sums,
-// which are 23 us in the kernel below); 4000 tokens 258-265 us for the whole call against 673.  344 tiles on 512
-// resident places is not even: the launch lasts as long as its heaviest tile.
-// FOURS = 2: eight waves, of which four take the even steps and four the odd ones, with rows and tables of their own (160 KB of
+// hide it (254 registers, 80 KB of LDS): a 64-row step of a workgroup alone on its compute unit takes 2850 cycles for
+// 1024 of matrix work (64-query tiles of 16x16x32 products whose weights cross the waves through LDS: 1568 new tokens over 768
+// rows, 7B head layout, 186 us with the column sums, which are 23 us in the kernel below; 4000 tokens 269 us for the whole call
+// against 673).
+// FOURS = 2: eight waves, of which four take the even steps and four the odd ones, with rows and tables of their own (158 KB of
 // LDS, one workgroup per compute unit), and join at the end: a tile's chain is half as long, which is what counts where there
-// are no more tiles than compute units (flash_split; 600 tokens over 768 rows 47.2 -> 38.9 us a call).  Where there are somewhat
-// more the smallest tiles take a four each, two to a workgroup, at the larger one's barriers: every compute unit then has about the
-// same to do (1568 tokens 79.4 -> 72.9).  Also built and slower: the next block's scores
-// interleaved instruction by instruction with this block's weights and values (66 us), 64 queries per wave (85 us: the accumulators pass 256
-// registers and are moved in and out of the accumulation registers).
+// are no more tiles than compute units (600 tokens over 768 rows 44.4 -> 39.4 us a call).  Where there are somewhat
+// more the smallest tiles take a four each, two to a workgroup, at the larger one's barriers: under the mask every compute unit then
+// has about the same to do (1568 tokens, 344 tiles, 79.7 -> 72.5 us a call, 54 of them here, its matrix pipes busy 40 % of the time).
+// flash_split says where.  Also built and slower, measured with four waves and 1568 tokens at 60-64 us a launch: the next block's
+// scores interleaved instruction by instruction with this block's weights and values (66 us), 64 queries per wave (85 us: the
+// accumulators pass 256 registers and are moved in and out of the accumulation registers).
 // SPLIT: a short prefill has too few tiles to fill the chip, so its rows are shared by n_split workgroups per
 // tile; the split's (maximum, normaliser, unnormalised output) go to the records attend_combine_kernel merges
 // (aux = records).  Otherwise the output is final here, and so are the log-sum-exps: they go to aux for the key sums'
